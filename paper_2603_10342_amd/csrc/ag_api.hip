@@ -260,6 +260,7 @@ static ag_status decode_common(const ag_kv_cache* cache, const void* q, void* ou
     a.prefix_lens = nullptr; a.new_lens = nullptr; a.cu_new = nullptr; a.ctx_lens = ctx_lens;
     a.batch = batch; a.total_rows = batch; a.max_new = 1; a.max_ctx = max_ctx; a.hq = num_q_heads; a.scale = scale;
     if (decode_mfma_supported(a)) return launch_decode_mfma(a, workspace, (hipStream_t)stream);
+    if (decode_any_supported(a)) return launch_decode_any(a, workspace, (hipStream_t)stream);
     return launch_attn_general(a, (hipStream_t)stream);
 }
 

@@ -65,6 +65,11 @@ ag_status launch_prefill_mfma(const AttnArgs& a, hipStream_t st);
 bool      decode_mfma_supported(const AttnArgs& a);
 size_t    decode_workspace_bytes(int batch, int hq, int d, int max_ctx);
 ag_status launch_decode_mfma(const AttnArgs& a, void* ws, hipStream_t st);
+// Workgroups of a launch that deals f_max steps of 32 tokens in equal shares on the stream's CUs.
+int       share_workgroups(int64_t f_max, hipStream_t st);
+// every other bf16 / fp32 shape with pages of 16 tokens or more
+bool      decode_any_supported(const AttnArgs& a);
+ag_status launch_decode_any(const AttnArgs& a, void* ws, hipStream_t st);
 // the whole decode step (append + attention + merge) in one launch; same shapes as the matrix-core decode
 size_t    decode_step_workspace_bytes(int batch, int hq, int d, int max_ctx);
 ag_status launch_decode_step(const AttnArgs& a, const void* k_new, const void* v_new, void* ws, hipStream_t st);

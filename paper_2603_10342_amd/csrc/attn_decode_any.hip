@@ -1,0 +1,375 @@
+// Decode over paged KV caches of any supported head_dim and dtype with pages of 16 tokens or more (bf16 with
+// head_dim 128 on 16-token pages has a kernel of its own, attn_decode_mfma.hip).
+//
+// Bound by HBM, like that kernel, and built like it: the batch's (session, KV head) contexts are laid end to end in
+// steps of 32 tokens and dealt to the workgroups in equal shares (find_share), all query heads of a KV head share
+// one pass over the keys and values, both contractions run on the matrix cores with the heads padded to 16 columns,
+// and a merge kernel combines the segments' partials in order.  Groups of more than 16 heads are cut into blocks
+// of 16, each a pair of its own.  What differs:
+//   - Arithmetic keeps 32 bits where the caches do: fp32 runs on 16x16x4 fp32 products (256 flop per clock and CU:
+//     a step of 16 tokens takes a third of the time its bytes take), with expf on unscaled exponents; bf16 caches
+//     multiply the weights as two bf16 terms (hi + lo, 16 bits of mantissa), so no weight is cut to 8 bits.
+//   - The 16-token group is the unit of addressing: group i of a context lies in page i / (page_size / 16), and a
+//     group's keys and values sit in the page as in a 16-token page, only with a larger chunk stride for K.
+//   - Two sub-steps of loads are in flight per wave where a sub-step is 16 KiB or less (head_dim 64 and 128):
+//     with half the bytes per token, one in flight does not cover the latency.
+// Whole decode step, append included (one wave per (row, query head) before -> now): 16 fp32 sessions of 1024..4096
+// tokens at 32 / 8 heads x 128, 2760 -> 75 us (369 MB, 4.9 TB/s; split kernel 66 us); 48 bf16 sessions of 700..5000 at
+// head_dim 64, 32-token pages, 2238 -> 65 us (333 MB, 5.2 TB/s); two fp32 sessions of 300, 4 / 2 heads x 64, 106 -> 12 us.
+// head_dim below its template's DT: channels beyond head_dim read the last channel again and meet a zero query
+// (keys) or land in rows that are not stored (values).
+#include "attn_split_common.h"
+
+namespace ag {
+
+namespace {
+
+using splitk::f32x4;
+using splitk::u32x4;
+using splitk::bf16x8;
+using splitk::kLog2e;
+using splitk::steps_of;
+
+constexpr int kCols = 16;               // query heads of a pair (a block of the group's heads)
+
+template <typename E>
+__device__ __forceinline__ u32x4 load16(const E* p)
+{
+    return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));    // read once per step
+}
+
+template <typename E, int DT>
+struct SubStep {
+    static constexpr bool kBf16 = sizeof(E) == 2;
+    static constexpr int kTok = kBf16 ? 32 : 16;                 // tokens
+    static constexpr int kK = kBf16 ? DT / 16 : DT / 16;         // 16-byte loads of a lane: keys
+    static constexpr int kV = DT / 16;                           // ... and values
+    u32x4 k[kK], v[kV];
+};
+
+template <typename E, int DT, bool kExact>
+__global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, int32_t* __restrict__ hdr,
+                                                                  float* __restrict__ ws_o, float* __restrict__ ws_ml,
+                                                                  int pmax, int head_blocks)
+{
+    using X = SubStep<E, DT>;
+    constexpr bool kBf16 = X::kBf16;
+    constexpr int kSub = 32 / X::kTok;                           // sub-steps of a step
+    constexpr bool kTwoInFlight = X::kK + X::kV <= 16;
+    constexpr int kChan = DT < 128 ? DT : 128;                   // channels the waves' results go through LDS at a time
+    constexpr int kQRow = DT * (int)sizeof(E) + 16;
+    __shared__ float s_o[4][kCols][kChan];
+    __shared__ float s_m[4][kCols];
+    __shared__ float s_l[4][kCols];
+    __shared__ __attribute__((aligned(16))) unsigned char s_q[kCols * kQRow];
+
+    const int B = a.batch, hkv = a.c.hkv, hq = a.hq, G = hq / hkv;
+    const int heads = hkv * head_blocks;                         // pairs of a session
+    const int D = kExact ? DT : a.c.d, ps = a.c.ps;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wg = blockIdx.x;
+
+    splitk::Share sh;
+    if (!splitk::find_share<true>(a.ctx_lens, B, heads, hdr, sh)) return;
+    int s = sh.s, base = sh.base, ctx = sh.ctx;
+    int n = steps_of(ctx);
+    int pair = (sh.f0 - base) / n;                               // (KV head, block of its heads)
+    int u = (sh.f0 - base) - pair * n;                           // first step inside the pair
+
+    const int r = lane & 15, c = lane >> 4;
+    const int gshift = a.c.ps_shift - 4, gmask = (1 << gshift) - 1;       // 16-token groups of a page
+    const int64_t block = (int64_t)D * ps;                       // elements of one (page, head)
+    // bf16: score row r is slot r & 7 of group r >> 3, the second product takes slots 8..15, so that lane group c owns
+    // the 8 tokens of value chunk c & 1 of group c >> 1.  fp32: score row r is slot r, lane group c owns tokens
+    // 4 c .. 4 c + 3: elements 4 (c >> 1) .. + 3 of value chunk c & 1.
+    const int k_slot = kBf16 ? (r & 7) * 8 : r * 8 + (c & 1) * 4;
+    const int k_chunk = kBf16 ? c : c >> 1;                      // + 4 (bf16) or 2 (fp32) per load
+    const int v_lane = kBf16 ? ((c & 1) * D) * 8 : ((c & 1) * D) * 8 + (c >> 1) * 4;
+    const float unit = kBf16 ? a.scale * kLog2e : a.scale;       // bf16 takes its weights as powers of two
+    auto power = [](float x) { return kBf16 ? __builtin_amdgcn_exp2f(x) : expf(x); };
+
+    for (int f = sh.f0; f < sh.f1 && s < B;) {                   // one segment per pass; every value here is uniform
+        const int k = min(n - u, sh.f1 - f);
+        if (k <= 0) break;                                       // (only if the lengths changed under the kernel)
+        const int g = pair / head_blocks, h0 = (pair - g * head_blocks) * kCols;
+        const int nh = min(kCols, G - h0);                       // heads of this block
+        const int per = (k + 3) >> 2;
+        const int my_u = u + w * per;
+        const int my_n = max(0, min(per, k - w * per));
+
+        const int last_grp = (ctx - 1) >> 4;
+        int my_pid = 0;                                          // lane i: page of the wave's group i
+        if (my_n > 0) my_pid = a.bt[(int64_t)s * a.max_pages + (min(2 * my_u + lane, last_grp) >> gshift)];
+        {
+            constexpr int kPieces = DT * (int)sizeof(E) / 16;    // of a query row
+            const int pieces = D * (int)sizeof(E) / 16;
+            const unsigned char* qs = (const unsigned char*)a.q + ((int64_t)s * hq + (int64_t)g * G + h0) * D * (int)sizeof(E);
+            for (int idx = tid; idx < kCols * kPieces; idx += 256) {
+                const int head = idx / kPieces, p = idx - head * kPieces;
+                u32x4 x = {0, 0, 0, 0};
+                if (head < nh && p < pieces) x = *reinterpret_cast<const u32x4*>(qs + ((int64_t)head * pieces + p) * 16);
+                *reinterpret_cast<u32x4*>(s_q + head * kQRow + p * 16) = x;
+            }
+        }
+        const E* kpool = (const E*)a.c.k;
+        const E* vpool = (const E*)a.c.v;
+        auto load = [&](X& x, int i) {                           // sub-step i of the wave
+            if constexpr (kBf16) {
+                const int64_t pA = __builtin_amdgcn_readlane(my_pid, 2 * i), pB = __builtin_amdgcn_readlane(my_pid, 2 * i + 1);
+                const int gA = min(2 * (my_u + i), last_grp) & gmask, gB = min(2 * (my_u + i) + 1, last_grp) & gmask;
+                const int64_t baseA = (pA * hkv + g) * block, baseB = (pB * hkv + g) * block;
+                const E* kp = kpool + (r >> 3 ? baseB + gB * 128 : baseA + gA * 128) + k_slot;
+                const E* vp = vpool + (c >> 1 ? baseB + gB * 16 * D : baseA + gA * 16 * D) + v_lane;
+#pragma unroll
+                for (int kk = 0; kk < X::kK / 2; ++kk) {
+                    const int chunk = kExact ? k_chunk + 4 * kk : min(k_chunk + 4 * kk, (D >> 3) - 1);
+                    x.k[2 * kk] = load16(kp + (int64_t)chunk * ps * 8);
+                    x.k[2 * kk + 1] = load16(kp + (int64_t)chunk * ps * 8 + 64);
+                }
+#pragma unroll
+                for (int mb = 0; mb < X::kV; ++mb) x.v[mb] = load16(vp + (kExact ? mb * 16 + r : min(mb * 16 + r, D - 1)) * 8);
+            } else {
+                const int64_t p = __builtin_amdgcn_readlane(my_pid, i);
+                const int gi = min(2 * my_u + i, last_grp) & gmask;
+                const int64_t at = (p * hkv + g) * block;
+                const E* kp = kpool + at + gi * 128 + k_slot;
+                const E* vp = vpool + at + gi * 16 * D + v_lane;
+#pragma unroll
+                for (int kk = 0; kk < X::kK; ++kk) {
+                    const int chunk = kExact ? k_chunk + 2 * kk : min(k_chunk + 2 * kk, (D >> 3) - 1);
+                    x.k[kk] = load16(kp + (int64_t)chunk * ps * 8);
+                }
+#pragma unroll
+                for (int mb = 0; mb < X::kV; ++mb) x.v[mb] = load16(vp + (kExact ? mb * 16 + r : min(mb * 16 + r, D - 1)) * 8);
+            }
+        };
+
+        float m = -INFINITY, lsum = 0.0f;
+        f32x4 o[DT / 16];
+#pragma unroll
+        for (int mb = 0; mb < DT / 16; ++mb) o[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const unsigned char* q_lane = s_q + r * kQRow + c * 16;
+
+        auto compute = [&](X& x, int i) {
+            constexpr int kScores = kBf16 ? 8 : 4;
+            const int tok0 = my_u * 32 + i * X::kTok;
+            const int tokb = kBf16 ? tok0 + (c >> 1) * 16 + (c & 1) * 4 : tok0 + c * 4;
+            const int keep = ctx - tokb;                         // token tokb + j exists iff j < keep
+            f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
+            float xs[kScores];
+            if constexpr (kBf16) {
+#pragma unroll
+                for (int kk = 0; kk < X::kK / 2; ++kk) {
+                    const bf16x8 qk = *reinterpret_cast<const bf16x8*>(q_lane + kk * 64);
+                    s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x.k[2 * kk]), qk, s1, 0, 0, 0);
+                    s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x.k[2 * kk + 1]), qk, s2, 0, 0, 0);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    xs[j] = j < keep ? s1[j] * unit : -INFINITY;
+                    xs[4 + j] = 8 + j < keep ? s2[j] * unit : -INFINITY;
+                }
+            } else {
+#pragma unroll
+                for (int kk = 0; kk < X::kK; ++kk) {
+                    const f32x4 qk = *reinterpret_cast<const f32x4*>(q_lane + kk * 64);
+                    const f32x4 kv = __builtin_bit_cast(f32x4, x.k[kk]);
+                    s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[0], qk[0], s1, 0, 0, 0);
+                    s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[1], qk[1], s2, 0, 0, 0);
+                    s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[2], qk[2], s1, 0, 0, 0);
+                    s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[3], qk[3], s2, 0, 0, 0);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) xs[j] = j < keep ? (s1[j] + s2[j]) * unit : -INFINITY;
+            }
+            float mx = fmaxf(fmaxf(xs[0], xs[1]), fmaxf(xs[2], xs[3]));
+            if constexpr (kBf16) mx = fmaxf(mx, fmaxf(fmaxf(xs[4], xs[5]), fmaxf(xs[6], xs[7])));
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m, mx);
+            // (fp32: the second sub-step of a context's last step may hold no token)
+            const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = power(m - m_ref);
+            float p[kScores], psum = 0.f;
+#pragma unroll
+            for (int j = 0; j < kScores; ++j) { p[j] = power(xs[j] - m_ref); psum += p[j]; }
+            lsum = lsum * alpha + psum;
+            m = m_new;
+            if (tok0 + X::kTok > ctx) {          // slots past the last token may hold anything, NaN included
+#pragma unroll
+                for (int mb = 0; mb < X::kV; ++mb) {
+                    if constexpr (kBf16) {
+                        x.v[mb] = __builtin_bit_cast(u32x4, splitk::keep_quads(__builtin_bit_cast(bf16x8, x.v[mb]), keep, keep - 8));
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) x.v[mb][j] = j < keep ? x.v[mb][j] : 0u;
+                    }
+                }
+            }
+            if constexpr (kBf16) {
+                bf16x8 hi, lo;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) { hi[j] = (__bf16)p[j]; lo[j] = (__bf16)(p[j] - (float)hi[j]); }
+#pragma unroll
+                for (int mb = 0; mb < X::kV; ++mb) {
+                    const bf16x8 v = __builtin_bit_cast(bf16x8, x.v[mb]);
+                    o[mb] *= alpha;
+                    o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, lo, o[mb], 0, 0, 0);
+                    o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, hi, o[mb], 0, 0, 0);
+                }
+            } else {
+#pragma unroll
+                for (int mb = 0; mb < X::kV; ++mb) o[mb] *= alpha;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int mb = 0; mb < X::kV; ++mb)
+                        o[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f32x4, x.v[mb])[j], p[j], o[mb], 0, 0, 0);
+            }
+        };
+
+        const int subs = my_n * kSub;
+        if constexpr (kTwoInFlight) {
+            X x0, x1;
+            if (subs > 0) load(x0, 0);
+            __syncthreads();                                     // Q is in LDS
+#pragma unroll 1
+            for (int i = 0; i < subs; i += 2) {
+                if (i + 1 < subs) load(x1, i + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                compute(x0, i);
+                if (i + 2 < subs) load(x0, i + 2);
+                __builtin_amdgcn_sched_barrier(0);
+                if (i + 1 < subs) compute(x1, i + 1);
+            }
+        } else {
+            X x;
+            __syncthreads();
+#pragma unroll 1
+            for (int i = 0; i < subs; ++i) {
+                load(x, i);
+                __builtin_amdgcn_sched_barrier(0);               // all loads in flight before anything waits
+                compute(x, i);
+            }
+        }
+        lsum += __shfl_xor(lsum, 16);
+        lsum += __shfl_xor(lsum, 32);
+
+        // o[mb][i] is O^T[channel mb * 16 + c * 4 + i][head r]; the four waves are merged in LDS, kChan channels at a time
+        const int first_wg = (base + pair * n) / sh.q;           // the pair's segments are numbered from this workgroup
+        const int piece = wg - first_wg;
+        if (c == 0) { s_m[w][r] = m; s_l[w][r] = lsum; }
+#pragma unroll
+        for (int d0 = 0; d0 < DT; d0 += kChan) {
+#pragma unroll
+            for (int mb = 0; mb < kChan / 16; ++mb) *reinterpret_cast<f32x4*>(&s_o[w][r][mb * 16 + c * 4]) = o[d0 / 16 + mb];
+            __syncthreads();
+            if (piece < pmax) {
+                for (int idx = tid; idx < nh * kChan; idx += 256) {
+                    const int head = idx / kChan, dl = idx - head * kChan, d = d0 + dl;
+                    if (d >= D) continue;
+                    float ms = s_m[0][head];                     // wave 0 always has a step: finite unless the scores are not
+#pragma unroll
+                    for (int ww = 1; ww < 4; ++ww) ms = fmaxf(ms, s_m[ww][head]);
+                    float acc = 0.f, l = 0.f;
+#pragma unroll
+                    for (int ww = 0; ww < 4; ++ww) {
+                        const float fw = power(s_m[ww][head] - ms);        // a wave without steps has m = -inf -> 0
+                        acc += fw * s_o[ww][head][dl];
+                        l += fw * s_l[ww][head];
+                    }
+                    const int64_t slot = ((int64_t)s * hq + (int64_t)g * G + h0 + head) * pmax + piece;
+                    ws_o[slot * D + d] = acc;
+                    if (d == 0) { ws_ml[slot * 2] = ms; ws_ml[slot * 2 + 1] = l; }
+                }
+            }
+            __syncthreads();                                     // s_o, s_m and s_q are written again
+        }
+
+        f += k;
+        u += k;
+        if (u == n) {                                            // on to the next pair
+            u = 0;
+            if (++pair == heads) {
+                pair = 0;
+                base += heads * n;
+                do {
+                    ++s;
+                    ctx = s < B ? a.ctx_lens[s] : 0;
+                    n = steps_of(ctx);
+                } while (s < B && n == 0);
+            }
+        }
+    }
+}
+
+template <typename E>
+__global__ __launch_bounds__(256) void decode_any_merge_kernel(AttnArgs a, const int32_t* __restrict__ hdr,
+                                                               const float* __restrict__ ws_o,
+                                                               const float* __restrict__ ws_ml, int pmax, int head_blocks)
+{
+    const int row = blockIdx.x;                 // s * hq + h
+    const int s = row / a.hq, h = row - s * a.hq;
+    const int d = threadIdx.x, D = a.c.d;
+    if (d >= D) return;
+    const int ctx = a.ctx_lens[s];
+    E* out = (E*)a.out + (int64_t)row * D;
+    if (ctx <= 0) { out[d] = (E)0.0f; return; }
+    const int G = a.hq / a.c.hkv, g = h / G;
+    const int q = max(1, hdr[0]), n = steps_of(ctx);
+    const int first = a.c.hkv * head_blocks * hdr[1 + s] + (g * head_blocks + (h - g * G) / kCols) * n;
+    const int pieces = min(pmax, (first + n - 1) / q - first / q + 1);       // as the split kernel cuts them
+    out[d] = (E)splitk::merge_partials<false, sizeof(E) == 4>(ws_o, ws_ml, (int64_t)row * pmax, pieces, d, D);
+}
+
+inline int head_blocks_of(const AttnArgs& a) { return (a.hq / a.c.hkv + kCols - 1) / kCols; }
+inline int64_t steps_bound(const AttnArgs& a)
+{
+    return (int64_t)a.c.hkv * head_blocks_of(a) * a.batch * ((a.max_ctx + 31) / 32);
+}
+
+template <typename E, int DT>
+ag_status launch(const AttnArgs& a, void* ws, hipStream_t st)
+{
+    const int pmax = splitk::pieces_max(a.max_ctx), blocks = head_blocks_of(a);
+    int32_t* hdr = (int32_t*)ws;
+    float* ws_o = (float*)(hdr + splitk::header_ints(a.batch));
+    float* ws_ml = ws_o + (size_t)a.batch * a.hq * pmax * a.c.d;
+    prof_before(st);
+    if (a.max_ctx > 0) {
+        const dim3 grid(share_workgroups(steps_bound(a), st)), wg(256);
+        if (a.c.d == DT) hipLaunchKernelGGL((decode_any_split_kernel<E, DT, true>), grid, wg, 0, st, a, hdr, ws_o, ws_ml, pmax, blocks);
+        else hipLaunchKernelGGL((decode_any_split_kernel<E, DT, false>), grid, wg, 0, st, a, hdr, ws_o, ws_ml, pmax, blocks);
+        ag_status e = hip_check(hipGetLastError(), "decode split launch");
+        if (e) return e;
+    }
+    hipLaunchKernelGGL(decode_any_merge_kernel<E>, dim3(a.batch * a.hq), dim3((a.c.d + 63) & ~63), 0, st, a, hdr, ws_o, ws_ml, pmax, blocks);
+    prof_after(st);
+    return hip_check(hipGetLastError(), "decode merge launch");
+}
+
+template <typename E>
+ag_status launch_for_dim(const AttnArgs& a, void* ws, hipStream_t st)
+{
+    if (a.c.d <= 64) return launch<E, 64>(a, ws, st);
+    if (a.c.d <= 128) return launch<E, 128>(a, ws, st);
+    return launch<E, 256>(a, ws, st);
+}
+
+}  // namespace
+
+// Pages below 16 tokens store V transposed without the 8-key chunks these loads rely on, and unaligned pointers rule
+// out 16-byte loads: both stay with the general kernel, as do batches whose steps do not fit an int.
+bool decode_any_supported(const AttnArgs& a)
+{
+    return a.c.ps >= 16 && (((uintptr_t)a.q | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 == 0) && steps_bound(a) <= (1 << 30) &&
+           (int64_t)a.batch * a.hq <= 0x7fffffff;
+}
+
+ag_status launch_decode_any(const AttnArgs& a, void* ws, hipStream_t st)
+{
+    return a.c.dtype == AG_BF16 ? launch_for_dim<__bf16>(a, ws, st) : launch_for_dim<float>(a, ws, st);
+}
+
+}  // namespace ag

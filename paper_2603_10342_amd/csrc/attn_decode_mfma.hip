@@ -52,16 +52,6 @@ namespace {
 
 using namespace splitk;
 
-constexpr int kMinSteps = kMinSplit / 32;      // a workgroup's share is at least this many steps (256 tokens)
-constexpr int kMaxSteps = 128;                 // and at most this many (the launcher sizes the grid for it)
-
-__device__ __forceinline__ int steps_of(int ctx) { return ctx > 0 ? (ctx + 31) >> 5 : 0; }
-
-// Segments a pair of n steps starting at flat step a may be cut into when shares are q >= kMinSteps steps.
-inline int pieces_max(int max_ctx) { return (((max_ctx + 31) / 32) - 1) / kMinSteps + 2; }
-// Workspace: header [q, then the exclusive step count before each session], partials O, partials (m, l).
-inline size_t header_ints(int batch) { return ((size_t)batch + 1 + 3) & ~(size_t)3; }
-
 // What the whole-step form of the kernel gets on top: the step's new token of every session (one row each),
 // which it appends itself, and one counter per (session, KV head), zero on entry and zero again on exit.
 struct StepArgs {
@@ -84,10 +74,8 @@ __global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_
     __shared__ float s_o[4][16][D];     // per wave, per (padded) head: unnormalised O
     __shared__ float s_m[4][16];
     __shared__ float s_l[4][16];
-    __shared__ int s_red[4];
     constexpr int kQRow = 2 * D + 16;
     __shared__ __attribute__((aligned(16))) unsigned char s_q[16 * kQRow];
-    __shared__ int s_start[3];          // session holding the workgroup's first step, steps before it, its length
     __shared__ int s_arrived;           // kStep: how many of the pair's segments had been finished before this one
 
     const int B = a.batch, hkv = a.c.hkv, hq = a.hq;
@@ -96,58 +84,17 @@ __global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wg = blockIdx.x, W = gridDim.x;
 
-    // ---- the plan: F, q and where this workgroup's share starts ----
-    int total;
-    {
-        int loc = 0;
-        for (int s = tid; s < B; s += 256) loc += steps_of(a.ctx_lens[s]);
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) loc += __shfl_xor(loc, d);
-        if (lane == 0) s_red[w] = loc;
-        __syncthreads();
-        total = s_red[0] + s_red[1] + s_red[2] + s_red[3];
-        __syncthreads();
-    }
     if (kStep) {                        // a session without context gets a row of zeros (no workgroup's share holds it)
         for (int se = wg; se < B; se += W)
             if (a.ctx_lens[se] <= 0)
                 for (int idx = tid; idx < hq * D; idx += 256) ((__bf16*)a.out)[(int64_t)se * hq * D + idx] = (__bf16)0.0f;
     }
-    const int F = hkv * total;
-    if (F == 0) return;
-    const int q = max(kMinSteps, (F + W - 1) / W);
-    const int f0 = wg * q;              // q <= kMaxSteps by the launcher's choice of W: no overflow
-    if (!kStep && wg == 0 && tid == 0) hdr[0] = q;
-    if (f0 >= F) return;                // uniform over the workgroup
-    const int f1 = min(f0 + q, F);
-    {
-        int carry = 0;                  // steps of the sessions before this chunk of 256
-        for (int s0 = 0; s0 < B; s0 += 256) {
-            const int s = s0 + tid;
-            const int len = s < B ? a.ctx_lens[s] : 0;
-            const int n = steps_of(len);
-            int incl = n;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int t = __shfl_up(incl, d);
-                if (lane >= d) incl += t;
-            }
-            if (lane == 63) s_red[w] = incl;
-            __syncthreads();
-            int woff = 0;
-            for (int ww = 0; ww < w; ++ww) woff += s_red[ww];
-            const int chunk = s_red[0] + s_red[1] + s_red[2] + s_red[3];
-            const int excl = carry + woff + incl - n;
-            if (n > 0 && hkv * excl <= f0 && f0 < hkv * (excl + n)) { s_start[0] = s; s_start[1] = excl; s_start[2] = len; }
-            if (!kStep && wg == 0 && s < B) hdr[1 + s] = excl;       // workgroup 0 publishes the plan for the merge kernel
-            __syncthreads();
-            carry += chunk;
-            if ((kStep || wg != 0) && hkv * carry > f0) break;     // found (uniform); workgroup 0 goes on publishing
-        }
-    }
-    int s = s_start[0];
-    int base = hkv * s_start[1];        // flat step at which session s starts
-    int ctx = s_start[2];
+    Share sh;
+    if (!find_share<!kStep>(a.ctx_lens, B, hkv, hdr, sh)) return;
+    const int q = sh.q, f0 = sh.f0, f1 = sh.f1;
+    int s = sh.s;
+    int base = sh.base;                 // flat step at which session s starts
+    int ctx = sh.ctx;
     int n = steps_of(ctx);
     int g = (f0 - base) / n;
     int u = (f0 - base) - g * n;        // first step inside (s, g)
@@ -418,20 +365,16 @@ int stream_cus(hipStream_t st)
     return n > 0 && n <= all ? n : all;
 }
 
-namespace {
-
 // Workgroups of a launch: the shares are equal, so what matters is that every CU gets the same number of
 // them, and as few as the longest share (kMaxSteps) allows: each workgroup pays the plan and each segment a
 // dependent page-id read (two per CU measured 1.5 % faster than four on the whole device, and 2-4 % on
 // partitions whose CU count divides the grid; a grid that leaves some CUs one workgroup short loses 4-5 %).
-int workgroups_for(int64_t f_max, hipStream_t st)
+int share_workgroups(int64_t f_max, hipStream_t st)
 {
     const int64_t unit = 2 * (int64_t)stream_cus(st);
     const int64_t need = std::max<int64_t>(1, (f_max + kMaxSteps - 1) / kMaxSteps);
     return (int)(unit * ((need + unit - 1) / unit));
 }
-
-}  // namespace
 
 size_t decode_workspace_bytes(int batch, int hq, int d, int max_ctx)
 {
@@ -476,7 +419,7 @@ ag_status launch_decode_mfma(const AttnArgs& a, void* ws, hipStream_t st)
     const int64_t f_max = (int64_t)a.c.hkv * a.batch * ((a.max_ctx + 31) / 32);
     if (f_max > (1 << 30)) { set_error("decode batch of %lld steps of 32 tokens is beyond one launch", (long long)f_max); return AG_ERR_INVALID_ARG; }
     if (a.max_ctx > 0) {
-        const int grid = workgroups_for(f_max, st);
+        const int grid = share_workgroups(f_max, st);
         // the event bracket covers both kernels of the call: the merge kernel writes the output the byte count includes
         prof_before(st);
         hipLaunchKernelGGL(decode_split_kernel<false>, dim3(grid), dim3(256), 0, st, a, hdr, ws_o, ws_ml, pmax, StepArgs{});
@@ -514,7 +457,7 @@ ag_status launch_decode_step(const AttnArgs& a, const void* k_new, const void* v
     float* ws_ml = ws_o + (size_t)a.batch * a.hq * pmax * D;
     const int64_t f_max = (int64_t)a.c.hkv * a.batch * ((a.max_ctx + 31) / 32);
     if (f_max > (1 << 30)) { set_error("decode batch of %lld steps of 32 tokens is beyond one launch", (long long)f_max); return AG_ERR_INVALID_ARG; }
-    const int grid = workgroups_for(std::max<int64_t>(f_max, 1), st);
+    const int grid = share_workgroups(std::max<int64_t>(f_max, 1), st);
     prof_before(st);
     hipLaunchKernelGGL(decode_split_kernel<true>, dim3(grid), dim3(256), 0, st, a, hdr, ws_o, ws_ml, pmax,
                        StepArgs{(const __bf16*)k_new, (const __bf16*)v_new, counters});

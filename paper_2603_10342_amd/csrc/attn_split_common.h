@@ -14,13 +14,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int D = 128;
 constexpr int PS = 16;
 
-// Tokens of one part of a session's context when it is cut for splits of at most `split` tokens:
-// n = ceil(ctx / split) equal parts, each a multiple of 128 (32 per wave step x 4 waves).
-__host__ __device__ inline int part_tokens(int ctx, int split)
-{
-    const int n = (ctx + split - 1) / split;
-    return (((ctx + n - 1) / n) + 127) & ~127;
-}
 constexpr float kLog2e = 1.4426950408889634f;
 
 __device__ __forceinline__ bf16x8 ld16(const __bf16* p) { return *reinterpret_cast<const bf16x8*>(p); }
@@ -57,10 +50,12 @@ struct StepRegs {       // one wave's K and V operands for 32 tokens (two pages)
 __device__ __forceinline__ float load_coherent(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void store_coherent(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-template <bool kCoherent = false>
+// kNatural: the partials' maxima are in natural units (fp32 caches), not in powers of two.  D_: channels per partial.
+template <bool kCoherent = false, bool kNatural = false>
 __device__ __forceinline__ float merge_partials(const float* __restrict__ ws_o, const float* __restrict__ ws_ml,
-                                                int64_t base, int n, int d)
+                                                int64_t base, int n, int d, int D_ = D)
 {
+    auto power = [](float x) { return kNatural ? expf(x) : exp2f(x); };
     float ms = -INFINITY, acc = 0.f, l = 0.f;
     for (int i0 = 0; i0 < n; i0 += 4) {
         float mi[4], li[4], oi[4];
@@ -69,16 +64,16 @@ __device__ __forceinline__ float merge_partials(const float* __restrict__ ws_o, 
             const int64_t p = base + min(i0 + j, n - 1);
             mi[j] = kCoherent ? load_coherent(ws_ml + p * 2) : ws_ml[p * 2];
             li[j] = kCoherent ? load_coherent(ws_ml + p * 2 + 1) : ws_ml[p * 2 + 1];
-            oi[j] = kCoherent ? load_coherent(ws_o + p * D + d) : ws_o[p * D + d];
+            oi[j] = kCoherent ? load_coherent(ws_o + p * D_ + d) : ws_o[p * D_ + d];
             if (i0 + j >= n) mi[j] = -INFINITY;
         }
         const float m_new = fmaxf(fmaxf(ms, fmaxf(mi[0], mi[1])), fmaxf(mi[2], mi[3]));
-        const float keep = ms == -INFINITY ? 0.f : exp2f(ms - m_new);
+        const float keep = ms == -INFINITY ? 0.f : power(ms - m_new);
         acc *= keep;
         l *= keep;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float f = mi[j] == -INFINITY ? 0.f : exp2f(mi[j] - m_new);     // a partial that saw no key
+            const float f = mi[j] == -INFINITY ? 0.f : power(mi[j] - m_new);     // a partial that saw no key
             acc += f * oi[j];
             l += f * li[j];
         }
@@ -89,7 +84,84 @@ __device__ __forceinline__ float merge_partials(const float* __restrict__ ws_o, 
 
 // Workspace is sized for the smallest split a launcher may choose.
 constexpr int kMinSplit = 256;
-inline int splits_for(int max_ctx, int split) { return max_ctx <= 0 ? 1 : (max_ctx + split - 1) / split; }
+
+// Workgroup w of W takes steps [w q, (w + 1) q) of the batch's (session, KV head) contexts laid end to end, one step =
+// 32 tokens, q = max(kMinSteps, ceil(F / W)).
+constexpr int kMinSteps = kMinSplit / 32;      // a workgroup's share is at least this many steps (256 tokens)
+constexpr int kMaxSteps = 128;                 // and at most this many (the launcher sizes the grid for it)
+
+__device__ __forceinline__ int steps_of(int ctx) { return ctx > 0 ? (ctx + 31) >> 5 : 0; }
+
+// Segments a pair of n steps starting at flat step a may be cut into when shares are q >= kMinSteps steps.
+inline int pieces_max(int max_ctx) { return (((max_ctx + 31) / 32) - 1) / kMinSteps + 2; }
+// Workspace: header [q, then the exclusive step count before each session], partials O, partials (m, l).
+inline size_t header_ints(int batch) { return ((size_t)batch + 1 + 3) & ~(size_t)3; }
+
+struct Share {
+    int q;                  // steps of a share
+    int f0, f1;             // this workgroup's steps
+    int s, base, ctx;       // session holding step f0, the flat step at which that session starts, its length
+};
+
+// Finds this workgroup's share from the lengths (256 threads; `heads` pairs per session); false if it has none.
+// With kPublish workgroup 0 also writes the plan for the merge kernel: hdr[0] = q, hdr[1 + s] = steps before session s.
+template <bool kPublish>
+__device__ __forceinline__ bool find_share(const int32_t* __restrict__ ctx_lens, int B, int heads, int32_t* __restrict__ hdr,
+                                           Share& sh)
+{
+    __shared__ int s_red[4];
+    __shared__ int s_start[3];          // session holding the workgroup's first step, steps before it, its length
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wg = blockIdx.x, W = gridDim.x;
+    int total;
+    {
+        int loc = 0;
+        for (int s = tid; s < B; s += 256) loc += steps_of(ctx_lens[s]);
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) loc += __shfl_xor(loc, d);
+        if (lane == 0) s_red[w] = loc;
+        __syncthreads();
+        total = s_red[0] + s_red[1] + s_red[2] + s_red[3];
+        __syncthreads();
+    }
+    const int F = heads * total;
+    if (F == 0) return false;
+    const int q = max(kMinSteps, (F + W - 1) / W);
+    const int f0 = wg * q;              // q <= kMaxSteps by the launcher's choice of W: no overflow
+    if (kPublish && wg == 0 && tid == 0) hdr[0] = q;
+    if (f0 >= F) return false;          // uniform over the workgroup
+    int carry = 0;                      // steps of the sessions before this chunk of 256
+    for (int s0 = 0; s0 < B; s0 += 256) {
+        const int s = s0 + tid;
+        const int len = s < B ? ctx_lens[s] : 0;
+        const int n = steps_of(len);
+        int incl = n;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int t = __shfl_up(incl, d);
+            if (lane >= d) incl += t;
+        }
+        if (lane == 63) s_red[w] = incl;
+        __syncthreads();
+        int woff = 0;
+        for (int ww = 0; ww < w; ++ww) woff += s_red[ww];
+        const int chunk = s_red[0] + s_red[1] + s_red[2] + s_red[3];
+        const int excl = carry + woff + incl - n;
+        if (n > 0 && heads * excl <= f0 && f0 < heads * (excl + n)) { s_start[0] = s; s_start[1] = excl; s_start[2] = len; }
+        if (kPublish && wg == 0 && s < B) hdr[1 + s] = excl;       // workgroup 0 publishes the plan for the merge kernel
+        __syncthreads();
+        carry += chunk;
+        if ((!kPublish || wg != 0) && heads * carry > f0) break;   // found (uniform); workgroup 0 goes on publishing
+    }
+    sh.q = q;
+    sh.f0 = f0;
+    sh.f1 = min(f0 + q, F);
+    sh.s = s_start[0];
+    sh.base = heads * s_start[1];
+    sh.ctx = s_start[2];
+    return true;
+}
 
 }  // namespace splitk
 }  // namespace ag

@@ -1,0 +1,83 @@
+"""GPU parity of the kernels for every geometry beside bf16 / head_dim 128 / 16-token pages, against the fp64 oracle:
+head dimensions at, below and between the sizes the kernels are compiled for, pages of 16 to 256 tokens, groups of one
+to more than 16 query heads, fp32 and bf16, contexts around the group, step and share boundaries."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import DevBatch, check_close, gpu_append, gpu_decode, i32, make_cache, run_phase, to_dev
+from helpers import fresh_pools, make_batch, oracle_append
+from oracle import oracle as O
+from paper_2603_10342_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+GEOMETRIES = [  # dtype, D, page, hq, hkv
+    (I.BF16, 64, 16, 8, 2), (I.BF16, 64, 256, 4, 4), (I.BF16, 128, 32, 8, 2), (I.BF16, 256, 64, 6, 2), (I.BF16, 8, 16, 4, 2),
+    (I.BF16, 72, 32, 16, 1), (I.BF16, 200, 16, 3, 1), (I.BF16, 128, 16, 40, 2), (I.F32, 64, 16, 8, 2), (I.F32, 128, 64, 4, 4),
+    (I.F32, 256, 16, 6, 2), (I.F32, 24, 128, 5, 1), (I.F32, 136, 32, 17, 1), (I.F32, 128, 16, 32, 8)]
+
+
+@pytest.mark.parametrize("dtype,d,ps,hq,hkv", GEOMETRIES)
+def test_decode_boundary_lengths(dtype, d, ps, hq, hkv):
+    """One token up to several shares; slots behind the last token and unused pages hold NaN."""
+    ctx = np.array([1, 15, 16, 17, 0, 31, 32, 33, 48, 127, 129, 255, 257, 513, 1100], np.int32)
+    pages = int(sum((max(int(c), 1) + ps - 1) // ps for c in ctx)) + 3
+    g = I.Geometry(hq, hkv, d, ps, pages, dtype)
+    bt = I.deal_block_tables(I.rng_for(51, 0), np.maximum(ctx, 1), ps, pages)
+    fill = make_batch(g, np.zeros_like(ctx), ctx, seed=51, bt=bt, sigma_qk=1.0, sigma_v=1.0)
+    cache = make_cache(g)
+    kp, vp = fresh_pools(g)
+    d_fill = DevBatch(fill)
+    gpu_append(cache, d_fill)
+    oracle_append(kp, vp, fill)
+    qn = I.normal_values(51, 9, 0, (len(ctx), hq, d), 1.0, dtype)
+    got = gpu_decode(cache, to_dev(qn, dtype), d_fill.bt, i32(ctx), int(ctx.max()), g)
+    live = np.nonzero(ctx > 0)[0]
+    assert np.all(got[ctx == 0] == 0)
+    ref = O.decode(kp, vp, dtype, qn[live], bt[live], ctx[live], hq, g.scale)
+    check_close(got[live], ref, dtype, f"decode D={d} page={ps} {hq}/{hkv}")
+
+
+@pytest.mark.parametrize("dtype,d", [(I.BF16, 64), (I.F32, 128)])
+def test_decode_shares_that_span_many_short_sessions(dtype, d):
+    """More sessions than one pass of the plan covers, some empty; then a bound far above the lengths."""
+    g = I.Geometry(8, 2, d, 32, 1500, dtype)
+    rng = np.random.default_rng(52)
+    ctx = rng.integers(1, 130, size=300).astype(np.int32)
+    ctx[rng.integers(0, 300, size=40)] = 0
+    ctx[[0, 255, 256, 299]] = [0, 33, 0, 1]
+    bt = I.deal_block_tables(I.rng_for(52, 0), np.maximum(ctx, 1), 32, g.num_pages)
+    fill = make_batch(g, np.zeros_like(ctx), ctx, seed=52, bt=bt, sigma_qk=1.0, sigma_v=1.0)
+    cache = make_cache(g)
+    kp, vp = fresh_pools(g)
+    d_fill = DevBatch(fill)
+    gpu_append(cache, d_fill)
+    oracle_append(kp, vp, fill)
+    qn = I.normal_values(52, 9, 0, (300, 8, d), 1.0, dtype)
+    live = np.nonzero(ctx > 0)[0]
+    ref = O.decode(kp, vp, dtype, qn[live], bt[live], ctx[live], 8, g.scale)
+    wide = np.concatenate([bt, np.zeros((300, 600), np.int32)], axis=1)
+    for table, bound in ((bt, int(ctx.max())), (wide, 16000)):
+        got = gpu_decode(cache, to_dev(qn, dtype), i32(table), i32(ctx), bound, g)
+        assert np.all(got[ctx == 0] == 0)
+        check_close(got[live], ref, dtype, f"decode, 300 sessions, bound {bound}")
+
+
+def test_decode_of_a_q_that_is_not_16_byte_aligned_still_runs():
+    g = I.Geometry(3, 1, 24, 16, 8, I.F32)
+    ctx = np.array([40, 7], np.int32)
+    bt = I.deal_block_tables(I.rng_for(53, 0), ctx, 16, 8)
+    fill = make_batch(g, [0, 0], ctx, seed=53, bt=bt, sigma_qk=1.0, sigma_v=1.0)
+    cache = make_cache(g)
+    kp, vp = fresh_pools(g)
+    d_fill = DevBatch(fill)
+    gpu_append(cache, d_fill)
+    oracle_append(kp, vp, fill)
+    qn = I.normal_values(53, 9, 0, (2, 3, 24), 1.0, I.F32)
+    buf = torch.empty(2 * 3 * 24 + 1, dtype=torch.float32, device="cuda")
+    q = buf[1:].view(2, 3, 24)
+    q.copy_(torch.from_numpy(qn))
+    assert q.data_ptr() % 16
+    got = gpu_decode(cache, q, d_fill.bt, i32(ctx), 40, g)
+    check_close(got, O.decode(kp, vp, I.F32, qn, bt, ctx, 3, g.scale), I.F32, "decode, unaligned q")
