@@ -259,8 +259,8 @@ static ag_status decode_common(const ag_kv_cache* cache, const void* q, void* ou
     a.q = q; a.out = out; a.c = c; a.bt = block_tables; a.max_pages = max_pages_per_seq;
     a.prefix_lens = nullptr; a.new_lens = nullptr; a.cu_new = nullptr; a.ctx_lens = ctx_lens;
     a.batch = batch; a.total_rows = batch; a.max_new = 1; a.max_ctx = max_ctx; a.hq = num_q_heads; a.scale = scale;
+    a.ws = workspace;
     if (decode_mfma_supported(a)) return launch_decode_mfma(a, workspace, (hipStream_t)stream);
-    if (decode_any_supported(a)) return launch_decode_any(a, workspace, (hipStream_t)stream);
     return launch_attn_general(a, (hipStream_t)stream);
 }
 

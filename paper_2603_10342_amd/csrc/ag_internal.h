@@ -44,6 +44,7 @@ struct AttnArgs {
     const int32_t* ctx_lens;      // decode only
     int batch, total_rows, max_new, max_ctx, hq;
     float scale;
+    void* ws = nullptr;           // decode: the call's workspace (host side only)
 };
 
 void set_error(const char* fmt, ...);
@@ -57,6 +58,7 @@ void prof_after(hipStream_t st);
 ag_status launch_kv_append(const CacheView& c, const void* k_new, const void* v_new, const int32_t* bt, int max_pages,
                            const int32_t* prefix_lens, const int32_t* new_lens, const int32_t* cu_new, int batch,
                            int total_new, hipStream_t st);
+// every shape without a kernel of its own; picks among the kernels below and the one-wave-per-row one
 ag_status launch_attn_general(const AttnArgs& a, hipStream_t st);
 
 // bf16, head_dim 128, page 16 matrix-core paths
@@ -69,7 +71,7 @@ ag_status launch_decode_mfma(const AttnArgs& a, void* ws, hipStream_t st);
 int       share_workgroups(int64_t f_max, hipStream_t st);
 // every other bf16 / fp32 shape with pages of 16 tokens or more
 bool      decode_any_supported(const AttnArgs& a);
-ag_status launch_decode_any(const AttnArgs& a, void* ws, hipStream_t st);
+ag_status launch_decode_any(const AttnArgs& a, hipStream_t st);
 // the whole decode step (append + attention + merge) in one launch; same shapes as the matrix-core decode
 size_t    decode_step_workspace_bytes(int batch, int hq, int d, int max_ctx);
 ag_status launch_decode_step(const AttnArgs& a, const void* k_new, const void* v_new, void* ws, hipStream_t st);

@@ -330,10 +330,10 @@ inline int64_t steps_bound(const AttnArgs& a)
 }
 
 template <typename E, int DT>
-ag_status launch(const AttnArgs& a, void* ws, hipStream_t st)
+ag_status launch(const AttnArgs& a, hipStream_t st)
 {
     const int pmax = splitk::pieces_max(a.max_ctx), blocks = head_blocks_of(a);
-    int32_t* hdr = (int32_t*)ws;
+    int32_t* hdr = (int32_t*)a.ws;
     float* ws_o = (float*)(hdr + splitk::header_ints(a.batch));
     float* ws_ml = ws_o + (size_t)a.batch * a.hq * pmax * a.c.d;
     prof_before(st);
@@ -350,11 +350,11 @@ ag_status launch(const AttnArgs& a, void* ws, hipStream_t st)
 }
 
 template <typename E>
-ag_status launch_for_dim(const AttnArgs& a, void* ws, hipStream_t st)
+ag_status launch_for_dim(const AttnArgs& a, hipStream_t st)
 {
-    if (a.c.d <= 64) return launch<E, 64>(a, ws, st);
-    if (a.c.d <= 128) return launch<E, 128>(a, ws, st);
-    return launch<E, 256>(a, ws, st);
+    if (a.c.d <= 64) return launch<E, 64>(a, st);
+    if (a.c.d <= 128) return launch<E, 128>(a, st);
+    return launch<E, 256>(a, st);
 }
 
 }  // namespace
@@ -367,9 +367,9 @@ bool decode_any_supported(const AttnArgs& a)
            (int64_t)a.batch * a.hq <= 0x7fffffff;
 }
 
-ag_status launch_decode_any(const AttnArgs& a, void* ws, hipStream_t st)
+ag_status launch_decode_any(const AttnArgs& a, hipStream_t st)
 {
-    return a.c.dtype == AG_BF16 ? launch_for_dim<__bf16>(a, ws, st) : launch_for_dim<float>(a, ws, st);
+    return a.c.dtype == AG_BF16 ? launch_for_dim<__bf16>(a, st) : launch_for_dim<float>(a, st);
 }
 
 }  // namespace ag

@@ -6,8 +6,8 @@
 // One wavefront per (row, query head).  Keys are taken 64 at a time, one per
 // lane (score = scale * q.k in fp32, then a streaming softmax: running max m,
 // running sum l, accumulator rescaled when m grows); values are accumulated
-// with lane = channel.  It is the path for fp32 caches and for shapes the
-// matrix-core kernels do not cover; it is not tuned for bandwidth.
+// with lane = channel.  It is the path for what the other kernels do not
+// cover (pages below 16 tokens, pointers off 16 bytes); it is not tuned.
 #include "ag_internal.h"
 
 namespace ag {
@@ -119,6 +119,7 @@ __global__ __launch_bounds__(256) void attn_general_kernel(AttnArgs a)
 
 ag_status launch_attn_general(const AttnArgs& a, hipStream_t st)
 {
+    if (a.ctx_lens && decode_any_supported(a)) return launch_decode_any(a, st);
     const int64_t items = (int64_t)a.total_rows * a.hq;
     const int64_t blocks = (items + 3) / 4;
     if (blocks > 0x7fffffff) { set_error("too many rows for one launch"); return AG_ERR_INVALID_ARG; }
