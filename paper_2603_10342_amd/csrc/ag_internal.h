@@ -72,6 +72,8 @@ int       share_workgroups(int64_t f_max, hipStream_t st);
 // every other bf16 / fp32 shape with pages of 16 tokens or more
 bool      decode_any_supported(const AttnArgs& a);
 ag_status launch_decode_any(const AttnArgs& a, hipStream_t st);
+bool      prefill_any_supported(const AttnArgs& a);
+ag_status launch_prefill_any(const AttnArgs& a, hipStream_t st);
 // the whole decode step (append + attention + merge) in one launch; same shapes as the matrix-core decode
 size_t    decode_step_workspace_bytes(int batch, int hq, int d, int max_ctx);
 ag_status launch_decode_step(const AttnArgs& a, const void* k_new, const void* v_new, void* ws, hipStream_t st);

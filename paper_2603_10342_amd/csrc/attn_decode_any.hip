@@ -16,8 +16,8 @@
 // Whole decode step, append included (one wave per (row, query head) before -> now): 16 fp32 sessions of 1024..4096
 // tokens at 32 / 8 heads x 128, 2760 -> 75 us (369 MB, 4.9 TB/s; split kernel 66 us); 48 bf16 sessions of 700..5000 at
 // head_dim 64, 32-token pages, 2238 -> 65 us (333 MB, 5.2 TB/s); two fp32 sessions of 300, 4 / 2 heads x 64, 106 -> 12 us.
-// head_dim below its template's DT: channels beyond head_dim read the last channel again and meet a zero query
-// (keys) or land in rows that are not stored (values).
+// head_dim below its template's DT: loads beyond head_dim repeat its last channels; keys become zeros (as the query
+// does), values land in rows that are not stored.
 #include "attn_split_common.h"
 
 namespace ag {
@@ -126,6 +126,7 @@ __global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, in
                     const int chunk = kExact ? k_chunk + 4 * kk : min(k_chunk + 4 * kk, (D >> 3) - 1);
                     x.k[2 * kk] = load16(kp + (int64_t)chunk * ps * 8);
                     x.k[2 * kk + 1] = load16(kp + (int64_t)chunk * ps * 8 + 64);
+                    if (!kExact && chunk != k_chunk + 4 * kk) x.k[2 * kk] = x.k[2 * kk + 1] = u32x4{0, 0, 0, 0};
                 }
 #pragma unroll
                 for (int mb = 0; mb < X::kV; ++mb) x.v[mb] = load16(vp + (kExact ? mb * 16 + r : min(mb * 16 + r, D - 1)) * 8);
@@ -139,6 +140,7 @@ __global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, in
                 for (int kk = 0; kk < X::kK; ++kk) {
                     const int chunk = kExact ? k_chunk + 2 * kk : min(k_chunk + 2 * kk, (D >> 3) - 1);
                     x.k[kk] = load16(kp + (int64_t)chunk * ps * 8);
+                    if (!kExact && chunk != k_chunk + 2 * kk) x.k[kk] = u32x4{0, 0, 0, 0};
                 }
 #pragma unroll
                 for (int mb = 0; mb < X::kV; ++mb) x.v[mb] = load16(vp + (kExact ? mb * 16 + r : min(mb * 16 + r, D - 1)) * 8);

@@ -120,6 +120,7 @@ __global__ __launch_bounds__(256) void attn_general_kernel(AttnArgs a)
 ag_status launch_attn_general(const AttnArgs& a, hipStream_t st)
 {
     if (a.ctx_lens && decode_any_supported(a)) return launch_decode_any(a, st);
+    if (!a.ctx_lens && prefill_any_supported(a)) return launch_prefill_any(a, st);
     const int64_t items = (int64_t)a.total_rows * a.hq;
     const int64_t blocks = (items + 3) / 4;
     if (blocks > 0x7fffffff) { set_error("too many rows for one launch"); return AG_ERR_INVALID_ARG; }

@@ -5,8 +5,8 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_helpers import DevBatch, check_close, gpu_append, gpu_decode, i32, make_cache, run_phase, to_dev
-from helpers import fresh_pools, make_batch, oracle_append
+from gpu_helpers import DevBatch, check_close, gpu_append, gpu_decode, gpu_merged, i32, make_cache, run_phase, to_dev
+from helpers import fresh_pools, make_batch, oracle_append, oracle_attn
 from oracle import oracle as O
 from paper_2603_10342_amd import inputs as I
 
@@ -81,3 +81,44 @@ def test_decode_of_a_q_that_is_not_16_byte_aligned_still_runs():
     assert q.data_ptr() % 16
     got = gpu_decode(cache, q, d_fill.bt, i32(ctx), 40, g)
     check_close(got, O.decode(kp, vp, I.F32, qn, bt, ctx, 3, g.scale), I.F32, "decode, unaligned q")
+
+
+@pytest.mark.parametrize("dtype,d,ps,hq,hkv", GEOMETRIES)
+def test_cold_then_resume_around_tile_edges(dtype, d, ps, hq, hkv):
+    """Chunks around the 32- and 64-key tiles and the 128-column workgroups, an empty one, ragged prefixes; NaN behind
+    every context."""
+    lens_a, lens_b = [33, 0, 64, 1, 150, 16], [31, 40, 65, 130, 5, 0]
+    pages = sum((a + b + ps - 1) // ps for a, b in zip(lens_a, lens_b)) + 3
+    g = I.Geometry(hq, hkv, d, ps, pages, dtype)
+    bt = I.deal_block_tables(I.rng_for(54, 0), [a + b for a, b in zip(lens_a, lens_b)], ps, pages)
+    cache = make_cache(g)
+    kp, vp = fresh_pools(g)
+    cold = make_batch(g, [0] * 6, lens_a, seed=54, bt=bt)
+    got, ref = run_phase(cache, kp, vp, cold, "cold")
+    check_close(got, ref, dtype, f"cold D={d} page={ps} {hq}/{hkv}")
+    more = make_batch(g, lens_a, lens_b, seed=54, bt=bt, stream=2)
+    got, ref = run_phase(cache, kp, vp, more, "resume")
+    check_close(got, ref, dtype, f"resume D={d} page={ps} {hq}/{hkv}")
+
+
+@pytest.mark.parametrize("dtype,d,ps", [(I.BF16, 64, 32), (I.F32, 128, 16)])
+def test_merged_queue_and_sharp_logits(dtype, d, ps):
+    """150 sessions, many without rows, with logits of standard deviation 4 (the reference maximum moves).  Queries and
+    keys of sigma 2 each: an fp32 score of 128 such products is off by about sqrt(128) 2^-24 times the sum of its terms'
+    sizes over sqrt(D), 29 here - a few 1e-6 in a weight, inside the 1e-5 gate, where sigma 4 (sum 115) would not be."""
+    rng = np.random.default_rng(55)
+    p, n = rng.integers(0, 101, size=150), rng.integers(0, 41, size=150)
+    n[rng.integers(0, 150, size=30)] = 0
+    n[[0, 63, 64, 127, 128, 149]] = [0, 40, 0, 1, 33, 0]
+    pages = int(sum((int(a + b) + ps - 1) // ps for a, b in zip(p, n))) + 40
+    g = I.Geometry(8, 2, d, ps, pages, dtype)
+    bt = I.deal_block_tables(I.rng_for(55, 0), np.maximum(p + n, 1), ps, g.num_pages)
+    fill = make_batch(g, np.zeros_like(p), p, seed=55, bt=bt)
+    chunk = make_batch(g, p, n, seed=55, bt=bt, stream=2, sigma_qk=2.0)
+    cache = make_cache(g)
+    kp, vp = fresh_pools(g)
+    for b in (fill, chunk):
+        gpu_append(cache, DevBatch(b))
+        oracle_append(kp, vp, b)
+    got, ref = gpu_merged(cache, DevBatch(chunk)), oracle_attn(kp, vp, chunk)
+    check_close(got, ref, dtype, f"queue D={d} page={ps}")
