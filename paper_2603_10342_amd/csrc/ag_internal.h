@@ -74,6 +74,9 @@ bool      decode_any_supported(const AttnArgs& a);
 ag_status launch_decode_any(const AttnArgs& a, hipStream_t st);
 bool      prefill_any_supported(const AttnArgs& a);
 ag_status launch_prefill_any(const AttnArgs& a, hipStream_t st);
+// few rows on long contexts: the keys of a query tile split over the waves of one workgroup
+bool      prefill_split_preferred(const AttnArgs& a, hipStream_t st);
+ag_status launch_prefill_split(const AttnArgs& a, hipStream_t st);
 // the whole decode step (append + attention + merge) in one launch; same shapes as the matrix-core decode
 size_t    decode_step_workspace_bytes(int batch, int hq, int d, int max_ctx);
 ag_status launch_decode_step(const AttnArgs& a, const void* k_new, const void* v_new, void* ws, hipStream_t st);

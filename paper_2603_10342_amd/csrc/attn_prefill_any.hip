@@ -354,6 +354,7 @@ bool prefill_any_supported(const AttnArgs& a)
 
 ag_status launch_prefill_any(const AttnArgs& a, hipStream_t st)
 {
+    if (prefill_split_preferred(a, st)) return launch_prefill_split(a, st);
     return a.c.dtype == AG_BF16 ? launch_for_dim<__bf16>(a, st) : launch_for_dim<float>(a, st);
 }
 

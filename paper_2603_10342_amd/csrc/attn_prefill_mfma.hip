@@ -357,11 +357,17 @@ static ag_status launch_prefill_nw(const AttnArgs& a, hipStream_t st)
 
 ag_status launch_prefill_mfma(const AttnArgs& a, hipStream_t st)
 {
+    if (prefill_split_preferred(a, st)) return launch_prefill_split(a, st);
     const int G = a.hq / a.c.hkv;
     // 256-row workgroups when chunks are long enough to fill them (a K/V tile then feeds twice the rows);
-    // 128-row workgroups keep short, ragged chunks efficient.  Groups of 2, 4 or 8 query heads share a workgroup
-    // (a group of 8 only fits the 256-row form).
-    const bool big = a.max_new >= 512;
+    // 128-row workgroups keep short, ragged chunks efficient, and spread a batch that the larger ones could not spread
+    // over 5/8 of the CUs (one chunk on 6000 tokens, whole call: 600 rows 152 -> 126 us, 1000 rows 167 -> 139; two of 600
+    // rows, 160 of the larger workgroups, 159 against 165).  Groups of 2, 4 or 8 query heads share a workgroup (a
+    // group of 8 only fits the 256-row form).
+    const int64_t rows = 256 / (G == 2 || G == 4 ? G : 1);
+    const int64_t wgs = (G == 2 || G == 4 ? a.c.hkv : a.hq) *
+                        std::min<int64_t>(a.total_rows / rows + a.batch, a.batch * ((a.max_new + rows - 1) / rows));
+    const bool big = a.max_new >= 512 && 8 * wgs >= 5 * (int64_t)stream_cus(st);
     if (G == 4) return big ? launch_prefill_nw<8, 4>(a, st) : launch_prefill_nw<4, 4>(a, st);
     if (G == 2) return big ? launch_prefill_nw<8, 2>(a, st) : launch_prefill_nw<4, 2>(a, st);
     if (G == 8) return launch_prefill_nw<8, 8>(a, st);

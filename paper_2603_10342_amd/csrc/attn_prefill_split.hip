@@ -1,0 +1,338 @@
+// Prefill of few rows on long contexts (a tool output appended to one agent's session, a handful of short prompts):
+// the keys of a query tile are split over the waves of one workgroup.  bf16 and fp32, head_dim 64 and 128, pages of 16
+// tokens or more.
+//
+// With few rows the other prefill kernels leave the chip idle: a workgroup of 128 columns walks all its keys alone
+// (211 rows at 32 / 8 heads are 56 workgroups of 98 key tiles each on 256 CUs).  Here a workgroup owns 32 columns - a
+// column is a (token, query head of the group) pair, numbered token * G + head - and its eight waves take every
+// eighth step of 32 keys, each with its own (m, l, O), which are merged through LDS at the end: four times the
+// workgroups, each an eighth as long.  Nothing goes through memory between them, so the entry point needs no workspace.
+// No wave shares its keys with another, so K and V go straight from the pages into the registers of the matrix
+// operands (no LDS stage, no barrier in the loop); K of the next step is requested as soon as the score product has
+// read this one's, V after the value product.  What bounds it is the load path of a CU (64 bytes per clock from L2: 16
+// KiB per wave and step against 512 clocks of products), about half the matrix rate; the line to the other kernels
+// is at prefill_split_preferred().
+#include <algorithm>
+#include <atomic>
+
+#include "ag_internal.h"
+#include "tile_list.h"
+
+namespace ag {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kColumns = 32;            // (token, head) pairs of a workgroup
+constexpr int kWaves = 8;               // which share its keys
+constexpr int kStep = 32;               // keys of a wave's step
+constexpr float kLog2e = 1.4426950408889634f;
+
+constexpr int o_row(int dt) { return dt + 4; }          // floats of a column's partial in LDS, padded
+constexpr int lds_bytes(int dt) { return kWaves * kColumns * (o_row(dt) + 2) * 4; }
+
+// kLo: bf16 weights as two terms (hi + lo); false keeps the rounded weights of the bf16 / 128 / 16 kernels.
+template <typename E, int DT, bool kLo>
+__global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs a, int tiles_max, int per_xcd, int64_t total_work)
+{
+    constexpr bool kBf16 = sizeof(E) == 2;
+    constexpr int kK = DT * (int)sizeof(E) / 32;    // 16-byte loads of a lane per step: keys
+    constexpr int kMb = DT / 32;
+    constexpr int kRuns = kBf16 ? 2 : 4;            // runs of keys a lane's weights fall into: 8 keys (bf16), 4 (fp32)
+    constexpr bool kQInLds = !kBf16;                // fp32 queries are twice the registers and are read a quarter as often
+    constexpr float kSlack = kBf16 ? 8.0f : 5.5f;   // how far a maximum may outgrow the reference before O is rescaled
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];       // Q in the loop (fp32), then the waves' partials
+
+    // ---- which (KV head, session, tile): the XCD a workgroup lands on owns a contiguous range of KV heads ----
+    const int xcd = blockIdx.x & 7, ord = blockIdx.x >> 3;
+    const int64_t wk = (int64_t)xcd * per_xcd + ord;
+    if (wk >= total_work) return;
+    const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv, ps = a.c.ps;
+    const int g = (int)(wk / tiles_max);
+    int s = -1, qt = 0, N = 0, P = 0, row0 = 0;
+    find_tile(a, (int)(wk % tiles_max), [G](int len) { return (int)(((int64_t)len * G + kColumns - 1) / kColumns); }, s, qt, N, P, row0);
+    if (s < 0) return;                              // beyond the batch's tiles
+    const int ctx = P + N;
+    const int64_t col0 = (int64_t)qt * kColumns;
+    const int cols = (int)min((int64_t)N * G - col0, (int64_t)kColumns);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, hi = lane >> 5;
+    const int first_token = (int)(col0 / G), last_token = (int)((col0 + cols - 1) / G);
+    const int64_t flat = col0 + min(n, cols - 1);               // columns beyond the tile repeat the last one
+    const int token = (int)(flat / G), head = (int)(flat - (int64_t)token * G);
+    const int qpos = P + token;
+    const int64_t q_row = ((int64_t)row0 + token) * hq + (int64_t)g * G + head;
+
+    const int n_steps = (P + last_token) / kStep + 1;           // of the tile
+    const int my_n = w < n_steps ? (n_steps - w - 1) / kWaves + 1 : 0;         // this wave's: steps w, w + 8, ...
+    const int first_masked = (P + first_token + 1) / kStep;     // first step holding a key that some column may not see
+
+    // ---- page ids: lane l holds those of own step l / 2 (counted from a multiple of 32), group l % 2 ----
+    const int last_grp = (ctx - 1) >> 4, gshift = a.c.ps_shift - 4, gmask = (1 << gshift) - 1;
+    const int32_t* const bt = a.bt + (int64_t)s * a.max_pages;
+    int my_pid = 0;
+    auto fetch_ids = [&](int i) { my_pid = bt[min(2 * (w + kWaves * (i + (lane >> 1))) + (lane & 1), last_grp) >> gshift]; };
+    if (my_n > 0) fetch_ids(0);
+
+    // ---- Q^T as B operand: bf16 k-step ks covers channels ks * 16 + hi * 8 .. + 7, fp32 chunk j channels 8 j + hi * 4 .. + 3
+    constexpr int kQRow = DT * 4 + 16;
+    u32x4 qf[kQInLds ? 1 : kK];
+    if constexpr (kQInLds) {
+        constexpr int kPieces = DT * 4 / 16;
+        for (int idx = tid; idx < kColumns * kPieces; idx += 64 * kWaves) {
+            const int c = idx / kPieces, p = idx - c * kPieces;
+            const int64_t f = col0 + min(c, cols - 1);
+            const int64_t r = ((int64_t)row0 + f / G) * hq + (int64_t)g * G + f % G;
+            *reinterpret_cast<u32x4*>(lds + c * kQRow + p * 16) = *reinterpret_cast<const u32x4*>((const E*)a.q + r * DT + p * 4);
+        }
+    } else {
+        const E* qp = (const E*)a.q + q_row * DT + hi * 8;
+#pragma unroll
+        for (int ks = 0; ks < kK; ++ks) qf[ks] = *reinterpret_cast<const u32x4*>(qp + ks * 16);
+    }
+
+    const int64_t block = (int64_t)DT * ps;                     // elements of one (page, head)
+    u32x4 kx[kK], vx[kRuns * kMb];
+    // the two groups' (page, head) blocks of own step i, with the groups' places inside them
+    auto group_at = [&](int i, int half, int& gi) -> int64_t {
+        gi = min(2 * (w + kWaves * i) + half, last_grp) & gmask;
+        return ((int64_t)__builtin_amdgcn_readlane(my_pid, 2 * (i & 31) + half) * hkv + g) * block;
+    };
+    auto load_k = [&](int i) {
+        int gA, gB;
+        const int64_t bA = group_at(i, 0, gA), bB = group_at(i, 1, gB);
+        const E* kp = (const E*)a.c.k + (n >> 4 ? bB + gB * 128 : bA + gA * 128) + (n & 15) * 8 + (kBf16 ? hi * ps * 8 : hi * 4);
+#pragma unroll
+        for (int j = 0; j < kK; ++j) kx[j] = *reinterpret_cast<const u32x4*>(kp + (int64_t)(kBf16 ? 2 * j : j) * ps * 8);
+    };
+    auto load_v = [&](int i) {
+        int gA, gB;
+        const int64_t bA = group_at(i, 0, gA), bB = group_at(i, 1, gB);
+        const E* vA = (const E*)a.c.v + bA + gA * 16 * DT + (hi * DT + n) * 8;
+        const E* vB = (const E*)a.c.v + bB + gB * 16 * DT + (hi * DT + n) * 8;
+#pragma unroll
+        for (int j = 0; j < kRuns; ++j)
+#pragma unroll
+            for (int mb = 0; mb < kMb; ++mb)
+                vx[j * kMb + mb] = *reinterpret_cast<const u32x4*>((j < kRuns / 2 ? vA : vB) + mb * 32 * 8 + (kBf16 ? 0 : (j & 1) * 4));
+    };
+
+    const float unit = kBf16 ? a.scale * kLog2e : a.scale;      // bf16 takes its weights as powers of two
+    float m = -INFINITY, lsum = 0.f;
+    f32x16 o[kMb];
+#pragma unroll
+    for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[mb][i] = 0.f;
+    if (kQInLds) __syncthreads();
+    if (my_n > 0) { load_k(0); load_v(0); }
+
+#pragma unroll 1
+    for (int i = 0; i < my_n; ++i) {
+        const int st = w + kWaves * i;
+        f32x16 sc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sc[e] = 0.f;
+#pragma unroll
+        for (int j = 0; j < kK; ++j) {
+            if constexpr (kBf16) {
+                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kx[j]), __builtin_bit_cast(bf16x8, qf[j]), sc, 0, 0, 0);
+            } else {
+                const f32x4 kf = __builtin_bit_cast(f32x4, kx[j]);
+                const f32x4 q4 = *reinterpret_cast<const f32x4*>(lds + n * kQRow + j * 32 + hi * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], q4[e], sc, 0, 0, 0);
+            }
+        }
+        if (i + 1 < my_n) {
+            if (((i + 1) & 31) == 0) fetch_ids(i + 1);
+            load_k(i + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (st >= first_masked) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int key = st * kStep + (e >> 2) * 8 + hi * 4 + (e & 3);
+                sc[e] = key <= qpos ? sc[e] : -INFINITY;
+            }
+        }
+        float mx = sc[0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sc[e]);
+        mx *= unit;                                             // scale > 0: max and scaling commute
+        // m is shared by the two lanes of a column: if either lane's own maximum outgrew it, combine them
+        if (__builtin_amdgcn_ballot_w64(mx > m + kSlack) != 0) {
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m, mx);
+            const float alpha = m_new == -INFINITY ? 1.f : kBf16 ? __builtin_amdgcn_exp2f(m - m_new) : expf(m - m_new);
+            lsum *= alpha;
+#pragma unroll
+            for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) o[mb][e] *= alpha;
+            m = m_new;
+        }
+        const float m_ref = m == -INFINITY ? 0.f : m;           // (a column may see none of this wave's keys so far)
+        if (ctx < (st + 1) * kStep) {                           // slots past the last token may hold anything, NaN included
+#pragma unroll
+            for (int j = 0; j < kRuns; ++j) {
+                const int keep = ctx - (st * kStep + j * (kBf16 ? 16 : 8) + hi * 4);
+#pragma unroll
+                for (int mb = 0; mb < kMb; ++mb) {
+                    u32x4& x = vx[j * kMb + mb];
+                    if constexpr (kBf16) {                      // elements 0..3: tokens + j, elements 4..7: + 8 + j
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            x[e] &= (2 * e < keep ? 0xFFFFu : 0u) | (2 * e + 1 < keep ? 0xFFFF0000u : 0u);
+                            x[2 + e] &= (2 * e + 8 < keep ? 0xFFFFu : 0u) | (2 * e + 9 < keep ? 0xFFFF0000u : 0u);
+                        }
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) x[e] = e < keep ? x[e] : 0u;
+                    }
+                }
+            }
+        }
+        if constexpr (kBf16) {
+            bf16x8 ph[2], pl[2];
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) {
+                const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[e], unit, -m_ref)), p1 = __builtin_amdgcn_exp2f(fmaf(sc[e + 1], unit, -m_ref));
+                const bf16x2 pr = {(__bf16)p0, (__bf16)p1};
+                ph[e >> 3][e & 7] = pr[0];
+                ph[e >> 3][(e & 7) + 1] = pr[1];
+                if constexpr (kLo) {
+                    pl[e >> 3][e & 7] = (__bf16)(p0 - (float)pr[0]);
+                    pl[e >> 3][(e & 7) + 1] = (__bf16)(p1 - (float)pr[1]);
+                    lsum += p0 + p1;
+                } else {
+                    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+                    lsum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum, false);       // the weights as rounded
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int mb = 0; mb < kMb; ++mb) {
+                    const bf16x8 v = __builtin_bit_cast(bf16x8, vx[j * kMb + mb]);
+                    if constexpr (kLo) o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pl[j], o[mb], 0, 0, 0);
+                    o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, ph[j], o[mb], 0, 0, 0);
+                }
+        } else {
+            float psum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                sc[e] = expf(fmaf(sc[e], unit, -m_ref));
+                psum += sc[e];
+            }
+            lsum += psum;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int mb = 0; mb < kMb; ++mb)
+                        o[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(f32x4, vx[j * kMb + mb])[e], sc[j * 4 + e], o[mb], 0, 0, 0);
+        }
+        if (i + 1 < my_n) load_v(i + 1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    // ---- the waves' partials through LDS; o[mb][q4 * 4 + e] is O^T[channel mb * 32 + q4 * 8 + hi * 4 + e][column n] ----
+    lsum += __shfl_xor(lsum, 32);
+    if (kQInLds) __syncthreads();                               // Q has been read
+    float* const s_o = reinterpret_cast<float*>(lds);           // [wave][column][o_row]
+    float* const s_m = s_o + kWaves * kColumns * o_row(DT);
+    float* const s_l = s_m + kWaves * kColumns;
+#pragma unroll
+    for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const f32x4 x = {o[mb][q4 * 4], o[mb][q4 * 4 + 1], o[mb][q4 * 4 + 2], o[mb][q4 * 4 + 3]};
+            *reinterpret_cast<f32x4*>(s_o + (w * kColumns + n) * o_row(DT) + mb * 32 + q4 * 8 + hi * 4) = x;
+        }
+    if (hi == 0) { s_m[w * kColumns + n] = m; s_l[w * kColumns + n] = lsum; }
+    __syncthreads();
+    auto power = [](float x) { return kBf16 ? __builtin_amdgcn_exp2f(x) : expf(x); };
+    for (int idx = tid; idx < cols * (DT / 8); idx += 64 * kWaves) {
+        const int c = idx / (DT / 8), d = (idx - c * (DT / 8)) * 8;
+        float ms = s_m[c];                                      // wave 0 has the first keys, which every column sees
+#pragma unroll
+        for (int ww = 1; ww < kWaves; ++ww) ms = fmaxf(ms, s_m[ww * kColumns + c]);
+        float l = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ww = 0; ww < kWaves; ++ww) {
+            const float f = power(s_m[ww * kColumns + c] - ms);       // a wave that saw no key has m = -inf -> 0
+            l += f * s_l[ww * kColumns + c];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] += f * s_o[(ww * kColumns + c) * o_row(DT) + d + e];
+        }
+        const float inv = 1.0f / l;
+        const int64_t f = col0 + c;
+        E* out = (E*)a.out + (((int64_t)row0 + f / G) * hq + (int64_t)g * G + f % G) * DT + d;
+        E y[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] = (E)(acc[e] * inv);
+#pragma unroll
+        for (int e = 0; e < (int)sizeof(E) / 2; ++e) reinterpret_cast<u32x4*>(out)[e] = reinterpret_cast<const u32x4*>(y)[e];
+    }
+}
+
+int64_t tiles_bound(const AttnArgs& a, int columns)
+{
+    const int64_t G = a.hq / a.c.hkv;
+    return std::min<int64_t>((int64_t)a.total_rows * G / columns + a.batch, (int64_t)a.batch * ((a.max_new * G + columns - 1) / columns));
+}
+
+template <typename E, int DT, bool kLo>
+ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
+{
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set.load()) {
+        ag_status e = hip_check(hipFuncSetAttribute((const void*)prefill_split_kernel<E, DT, kLo>,
+                                                    hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(DT)),
+                                "hipFuncSetAttribute(prefill split)");
+        if (e) return e;
+        attr_set.store(true);
+    }
+    const int64_t tiles_max = tiles_bound(a, kColumns), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
+    prof_before(st);
+    hipLaunchKernelGGL((prefill_split_kernel<E, DT, kLo>), dim3((unsigned)(per_xcd * 8)), dim3(64 * kWaves), lds_bytes(DT), st, a,
+                       (int)tiles_max, (int)per_xcd, total);
+    prof_after(st);
+    return hip_check(hipGetLastError(), "prefill launch");
+}
+
+}  // namespace
+
+// Whether the batch's query tiles are too few for the other kernels.  Counted in workgroups of 32 columns per CU of the
+// stream (one is resident at a time): up to 2 for the bf16 / 128 / 16 shape, 3 for other bf16 shapes (whose weights cost
+// their kernel half again the products), 10 for fp32 (its products are so slow that the load path does not bind).
+// Measured at 32 / 8 heads on 256 CUs, append included, the other kernel -> this one: bf16 / 128 / 16, one chunk of
+// 5 rows on 6007 tokens (8 workgroups) 114 -> 39 us, 211 rows (216) 119 -> 45, 400 rows (400) 122 -> 80; four chunks of
+// 150 rows on 3000 (608) 70 -> 70, eight of 100 on 2000 (832) 57 -> 71.  bf16 / 64 / 64: eight of 40 on 2000 (320) 49 ->
+// 30, 32 of 20 on 1000 (768) 31 -> 31, two prompts of 1000 (2000) 41 -> 50.  fp32 / 128: one chunk of 211 rows on 6007
+// 873 -> 227, two prompts of 1000 (2000) 276 -> 216, four of 300..1500 (3600) 377 -> 461.
+bool prefill_split_preferred(const AttnArgs& a, hipStream_t st)
+{
+    if ((a.c.d != 64 && a.c.d != 128) || a.c.ps < 16 ||
+        ((uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 != 0) return false;
+    const int per_cu = a.c.dtype == AG_F32 ? 10 : a.c.d == 128 && a.c.ps == 16 ? 2 : 3;
+    return a.c.hkv * tiles_bound(a, kColumns) <= (int64_t)per_cu * stream_cus(st);
+}
+
+ag_status launch_prefill_split(const AttnArgs& a, hipStream_t st)
+{
+    if (a.c.dtype == AG_F32) return a.c.d == 64 ? launch_kernel<float, 64, false>(a, st) : launch_kernel<float, 128, false>(a, st);
+    if (a.c.d == 64) return launch_kernel<__bf16, 64, true>(a, st);
+    return a.c.ps == 16 ? launch_kernel<__bf16, 128, false>(a, st) : launch_kernel<__bf16, 128, true>(a, st);
+}
+
+}  // namespace ag

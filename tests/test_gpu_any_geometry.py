@@ -8,6 +8,7 @@ import torch
 from gpu_helpers import DevBatch, check_close, gpu_append, gpu_decode, gpu_merged, i32, make_cache, run_phase, to_dev
 from helpers import fresh_pools, make_batch, oracle_append, oracle_attn
 from oracle import oracle as O
+from paper_2603_10342_amd import binding as B
 from paper_2603_10342_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
@@ -99,6 +100,37 @@ def test_cold_then_resume_around_tile_edges(dtype, d, ps, hq, hkv):
     more = make_batch(g, lens_a, lens_b, seed=54, bt=bt, stream=2)
     got, ref = run_phase(cache, kp, vp, more, "resume")
     check_close(got, ref, dtype, f"resume D={d} page={ps} {hq}/{hkv}")
+
+
+# Query tiles that do not fill the chip take a kernel that splits the keys over a workgroup's waves (head_dim 64 and
+# 128; every call of the tests above, and of the small tests of the bf16 / 128 / 16 shape); on a stream of 8 CUs the same
+# calls count as many tiles and take the kernels that the whole device uses for large batches.
+@pytest.mark.parametrize("dtype,d,ps,hq,hkv", [GEOMETRIES[i] for i in (0, 1, 2, 7, 8, 9, 13)] + [
+    (I.BF16, 128, 16, 8, 2), (I.BF16, 128, 16, 3, 1), (I.BF16, 128, 16, 4, 2), (I.BF16, 128, 16, 8, 1)])
+@pytest.mark.parametrize("cus_per_xcd", [0, 1])
+def test_split_and_whole_tiles_agree_with_the_oracle(dtype, d, ps, hq, hkv, cus_per_xcd):
+    lens_a, lens_b = [33, 0, 600, 1, 150, 290], [31, 40, 65, 530, 5, 0]
+    pages = sum((a + b + ps - 1) // ps for a, b in zip(lens_a, lens_b)) + 3
+    g = I.Geometry(hq, hkv, d, ps, pages, dtype)
+    bt = I.deal_block_tables(I.rng_for(56, 0), [a + b for a, b in zip(lens_a, lens_b)], ps, pages)
+    kp, vp = fresh_pools(g)
+    cold = make_batch(g, [0] * 6, lens_a, seed=56, bt=bt)
+    more = make_batch(g, lens_a, lens_b, seed=56, bt=bt, stream=2)
+    stream = None
+    if cus_per_xcd:
+        info = B.ag_device_info()
+        stream = B.ag_stream_create_cumask(B.ag_cumask_build(info["num_cus"], 8, 0, cus_per_xcd))
+    try:
+        cache = make_cache(g)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(torch.cuda.ExternalStream(stream) if stream else torch.cuda.current_stream()):
+            for b, kind in ((cold, "cold"), (more, "resume")):
+                got, ref = run_phase(cache, kp, vp, b, kind)
+                check_close(got, ref, dtype, f"{kind} D={d} page={ps} {hq}/{hkv} on {cus_per_xcd} CUs per XCD")
+    finally:
+        torch.cuda.synchronize()
+        if stream:
+            B.ag_stream_destroy(stream)
 
 
 @pytest.mark.parametrize("dtype,d,ps", [(I.BF16, 64, 32), (I.F32, 128, 16)])
