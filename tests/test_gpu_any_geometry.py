@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_helpers import DevBatch, check_close, gpu_append, gpu_decode, gpu_merged, i32, make_cache, run_phase, to_dev
+from gpu_helpers import DevBatch, check_close, gpu_append, gpu_decode, gpu_merged, i32, make_cache, pools_match, run_phase, to_dev
 from helpers import fresh_pools, make_batch, oracle_append, oracle_attn
 from oracle import oracle as O
 from paper_2603_10342_amd import binding as B
@@ -100,6 +100,7 @@ def test_cold_then_resume_around_tile_edges(dtype, d, ps, hq, hkv):
     more = make_batch(g, lens_a, lens_b, seed=54, bt=bt, stream=2)
     got, ref = run_phase(cache, kp, vp, more, "resume")
     check_close(got, ref, dtype, f"resume D={d} page={ps} {hq}/{hkv}")
+    pools_match(cache, kp, vp, dtype)
 
 
 # Query tiles that do not fill the chip take a kernel that splits the keys over a workgroup's waves (head_dim 64 and
