@@ -168,7 +168,8 @@ def _i32(t: Optional[torch.Tensor]):
 def _stream(stream) -> Optional[int]:
     """None -> torch's current stream; an int is a raw hipStream_t; a torch stream gives its handle."""
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream or None
+        # the raw handle: building a torch.cuda.Stream object around it takes 2.9 us a call, this 0.2
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None
