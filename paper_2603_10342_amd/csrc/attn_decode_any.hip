@@ -47,35 +47,24 @@ struct SubStep {
     u32x4 k[kK], v[kV];
 };
 
-template <typename E, int DT, bool kExact>
-__global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, int32_t* __restrict__ hdr,
-                                                                  float* __restrict__ ws_o, float* __restrict__ ws_ml,
-                                                                  int pmax, int head_blocks)
+template <typename E, int DT>
+constexpr int q_row() { return DT * (int)sizeof(E) + 16; }      // bytes of a query row in LDS, padded
+
+// One wave's part of a segment - steps my_u .. my_u + my_n - 1 (at most 32) of (session s, KV head g, heads h0 .. h0 + nh - 1
+// of its group), whose context has ctx tokens: running maximum, sum and O^T of the heads.  Contains one workgroup barrier (Q
+// goes through LDS).
+template <typename E, int DT, bool kExact, int kThreads>
+__device__ __forceinline__ void attend_steps(const AttnArgs& a, int s, int g, int h0, int nh, int ctx, int my_u, int my_n,
+                                             unsigned char* s_q, float& m, float& lsum, f32x4 (&o)[DT / 16])
 {
     using X = SubStep<E, DT>;
     constexpr bool kBf16 = X::kBf16;
     constexpr int kSub = 32 / X::kTok;                           // sub-steps of a step
     constexpr bool kTwoInFlight = X::kK + X::kV <= 16;
-    constexpr int kChan = DT < 128 ? DT : 128;                   // channels the waves' results go through LDS at a time
-    constexpr int kQRow = DT * (int)sizeof(E) + 16;
-    __shared__ float s_o[4][kCols][kChan];
-    __shared__ float s_m[4][kCols];
-    __shared__ float s_l[4][kCols];
-    __shared__ __attribute__((aligned(16))) unsigned char s_q[kCols * kQRow];
-
-    const int B = a.batch, hkv = a.c.hkv, hq = a.hq, G = hq / hkv;
-    const int heads = hkv * head_blocks;                         // pairs of a session
+    constexpr int kQRow = q_row<E, DT>();
+    const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv;
     const int D = kExact ? DT : a.c.d, ps = a.c.ps;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wg = blockIdx.x;
-
-    splitk::Share sh;
-    if (!splitk::find_share<true>(a.ctx_lens, B, heads, hdr, sh)) return;
-    int s = sh.s, base = sh.base, ctx = sh.ctx;
-    int n = steps_of(ctx);
-    int pair = (sh.f0 - base) / n;                               // (KV head, block of its heads)
-    int u = (sh.f0 - base) - pair * n;                           // first step inside the pair
 
     const int r = lane & 15, c = lane >> 4;
     const int gshift = a.c.ps_shift - 4, gmask = (1 << gshift) - 1;       // 16-token groups of a page
@@ -89,6 +78,196 @@ __global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, in
     const float unit = kBf16 ? a.scale * kLog2e : a.scale;       // bf16 takes its weights as powers of two
     auto power = [](float x) { return kBf16 ? __builtin_amdgcn_exp2f(x) : expf(x); };
 
+    const int last_grp = (ctx - 1) >> 4;
+    int my_pid = 0;                                          // lane i: page of the wave's group i
+    if (my_n > 0) my_pid = a.bt[(int64_t)s * a.max_pages + (min(2 * my_u + lane, last_grp) >> gshift)];
+    {
+        constexpr int kPieces = DT * (int)sizeof(E) / 16;    // of a query row
+        const int pieces = D * (int)sizeof(E) / 16;
+        const unsigned char* qs = (const unsigned char*)a.q + ((int64_t)s * hq + (int64_t)g * G + h0) * D * (int)sizeof(E);
+        for (int idx = tid; idx < kCols * kPieces; idx += kThreads) {
+            const int head = idx / kPieces, p = idx - head * kPieces;
+            u32x4 x = {0, 0, 0, 0};
+            if (head < nh && p < pieces) x = *reinterpret_cast<const u32x4*>(qs + ((int64_t)head * pieces + p) * 16);
+            *reinterpret_cast<u32x4*>(s_q + head * kQRow + p * 16) = x;
+        }
+    }
+    const E* kpool = (const E*)a.c.k;
+    const E* vpool = (const E*)a.c.v;
+    auto load = [&](X& x, int i) {                           // sub-step i of the wave
+        if constexpr (kBf16) {
+            const int64_t pA = __builtin_amdgcn_readlane(my_pid, 2 * i), pB = __builtin_amdgcn_readlane(my_pid, 2 * i + 1);
+            const int gA = min(2 * (my_u + i), last_grp) & gmask, gB = min(2 * (my_u + i) + 1, last_grp) & gmask;
+            const int64_t baseA = (pA * hkv + g) * block, baseB = (pB * hkv + g) * block;
+            const E* kp = kpool + (r >> 3 ? baseB + gB * 128 : baseA + gA * 128) + k_slot;
+            const E* vp = vpool + (c >> 1 ? baseB + gB * 16 * D : baseA + gA * 16 * D) + v_lane;
+#pragma unroll
+            for (int kk = 0; kk < X::kK / 2; ++kk) {
+                const int chunk = kExact ? k_chunk + 4 * kk : min(k_chunk + 4 * kk, (D >> 3) - 1);
+                x.k[2 * kk] = load16(kp + (int64_t)chunk * ps * 8);
+                x.k[2 * kk + 1] = load16(kp + (int64_t)chunk * ps * 8 + 64);
+                if (!kExact && chunk != k_chunk + 4 * kk) x.k[2 * kk] = x.k[2 * kk + 1] = u32x4{0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int mb = 0; mb < X::kV; ++mb) x.v[mb] = load16(vp + (kExact ? mb * 16 + r : min(mb * 16 + r, D - 1)) * 8);
+        } else {
+            const int64_t p = __builtin_amdgcn_readlane(my_pid, i);
+            const int gi = min(2 * my_u + i, last_grp) & gmask;
+            const int64_t at = (p * hkv + g) * block;
+            const E* kp = kpool + at + gi * 128 + k_slot;
+            const E* vp = vpool + at + gi * 16 * D + v_lane;
+#pragma unroll
+            for (int kk = 0; kk < X::kK; ++kk) {
+                const int chunk = kExact ? k_chunk + 2 * kk : min(k_chunk + 2 * kk, (D >> 3) - 1);
+                x.k[kk] = load16(kp + (int64_t)chunk * ps * 8);
+                if (!kExact && chunk != k_chunk + 2 * kk) x.k[kk] = u32x4{0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int mb = 0; mb < X::kV; ++mb) x.v[mb] = load16(vp + (kExact ? mb * 16 + r : min(mb * 16 + r, D - 1)) * 8);
+        }
+    };
+
+    m = -INFINITY;
+    lsum = 0.0f;
+#pragma unroll
+    for (int mb = 0; mb < DT / 16; ++mb) o[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const unsigned char* q_lane = s_q + r * kQRow + c * 16;
+
+    auto compute = [&](X& x, int i) {
+        constexpr int kScores = kBf16 ? 8 : 4;
+        const int tok0 = my_u * 32 + i * X::kTok;
+        const int tokb = kBf16 ? tok0 + (c >> 1) * 16 + (c & 1) * 4 : tok0 + c * 4;
+        const int keep = ctx - tokb;                         // token tokb + j exists iff j < keep
+        f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
+        float xs[kScores];
+        if constexpr (kBf16) {
+#pragma unroll
+            for (int kk = 0; kk < X::kK / 2; ++kk) {
+                const bf16x8 qk = *reinterpret_cast<const bf16x8*>(q_lane + kk * 64);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x.k[2 * kk]), qk, s1, 0, 0, 0);
+                s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x.k[2 * kk + 1]), qk, s2, 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                xs[j] = j < keep ? s1[j] * unit : -INFINITY;
+                xs[4 + j] = 8 + j < keep ? s2[j] * unit : -INFINITY;
+            }
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < X::kK; ++kk) {
+                const f32x4 qk = *reinterpret_cast<const f32x4*>(q_lane + kk * 64);
+                const f32x4 kv = __builtin_bit_cast(f32x4, x.k[kk]);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[0], qk[0], s1, 0, 0, 0);
+                s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[1], qk[1], s2, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[2], qk[2], s1, 0, 0, 0);
+                s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[3], qk[3], s2, 0, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) xs[j] = j < keep ? (s1[j] + s2[j]) * unit : -INFINITY;
+        }
+        float mx = fmaxf(fmaxf(xs[0], xs[1]), fmaxf(xs[2], xs[3]));
+        if constexpr (kBf16) mx = fmaxf(mx, fmaxf(fmaxf(xs[4], xs[5]), fmaxf(xs[6], xs[7])));
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m, mx);
+        // (fp32: the second sub-step of a context's last step may hold no token)
+        const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = power(m - m_ref);
+        float p[kScores], psum = 0.f;
+#pragma unroll
+        for (int j = 0; j < kScores; ++j) { p[j] = power(xs[j] - m_ref); psum += p[j]; }
+        lsum = lsum * alpha + psum;
+        m = m_new;
+        if (tok0 + X::kTok > ctx) {          // slots past the last token may hold anything, NaN included
+#pragma unroll
+            for (int mb = 0; mb < X::kV; ++mb) {
+                if constexpr (kBf16) {
+                    x.v[mb] = __builtin_bit_cast(u32x4, splitk::keep_quads(__builtin_bit_cast(bf16x8, x.v[mb]), keep, keep - 8));
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x.v[mb][j] = j < keep ? x.v[mb][j] : 0u;
+                }
+            }
+        }
+        if constexpr (kBf16) {
+            bf16x8 hi, lo;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { hi[j] = (__bf16)p[j]; lo[j] = (__bf16)(p[j] - (float)hi[j]); }
+#pragma unroll
+            for (int mb = 0; mb < X::kV; ++mb) {
+                const bf16x8 v = __builtin_bit_cast(bf16x8, x.v[mb]);
+                o[mb] *= alpha;
+                o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, lo, o[mb], 0, 0, 0);
+                o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, hi, o[mb], 0, 0, 0);
+            }
+        } else {
+#pragma unroll
+            for (int mb = 0; mb < X::kV; ++mb) o[mb] *= alpha;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int mb = 0; mb < X::kV; ++mb)
+                    o[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f32x4, x.v[mb])[j], p[j], o[mb], 0, 0, 0);
+        }
+    };
+
+    const int subs = my_n * kSub;
+    if constexpr (kTwoInFlight) {
+        X x0, x1;
+        if (subs > 0) load(x0, 0);
+        __syncthreads();                                     // Q is in LDS
+#pragma unroll 1
+        for (int i = 0; i < subs; i += 2) {
+            if (i + 1 < subs) load(x1, i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(x0, i);
+            if (i + 2 < subs) load(x0, i + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + 1 < subs) compute(x1, i + 1);
+        }
+    } else {
+        X x;
+        __syncthreads();
+#pragma unroll 1
+        for (int i = 0; i < subs; ++i) {
+            load(x, i);
+            __builtin_amdgcn_sched_barrier(0);               // all loads in flight before anything waits
+            compute(x, i);
+        }
+    }
+    lsum += __shfl_xor(lsum, 16);
+    lsum += __shfl_xor(lsum, 32);
+}
+
+template <typename E, int DT, bool kExact>
+__global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, int32_t* __restrict__ hdr,
+                                                                  float* __restrict__ ws_o, float* __restrict__ ws_ml,
+                                                                  int pmax, int head_blocks)
+{
+    constexpr bool kBf16 = sizeof(E) == 2;
+    constexpr int kChan = DT < 128 ? DT : 128;                   // channels the waves' results go through LDS at a time
+    __shared__ float s_o[4][kCols][kChan];
+    __shared__ float s_m[4][kCols];
+    __shared__ float s_l[4][kCols];
+    __shared__ __attribute__((aligned(16))) unsigned char s_q[kCols * q_row<E, DT>()];
+
+    const int B = a.batch, hkv = a.c.hkv, hq = a.hq, G = hq / hkv;
+    const int heads = hkv * head_blocks;                         // pairs of a session
+    const int D = kExact ? DT : a.c.d;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wg = blockIdx.x;
+
+    splitk::Share sh;
+    if (!splitk::find_share<true>(a.ctx_lens, B, heads, hdr, sh)) return;
+    int s = sh.s, base = sh.base, ctx = sh.ctx;
+    int n = steps_of(ctx);
+    int pair = (sh.f0 - base) / n;                               // (KV head, block of its heads)
+    int u = (sh.f0 - base) - pair * n;                           // first step inside the pair
+
+    const int r = lane & 15, c = lane >> 4;
+    auto power = [](float x) { return kBf16 ? __builtin_amdgcn_exp2f(x) : expf(x); };
+
     for (int f = sh.f0; f < sh.f1 && s < B;) {                   // one segment per pass; every value here is uniform
         const int k = min(n - u, sh.f1 - f);
         if (k <= 0) break;                                       // (only if the lengths changed under the kernel)
@@ -98,165 +277,9 @@ __global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, in
         const int my_u = u + w * per;
         const int my_n = max(0, min(per, k - w * per));
 
-        const int last_grp = (ctx - 1) >> 4;
-        int my_pid = 0;                                          // lane i: page of the wave's group i
-        if (my_n > 0) my_pid = a.bt[(int64_t)s * a.max_pages + (min(2 * my_u + lane, last_grp) >> gshift)];
-        {
-            constexpr int kPieces = DT * (int)sizeof(E) / 16;    // of a query row
-            const int pieces = D * (int)sizeof(E) / 16;
-            const unsigned char* qs = (const unsigned char*)a.q + ((int64_t)s * hq + (int64_t)g * G + h0) * D * (int)sizeof(E);
-            for (int idx = tid; idx < kCols * kPieces; idx += 256) {
-                const int head = idx / kPieces, p = idx - head * kPieces;
-                u32x4 x = {0, 0, 0, 0};
-                if (head < nh && p < pieces) x = *reinterpret_cast<const u32x4*>(qs + ((int64_t)head * pieces + p) * 16);
-                *reinterpret_cast<u32x4*>(s_q + head * kQRow + p * 16) = x;
-            }
-        }
-        const E* kpool = (const E*)a.c.k;
-        const E* vpool = (const E*)a.c.v;
-        auto load = [&](X& x, int i) {                           // sub-step i of the wave
-            if constexpr (kBf16) {
-                const int64_t pA = __builtin_amdgcn_readlane(my_pid, 2 * i), pB = __builtin_amdgcn_readlane(my_pid, 2 * i + 1);
-                const int gA = min(2 * (my_u + i), last_grp) & gmask, gB = min(2 * (my_u + i) + 1, last_grp) & gmask;
-                const int64_t baseA = (pA * hkv + g) * block, baseB = (pB * hkv + g) * block;
-                const E* kp = kpool + (r >> 3 ? baseB + gB * 128 : baseA + gA * 128) + k_slot;
-                const E* vp = vpool + (c >> 1 ? baseB + gB * 16 * D : baseA + gA * 16 * D) + v_lane;
-#pragma unroll
-                for (int kk = 0; kk < X::kK / 2; ++kk) {
-                    const int chunk = kExact ? k_chunk + 4 * kk : min(k_chunk + 4 * kk, (D >> 3) - 1);
-                    x.k[2 * kk] = load16(kp + (int64_t)chunk * ps * 8);
-                    x.k[2 * kk + 1] = load16(kp + (int64_t)chunk * ps * 8 + 64);
-                    if (!kExact && chunk != k_chunk + 4 * kk) x.k[2 * kk] = x.k[2 * kk + 1] = u32x4{0, 0, 0, 0};
-                }
-#pragma unroll
-                for (int mb = 0; mb < X::kV; ++mb) x.v[mb] = load16(vp + (kExact ? mb * 16 + r : min(mb * 16 + r, D - 1)) * 8);
-            } else {
-                const int64_t p = __builtin_amdgcn_readlane(my_pid, i);
-                const int gi = min(2 * my_u + i, last_grp) & gmask;
-                const int64_t at = (p * hkv + g) * block;
-                const E* kp = kpool + at + gi * 128 + k_slot;
-                const E* vp = vpool + at + gi * 16 * D + v_lane;
-#pragma unroll
-                for (int kk = 0; kk < X::kK; ++kk) {
-                    const int chunk = kExact ? k_chunk + 2 * kk : min(k_chunk + 2 * kk, (D >> 3) - 1);
-                    x.k[kk] = load16(kp + (int64_t)chunk * ps * 8);
-                    if (!kExact && chunk != k_chunk + 2 * kk) x.k[kk] = u32x4{0, 0, 0, 0};
-                }
-#pragma unroll
-                for (int mb = 0; mb < X::kV; ++mb) x.v[mb] = load16(vp + (kExact ? mb * 16 + r : min(mb * 16 + r, D - 1)) * 8);
-            }
-        };
-
-        float m = -INFINITY, lsum = 0.0f;
+        float m, lsum;
         f32x4 o[DT / 16];
-#pragma unroll
-        for (int mb = 0; mb < DT / 16; ++mb) o[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const unsigned char* q_lane = s_q + r * kQRow + c * 16;
-
-        auto compute = [&](X& x, int i) {
-            constexpr int kScores = kBf16 ? 8 : 4;
-            const int tok0 = my_u * 32 + i * X::kTok;
-            const int tokb = kBf16 ? tok0 + (c >> 1) * 16 + (c & 1) * 4 : tok0 + c * 4;
-            const int keep = ctx - tokb;                         // token tokb + j exists iff j < keep
-            f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
-            float xs[kScores];
-            if constexpr (kBf16) {
-#pragma unroll
-                for (int kk = 0; kk < X::kK / 2; ++kk) {
-                    const bf16x8 qk = *reinterpret_cast<const bf16x8*>(q_lane + kk * 64);
-                    s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x.k[2 * kk]), qk, s1, 0, 0, 0);
-                    s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x.k[2 * kk + 1]), qk, s2, 0, 0, 0);
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    xs[j] = j < keep ? s1[j] * unit : -INFINITY;
-                    xs[4 + j] = 8 + j < keep ? s2[j] * unit : -INFINITY;
-                }
-            } else {
-#pragma unroll
-                for (int kk = 0; kk < X::kK; ++kk) {
-                    const f32x4 qk = *reinterpret_cast<const f32x4*>(q_lane + kk * 64);
-                    const f32x4 kv = __builtin_bit_cast(f32x4, x.k[kk]);
-                    s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[0], qk[0], s1, 0, 0, 0);
-                    s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[1], qk[1], s2, 0, 0, 0);
-                    s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[2], qk[2], s1, 0, 0, 0);
-                    s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[3], qk[3], s2, 0, 0, 0);
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) xs[j] = j < keep ? (s1[j] + s2[j]) * unit : -INFINITY;
-            }
-            float mx = fmaxf(fmaxf(xs[0], xs[1]), fmaxf(xs[2], xs[3]));
-            if constexpr (kBf16) mx = fmaxf(mx, fmaxf(fmaxf(xs[4], xs[5]), fmaxf(xs[6], xs[7])));
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float m_new = fmaxf(m, mx);
-            // (fp32: the second sub-step of a context's last step may hold no token)
-            const float m_ref = m_new == -INFINITY ? 0.f : m_new;
-            const float alpha = power(m - m_ref);
-            float p[kScores], psum = 0.f;
-#pragma unroll
-            for (int j = 0; j < kScores; ++j) { p[j] = power(xs[j] - m_ref); psum += p[j]; }
-            lsum = lsum * alpha + psum;
-            m = m_new;
-            if (tok0 + X::kTok > ctx) {          // slots past the last token may hold anything, NaN included
-#pragma unroll
-                for (int mb = 0; mb < X::kV; ++mb) {
-                    if constexpr (kBf16) {
-                        x.v[mb] = __builtin_bit_cast(u32x4, splitk::keep_quads(__builtin_bit_cast(bf16x8, x.v[mb]), keep, keep - 8));
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) x.v[mb][j] = j < keep ? x.v[mb][j] : 0u;
-                    }
-                }
-            }
-            if constexpr (kBf16) {
-                bf16x8 hi, lo;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) { hi[j] = (__bf16)p[j]; lo[j] = (__bf16)(p[j] - (float)hi[j]); }
-#pragma unroll
-                for (int mb = 0; mb < X::kV; ++mb) {
-                    const bf16x8 v = __builtin_bit_cast(bf16x8, x.v[mb]);
-                    o[mb] *= alpha;
-                    o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, lo, o[mb], 0, 0, 0);
-                    o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, hi, o[mb], 0, 0, 0);
-                }
-            } else {
-#pragma unroll
-                for (int mb = 0; mb < X::kV; ++mb) o[mb] *= alpha;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int mb = 0; mb < X::kV; ++mb)
-                        o[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f32x4, x.v[mb])[j], p[j], o[mb], 0, 0, 0);
-            }
-        };
-
-        const int subs = my_n * kSub;
-        if constexpr (kTwoInFlight) {
-            X x0, x1;
-            if (subs > 0) load(x0, 0);
-            __syncthreads();                                     // Q is in LDS
-#pragma unroll 1
-            for (int i = 0; i < subs; i += 2) {
-                if (i + 1 < subs) load(x1, i + 1);
-                __builtin_amdgcn_sched_barrier(0);
-                compute(x0, i);
-                if (i + 2 < subs) load(x0, i + 2);
-                __builtin_amdgcn_sched_barrier(0);
-                if (i + 1 < subs) compute(x1, i + 1);
-            }
-        } else {
-            X x;
-            __syncthreads();
-#pragma unroll 1
-            for (int i = 0; i < subs; ++i) {
-                load(x, i);
-                __builtin_amdgcn_sched_barrier(0);               // all loads in flight before anything waits
-                compute(x, i);
-            }
-        }
-        lsum += __shfl_xor(lsum, 16);
-        lsum += __shfl_xor(lsum, 32);
+        attend_steps<E, DT, kExact, 256>(a, s, g, h0, nh, ctx, my_u, my_n, s_q, m, lsum, o);
 
         // o[mb][i] is O^T[channel mb * 16 + c * 4 + i][head r]; the four waves are merged in LDS, kChan channels at a time
         const int first_wg = (base + pair * n) / sh.q;           // the pair's segments are numbered from this workgroup
@@ -306,6 +329,66 @@ __global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, in
     }
 }
 
+// A batch of few, short contexts: one workgroup of eight waves per pair, which shares the pair's steps and writes the
+// result itself - no plan, no partials, no merge launch (see direct_preferred()).
+constexpr int kDirectWaves = 8;
+constexpr int kDirectMaxTokens = kDirectWaves * 32 * 32;         // page ids of a wave's steps: two per step, one per lane
+
+template <typename E, int DT, bool kExact>
+__global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel(AttnArgs a, int head_blocks)
+{
+    constexpr bool kBf16 = sizeof(E) == 2;
+    constexpr int kChan = 64, kThreads = 64 * kDirectWaves;
+    __shared__ float s_o[kDirectWaves][kCols][kChan];
+    __shared__ float s_m[kDirectWaves][kCols];
+    __shared__ float s_l[kDirectWaves][kCols];
+    __shared__ __attribute__((aligned(16))) unsigned char s_q[kCols * q_row<E, DT>()];
+    const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv, D = kExact ? DT : a.c.d;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int heads = hkv * head_blocks;
+    const int s = blockIdx.x / heads, pair = blockIdx.x - s * heads;
+    const int g = pair / head_blocks, h0 = (pair - g * head_blocks) * kCols;
+    const int nh = min(kCols, G - h0);
+    const int ctx = min(a.ctx_lens[s], kDirectMaxTokens);
+    E* out = (E*)a.out + ((int64_t)s * hq + (int64_t)g * G + h0) * D;
+    if (ctx <= 0) {                     // uniform over the workgroup
+        for (int idx = tid; idx < nh * D; idx += kThreads) out[idx] = (E)0.0f;
+        return;
+    }
+    const int n = steps_of(ctx), per = (n + kDirectWaves - 1) / kDirectWaves;
+    const int my_u = w * per, my_n = max(0, min(per, n - my_u));
+    float m, lsum;
+    f32x4 o[DT / 16];
+    attend_steps<E, DT, kExact, kThreads>(a, s, g, h0, nh, ctx, my_u, my_n, s_q, m, lsum, o);
+
+    const int r = lane & 15, c = lane >> 4;
+    auto power = [](float x) { return kBf16 ? __builtin_amdgcn_exp2f(x) : expf(x); };
+    if (c == 0) { s_m[w][r] = m; s_l[w][r] = lsum; }
+#pragma unroll
+    for (int d0 = 0; d0 < DT; d0 += kChan) {
+        if (d0 > 0) __syncthreads();
+#pragma unroll
+        for (int mb = 0; mb < kChan / 16; ++mb) *reinterpret_cast<f32x4*>(&s_o[w][r][mb * 16 + c * 4]) = o[d0 / 16 + mb];
+        __syncthreads();
+        for (int idx = tid; idx < nh * kChan; idx += kThreads) {
+            const int head = idx / kChan, dl = idx - head * kChan;
+            if (d0 + dl >= D) continue;
+            float ms = s_m[0][head];                             // wave 0 always has a step
+#pragma unroll
+            for (int ww = 1; ww < kDirectWaves; ++ww) ms = fmaxf(ms, s_m[ww][head]);
+            float acc = 0.f, l = 0.f;
+#pragma unroll
+            for (int ww = 0; ww < kDirectWaves; ++ww) {
+                const float fw = power(s_m[ww][head] - ms);      // a wave without steps has m = -inf -> 0
+                acc += fw * s_o[ww][head][dl];
+                l += fw * s_l[ww][head];
+            }
+            out[head * D + d0 + dl] = (E)(acc / l);
+        }
+    }
+}
+
 template <typename E>
 __global__ __launch_bounds__(256) void decode_any_merge_kernel(AttnArgs a, const int32_t* __restrict__ hdr,
                                                                const float* __restrict__ ws_o,
@@ -335,6 +418,16 @@ template <typename E, int DT>
 ag_status launch(const AttnArgs& a, hipStream_t st)
 {
     const int pmax = splitk::pieces_max(a.max_ctx), blocks = head_blocks_of(a);
+    const int64_t pair_bytes = (int64_t)a.max_ctx * 2 * DT * (int64_t)sizeof(E);
+    static_assert((512 << 10) / (2 * DT * (int)sizeof(E)) <= kDirectMaxTokens, "a wave's page ids fit its lanes");
+    if (a.max_ctx > 0 && splitk::direct_preferred((int64_t)a.batch * a.c.hkv * blocks, pair_bytes, stream_cus(st))) {
+        const dim3 grid(a.batch * a.c.hkv * blocks), wg(64 * kDirectWaves);
+        prof_before(st);
+        if (a.c.d == DT) hipLaunchKernelGGL((decode_any_direct_kernel<E, DT, true>), grid, wg, 0, st, a, blocks);
+        else hipLaunchKernelGGL((decode_any_direct_kernel<E, DT, false>), grid, wg, 0, st, a, blocks);
+        prof_after(st);
+        return hip_check(hipGetLastError(), "decode launch");
+    }
     int32_t* hdr = (int32_t*)a.ws;
     float* ws_o = (float*)(hdr + splitk::header_ints(a.batch));
     float* ws_ml = ws_o + (size_t)a.batch * a.hq * pmax * a.c.d;

@@ -35,6 +35,8 @@
 //
 //   merge kernel, one workgroup per (session, query head): combines the
 //   partials of the pair's segments in order (reproducible) and writes bf16.
+//
+// A batch of few, short contexts instead takes one workgroup per pair, which writes its result itself.
 #include <algorithm>
 #include <atomic>
 #include <mutex>
@@ -60,6 +62,145 @@ struct StepArgs {
     int32_t* counters;          // [B * Hkv]
 };
 
+constexpr int kQRow = 2 * D + 16;        // bytes of a query row in LDS, padded
+
+// One wave's part of a segment - steps my_u .. my_u + my_n - 1 (at most 32) of pair (s, g), whose context has ctx tokens:
+// the running maximum, the running sum (this lane's share) and O^T of the pair's heads.  Contains one workgroup barrier
+// (Q goes through LDS, written by the first 256 threads).  appends: this wave's last step is the pair's last, and it
+// writes the step's token first.
+__device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& sa, bool appends, int s, int g, int G, int ctx,
+                                             int my_u, int my_n, int tid, unsigned char* s_q, float& m, float& lsum, f32x4 (&o)[8])
+{
+    const int hkv = a.c.hkv, hq = a.hq, lane = tid & 63;
+    const __bf16* kpool = (const __bf16*)a.c.k;
+    const __bf16* vpool = (const __bf16*)a.c.v;
+    const float sl2 = a.scale * kLog2e;
+    // Everything a lane derives from its number is derived again in each segment, behind a barrier the
+    // compiler cannot see through: hoisted out of the segment loop those values would stay in registers across
+    // the step loop, which needs all 128 for the 16 loads of a step to be in flight together.
+    int lane_s = lane;
+    asm volatile("" : "+v"(lane_s));
+    const int r = lane_s & 15, c = lane_s >> 4;
+    // Row r of the first score product is slot (r & 7) of page (r >> 3) of the step; the second product takes
+    // slots 8..15.  K page layout [chunk][slot][8]: lanes r = 0..7 of one lane group read 128 contiguous bytes.
+    // Lane group c then owns slots (c&1)*4 + {0..3} and 8 + (c&1)*4 + {0..3} of page (c >> 1): exactly the 8
+    // keys of chunk (c&1) of that value page (see v_offset), so its 16-byte V load is its P operand's partner.
+    const int k_pg = r >> 3;
+    const int k_off = (c * PS + (r & 7)) * 8;            // + kk * 4 * PS * 8 per k-step; + 8 * 8 for slots 8..15
+    const int v_pg = c >> 1;
+    const int v_off = ((c & 1) * D + r) * 8;             // value page [half][channel][8 keys]; + mb * 16 * 8 per block
+
+    // Q of the pair's G heads goes through LDS (rows of 256 B + 16 B of padding, zero beyond G): as the B
+    // operand, column = head r, k = channels kk*32 + c*8 .. +7, read when a step needs it rather than
+    // held in 16 registers across the loads.
+    // Decode step: the segment that ends the pair also appends the step's token (position ctx - 1).  The wave whose
+    // part holds the pair's last step writes it - 16 lanes a 16-byte piece of the key each, every lane two
+    // channels of the value - and waits for these stores before it loads that step (below).
+    // Every load of this prologue (Q, page ids, the new token) is issued before the first of them is used.
+    int tid_q = tid;                                     // the first 256 threads: 16 heads x 16 pieces of 16 bytes
+    asm volatile("" : "+v"(tid_q));
+    const int head_q = tid_q >> 4, ch_q = tid_q & 15;
+    u32x4 qx = {0, 0, 0, 0};
+    if (head_q < G)
+        qx = *reinterpret_cast<const u32x4*>((const __bf16*)a.q + ((int64_t)s * hq + (int64_t)g * G + head_q) * D + ch_q * 8);
+    // physical pages of this wave's steps (lane i: page i of its run, clamped to the session's last page)
+    const int last_lp = ((ctx + PS - 1) >> 4) - 1;
+    int my_pid = 0;
+    if (my_n > 0) my_pid = a.bt[(int64_t)s * a.max_pages + min(2 * my_u + lane_s, last_lp)];
+    u32x4 new_k = {0, 0, 0, 0};
+    __bf16 new_v0 = (__bf16)0.0f, new_v1 = (__bf16)0.0f;
+    if (appends) {
+        const __bf16* ks = sa.k_new + ((int64_t)s * hkv + g) * D;
+        const __bf16* vs = sa.v_new + ((int64_t)s * hkv + g) * D;
+        if (lane_s < 16) new_k = *reinterpret_cast<const u32x4*>(ks + lane_s * 8);
+        new_v0 = vs[lane_s];
+        new_v1 = vs[lane_s + 64];
+    }
+    if (head_q < 16) *reinterpret_cast<u32x4*>(s_q + head_q * kQRow + ch_q * 16) = qx;
+    if (appends) {
+        const int slot = (ctx - 1) & (PS - 1);
+        const int64_t page = __builtin_amdgcn_readlane(my_pid, last_lp - 2 * my_u);   // the run holds the last page
+        __bf16* kdst = (__bf16*)a.c.k + (page * hkv + g) * (int64_t)(D * PS);
+        __bf16* vdst = (__bf16*)a.c.v + (page * hkv + g) * (int64_t)(D * PS);
+        if (lane_s < 16) *reinterpret_cast<u32x4*>(kdst + (lane_s * PS + slot) * 8) = new_k;
+        vdst[v_offset(slot, lane_s, PS, D)] = new_v0;
+        vdst[v_offset(slot, lane_s + 64, PS, D)] = new_v1;
+    }
+
+    m = -INFINITY;
+    lsum = 0.0f;
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) o[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    __syncthreads();                                 // Q is in LDS
+    const unsigned char* q_lane = s_q + r * kQRow + c * 16;
+
+#pragma unroll 1
+    for (int st = 0; st < my_n; ++st) {
+        StepRegs x;
+        if (appends && st == my_n - 1) {             // the token this wave appended lies in the page loaded next
+            __builtin_amdgcn_s_waitcnt(0x0070 | (0xF << 8));          // vmcnt(0): its stores have been performed
+            asm volatile("" ::: "memory");
+        }
+        {
+            const int64_t pA = __builtin_amdgcn_readlane(my_pid, 2 * st);
+            const int64_t pB = __builtin_amdgcn_readlane(my_pid, 2 * st + 1);
+            const __bf16* kp = kpool + ((k_pg ? pB : pA) * hkv + g) * (int64_t)(D * PS) + k_off;
+            const __bf16* vp = vpool + ((v_pg ? pB : pA) * hkv + g) * (int64_t)(D * PS) + v_off;
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                x.k1[kk] = ld16_stream(kp + kk * 4 * PS * 8);
+                x.k2[kk] = ld16_stream(kp + kk * 4 * PS * 8 + 64);
+            }
+#pragma unroll
+            for (int mb = 0; mb < 8; ++mb) x.v[mb] = ld16_stream(vp + mb * 16 * 8);
+            // all 16 loads are in flight before anything waits: left to itself the scheduler starts the
+            // score product on the first keys and issues the value loads a memory latency later
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const int tok0 = (my_u + st) * 32;
+        f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            const bf16x8 qk = *reinterpret_cast<const bf16x8*>(q_lane + kk * 64);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.k1[kk], qk, s1, 0, 0, 0);
+            s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.k2[kk], qk, s2, 0, 0, 0);
+        }
+        // s1[i]: token tokb + i, s2[i]: token tokb + 8 + i, of head r
+        const int tokb = tok0 + (c >> 1) * PS + (c & 1) * 4;
+        const int keep = ctx - tokb;     // token tokb + j exists iff j < keep
+        float xs[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            xs[i] = (i < keep) ? s1[i] * sl2 : -INFINITY;
+            xs[4 + i] = (8 + i < keep) ? s2[i] * sl2 : -INFINITY;
+        }
+        float mx = fmaxf(fmaxf(fmaxf(xs[0], xs[1]), fmaxf(xs[2], xs[3])), fmaxf(fmaxf(xs[4], xs[5]), fmaxf(xs[6], xs[7])));
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m, mx);          // finite: token tok0 exists
+        const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+        float psum = 0.f;
+        bf16x8 pb;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float p = __builtin_amdgcn_exp2f(xs[e] - m_new);
+            psum += p;
+            pb[e] = (__bf16)p;
+        }
+        lsum = lsum * alpha + psum;
+        m = m_new;
+        if (tok0 + 32 > ctx) {           // last, partial step: unwritten slots may hold anything, NaN included
+#pragma unroll
+            for (int mb = 0; mb < 8; ++mb) x.v[mb] = keep_quads(x.v[mb], keep, keep - 8);
+        }
+#pragma unroll
+        for (int mb = 0; mb < 8; ++mb) {
+            o[mb] *= alpha;
+            o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.v[mb], pb, o[mb], 0, 0, 0);
+        }
+    }
+}
+
 // kStep = false: the split half of ag_attn_decode (partials to the workspace, merged by decode_merge_kernel).
 // kStep = true: the whole decode step in one launch (ag_decode_step).  The workgroup whose share holds the last
 // step of a (session, KV head) pair first writes the step's token into the pair's last page - the wave that will
@@ -74,7 +215,6 @@ __global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_
     __shared__ float s_o[4][16][D];     // per wave, per (padded) head: unnormalised O
     __shared__ float s_m[4][16];
     __shared__ float s_l[4][16];
-    constexpr int kQRow = 2 * D + 16;
     __shared__ __attribute__((aligned(16))) unsigned char s_q[16 * kQRow];
     __shared__ int s_arrived;           // kStep: how many of the pair's segments had been finished before this one
 
@@ -99,10 +239,6 @@ __global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_
     int g = (f0 - base) / n;
     int u = (f0 - base) - g * n;        // first step inside (s, g)
 
-    const __bf16* kpool = (const __bf16*)a.c.k;
-    const __bf16* vpool = (const __bf16*)a.c.v;
-    const float sl2 = a.scale * kLog2e;
-
     for (int f = f0; f < f1 && s < B;) {                 // one segment per pass; every value here is uniform
         const int k = min(n - u, f1 - f);                // steps of this segment, 1 .. q
         if (k <= 0) break;                               // (only if the lengths changed under the kernel: never spin)
@@ -110,131 +246,10 @@ __global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_
         const int my_u = u + w * per;
         const int my_n = max(0, min(per, k - w * per));
 
-        // Everything a lane derives from its number is derived again in each segment, behind a barrier the
-        // compiler cannot see through: hoisted out of this loop those values would stay in registers across
-        // the step loop, which needs all 128 for the 16 loads of a step to be in flight together.
-        int lane_s = lane;
-        asm volatile("" : "+v"(lane_s));
-        const int r = lane_s & 15, c = lane_s >> 4;
-        // Row r of the first score product is slot (r & 7) of page (r >> 3) of the step; the second product takes
-        // slots 8..15.  K page layout [chunk][slot][8]: lanes r = 0..7 of one lane group read 128 contiguous bytes.
-        // Lane group c then owns slots (c&1)*4 + {0..3} and 8 + (c&1)*4 + {0..3} of page (c >> 1): exactly the 8
-        // keys of chunk (c&1) of that value page (see v_offset), so its 16-byte V load is its P operand's partner.
-        const int k_pg = r >> 3;
-        const int k_off = (c * PS + (r & 7)) * 8;            // + kk * 4 * PS * 8 per k-step; + 8 * 8 for slots 8..15
-        const int v_pg = c >> 1;
-        const int v_off = ((c & 1) * D + r) * 8;             // value page [half][channel][8 keys]; + mb * 16 * 8 per block
-
-        // Q of the pair's G heads goes through LDS (rows of 256 B + 16 B of padding, zero beyond G): as the B
-        // operand, column = head r, k = channels kk*32 + c*8 .. +7, read when a step needs it rather than
-        // held in 16 registers across the loads.
-        // kStep: the segment that ends the pair also appends the step's token (position ctx - 1).  The wave whose
-        // quarter holds the pair's last step writes it - 16 lanes a 16-byte piece of the key each, every lane two
-        // channels of the value - and waits for these stores before it loads that step (below).
-        // Every load of this prologue (Q, page ids, the new token) is issued before the first of them is used.
         const bool appends = kStep && u + k == n && w == (k - 1) / per;        // uniform over the wave
-        int tid_q = tid;                                     // 256 threads: 16 heads x 16 pieces of 16 bytes
-        asm volatile("" : "+v"(tid_q));
-        const int head_q = tid_q >> 4, ch_q = tid_q & 15;
-        u32x4 qx = {0, 0, 0, 0};
-        if (head_q < G)
-            qx = *reinterpret_cast<const u32x4*>((const __bf16*)a.q + ((int64_t)s * hq + (int64_t)g * G + head_q) * D + ch_q * 8);
-        // physical pages of this wave's steps (lane i: page i of its run, clamped to the session's last page)
-        const int last_lp = ((ctx + PS - 1) >> 4) - 1;
-        int my_pid = 0;
-        if (my_n > 0) my_pid = a.bt[(int64_t)s * a.max_pages + min(2 * my_u + lane_s, last_lp)];
-        u32x4 new_k = {0, 0, 0, 0};
-        __bf16 new_v0 = (__bf16)0.0f, new_v1 = (__bf16)0.0f;
-        if (appends) {
-            const __bf16* ks = sa.k_new + ((int64_t)s * hkv + g) * D;
-            const __bf16* vs = sa.v_new + ((int64_t)s * hkv + g) * D;
-            if (lane_s < 16) new_k = *reinterpret_cast<const u32x4*>(ks + lane_s * 8);
-            new_v0 = vs[lane_s];
-            new_v1 = vs[lane_s + 64];
-        }
-        *reinterpret_cast<u32x4*>(s_q + head_q * kQRow + ch_q * 16) = qx;
-        if (appends) {
-            const int slot = (ctx - 1) & (PS - 1);
-            const int64_t page = __builtin_amdgcn_readlane(my_pid, last_lp - 2 * my_u);   // the run holds the last page
-            __bf16* kdst = (__bf16*)a.c.k + (page * hkv + g) * (int64_t)(D * PS);
-            __bf16* vdst = (__bf16*)a.c.v + (page * hkv + g) * (int64_t)(D * PS);
-            if (lane_s < 16) *reinterpret_cast<u32x4*>(kdst + (lane_s * PS + slot) * 8) = new_k;
-            vdst[v_offset(slot, lane_s, PS, D)] = new_v0;
-            vdst[v_offset(slot, lane_s + 64, PS, D)] = new_v1;
-        }
-
-        float m = -INFINITY, lsum = 0.0f;
+        float m, lsum;
         f32x4 o[8];
-#pragma unroll
-        for (int mb = 0; mb < 8; ++mb) o[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        __syncthreads();                                 // Q is in LDS
-        const unsigned char* q_lane = s_q + r * kQRow + c * 16;
-
-#pragma unroll 1
-        for (int st = 0; st < my_n; ++st) {
-            StepRegs x;
-            if (appends && st == my_n - 1) {             // the token this wave appended lies in the page loaded next
-                __builtin_amdgcn_s_waitcnt(0x0070 | (0xF << 8));          // vmcnt(0): its stores have been performed
-                asm volatile("" ::: "memory");
-            }
-            {
-                const int64_t pA = __builtin_amdgcn_readlane(my_pid, 2 * st);
-                const int64_t pB = __builtin_amdgcn_readlane(my_pid, 2 * st + 1);
-                const __bf16* kp = kpool + ((k_pg ? pB : pA) * hkv + g) * (int64_t)(D * PS) + k_off;
-                const __bf16* vp = vpool + ((v_pg ? pB : pA) * hkv + g) * (int64_t)(D * PS) + v_off;
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) {
-                    x.k1[kk] = ld16_stream(kp + kk * 4 * PS * 8);
-                    x.k2[kk] = ld16_stream(kp + kk * 4 * PS * 8 + 64);
-                }
-#pragma unroll
-                for (int mb = 0; mb < 8; ++mb) x.v[mb] = ld16_stream(vp + mb * 16 * 8);
-                // all 16 loads are in flight before anything waits: left to itself the scheduler starts the
-                // score product on the first keys and issues the value loads a memory latency later
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            const int tok0 = (my_u + st) * 32;
-            f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const bf16x8 qk = *reinterpret_cast<const bf16x8*>(q_lane + kk * 64);
-                s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.k1[kk], qk, s1, 0, 0, 0);
-                s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.k2[kk], qk, s2, 0, 0, 0);
-            }
-            // s1[i]: token tokb + i, s2[i]: token tokb + 8 + i, of head r
-            const int tokb = tok0 + (c >> 1) * PS + (c & 1) * 4;
-            const int keep = ctx - tokb;     // token tokb + j exists iff j < keep
-            float xs[8];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                xs[i] = (i < keep) ? s1[i] * sl2 : -INFINITY;
-                xs[4 + i] = (8 + i < keep) ? s2[i] * sl2 : -INFINITY;
-            }
-            float mx = fmaxf(fmaxf(fmaxf(xs[0], xs[1]), fmaxf(xs[2], xs[3])), fmaxf(fmaxf(xs[4], xs[5]), fmaxf(xs[6], xs[7])));
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float m_new = fmaxf(m, mx);          // finite: token tok0 exists
-            const float alpha = __builtin_amdgcn_exp2f(m - m_new);
-            float psum = 0.f;
-            bf16x8 pb;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float p = __builtin_amdgcn_exp2f(xs[e] - m_new);
-                psum += p;
-                pb[e] = (__bf16)p;
-            }
-            lsum = lsum * alpha + psum;
-            m = m_new;
-            if (tok0 + 32 > ctx) {           // last, partial step: unwritten slots may hold anything, NaN included
-#pragma unroll
-                for (int mb = 0; mb < 8; ++mb) x.v[mb] = keep_quads(x.v[mb], keep, keep - 8);
-            }
-#pragma unroll
-            for (int mb = 0; mb < 8; ++mb) {
-                o[mb] *= alpha;
-                o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.v[mb], pb, o[mb], 0, 0, 0);
-            }
-        }
+        attend_steps(a, sa, appends, s, g, G, ctx, my_u, my_n, tid, s_q, m, lsum, o);
         lsum += __shfl_xor(lsum, 16);
         lsum += __shfl_xor(lsum, 32);
 
@@ -314,6 +329,60 @@ __global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_
                 } while (s < B && n == 0);
             }
         }
+    }
+}
+
+// A batch of few, short contexts: one workgroup of 16 waves per (session, KV head) pair, which shares the pair's steps
+// and writes the result itself - no plan, no partials, no merge (whose dependent round trips are most of a small step:
+// see direct_preferred()).  The waves' results meet in LDS, of which a launch takes what its group size needs.
+constexpr int kDirectWaves = 16;
+constexpr int kDirectMaxSteps = kDirectWaves * 32;                       // page ids of a wave's steps: one per lane
+inline size_t direct_lds(int G) { return (size_t)kDirectWaves * G * (D + 2) * sizeof(float); }
+
+template <bool kStep>
+__global__ __launch_bounds__(64 * kDirectWaves, 4) void decode_direct_kernel(AttnArgs a, StepArgs sa)
+{
+    extern __shared__ __attribute__((aligned(16))) float s_dyn[];          // [wave][head][D], then m and l [wave][head]
+    __shared__ __attribute__((aligned(16))) unsigned char s_q[16 * kQRow];
+    const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int s = blockIdx.x / hkv, g = blockIdx.x - s * hkv;
+    const int ctx = min(a.ctx_lens[s], kDirectMaxSteps * 32);
+    __bf16* out = (__bf16*)a.out + ((int64_t)s * hq + (int64_t)g * G) * D;
+    if (ctx <= 0) {                     // uniform over the workgroup
+        for (int idx = tid; idx < G * D; idx += 64 * kDirectWaves) out[idx] = (__bf16)0.0f;
+        return;
+    }
+    const int n = steps_of(ctx), per = (n + kDirectWaves - 1) / kDirectWaves;
+    const int my_u = w * per, my_n = max(0, min(per, n - my_u));
+    float m, lsum;
+    f32x4 o[8];
+    attend_steps(a, sa, kStep && w == (n - 1) / per, s, g, G, ctx, my_u, my_n, tid, s_q, m, lsum, o);
+    lsum += __shfl_xor(lsum, 16);
+    lsum += __shfl_xor(lsum, 32);
+    const int r = lane & 15, c = lane >> 4;
+    float* const s_m = s_dyn + kDirectWaves * G * D;
+    float* const s_l = s_m + kDirectWaves * G;
+    if (r < G) {
+#pragma unroll
+        for (int mb = 0; mb < 8; ++mb) *reinterpret_cast<f32x4*>(s_dyn + (w * G + r) * D + mb * 16 + c * 4) = o[mb];
+        if (c == 0) { s_m[w * G + r] = m; s_l[w * G + r] = lsum; }
+    }
+    __syncthreads();
+    for (int idx = tid; idx < G * D; idx += 64 * kDirectWaves) {
+        const int head = idx >> 7, d = idx & (D - 1);
+        float ms = s_m[head];                               // wave 0 always has a step: finite
+#pragma unroll
+        for (int ww = 1; ww < kDirectWaves; ++ww) ms = fmaxf(ms, s_m[ww * G + head]);
+        float acc = 0.f, l = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < kDirectWaves; ++ww) {
+            const float fw = exp2f(s_m[ww * G + head] - ms);               // a wave without steps has m = -inf -> 0
+            acc += fw * s_dyn[(ww * G + head) * D + d];
+            l += fw * s_l[ww * G + head];
+        }
+        out[idx] = (__bf16)(acc / l);
     }
 }
 
@@ -408,8 +477,34 @@ ag_status decode_static_scratch(void** ptr_out)
     return AG_OK;
 }
 
+// The same rule for ag_attn_decode and ag_decode_step: their results are bit for bit the same.
+static bool takes_direct(const AttnArgs& a, hipStream_t st)
+{
+    static_assert((512 << 10) / (4 * D) <= kDirectMaxSteps * 32, "a wave's page ids fit its lanes");
+    return a.max_ctx > 0 && direct_preferred((int64_t)a.batch * a.c.hkv, (int64_t)a.max_ctx * 4 * D, stream_cus(st));
+}
+
+template <bool kStep>
+static ag_status launch_direct(const AttnArgs& a, const StepArgs& sa, hipStream_t st)
+{
+    static std::atomic<bool> attr_set{false};
+    const size_t lds = direct_lds(a.hq / a.c.hkv);
+    if (lds > 64 * 1024 && !attr_set.load()) {      // (groups of 8 heads and more) beyond what a kernel may use without being told so
+        ag_status e = hip_check(hipFuncSetAttribute((const void*)decode_direct_kernel<kStep>,
+                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)direct_lds(16)),
+                                "hipFuncSetAttribute(decode direct)");
+        if (e) return e;
+        attr_set.store(true);
+    }
+    prof_before(st);
+    hipLaunchKernelGGL(decode_direct_kernel<kStep>, dim3(a.batch * a.c.hkv), dim3(64 * kDirectWaves), lds, st, a, sa);
+    prof_after(st);
+    return hip_check(hipGetLastError(), "decode launch");
+}
+
 ag_status launch_decode_mfma(const AttnArgs& a, void* ws, hipStream_t st)
 {
+    if (takes_direct(a, st)) return launch_direct<false>(a, StepArgs{}, st);
     const int pmax = pieces_max(a.max_ctx);
     int32_t* hdr = (int32_t*)ws;
     float* ws_o = (float*)(hdr + header_ints(a.batch));
@@ -457,6 +552,7 @@ ag_status launch_decode_step(const AttnArgs& a, const void* k_new, const void* v
     float* ws_ml = ws_o + (size_t)a.batch * a.hq * pmax * D;
     const int64_t f_max = (int64_t)a.c.hkv * a.batch * ((a.max_ctx + 31) / 32);
     if (f_max > (1 << 30)) { set_error("decode batch of %lld steps of 32 tokens is beyond one launch", (long long)f_max); return AG_ERR_INVALID_ARG; }
+    if (takes_direct(a, st)) return launch_direct<true>(a, StepArgs{(const __bf16*)k_new, (const __bf16*)v_new, counters}, st);
     const int grid = share_workgroups(std::max<int64_t>(f_max, 1), st);
     prof_before(st);
     hipLaunchKernelGGL(decode_split_kernel<true>, dim3(grid), dim3(256), 0, st, a, hdr, ws_o, ws_ml, pmax,

@@ -103,38 +103,33 @@ struct Share {
     int s, base, ctx;       // session holding step f0, the flat step at which that session starts, its length
 };
 
-// Finds this workgroup's share from the lengths (256 threads; `heads` pairs per session); false if it has none.
+// Finds this workgroup's share from the lengths (`heads` pairs per session); false if it has none.  Every wave scans the
+// lengths for itself, 64 sessions at a time: one memory round trip and no barrier for up to 64 sessions.
 // With kPublish workgroup 0 also writes the plan for the merge kernel: hdr[0] = q, hdr[1 + s] = steps before session s.
 template <bool kPublish>
 __device__ __forceinline__ bool find_share(const int32_t* __restrict__ ctx_lens, int B, int heads, int32_t* __restrict__ hdr,
                                            Share& sh)
 {
-    __shared__ int s_red[4];
-    __shared__ int s_start[3];          // session holding the workgroup's first step, steps before it, its length
     const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wg = blockIdx.x, W = gridDim.x;
-    int total;
-    {
-        int loc = 0;
-        for (int s = tid; s < B; s += 256) loc += steps_of(ctx_lens[s]);
+    int len = lane < B ? ctx_lens[lane] : 0;
+    int total = steps_of(len);
+    for (int s = lane + 64; s < B; s += 64) total += steps_of(ctx_lens[s]);
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) loc += __shfl_xor(loc, d);
-        if (lane == 0) s_red[w] = loc;
-        __syncthreads();
-        total = s_red[0] + s_red[1] + s_red[2] + s_red[3];
-        __syncthreads();
-    }
-    const int F = heads * total;
+    for (int d = 32; d >= 1; d >>= 1) total += __shfl_xor(total, d);
+    const int F = heads * __builtin_amdgcn_readfirstlane(total);
     if (F == 0) return false;
     const int q = max(kMinSteps, (F + W - 1) / W);
     const int f0 = wg * q;              // q <= kMaxSteps by the launcher's choice of W: no overflow
     if (kPublish && wg == 0 && tid == 0) hdr[0] = q;
     if (f0 >= F) return false;          // uniform over the workgroup
-    int carry = 0;                      // steps of the sessions before this chunk of 256
-    for (int s0 = 0; s0 < B; s0 += 256) {
-        const int s = s0 + tid;
-        const int len = s < B ? ctx_lens[s] : 0;
+    sh.q = q;
+    sh.f0 = f0;
+    sh.f1 = min(f0 + q, F);
+    bool found = false;
+    int carry = 0;                      // steps of the sessions before this pass of 64
+    for (int s0 = 0; s0 < B; s0 += 64) {
+        if (s0 > 0) len = s0 + lane < B ? ctx_lens[s0 + lane] : 0;
         const int n = steps_of(len);
         int incl = n;
 #pragma unroll
@@ -142,25 +137,33 @@ __device__ __forceinline__ bool find_share(const int32_t* __restrict__ ctx_lens,
             const int t = __shfl_up(incl, d);
             if (lane >= d) incl += t;
         }
-        if (lane == 63) s_red[w] = incl;
-        __syncthreads();
-        int woff = 0;
-        for (int ww = 0; ww < w; ++ww) woff += s_red[ww];
-        const int chunk = s_red[0] + s_red[1] + s_red[2] + s_red[3];
-        const int excl = carry + woff + incl - n;
-        if (n > 0 && heads * excl <= f0 && f0 < heads * (excl + n)) { s_start[0] = s; s_start[1] = excl; s_start[2] = len; }
-        if (kPublish && wg == 0 && s < B) hdr[1 + s] = excl;       // workgroup 0 publishes the plan for the merge kernel
-        __syncthreads();
-        carry += chunk;
-        if ((!kPublish || wg != 0) && heads * carry > f0) break;   // found (uniform); workgroup 0 goes on publishing
+        const unsigned long long hit = __builtin_amdgcn_ballot_w64(f0 < heads * (carry + incl));
+        if (!found && hit) {            // the first session that ends behind f0
+            const int l = __builtin_ctzll(hit);
+            found = true;
+            sh.s = s0 + l;
+            sh.base = heads * (carry + __builtin_amdgcn_readlane(incl, l) - __builtin_amdgcn_readlane(n, l));
+            sh.ctx = __builtin_amdgcn_readlane(len, l);
+        }
+        if (kPublish && wg == 0 && tid < 64 && s0 + lane < B) hdr[1 + s0 + lane] = carry + incl - n;
+        if (found && (!kPublish || wg != 0)) break;      // (uniform; workgroup 0 goes on publishing)
+        carry += __builtin_amdgcn_readlane(incl, 63);
     }
-    sh.q = q;
-    sh.f0 = f0;
-    sh.f1 = min(f0 + q, F);
-    sh.s = s_start[0];
-    sh.base = heads * s_start[1];
-    sh.ctx = s_start[2];
-    return true;
+    return found;
+}
+
+// Whether a decode batch of `pairs` (session, KV head) pairs, each with at most `bytes` of keys and values, takes one
+// workgroup per pair and no merge instead of equal shares.  A step of a small batch is a chain of memory round trips, and
+// the plan, the partials and their merge are most of them; but a CU draws no more than about 57 GB/s, so a pair that one
+// workgroup reads alone must be short, and every pair must have a CU to itself.  256 KiB (512 tokens of bf16 / 128)
+// is where that turns for a single session; with more than half of the CUs busy either way, 512 KiB.
+// Measured at 32 / 8 heads, graph replay, shares -> direct.  ag_decode_step, bf16 / 128: one session of 100 tokens 8.5 -> 5.3
+// us, of 512 8.1 -> 7.2, of 1000 8.3 -> 8.8; four of 1000 9.3 -> 12.7; 32 of 100..512 18.2 -> 10.5, 32 of 500..1000 24.4
+// -> 20.0.  Append + ag_attn_decode: fp32 / 128, one of 256 tokens 16.8 -> 13.9, of 512 16.7 -> 18.7, 32 of 512 34.8 ->
+// 31.1; bf16 / 64, one of 1000 10.7 -> 9.4.
+inline bool direct_preferred(int64_t pairs, int64_t bytes, int cus)
+{
+    return pairs <= cus && bytes <= (2 * pairs > cus ? 512 << 10 : 256 << 10);
 }
 
 }  // namespace splitk

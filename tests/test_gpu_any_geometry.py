@@ -65,6 +65,42 @@ def test_decode_shares_that_span_many_short_sessions(dtype, d):
         check_close(got[live], ref, dtype, f"decode, 300 sessions, bound {bound}")
 
 
+@pytest.mark.parametrize("dtype,d,ps,hq,hkv", [(I.BF16, 128, 16, 8, 2), (I.BF16, 128, 16, 16, 1), (I.BF16, 64, 32, 8, 2),
+                                               (I.BF16, 256, 16, 6, 2), (I.F32, 64, 16, 40, 2), (I.F32, 128, 16, 8, 2)])
+@pytest.mark.parametrize("cus_per_xcd", [0, 1])
+def test_decode_at_the_line_between_one_workgroup_per_pair_and_shares(dtype, d, ps, hq, hkv, cus_per_xcd):
+    """max_ctx at and one past 256 KiB of keys and values per pair, on the whole device and on 8 CUs (where six pairs or
+    more are over half of them, and nine or more never get one each); lengths from one token to the bound, some empty."""
+    line = (256 << 10) // (2 * d * (4 if dtype == I.F32 else 2))
+    stream = None
+    if cus_per_xcd:
+        stream = B.ag_stream_create_cumask(B.ag_cumask_build(B.ag_device_info()["num_cus"], 8, 0, cus_per_xcd))
+    try:
+        for top in (line, line + 1):
+            ctx = np.array([top, 0, 1, 33, top // 2 + 5, top - 1], np.int32)
+            pages = int(sum((max(int(c), 1) + ps - 1) // ps for c in ctx)) + 3
+            g = I.Geometry(hq, hkv, d, ps, pages, dtype)
+            bt = I.deal_block_tables(I.rng_for(57, 0), np.maximum(ctx, 1), ps, pages)
+            fill = make_batch(g, np.zeros_like(ctx), ctx, seed=57, bt=bt)
+            cache = make_cache(g)
+            kp, vp = fresh_pools(g)
+            df = DevBatch(fill)
+            gpu_append(cache, df)
+            oracle_append(kp, vp, fill)
+            qn = I.normal_values(57, 9, 0, (len(ctx), hq, d), 1.0, dtype)
+            live = np.nonzero(ctx > 0)[0]
+            ref = O.decode(kp, vp, dtype, qn[live], bt[live], ctx[live], hq, g.scale)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(torch.cuda.ExternalStream(stream) if stream else torch.cuda.current_stream()):
+                got = gpu_decode(cache, to_dev(qn, dtype), df.bt, i32(ctx), top, g)
+            assert np.all(got[ctx == 0] == 0)
+            check_close(got[live], ref, dtype, f"decode up to {top} D={d} {hq}/{hkv}")
+    finally:
+        torch.cuda.synchronize()
+        if stream:
+            B.ag_stream_destroy(stream)
+
+
 def test_decode_of_a_q_that_is_not_16_byte_aligned_still_runs():
     g = I.Geometry(3, 1, 24, 16, 8, I.F32)
     ctx = np.array([40, 7], np.int32)
