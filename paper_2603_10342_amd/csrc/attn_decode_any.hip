@@ -394,18 +394,22 @@ __global__ __launch_bounds__(256) void decode_any_merge_kernel(AttnArgs a, const
                                                                const float* __restrict__ ws_o,
                                                                const float* __restrict__ ws_ml, int pmax, int head_blocks)
 {
-    const int row = blockIdx.x;                 // s * hq + h
-    const int s = row / a.hq, h = row - s * a.hq;
-    const int d = threadIdx.x, D = a.c.d;
-    if (d >= D) return;
+    const int D = a.c.d, quads = D >> 2;        // lanes of a row
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x, row = idx / quads;      // s * hq + h
+    if (row >= (int64_t)a.batch * a.hq) return;
+    const int s = (int)(row / a.hq), h = (int)(row - (int64_t)s * a.hq), d = (int)(idx - row * quads) * 4;
     const int ctx = a.ctx_lens[s];
-    E* out = (E*)a.out + (int64_t)row * D;
-    if (ctx <= 0) { out[d] = (E)0.0f; return; }
+    E* out = (E*)a.out + row * D;
+    if (ctx <= 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[d + e] = (E)0.0f;
+        return;
+    }
     const int G = a.hq / a.c.hkv, g = h / G;
     const int q = max(1, hdr[0]), n = steps_of(ctx);
     const int first = a.c.hkv * head_blocks * hdr[1 + s] + (g * head_blocks + (h - g * G) / kCols) * n;
     const int pieces = min(pmax, (first + n - 1) / q - first / q + 1);       // as the split kernel cuts them
-    out[d] = (E)splitk::merge_partials<false, sizeof(E) == 4>(ws_o, ws_ml, (int64_t)row * pmax, pieces, d, D);
+    splitk::merge_quad<E, sizeof(E) == 4>(ws_o, ws_ml, row * pmax, pieces, d, D, out);
 }
 
 inline int head_blocks_of(const AttnArgs& a) { return (a.hq / a.c.hkv + kCols - 1) / kCols; }
@@ -439,7 +443,7 @@ ag_status launch(const AttnArgs& a, hipStream_t st)
         ag_status e = hip_check(hipGetLastError(), "decode split launch");
         if (e) return e;
     }
-    hipLaunchKernelGGL(decode_any_merge_kernel<E>, dim3(a.batch * a.hq), dim3((a.c.d + 63) & ~63), 0, st, a, hdr, ws_o, ws_ml, pmax, blocks);
+    hipLaunchKernelGGL(decode_any_merge_kernel<E>, dim3((unsigned)(((int64_t)a.batch * a.hq * (a.c.d / 4) + 255) / 256)), dim3(256), 0, st, a, hdr, ws_o, ws_ml, pmax, blocks);
     prof_after(st);
     return hip_check(hipGetLastError(), "decode merge launch");
 }
@@ -459,7 +463,7 @@ ag_status launch_for_dim(const AttnArgs& a, hipStream_t st)
 bool decode_any_supported(const AttnArgs& a)
 {
     return a.c.ps >= 16 && (((uintptr_t)a.q | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 == 0) && steps_bound(a) <= (1 << 30) &&
-           (int64_t)a.batch * a.hq <= 0x7fffffff;
+           (int64_t)a.batch * a.hq <= 0x1fffffff;
 }
 
 ag_status launch_decode_any(const AttnArgs& a, hipStream_t st)

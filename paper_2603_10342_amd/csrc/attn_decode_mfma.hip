@@ -33,8 +33,8 @@
 //   The 4 waves are merged in LDS and the workgroup writes one partial
 //   (m, l, O) per query head and segment to the workspace;
 //
-//   merge kernel, one workgroup per (session, query head): combines the
-//   partials of the pair's segments in order (reproducible) and writes bf16.
+//   merge kernel, 32 lanes per (session, query head): combines the partials
+//   of the pair's segments in order (reproducible) and writes bf16.
 //
 // A batch of few, short contexts instead takes one workgroup per pair, which writes its result itself.
 #include <algorithm>
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_
                 for (int idx = tid_e; idx < G * D; idx += 256) {
                     const int head = idx >> 7, d = idx & (D - 1);
                     const int64_t row = (int64_t)s * hq + (int64_t)g * G + head;
-                    ((__bf16*)a.out)[row * D + d] = (__bf16)merge_partials<true>(ws_o, ws_ml, row * pmax, min(pieces, pmax), d);
+                    ((__bf16*)a.out)[row * D + d] = (__bf16)merge_coherent(ws_o, ws_ml, row * pmax, min(pieces, pmax), d);
                 }
                 if (tid_e == 0) sa.counters[s * hkv + g] = 0;      // as the next call expects it
             }
@@ -386,20 +386,27 @@ __global__ __launch_bounds__(64 * kDirectWaves, 4) void decode_direct_kernel(Att
     }
 }
 
-__global__ __launch_bounds__(128) void decode_merge_kernel(AttnArgs a, const int32_t* __restrict__ hdr,
-                                                           const float* __restrict__ ws_o,
-                                                           const float* __restrict__ ws_ml, int pmax)
+constexpr int kMergeRows = 8;               // (session, query head) rows of a merge workgroup, 32 lanes each
+
+__global__ __launch_bounds__(32 * kMergeRows) void decode_merge_kernel(AttnArgs a, const int32_t* __restrict__ hdr,
+                                                                       const float* __restrict__ ws_o,
+                                                                       const float* __restrict__ ws_ml, int pmax)
 {
-    const int row = blockIdx.x;                 // s * hq + h
-    const int s = row / a.hq, h = row - s * a.hq;
-    const int d = threadIdx.x;
+    const int64_t row = (int64_t)blockIdx.x * kMergeRows + (threadIdx.x >> 5);      // s * hq + h
+    if (row >= (int64_t)a.batch * a.hq) return;
+    const int s = (int)(row / a.hq), h = (int)(row - (int64_t)s * a.hq);
+    const int d = (threadIdx.x & 31) * 4;
     const int ctx = a.ctx_lens[s];
-    __bf16* out = (__bf16*)a.out + (int64_t)row * D;
-    if (ctx <= 0) { out[d] = (__bf16)0.0f; return; }
+    __bf16* out = (__bf16*)a.out + row * D;
+    if (ctx <= 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[d + e] = (__bf16)0.0f;
+        return;
+    }
     const int q = max(1, hdr[0]), n = steps_of(ctx);
     const int first = a.c.hkv * hdr[1 + s] + (h / (a.hq / a.c.hkv)) * n;       // the pair's first flat step
     const int pieces = min(pmax, (first + n - 1) / q - first / q + 1);          // as the split kernel cuts them
-    out[d] = (__bf16)merge_partials(ws_o, ws_ml, (int64_t)row * pmax, pieces, d);
+    merge_quad(ws_o, ws_ml, row * pmax, pieces, d, D, out);
 }
 
 }  // namespace
@@ -521,7 +528,7 @@ ag_status launch_decode_mfma(const AttnArgs& a, void* ws, hipStream_t st)
         ag_status e = hip_check(hipGetLastError(), "decode split launch");
         if (e) return e;
     }
-    hipLaunchKernelGGL(decode_merge_kernel, dim3(a.batch * a.hq), dim3(128), 0, st, a, hdr, ws_o, ws_ml, pmax);
+    hipLaunchKernelGGL(decode_merge_kernel, dim3((unsigned)(((int64_t)a.batch * a.hq + kMergeRows - 1) / kMergeRows)), dim3(32 * kMergeRows), 0, st, a, hdr, ws_o, ws_ml, pmax);
     prof_after(st);
     return hip_check(hipGetLastError(), "decode merge launch");
 }

@@ -619,21 +619,24 @@ __global__ __launch_bounds__(256, 2) void merged_split_kernel(AttnArgs a, int32_
     }
 }
 
-// Two (row, head) pairs per workgroup: the pair's partials are those of the workgroups its units were dealt to.
-__global__ __launch_bounds__(256) void merged_merge_kernel(AttnArgs a, const int32_t* __restrict__ hdr,
-                                                           const RowInfo* __restrict__ row_info,
-                                                           const float* __restrict__ ws_o,
-                                                           const float* __restrict__ ws_ml, int pmax)
+// Eight (row, head) pairs per workgroup, 32 lanes each: the pair's partials are those of the workgroups its units were
+// dealt to.
+constexpr int kMergePairs = 8;
+
+__global__ __launch_bounds__(32 * kMergePairs) void merged_merge_kernel(AttnArgs a, const int32_t* __restrict__ hdr,
+                                                                        const RowInfo* __restrict__ row_info,
+                                                                        const float* __restrict__ ws_o,
+                                                                        const float* __restrict__ ws_ml, int pmax)
 {
-    const int64_t rh = (int64_t)blockIdx.x * 2 + (threadIdx.x >> 7);        // row * hq + head
+    const int64_t rh = (int64_t)blockIdx.x * kMergePairs + (threadIdx.x >> 5);        // row * hq + head
     if (rh >= (int64_t)a.total_rows * a.hq) return;
     const int row = (int)(rh / a.hq), head = (int)(rh - (int64_t)row * a.hq);
-    const int d = threadIdx.x & 127;
+    const int d = (threadIdx.x & 31) * 4;
     const RowInfo ri = row_info[row];
     const int q = max(1, hdr[ri.kind == kRowsItem ? 1 : 0]);
     const int first = ri.first + (head / (a.hq / a.c.hkv)) * ri.stride;
     const int pieces = min(pmax, (first + ri.n - 1) / q - first / q + 1);
-    ((__bf16*)a.out)[rh * D + d] = (__bf16)merge_partials(ws_o, ws_ml, rh * pmax, pieces, d);
+    merge_quad(ws_o, ws_ml, rh * pmax, pieces, d, D, (__bf16*)a.out + rh * D);
 }
 
 inline int rows_per_group(int hq, int hkv) { return 16 / (hq / hkv); }
@@ -711,7 +714,7 @@ ag_status launch_merged_mfma(const AttnArgs& a, void* ws, hipStream_t st)
     if (e) return e;
     if ((e = hip_check(hipGetLastError(), "merged split launch"))) return e;
     const int64_t pairs = (int64_t)a.total_rows * a.hq;
-    hipLaunchKernelGGL(merged_merge_kernel, dim3((unsigned)((pairs + 1) / 2)), dim3(256), 0, st, a, hdr, row_info, ws_o, ws_ml, pmax);
+    hipLaunchKernelGGL(merged_merge_kernel, dim3((unsigned)((pairs + kMergePairs - 1) / kMergePairs)), dim3(32 * kMergePairs), 0, st, a, hdr, row_info, ws_o, ws_ml, pmax);
     return hip_check(hipGetLastError(), "merged merge launch");
 }
 

@@ -44,42 +44,81 @@ struct StepRegs {       // one wave's K and V operands for 32 tokens (two pages)
 
 // The partials (m, l, O[D]) of one (row, head) lie at slots base .. base + n - 1 (n >= 1, the first of them with a
 // finite m); combine them in slot order - reproducible - four at a time, so that a group's loads are in flight
-// together instead of one dependent round trip per partial.  Returns channel d of the normalised output.
-// kCoherent: the partials were written by other workgroups of the SAME launch (device-scope stores, see
-// store_coherent): read them with device-scope loads, which do not hit in this XCD's caches.
+// together instead of one dependent round trip per partial.
 __device__ __forceinline__ float load_coherent(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void store_coherent(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// kNatural: the partials' maxima are in natural units (fp32 caches), not in powers of two.  D_: channels per partial.
-template <bool kCoherent = false, bool kNatural = false>
-__device__ __forceinline__ float merge_partials(const float* __restrict__ ws_o, const float* __restrict__ ws_ml,
-                                                int64_t base, int n, int d, int D_ = D)
+// kNatural: the partials' maxima are in natural units (fp32 caches), not in powers of two.
+template <bool kNatural>
+__device__ __forceinline__ float merge_power(float x) { return kNatural ? expf(x) : exp2f(x); }
+
+// The combination itself, for N neighbouring channels of a pair: load(i, m, l, o) fetches partial i < n.
+template <int N, bool kNatural, class Load>
+__device__ __forceinline__ void merge_channels(int n, Load load, float (&out)[N])
 {
-    auto power = [](float x) { return kNatural ? expf(x) : exp2f(x); };
-    float ms = -INFINITY, acc = 0.f, l = 0.f;
+    float ms = -INFINITY, l = 0.f, acc[N];
+#pragma unroll
+    for (int e = 0; e < N; ++e) acc[e] = 0.f;
     for (int i0 = 0; i0 < n; i0 += 4) {
-        float mi[4], li[4], oi[4];
+        float mi[4], li[4], oi[4][N];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int64_t p = base + min(i0 + j, n - 1);
-            mi[j] = kCoherent ? load_coherent(ws_ml + p * 2) : ws_ml[p * 2];
-            li[j] = kCoherent ? load_coherent(ws_ml + p * 2 + 1) : ws_ml[p * 2 + 1];
-            oi[j] = kCoherent ? load_coherent(ws_o + p * D_ + d) : ws_o[p * D_ + d];
+            load(min(i0 + j, n - 1), mi[j], li[j], oi[j]);
             if (i0 + j >= n) mi[j] = -INFINITY;
         }
         const float m_new = fmaxf(fmaxf(ms, fmaxf(mi[0], mi[1])), fmaxf(mi[2], mi[3]));
-        const float keep = ms == -INFINITY ? 0.f : power(ms - m_new);
-        acc *= keep;
+        const float keep = ms == -INFINITY ? 0.f : merge_power<kNatural>(ms - m_new);
         l *= keep;
 #pragma unroll
+        for (int e = 0; e < N; ++e) acc[e] *= keep;
+#pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float f = mi[j] == -INFINITY ? 0.f : power(mi[j] - m_new);     // a partial that saw no key
-            acc += f * oi[j];
+            const float f = mi[j] == -INFINITY ? 0.f : merge_power<kNatural>(mi[j] - m_new);     // a partial that saw no key
             l += f * li[j];
+#pragma unroll
+            for (int e = 0; e < N; ++e) acc[e] += f * oi[j][e];
         }
         ms = m_new;
     }
-    return acc / l;
+#pragma unroll
+    for (int e = 0; e < N; ++e) out[e] = acc[e] / l;
+}
+
+// Channel d, from partials that other workgroups of the SAME launch wrote (device-scope stores, see store_coherent): read
+// with device-scope loads, which do not hit in this XCD's caches.
+__device__ __forceinline__ float merge_coherent(const float* __restrict__ ws_o, const float* __restrict__ ws_ml, int64_t base, int n, int d)
+{
+    float y[1];
+    merge_channels<1, false>(n, [&](int i, float& m, float& l, float (&o)[1]) {
+        m = load_coherent(ws_ml + (base + i) * 2);
+        l = load_coherent(ws_ml + (base + i) * 2 + 1);
+        o[0] = load_coherent(ws_o + (base + i) * D + d);
+    }, y);
+    return y[0];
+}
+
+// Channels d .. d + 3 of a pair with D_ channels, by the merge kernels: four channels a thread, so that a (row, head) takes
+// 32 lanes at 128 channels and 16-byte loads, and a launch a quarter of the workgroups.
+template <typename E, bool kNatural = false>
+__device__ __forceinline__ void merge_quad(const float* __restrict__ ws_o, const float* __restrict__ ws_ml, int64_t base, int n,
+                                           int d, int D_, E* __restrict__ out)
+{
+    float y[4];
+    merge_channels<4, kNatural>(n, [&](int i, float& m, float& l, float (&o)[4]) {
+        m = ws_ml[(base + i) * 2];
+        l = ws_ml[(base + i) * 2 + 1];
+        const f32x4 x = *reinterpret_cast<const f32x4*>(ws_o + (base + i) * D_ + d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = x[e];
+    }, y);
+    typedef E quad __attribute__((ext_vector_type(4)));
+    const quad q = {(E)y[0], (E)y[1], (E)y[2], (E)y[3]};
+    if ((uintptr_t)out % sizeof(quad) == 0) {            // (uniform: rows are multiples of it apart)
+        *reinterpret_cast<quad*>(out + d) = q;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[d + e] = q[e];
+    }
 }
 
 // Workspace is sized for the smallest split a launcher may choose.
