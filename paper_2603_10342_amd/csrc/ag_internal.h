@@ -63,6 +63,7 @@ ag_status launch_attn_general(const AttnArgs& a, hipStream_t st);
 
 // bf16, head_dim 128, page 16 matrix-core paths
 bool      prefill_mfma_supported(const AttnArgs& a);
+bool      prefill_mfma_lo_supported(const AttnArgs& a);        // other bf16 shapes that launch_prefill_mfma takes
 ag_status launch_prefill_mfma(const AttnArgs& a, hipStream_t st);
 bool      decode_mfma_supported(const AttnArgs& a);
 size_t    decode_workspace_bytes(int batch, int hq, int d, int max_ctx);

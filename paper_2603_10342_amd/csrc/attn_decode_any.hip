@@ -19,6 +19,7 @@
 // head_dim below its template's DT: loads beyond head_dim repeat its last channels; keys become zeros (as the query
 // does), values land in rows that are not stored.
 #include "attn_split_common.h"
+#include "bf16_terms.h"
 
 namespace ag {
 
@@ -192,7 +193,13 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, int s, int g, in
         if constexpr (kBf16) {
             bf16x8 hi, lo;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) { hi[j] = (__bf16)p[j]; lo[j] = (__bf16)(p[j] - (float)hi[j]); }
+            for (int j = 0; j < 8; j += 2) {
+                const bf16_pair h = {(__bf16)p[j], (__bf16)p[j + 1]}, l = low_terms(p[j], p[j + 1], h);
+                hi[j] = h[0];
+                hi[j + 1] = h[1];
+                lo[j] = l[0];
+                lo[j + 1] = l[1];
+            }
 #pragma unroll
             for (int mb = 0; mb < X::kV; ++mb) {
                 const bf16x8 v = __builtin_bit_cast(bf16x8, x.v[mb]);

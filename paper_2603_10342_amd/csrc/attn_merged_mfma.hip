@@ -357,13 +357,13 @@ __device__ __forceinline__ void tile_segment(const AttnArgs& a, float* __restric
     AG_WAIT_VMCNT(0);
     __syncthreads();
     tile32::f32x16 sc[2];
-    bf16x8 pa[4], pb[4];
+    tile32::Weights<false> pa, pb;
 
     // Iteration t: S(t) from K(t); then P(t) side by side with O += V(t-1).P(t-1).  It starts by requesting V(t)
     // and K(t+2) and ends when V(t) and K(t+1) have landed.  Requests past the last tile repeat it into a buffer
     // nobody reads, so the loop has one shape; every wave runs all n_tiles + 1 iterations (the barriers are
     // workgroup-wide) and skips the pieces it does not need.
-    auto iter = [&](int t, bf16x8 (&p_prev)[4], bf16x8 (&p_cur)[4]) {
+    auto iter = [&](int t, tile32::Weights<false>& p_prev, tile32::Weights<false>& p_cur) {
         const int tv = min(t, n_tiles - 1);
         request_v(t & 1, pg.v);
         request_k(t + 2, pg.k);
@@ -373,7 +373,7 @@ __device__ __forceinline__ void tile_segment(const AttnArgs& a, float* __restric
         const unsigned char* kb = k_lane + (t % kKStages) * kTile;
         const unsigned char* vb = v_lane + ((t + 1) & 1) * kTile;    // V(t-1)
         if (do_sm) {
-            tile32::qk_tile(kb, qf, sc);
+            tile32::qk_tile<D>(kb, qf, sc);
             if (t >= first_masked) {                 // the tile straddles this wave's diagonal
                 const int kbase = (tb + t) * BN + hi * 4;
 #pragma unroll
@@ -385,7 +385,7 @@ __device__ __forceinline__ void tile_segment(const AttnArgs& a, float* __restric
                     }
             }
         }
-        tile32::softmax_and_value_product(do_sm, do_pv, vb, sc, sl2, m, lsum, p_prev, p_cur, o);
+        tile32::softmax_and_value_product<D, false>(do_sm, do_pv, vb, sc, sl2, m, lsum, p_prev, p_cur, o);
         AG_WAIT_VMCNT(kPer);
         scrub_v(t & 1, tb + tv);
         pg = nxt;

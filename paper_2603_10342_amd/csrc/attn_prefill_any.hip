@@ -1,5 +1,5 @@
 // Cold and resume prefill over paged KV caches of any supported head_dim and dtype with pages of 16 tokens or more
-// (bf16 with head_dim 128 on 16-token pages has a kernel of its own, attn_prefill_mfma.hip).
+// (bf16 at head_dim 128, and at 64 on long contexts, takes attn_prefill_mfma.hip: see prefill_mfma_lo_supported()).
 //
 // A dense contraction, bound by the matrix cores.  A workgroup of four waves owns 128 columns of one (session, KV
 // head): a column is a (token, query head of the group) pair, numbered token * G + head, so that any group size fills
@@ -12,12 +12,13 @@
 // Precision: fp32 runs in fp32 throughout (expf, fp32 products: 157 TFLOP/s at most); bf16 caches multiply the weights
 // as two bf16 terms (hi + lo), half again the matrix work, so that no weight is cut to 8 bits.
 // Measured, append included (one wave per (row, query head) before -> now): four fp32 prompts of 300..1500 rows at
-// 32 / 8 heads x 128, 30.4 ms -> 0.38 ms (95 TFLOP/s); eight bf16 chunks of 40..500 rows on 500..4000 tokens at head_dim
-// 64, 64-token pages, 20.4 -> 0.117 ms (420 TFLOP/s of result, 630 of products).
+// 32 / 8 heads x 128, 30.4 ms -> 0.38 ms (95 TFLOP/s); eight bf16 prompts of 2048 rows at head_dim 64, 64-token pages,
+// 57 -> 0.266 ms (517 TFLOP/s of result, 776 of products).
 #include <algorithm>
 #include <atomic>
 
 #include "ag_internal.h"
+#include "bf16_terms.h"
 #include "lds_dma.h"
 #include "tile_list.h"
 
@@ -51,7 +52,7 @@ __device__ __forceinline__ void with_operands(At at, Use use)
 }
 
 template <typename E, int DT, bool kExact>
-__global__ __launch_bounds__(256, DT > 128 ? 1 : 2) void prefill_any_kernel(AttnArgs a, int tiles_max, int per_xcd, int64_t total_work)
+__global__ __launch_bounds__(256, DT > 128 ? 1 : 2) void prefill_any_kernel(AttnArgs a, int tiles_max, int per_xcd, int total_work)
 {
     constexpr bool kBf16 = sizeof(E) == 2;
     constexpr int BN = 128 / (int)sizeof(E);        // keys per tile
@@ -65,30 +66,29 @@ __global__ __launch_bounds__(256, DT > 128 ? 1 : 2) void prefill_any_kernel(Attn
 
     // ---- which (KV head, session, tile): the XCD a workgroup lands on owns a contiguous range of KV heads ----
     const int xcd = blockIdx.x & 7, ord = blockIdx.x >> 3;
-    const int64_t wk = (int64_t)xcd * per_xcd + ord;
-    if (wk >= total_work) return;
+    const unsigned wk = (unsigned)(xcd * per_xcd + ord);
+    if (wk >= (unsigned)total_work) return;
     const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv;
     const int D = kExact ? DT : a.c.d, ps = a.c.ps;
-    const int g = (int)(wk / tiles_max);
+    const int g = (int)(wk / (unsigned)tiles_max);
     int s = -1, qt = 0, N = 0, P = 0, row0 = 0;
-    find_tile(a, (int)(wk % tiles_max), [G](int len) { return (int)(((int64_t)len * G + kColumns - 1) / kColumns); }, s, qt, N, P, row0);
+    find_tile(a, (int)(wk - (unsigned)g * (unsigned)tiles_max), [G](int len) { return (int)(((int64_t)len * G + kColumns - 1) / kColumns); }, s, qt, N, P, row0);
     if (s < 0) return;                              // beyond the batch's tiles
     const int ctx = P + N;
-    const int cols = (int)min((int64_t)N * G - (int64_t)qt * kColumns, (int64_t)kColumns);      // valid columns of the tile
-    const int64_t col0 = (int64_t)qt * kColumns;
+    const int col0 = qt * kColumns, cols = min(N * G - col0, kColumns);       // valid columns of the tile
+    const Columns columns(col0, G);
 
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
     const int wu = __builtin_amdgcn_readfirstlane(w);           // the same value, known to be uniform
     const int n = lane & 31, hi = lane >> 5;
     const int cols_w = max(0, min(32, cols - 32 * wu));
-    auto token_of = [&](int col) { return (int)((col0 + col) / G); };
-    const int last_token = token_of(cols - 1);
+    const int last_token = columns.token(cols - 1);
     const int n_tiles = (P + last_token) / BN + 1;                            // tiles the workgroup stages
-    const int wave_tiles = cols_w > 0 ? (P + token_of(32 * wu + cols_w - 1)) / BN + 1 : 0;     // tiles this wave uses
-    const int first_masked = (P + token_of(32 * wu) + 1) / BN;  // first tile holding a key this wave's first column may not see
+    const int wave_tiles = cols_w > 0 ? (P + columns.token(32 * wu + cols_w - 1)) / BN + 1 : 0;     // tiles this wave uses
+    const int first_masked = (P + columns.token(32 * wu) + 1) / BN;  // first tile holding a key this wave's first column may not see
 
     const int col = min(32 * w + n, cols - 1);                  // columns beyond the tile repeat the last one
-    const int token = token_of(col), head = (int)(col0 + col - (int64_t)token * G);
+    const int token = columns.token(col), head = columns.head(col, token);
     const int qpos = P + token;
     const int64_t row = ((int64_t)row0 + token) * hq + (int64_t)g * G + head;
 
@@ -257,9 +257,12 @@ __global__ __launch_bounds__(256, DT > 128 ? 1 : 2) void prefill_any_kernel(Attn
             if constexpr (kBf16) {
                 bf16x8 ph[4], pl[4];                            // weights as two bf16 terms, in k-step order
 #pragma unroll
-                for (int i = 0; i < 32; ++i) {
-                    ph[i >> 3][i & 7] = (__bf16)x[i];
-                    pl[i >> 3][i & 7] = (__bf16)(x[i] - (float)ph[i >> 3][i & 7]);
+                for (int i = 0; i < 32; i += 2) {
+                    const bf16_pair h = {(__bf16)x[i], (__bf16)x[i + 1]}, l = low_terms(x[i], x[i + 1], h);
+                    ph[i >> 3][i & 7] = h[0];
+                    ph[i >> 3][(i & 7) + 1] = h[1];
+                    pl[i >> 3][i & 7] = l[0];
+                    pl[i >> 3][(i & 7) + 1] = l[1];
                 }
                 with_operands<4 * kMb>([&](int i) { return vb + (i / kMb) * 2 * DT * 16 + (i % kMb) * 512; }, [&](int i, u32x4 v) {
                     const bf16x8 vv = __builtin_bit_cast(bf16x8, v);
@@ -329,7 +332,7 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
     const int64_t tiles_max = tiles_bound(a), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
     prof_before(st);
     hipLaunchKernelGGL((prefill_any_kernel<E, DT, kExact>), dim3((unsigned)(per_xcd * 8)), dim3(256), lds, st, a, (int)tiles_max,
-                       (int)per_xcd, total);
+                       (int)per_xcd, (int)total);
     prof_after(st);
     return hip_check(hipGetLastError(), "prefill launch");
 }
@@ -338,7 +341,10 @@ template <typename E>
 ag_status launch_for_dim(const AttnArgs& a, hipStream_t st)
 {
     if (a.c.d <= 64) return a.c.d == 64 ? launch_kernel<E, 64, true>(a, st) : launch_kernel<E, 64, false>(a, st);
-    if (a.c.d <= 128) return a.c.d == 128 ? launch_kernel<E, 128, true>(a, st) : launch_kernel<E, 128, false>(a, st);
+    if constexpr (sizeof(E) == 4) {                 // (bf16 at 128 never comes here)
+        if (a.c.d == 128) return launch_kernel<E, 128, true>(a, st);
+    }
+    if (a.c.d <= 128) return launch_kernel<E, 128, false>(a, st);
     return a.c.d == 256 ? launch_kernel<E, 256, true>(a, st) : launch_kernel<E, 256, false>(a, st);
 }
 
@@ -349,11 +355,12 @@ ag_status launch_for_dim(const AttnArgs& a, hipStream_t st)
 bool prefill_any_supported(const AttnArgs& a)
 {
     return a.c.ps >= 16 && (((uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 == 0) &&
-           a.c.hkv * tiles_bound(a) + 8 <= 0x7fffffff;
+           a.c.hkv * tiles_bound(a) + 8 <= 0x7fffffff && (int64_t)a.total_rows * (a.hq / a.c.hkv) <= 0x7fffffff;
 }
 
 ag_status launch_prefill_any(const AttnArgs& a, hipStream_t st)
 {
+    if (prefill_mfma_lo_supported(a)) return launch_prefill_mfma(a, st);
     if (prefill_split_preferred(a, st)) return launch_prefill_split(a, st);
     return a.c.dtype == AG_BF16 ? launch_for_dim<__bf16>(a, st) : launch_for_dim<float>(a, st);
 }

@@ -16,6 +16,7 @@
 #include <atomic>
 
 #include "ag_internal.h"
+#include "bf16_terms.h"
 #include "tile_list.h"
 
 namespace ag {
@@ -38,7 +39,7 @@ constexpr int lds_bytes(int dt) { return kWaves * kColumns * (o_row(dt) + 2) * 4
 
 // kLo: bf16 weights as two terms (hi + lo); false keeps the rounded weights of the bf16 / 128 / 16 kernels.
 template <typename E, int DT, bool kLo>
-__global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs a, int tiles_max, int per_xcd, int64_t total_work)
+__global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs a, int tiles_max, int per_xcd, int total_work)
 {
     constexpr bool kBf16 = sizeof(E) == 2;
     constexpr int kK = DT * (int)sizeof(E) / 32;    // 16-byte loads of a lane per step: keys
@@ -50,25 +51,28 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
 
     // ---- which (KV head, session, tile): the XCD a workgroup lands on owns a contiguous range of KV heads ----
     const int xcd = blockIdx.x & 7, ord = blockIdx.x >> 3;
-    const int64_t wk = (int64_t)xcd * per_xcd + ord;
-    if (wk >= total_work) return;
+    const unsigned wk = (unsigned)(xcd * per_xcd + ord);
+    if (wk >= (unsigned)total_work) return;
     const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv, ps = a.c.ps;
-    const int g = (int)(wk / tiles_max);
+    const int g = (int)(wk / (unsigned)tiles_max);
     int s = -1, qt = 0, N = 0, P = 0, row0 = 0;
-    find_tile(a, (int)(wk % tiles_max), [G](int len) { return (int)(((int64_t)len * G + kColumns - 1) / kColumns); }, s, qt, N, P, row0);
+    find_tile(a, (int)(wk - (unsigned)g * (unsigned)tiles_max), [G](int len) { return (int)(((int64_t)len * G + kColumns - 1) / kColumns); }, s, qt, N, P, row0);
     if (s < 0) return;                              // beyond the batch's tiles
     const int ctx = P + N;
-    const int64_t col0 = (int64_t)qt * kColumns;
-    const int cols = (int)min((int64_t)N * G - col0, (int64_t)kColumns);
+    const int col0 = qt * kColumns, cols = min(N * G - col0, kColumns);
+    const Columns columns(col0, G);
+    auto row_of = [&](int col, int& token) {                    // row (token, head) of Q and O that a column is
+        token = columns.token(col);
+        return ((int64_t)row0 + token) * hq + (int64_t)g * G + columns.head(col, token);
+    };
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, hi = lane >> 5;
-    const int first_token = (int)(col0 / G), last_token = (int)((col0 + cols - 1) / G);
-    const int64_t flat = col0 + min(n, cols - 1);               // columns beyond the tile repeat the last one
-    const int token = (int)(flat / G), head = (int)(flat - (int64_t)token * G);
+    const int first_token = columns.token(0), last_token = columns.token(cols - 1);
+    int token;
+    const int64_t q_row = row_of(min(n, cols - 1), token);      // columns beyond the tile repeat the last one
     const int qpos = P + token;
-    const int64_t q_row = ((int64_t)row0 + token) * hq + (int64_t)g * G + head;
 
     const int n_steps = (P + last_token) / kStep + 1;           // of the tile
     const int my_n = w < n_steps ? (n_steps - w - 1) / kWaves + 1 : 0;         // this wave's: steps w, w + 8, ...
@@ -88,8 +92,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
         constexpr int kPieces = DT * 4 / 16;
         for (int idx = tid; idx < kColumns * kPieces; idx += 64 * kWaves) {
             const int c = idx / kPieces, p = idx - c * kPieces;
-            const int64_t f = col0 + min(c, cols - 1);
-            const int64_t r = ((int64_t)row0 + f / G) * hq + (int64_t)g * G + f % G;
+            int t;
+            const int64_t r = row_of(min(c, cols - 1), t);
             *reinterpret_cast<u32x4*>(lds + c * kQRow + p * 16) = *reinterpret_cast<const u32x4*>((const E*)a.q + r * DT + p * 4);
         }
     } else {
@@ -209,8 +213,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
                 ph[e >> 3][e & 7] = pr[0];
                 ph[e >> 3][(e & 7) + 1] = pr[1];
                 if constexpr (kLo) {
-                    pl[e >> 3][e & 7] = (__bf16)(p0 - (float)pr[0]);
-                    pl[e >> 3][(e & 7) + 1] = (__bf16)(p1 - (float)pr[1]);
+                    const bf16x2 rest = low_terms(p0, p1, pr);
+                    pl[e >> 3][e & 7] = rest[0];
+                    pl[e >> 3][(e & 7) + 1] = rest[1];
                     lsum += p0 + p1;
                 } else {
                     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
@@ -275,8 +280,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
             for (int e = 0; e < 8; ++e) acc[e] += f * s_o[(ww * kColumns + c) * o_row(DT) + d + e];
         }
         const float inv = 1.0f / l;
-        const int64_t f = col0 + c;
-        E* out = (E*)a.out + (((int64_t)row0 + f / G) * hq + (int64_t)g * G + f % G) * DT + d;
+        int t;
+        E* out = (E*)a.out + row_of(c, t) * DT + d;
         E y[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) y[e] = (E)(acc[e] * inv);
@@ -305,7 +310,7 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
     const int64_t tiles_max = tiles_bound(a, kColumns), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
     prof_before(st);
     hipLaunchKernelGGL((prefill_split_kernel<E, DT, kLo>), dim3((unsigned)(per_xcd * 8)), dim3(64 * kWaves), lds_bytes(DT), st, a,
-                       (int)tiles_max, (int)per_xcd, total);
+                       (int)tiles_max, (int)per_xcd, (int)total);
     prof_after(st);
     return hip_check(hipGetLastError(), "prefill launch");
 }
@@ -322,7 +327,7 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 // 873 -> 227, two prompts of 1000 (2000) 276 -> 216, four of 300..1500 (3600) 377 -> 461.
 bool prefill_split_preferred(const AttnArgs& a, hipStream_t st)
 {
-    if ((a.c.d != 64 && a.c.d != 128) || a.c.ps < 16 ||
+    if ((a.c.d != 64 && a.c.d != 128) || a.c.ps < 16 || (int64_t)a.total_rows * (a.hq / a.c.hkv) > 0x7fffffff ||
         ((uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 != 0) return false;
     const int per_cu = a.c.dtype == AG_F32 ? 10 : a.c.d == 128 && a.c.ps == 16 ? 2 : 3;
     return a.c.hkv * tiles_bound(a, kColumns) <= (int64_t)per_cu * stream_cus(st);

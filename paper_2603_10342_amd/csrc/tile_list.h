@@ -71,4 +71,16 @@ __device__ __forceinline__ void find_tile(const AttnArgs& a, int j, TilesOf tile
     }
 }
 
+// Columns of a (session, KV head): number token * G + head.  A workgroup's columns start at col0 (total_rows * G fits an
+// int); token and head of a column are found from those of col0 with one multiplication - a 64-bit division for each of the
+// handful a workgroup needs took 1 % of a long prefill.
+struct Columns {
+    int t0, r0, G;          // token of col0, its head
+    float inv;
+    __device__ __forceinline__ Columns(int col0, int G_) : t0((unsigned)col0 / (unsigned)G_), r0(col0 - t0 * G_), G(G_), inv(1.0f / (float)G_) {}
+    // exact: r0 + col < G + 256, and half a column is far more than the product's rounding
+    __device__ __forceinline__ int token(int col) const { return t0 + (int)(((float)(r0 + col) + 0.5f) * inv); }
+    __device__ __forceinline__ int head(int col, int token) const { return r0 + col - (token - t0) * G; }
+};
+
 }  // namespace ag
