@@ -18,6 +18,7 @@
 // head_dim 64, 32-token pages, 2238 -> 65 us (333 MB, 5.2 TB/s); two fp32 sessions of 300, 4 / 2 heads x 64, 106 -> 12 us.
 // head_dim below its template's DT: loads beyond head_dim repeat its last channels; keys become zeros (as the query
 // does), values land in rows that are not stored.
+#include "attn_general_row.h"
 #include "attn_split_common.h"
 #include "bf16_terms.h"
 
@@ -349,6 +350,7 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
     __shared__ float s_o[kDirectWaves][kCols][kChan];
     __shared__ float s_m[kDirectWaves][kCols];
     __shared__ float s_l[kDirectWaves][kCols];
+    __shared__ uint32_t s_again;                                 // bit h: head h has an element that is not finite
     __shared__ __attribute__((aligned(16))) unsigned char s_q[kCols * q_row<E, DT>()];
     const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv, D = kExact ? DT : a.c.d;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -372,6 +374,7 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
     const int r = lane & 15, c = lane >> 4;
     auto power = [](float x) { return kBf16 ? __builtin_amdgcn_exp2f(x) : expf(x); };
     if (c == 0) { s_m[w][r] = m; s_l[w][r] = lsum; }
+    if (tid == 0) s_again = 0;
 #pragma unroll
     for (int d0 = 0; d0 < DT; d0 += kChan) {
         if (d0 > 0) __syncthreads();
@@ -391,9 +394,14 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
                 acc += fw * s_o[ww][head][dl];
                 l += fw * s_l[ww][head];
             }
-            out[head * D + d0 + dl] = (E)(acc / l);
+            const float y = acc / l;
+            out[head * D + d0 + dl] = (E)y;
+            if (!(general::trouble_of(y) == 0.f)) atomicOr(&s_again, 1u << head);
         }
     }
+    __syncthreads();                                             // (two-term weights turn an infinite sum into NaN)
+    const uint32_t all = __builtin_amdgcn_readfirstlane(s_again);
+    if (all) general::attend_rows_again<E>(a, all & (0x0101u << w), (int64_t)s * hq + (int64_t)g * G + h0 + r, s, s, ctx - 1, &s_o[w][0][0]);
 }
 
 template <typename E>
@@ -403,20 +411,30 @@ __global__ __launch_bounds__(256) void decode_any_merge_kernel(AttnArgs a, const
 {
     const int D = a.c.d, quads = D >> 2;        // lanes of a row
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x, row = idx / quads;      // s * hq + h
-    if (row >= (int64_t)a.batch * a.hq) return;
     const int s = (int)(row / a.hq), h = (int)(row - (int64_t)s * a.hq), d = (int)(idx - row * quads) * 4;
-    const int ctx = a.ctx_lens[s];
+    const int ctx = row < (int64_t)a.batch * a.hq ? max(a.ctx_lens[s], 0) : -1;      // -1: no row
     E* out = (E*)a.out + row * D;
-    if (ctx <= 0) {
+    float trouble = 0.f;
+    if (ctx == 0) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) out[d + e] = (E)0.0f;
-        return;
+    } else if (ctx > 0) {
+        const int G = a.hq / a.c.hkv, g = h / G;
+        const int q = max(1, hdr[0]), n = steps_of(ctx);
+        const int first = a.c.hkv * head_blocks * hdr[1 + s] + (g * head_blocks + (h - g * G) / kCols) * n;
+        const int pieces = min(pmax, (first + n - 1) / q - first / q + 1);   // as the split kernel cuts them
+        const f32x4 y = splitk::merge_quad<E, sizeof(E) == 4>(ws_o, ws_ml, row * pmax, pieces, d, D, out);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) trouble = general::trouble_of(y[e], trouble);
     }
-    const int G = a.hq / a.c.hkv, g = h / G;
-    const int q = max(1, hdr[0]), n = steps_of(ctx);
-    const int first = a.c.hkv * head_blocks * hdr[1 + s] + (g * head_blocks + (h - g * G) / kCols) * n;
-    const int pieces = min(pmax, (first + n - 1) / q - first / q + 1);       // as the split kernel cuts them
-    splitk::merge_quad<E, sizeof(E) == 4>(ws_o, ws_ml, row * pmax, pieces, d, D, out);
+    // (two-term weights, and partials taken with a weight of zero, turn an infinite sum into NaN)
+    __shared__ float s_q[4][256];
+    uint64_t again = __builtin_amdgcn_ballot_w64(!(trouble == 0.f));
+    while (again) {                             // one row at a time: other waves that hold a part of it write the same
+        const int l = __builtin_ctzll(again), r = __builtin_amdgcn_readlane((int)row, l), rs = __builtin_amdgcn_readlane(s, l);
+        general::attend_rows_again<E>(a, 1ull << l, row, rs, rs, __builtin_amdgcn_readlane(ctx, l) - 1, s_q[threadIdx.x >> 6]);
+        again &= ~__builtin_amdgcn_ballot_w64((int)row == r);
+    }
 }
 
 inline int head_blocks_of(const AttnArgs& a) { return (a.hq / a.c.hkv + kCols - 1) / kCols; }

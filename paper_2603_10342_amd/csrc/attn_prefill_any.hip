@@ -18,6 +18,7 @@
 #include <atomic>
 
 #include "ag_internal.h"
+#include "attn_general_row.h"
 #include "bf16_terms.h"
 #include "lds_dma.h"
 #include "tile_list.h"
@@ -285,7 +286,14 @@ __global__ __launch_bounds__(256, DT > 128 ? 1 : 2) void prefill_any_kernel(Attn
     // o[mb][q4 * 4 + e] is O^T[channel mb * 32 + q4 * 8 + hi * 4 + e][column n]
     lsum += __shfl_xor(lsum, 32);
     const float inv = 1.0f / lsum;
-    if (n < cols_w) {
+    float trouble = general::trouble_of(inv);
+#pragma unroll
+    for (int mb = 0; mb < DT / 32; ++mb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) trouble = general::trouble_of(o[mb][i], trouble);
+    uint64_t again = __builtin_amdgcn_ballot_w64(n < cols_w && !(trouble == 0.f));
+    again = (again | (again >> 32)) & 0xFFFFFFFFu;              // bit c: column c of this wave
+    if (n < cols_w && !((again >> n) & 1)) {
         E* out = (E*)a.out + row * D + hi * 4;
 #pragma unroll
         for (int mb = 0; mb < DT / 32; ++mb)
@@ -306,6 +314,7 @@ __global__ __launch_bounds__(256, DT > 128 ? 1 : 2) void prefill_any_kernel(Attn
                 }
             }
     }
+    general::attend_rows_again<E>(a, again, row, s, row0, P, reinterpret_cast<float*>(lds) + 256 * wu);       // (all are past the last tile)
 }
 
 // sum_s ceil(N_s G / 128) <= total G / 128 + batch, and no session has more than ceil(max_new G / 128)

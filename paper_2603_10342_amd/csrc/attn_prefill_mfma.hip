@@ -47,6 +47,7 @@
 #include <atomic>
 
 #include "ag_internal.h"
+#include "attn_general_row.h"
 #include "attn_tile32.h"
 #include "lds_dma.h"
 #include "tile_list.h"
@@ -289,6 +290,15 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, in
     lsum += __shfl_xor(lsum, 32);
     const float inv = 1.0f / lsum;
     constexpr int kChunks = DT / 8;                 // 16-byte pieces of a row
+    uint64_t again = 0;
+    if constexpr (kLo) {
+        float trouble = general::trouble_of(inv);
+#pragma unroll
+        for (int mb = 0; mb < DT / 32; ++mb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) trouble = general::trouble_of(o[mb][i], trouble);
+        again = __builtin_amdgcn_ballot_w64(n < cols_w && !(trouble == 0.f));
+    }
     unsigned char* ob = lds + w * (32 * DT * 2);    // this wave's [32 columns][DT ch] bf16, rows XOR-swizzled
 #pragma unroll
     for (int mb = 0; mb < DT / 32; ++mb)
@@ -314,6 +324,10 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, in
                 *reinterpret_cast<u32x4*>(outp + (int64_t)row * DT) = x;
             }
         }
+    }
+    if constexpr (kLo) {
+        again = (again | (again >> 32)) & 0xFFFFFFFFu;          // bit c: column c of this wave
+        general::attend_rows_again<__bf16>(a, again, (int64_t)base_row + (unsigned)my_row, s, row0, P, reinterpret_cast<float*>(ob));
     }
 }
 

@@ -16,6 +16,7 @@
 #include <atomic>
 
 #include "ag_internal.h"
+#include "attn_general_row.h"
 #include "bf16_terms.h"
 #include "tile_list.h"
 
@@ -35,7 +36,7 @@ constexpr int kStep = 32;               // keys of a wave's step
 constexpr float kLog2e = 1.4426950408889634f;
 
 constexpr int o_row(int dt) { return dt + 4; }          // floats of a column's partial in LDS, padded
-constexpr int lds_bytes(int dt) { return kWaves * kColumns * (o_row(dt) + 2) * 4; }
+constexpr int lds_bytes(int dt) { return kWaves * kColumns * (o_row(dt) + 2) * 4 + 16; }
 
 // kLo: bf16 weights as two terms (hi + lo); false keeps the rounded weights of the bf16 / 128 / 16 kernels.
 template <typename E, int DT, bool kLo>
@@ -44,6 +45,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
     constexpr bool kBf16 = sizeof(E) == 2;
     constexpr int kK = DT * (int)sizeof(E) / 32;    // 16-byte loads of a lane per step: keys
     constexpr int kMb = DT / 32;
+    constexpr bool kTakeAgain = kLo || !kBf16;      // columns that are not finite, in plain arithmetic (attn_general_row.h)
     constexpr int kRuns = kBf16 ? 2 : 4;            // runs of keys a lane's weights fall into: 8 keys (bf16), 4 (fp32)
     constexpr bool kQInLds = !kBf16;                // fp32 queries are twice the registers and are read a quarter as often
     constexpr float kSlack = kBf16 ? 8.0f : 5.5f;   // how far a maximum may outgrow the reference before O is rescaled
@@ -263,7 +265,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
             const f32x4 x = {o[mb][q4 * 4], o[mb][q4 * 4 + 1], o[mb][q4 * 4 + 2], o[mb][q4 * 4 + 3]};
             *reinterpret_cast<f32x4*>(s_o + (w * kColumns + n) * o_row(DT) + mb * 32 + q4 * 8 + hi * 4) = x;
         }
+    uint32_t* const s_again = reinterpret_cast<uint32_t*>(s_l + kWaves * kColumns);       // bit c: column c is not finite
     if (hi == 0) { s_m[w * kColumns + n] = m; s_l[w * kColumns + n] = lsum; }
+    if (kTakeAgain && tid == 0) *s_again = 0;
     __syncthreads();
     auto power = [](float x) { return kBf16 ? __builtin_amdgcn_exp2f(x) : expf(x); };
     for (int idx = tid; idx < cols * (DT / 8); idx += 64 * kWaves) {
@@ -287,6 +291,18 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
         for (int e = 0; e < 8; ++e) y[e] = (E)(acc[e] * inv);
 #pragma unroll
         for (int e = 0; e < (int)sizeof(E) / 2; ++e) reinterpret_cast<u32x4*>(out)[e] = reinterpret_cast<const u32x4*>(y)[e];
+        if constexpr (kTakeAgain) {
+            float trouble = general::trouble_of(inv);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) trouble = general::trouble_of(acc[e], trouble);
+            if (!(trouble == 0.f)) atomicOr(s_again, 1u << c);
+        }
+    }
+    if constexpr (kTakeAgain) {
+        __syncthreads();                                        // what the waves write once more is behind what is there
+        const uint32_t all = __builtin_amdgcn_readfirstlane(*s_again);
+        int t;
+        if (all) general::attend_rows_again<E>(a, all & (0x01010101u << w), row_of(min(n, cols - 1), t), s, row0, P, s_o + 256 * w);
     }
 }
 

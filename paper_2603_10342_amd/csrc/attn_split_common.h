@@ -100,7 +100,7 @@ __device__ __forceinline__ float merge_coherent(const float* __restrict__ ws_o, 
 // Channels d .. d + 3 of a pair with D_ channels, by the merge kernels: four channels a thread, so that a (row, head) takes
 // 32 lanes at 128 channels and 16-byte loads, and a launch a quarter of the workgroups.
 template <typename E, bool kNatural = false>
-__device__ __forceinline__ void merge_quad(const float* __restrict__ ws_o, const float* __restrict__ ws_ml, int64_t base, int n,
+__device__ __forceinline__ f32x4 merge_quad(const float* __restrict__ ws_o, const float* __restrict__ ws_ml, int64_t base, int n,
                                            int d, int D_, E* __restrict__ out)
 {
     float y[4];
@@ -119,6 +119,7 @@ __device__ __forceinline__ void merge_quad(const float* __restrict__ ws_o, const
 #pragma unroll
         for (int e = 0; e < 4; ++e) out[d + e] = q[e];
     }
+    return f32x4{y[0], y[1], y[2], y[3]};
 }
 
 // Workspace is sized for the smallest split a launcher may choose.

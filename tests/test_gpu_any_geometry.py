@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_helpers import DevBatch, check_close, gpu_append, gpu_decode, gpu_merged, i32, make_cache, pools_match, run_phase, to_dev
+from gpu_helpers import DevBatch, check_close, gpu_append, gpu_decode, gpu_merged, gpu_prefill, i32, make_cache, pools_match, run_phase, to_dev
 from helpers import fresh_pools, make_batch, oracle_append, oracle_attn
 from oracle import oracle as O
 from paper_2603_10342_amd import binding as B
@@ -191,3 +191,46 @@ def test_merged_queue_and_sharp_logits(dtype, d, ps):
         oracle_append(kp, vp, b)
     got, ref = gpu_merged(cache, DevBatch(chunk)), oracle_attn(kp, vp, chunk)
     check_close(got, ref, dtype, f"queue D={d} page={ps}")
+
+
+# An infinity among the values belongs to the rows that see its token, and only to its channel; an infinite key makes the
+# rows that see it infinite or leaves it out, by the sign of the query's channel.
+@pytest.mark.parametrize("dtype,d,ps,hq,hkv", [GEOMETRIES[i] for i in (0, 2, 3, 5, 6, 8, 9, 10, 11, 13)])
+@pytest.mark.parametrize("cus_per_xcd", [0, 1])
+def test_an_infinite_value_stays_with_the_rows_that_see_it(dtype, d, ps, hq, hkv, cus_per_xcd):
+    lens, at, ch, G = [150, 290], 100, d // 2 + 3, hq // hkv
+    pages = sum((n + 1 + ps - 1) // ps for n in lens) + 3
+    g = I.Geometry(hq, hkv, d, ps, pages, dtype)
+    bt = I.deal_block_tables(I.rng_for(58, 0), [n + 1 for n in lens], ps, pages)
+    b = make_batch(g, [0, 0], lens, seed=58, bt=bt)
+    one = make_batch(g, lens, [1, 1], seed=58, bt=bt, stream=2)
+    kp, vp = fresh_pools(g)
+    oracle_append(kp, vp, b)
+    ref = oracle_attn(kp, vp, b)
+    oracle_append(kp, vp, one)
+    ref_one = oracle_attn(kp, vp, one)
+    cache, db, d1 = make_cache(g), DevBatch(b), DevBatch(one)
+    db.v_new[at, 0, ch] = float("inf")                     # session 0, token 100
+    db.k_new[lens[0] + at, hkv - 1, ch] = float("-inf")    # session 1, token 100
+    stream = None
+    if cus_per_xcd:
+        stream = B.ag_stream_create_cumask(B.ag_cumask_build(B.ag_device_info()["num_cus"], 8, 0, cus_per_xcd))
+    try:
+        torch.cuda.synchronize()
+        with torch.cuda.stream(torch.cuda.ExternalStream(stream) if stream else torch.cuda.current_stream()):
+            gpu_append(cache, db)
+            got = gpu_prefill(cache, db)
+            gpu_append(cache, d1)
+            got_one = gpu_decode(cache, d1.q, d1.bt, d1.ctx, d1.max_ctx, g)
+    finally:
+        torch.cuda.synchronize()
+        if stream:
+            B.ag_stream_destroy(stream)
+    for x, r, q, first, last, second in ((got, ref, b.q, at, lens[0], lens[0] + at), (got_one, ref_one, one.q, 0, 1, 1)):
+        assert np.all(x[first:last, :G, ch] == np.inf)
+        x[first:last, :G, ch] = r[first:last, :G, ch]
+        seen, want = x[second:, (hkv - 1) * G:], r[second:, (hkv - 1) * G:]
+        plus = I.stored_to_f64(q, dtype)[second:, (hkv - 1) * G:, ch] > 0        # score -inf: a weight of zero
+        assert np.isfinite(seen[plus]).all() and np.isnan(seen[~plus]).all()
+        seen[...] = want
+        check_close(x, r, dtype, f"D={d} page={ps} {hq}/{hkv} on {cus_per_xcd} CUs per XCD")
