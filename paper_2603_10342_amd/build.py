@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libagattn.so")
-SOURCES = ["ag_api.hip", "kv_append.hip", "attn_general.hip", "attn_decode_mfma.hip", "attn_decode_any.hip", "attn_prefill_mfma.hip", "attn_prefill_any.hip", "attn_prefill_split.hip",
+SOURCES = ["ag_api.hip", "kv_append.hip", "attn_general.hip", "attn_decode_mfma.hip", "attn_decode_any.hip", "attn_prefill_mfma.hip", "attn_prefill_any.hip", "attn_prefill_split.hip", "attn_prefill_f32.hip",
            "attn_merged_mfma.hip",
            "ag_sched.hip", "ag_pager.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

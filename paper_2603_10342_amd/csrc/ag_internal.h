@@ -75,6 +75,9 @@ bool      decode_any_supported(const AttnArgs& a);
 ag_status launch_decode_any(const AttnArgs& a, hipStream_t st);
 bool      prefill_any_supported(const AttnArgs& a);
 ag_status launch_prefill_any(const AttnArgs& a, hipStream_t st);
+// fp32 at head_dim 64 and 128 on the bf16 matrix cores
+bool      prefill_f32_supported(const AttnArgs& a);
+ag_status launch_prefill_f32(const AttnArgs& a, hipStream_t st);
 // few rows on long contexts: the keys of a query tile split over the waves of one workgroup
 bool      prefill_split_preferred(const AttnArgs& a, hipStream_t st);
 ag_status launch_prefill_split(const AttnArgs& a, hipStream_t st);

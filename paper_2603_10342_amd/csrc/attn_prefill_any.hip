@@ -1,5 +1,6 @@
 // Cold and resume prefill over paged KV caches of any supported head_dim and dtype with pages of 16 tokens or more
-// (bf16 at head_dim 128, and at 64 on long contexts, takes attn_prefill_mfma.hip: see prefill_mfma_lo_supported()).
+// (bf16 at head_dim 128, and at 64 on long contexts, takes attn_prefill_mfma.hip, see prefill_mfma_lo_supported(); fp32 at
+// 64 and 128 takes attn_prefill_f32.hip; few rows take attn_prefill_split.hip).
 //
 // A dense contraction, bound by the matrix cores.  A workgroup of four waves owns 128 columns of one (session, KV
 // head): a column is a (token, query head of the group) pair, numbered token * G + head, so that any group size fills
@@ -11,9 +12,8 @@
 // and both pools store those runs contiguously (ag.h), so P stays in registers in both types.
 // Precision: fp32 runs in fp32 throughout (expf, fp32 products: 157 TFLOP/s at most); bf16 caches multiply the weights
 // as two bf16 terms (hi + lo), half again the matrix work, so that no weight is cut to 8 bits.
-// Measured, append included (one wave per (row, query head) before -> now): four fp32 prompts of 300..1500 rows at
-// 32 / 8 heads x 128, 30.4 ms -> 0.38 ms (95 TFLOP/s); eight bf16 prompts of 2048 rows at head_dim 64, 64-token pages,
-// 57 -> 0.266 ms (517 TFLOP/s of result, 776 of products).
+// Measured, append included (one wave per (row, query head) before -> now): eight bf16 prompts of 2048 rows at 32 / 8 heads
+// x 64, 64-token pages, 57 -> 0.266 ms (517 TFLOP/s of result, 776 of products).
 #include <algorithm>
 #include <atomic>
 
@@ -349,10 +349,10 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 template <typename E>
 ag_status launch_for_dim(const AttnArgs& a, hipStream_t st)
 {
-    if (a.c.d <= 64) return a.c.d == 64 ? launch_kernel<E, 64, true>(a, st) : launch_kernel<E, 64, false>(a, st);
-    if constexpr (sizeof(E) == 4) {                 // (bf16 at 128 never comes here)
-        if (a.c.d == 128) return launch_kernel<E, 128, true>(a, st);
+    if constexpr (sizeof(E) == 2) {                 // (fp32 at 64 and 128, and bf16 at 128, never come here)
+        if (a.c.d == 64) return launch_kernel<E, 64, true>(a, st);
     }
+    if (a.c.d <= 64) return launch_kernel<E, 64, false>(a, st);
     if (a.c.d <= 128) return launch_kernel<E, 128, false>(a, st);
     return a.c.d == 256 ? launch_kernel<E, 256, true>(a, st) : launch_kernel<E, 256, false>(a, st);
 }
@@ -371,6 +371,7 @@ ag_status launch_prefill_any(const AttnArgs& a, hipStream_t st)
 {
     if (prefill_mfma_lo_supported(a)) return launch_prefill_mfma(a, st);
     if (prefill_split_preferred(a, st)) return launch_prefill_split(a, st);
+    if (prefill_f32_supported(a)) return launch_prefill_f32(a, st);
     return a.c.dtype == AG_BF16 ? launch_for_dim<__bf16>(a, st) : launch_for_dim<float>(a, st);
 }
 

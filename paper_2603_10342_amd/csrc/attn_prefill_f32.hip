@@ -1,0 +1,428 @@
+// Cold and resume prefill over fp32 caches, head_dim 64 or 128, pages of 16 tokens or more, on the bf16 matrix cores.
+//
+// The fp32 products of the matrix cores run at a sixteenth of the bf16 rate (157 against 2500 TFLOP/s), which is what
+// bounds the fp32 form of attn_prefill_any.hip.  Here every fp32 number is taken as three bf16 terms, x = h + m + l
+// (each the rounded rest of the ones before: 24 bits and more), and a product as the six of their nine products that
+// reach 2^-24 of it: h h + (h m + m h) + (h l + l h + m m).  What is dropped is below 2^-25, less than the rounding of an
+// fp32 product; sums are fp32 sums as before.  (Published as bf16x3: Henry, Tang and Heinecke, "Leveraging the bfloat16
+// artificial intelligence datatype for higher-precision computations", 2019.)  Relative error against 64 bits: 2.4e-7 over
+// four prompts of 300..1500 rows and 1.2e-6 over 600 rows on 6000 tokens at 32 / 8 heads x 128; one wave per row, in plain
+// fp32 and in the order of the keys, had 3.9e-7 and 1.4e-6.
+//
+// A workgroup of four waves owns 128 (token, head) columns of one (session, KV head), 32 a wave, whose queries lie in
+// registers as terms.  Keys and values are taken 32 at a time: every thread fetches its share of the next tile into
+// registers while the current one is multiplied, splits it - once for all four waves - and writes the terms to LDS in
+// the layouts of the bf16 kernels, [chunk of 8 channels][key][8] and [chunk of 8 keys][channel][8], two stages.
+// Weights are split in registers.  What bounds it is matrix and vector work one after the other: 96 products of 32 clocks a
+// tile and wave at 128 channels against 128 of 64, and about as much in softmax, splitting and operand reads.
+// Measured, append included, 32 / 8 heads, fp32 products -> terms: four prompts of 300..1500 rows, 128 channels 377 -> 296
+// us (120 TFLOP/s of result), 64 channels 208 -> 139; eight of 2048, 2430 -> 1828; eight chunks of 40..500 on 500..4000
+// tokens 811 -> 638; 32 of 10..60, 235 -> 193.  Scores in three accumulators and value products grouped by term: 3..5 % slower.
+#include <algorithm>
+#include <atomic>
+
+#include "ag_internal.h"
+#include "attn_general_row.h"
+#include "tile_list.h"
+
+namespace ag {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kColumns = 128;           // (token, head) pairs of a workgroup
+constexpr int BN = 32;                  // keys per tile
+constexpr float kSlack = 5.5f;          // how far a maximum may outgrow the reference before O is rescaled
+
+constexpr int plane_bytes(int dt) { return BN * dt * 2; }           // one term of a tile of keys, or of values
+constexpr int lds_bytes(int dt) { return 12 * plane_bytes(dt); }    // two stages of K h, m, l, then two of V h, m, l
+
+__device__ __forceinline__ float widen_lo(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float widen_hi(uint32_t p) { return __builtin_bit_cast(float, p & 0xFFFF0000u); }
+__device__ __forceinline__ uint32_t pack(float a, float b) { return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b}); }
+
+// Two numbers as packed terms.  An infinity (or what rounds to one) leaves NaN as its rest.
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l)
+{
+    h = pack(a, b);
+    const float ra = a - widen_lo(h), rb = b - widen_hi(h);
+    m = pack(ra, rb);
+    l = pack(ra - widen_lo(m), rb - widen_hi(m));
+}
+
+struct Terms { u32x4 h, m, l; };        // eight numbers
+
+// e^x for x <= 0 or little above: 2^t with the rounding of t = x log2(e) put back to first order (within 1.5 units in the
+// last place, eight instructions).  -inf gives 0, NaN stays NaN.
+__device__ __forceinline__ float exp_near(float x)
+{
+    x = x < -200.f ? -200.f : x;
+    const float t = x * 1.44269502f;
+    const float r = fmaf(x, 1.92596299e-8f, fmaf(x, 1.44269502f, -t));        // log2(e) = 1.44269502 + 1.926e-8
+    const float e = __builtin_amdgcn_exp2f(t);
+    return fmaf(e, r * 0.693147182f, e);
+}
+
+__device__ __forceinline__ Terms split8(const f32x4& a, const f32x4& b)
+{
+    Terms t;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t h, m, l;
+        split_pair(i < 2 ? a[2 * i] : b[2 * i - 4], i < 2 ? a[2 * i + 1] : b[2 * i - 3], h, m, l);
+        t.h[i] = h;
+        t.m[i] = m;
+        t.l[i] = l;
+    }
+    return t;
+}
+
+__device__ __forceinline__ f32x16 product(const u32x4& a, const u32x4& b, const f32x16& c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+template <int DT>
+__global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnArgs a, int tiles_max, int per_xcd, int total_work)
+{
+    constexpr int kPlane = plane_bytes(DT);
+    constexpr int kUnits = BN * DT / 8 / 256;       // runs of eight numbers a thread moves of a K tile, and of a V tile
+    constexpr int kMb = DT / 32;
+    constexpr int kAhead = 4;                       // LDS operand reads run this many operands ahead of their use
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+
+    // ---- which (KV head, session, tile): the XCD a workgroup lands on owns a contiguous range of KV heads ----
+    const int xcd = blockIdx.x & 7, ord = blockIdx.x >> 3;
+    const unsigned wk = (unsigned)(xcd * per_xcd + ord);
+    if (wk >= (unsigned)total_work) return;
+    const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv, ps = a.c.ps;
+    const int g = (int)(wk / (unsigned)tiles_max);
+    int s = -1, qt = 0, N = 0, P = 0, row0 = 0;
+    find_tile(a, (int)(wk - (unsigned)g * (unsigned)tiles_max), [G](int len) { return (int)(((int64_t)len * G + kColumns - 1) / kColumns); }, s, qt, N, P, row0);
+    if (s < 0) return;                              // beyond the batch's tiles
+    const int ctx = P + N;
+    const int col0 = qt * kColumns, cols = min(N * G - col0, kColumns);       // valid columns of the tile
+    const Columns columns(col0, G);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, hi = lane >> 5;
+    const int cols_w = max(0, min(32, cols - 32 * w));
+    const int n_tiles = (P + columns.token(cols - 1)) / BN + 1;               // tiles the workgroup stages
+    const int wave_tiles = cols_w > 0 ? (P + columns.token(32 * w + cols_w - 1)) / BN + 1 : 0;     // tiles this wave uses
+    const int first_masked = (P + columns.token(32 * w) + 1) / BN;  // first tile holding a key this wave's first column may not see
+    const int col = min(32 * w + n, cols - 1);                  // columns beyond the tile repeat the last one
+    const int token = columns.token(col);
+    const int qpos = P + token;
+    const int64_t row = ((int64_t)row0 + token) * hq + (int64_t)g * G + columns.head(col, token);
+
+    // ---- this thread's share of a tile: run i of K is eight channels of a key, of V eight keys of a channel (ag.h) ----
+    typedef const __attribute__((address_space(4))) int32_t* cptr_t;
+    const cptr_t bt = (cptr_t)(uintptr_t)(a.bt + (int64_t)s * a.max_pages);
+    const int last_grp = (ctx - 1) >> 4, gshift = a.c.ps_shift - 4, gmask = (1 << gshift) - 1;
+    const int64_t block = (int64_t)DT * ps;                     // numbers of one (page, head)
+    const int key = tid & 31;
+    f32x4 kx[kUnits][2], vx[kUnits][2];
+    auto fetch_k = [&](int t, int id0, int id1) {               // id0, id1: pages of the tile's two 16-token groups
+        const int id = key >> 4 ? id1 : id0, gi = min(2 * t + (key >> 4), last_grp) & gmask;
+        const float* kp = (const float*)a.c.k + ((int64_t)id * hkv + g) * block + gi * 128 + (key & 15) * 8;
+#pragma unroll
+        for (int i = 0; i < kUnits; ++i) {
+            const f32x4* p = reinterpret_cast<const f32x4*>(kp + (int64_t)((tid + 256 * i) >> 5) * ps * 8);
+            kx[i][0] = p[0];
+            kx[i][1] = p[1];
+        }
+    };
+    auto fetch_v = [&](int t, int id0, int id1) {
+#pragma unroll
+        for (int i = 0; i < kUnits; ++i) {
+            const int run = tid + 256 * i, q = run / DT, ch = run % DT;
+            const int id = q >> 1 ? id1 : id0, gi = min(2 * t + (q >> 1), last_grp) & gmask;
+            const f32x4* p = reinterpret_cast<const f32x4*>((const float*)a.c.v + ((int64_t)id * hkv + g) * block + (int64_t)gi * 16 * DT + ((q & 1) * DT + ch) * 8);
+            vx[i][0] = p[0];
+            vx[i][1] = p[1];
+        }
+    };
+    // What the fetches brought is split a pair at a time, so that the value product can hide it: pair c of the thread's
+    // 8 kUnits (K first), whose run goes to LDS with its last pair.
+    auto scrub = [&](int t) {                                   // slots past the last token may hold anything, NaN included
+        if (ctx < (t + 1) * BN) {
+#pragma unroll
+            for (int i = 0; i < kUnits; ++i) {
+                const int q = (tid + 256 * i) / DT, keep = ctx - (t * BN + (q >> 1) * 16 + (q & 1) * 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    vx[i][0][e] = e < keep ? vx[i][0][e] : 0.f;
+                    vx[i][1][e] = 8 + e < keep ? vx[i][1][e] : 0.f;
+                }
+            }
+        }
+    };
+    Terms run_terms;
+    auto store_pair = [&](int c, unsigned char* k_stage, unsigned char* v_stage) {
+        const bool of_v = c >= 4 * kUnits;
+        const int i = (c >> 2) % kUnits, e = c & 3;
+        const f32x4& src = of_v ? vx[i][e >> 1] : kx[i][e >> 1];
+        uint32_t h, m, l;
+        split_pair(src[2 * (e & 1)], src[2 * (e & 1) + 1], h, m, l);
+        run_terms.h[e] = h;
+        run_terms.m[e] = m;
+        run_terms.l[e] = l;
+        if (e == 3) {
+            unsigned char* at = (of_v ? v_stage : k_stage) + (tid + 256 * i) * 16;
+            *reinterpret_cast<u32x4*>(at) = run_terms.h;
+            *reinterpret_cast<u32x4*>(at + kPlane) = run_terms.m;
+            *reinterpret_cast<u32x4*>(at + 2 * kPlane) = run_terms.l;
+        }
+    };
+    constexpr int kPairs = 8 * kUnits;
+    unsigned char* const k_lds = lds;                           // K tile t lives at k_lds + (t & 1) * 3 * kPlane
+    unsigned char* const v_lds = lds + 6 * kPlane;              // V tile t lives at v_lds + (t & 1) * 3 * kPlane
+    auto id_of = [&](int grp) { return bt[min(grp, last_grp) >> gshift]; };
+
+    // ---- prologue: K(0), V(0) and K(1) into LDS, S(0) ----
+    fetch_k(0, id_of(0), id_of(1));
+    fetch_v(0, id_of(0), id_of(1));
+    // Q^T as B operand: k-step ks covers channels ks * 16 + hi * 8 .. + 7
+    Terms qf[DT / 16];
+    {
+        const float* qp = (const float*)a.q + row * DT + hi * 8;
+#pragma unroll
+        for (int ks = 0; ks < DT / 16; ++ks) {
+            const f32x4* p = reinterpret_cast<const f32x4*>(qp + ks * 16);
+            qf[ks] = split8(p[0], p[1]);
+        }
+    }
+    scrub(0);
+#pragma unroll
+    for (int c = 0; c < kPairs; ++c) store_pair(c, k_lds, v_lds);
+    int v0 = id_of(2), v1 = id_of(3), k0 = id_of(4), k1 = id_of(5);           // pages of tiles t + 1 and t + 2 in iteration t
+    fetch_k(1, v0, v1);                                       // (past a short context's last group the ids repeat: never used)
+#pragma unroll
+    for (int c = 0; c < kPairs / 2; ++c) store_pair(c, k_lds + 3 * kPlane, v_lds);
+
+    float m = -INFINITY, lsum = 0.f;
+    f32x16 o[kMb];
+#pragma unroll
+    for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[mb][i] = 0.f;
+    __syncthreads();
+
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float x[16];                                                // S(t), then what is left to exponentiate
+    Terms pf[2];                                                // the weights of tile t
+    // S of tile t into s0 + s1 (the h h products, and all smaller ones), with piece(i) of other work behind operand i's products
+    constexpr int kScoreSteps = 3 * (DT / 16);                  // operand i: k-step i / 3, term i % 3
+    auto scores = [&](int t, f32x16& s0, f32x16& s1, auto piece) {
+        const unsigned char* kb = k_lds + (t & 1) * 3 * kPlane + hi * 512 + n * 16;
+        u32x4 ring[kAhead + 1];
+        auto at = [&](int i) { return *reinterpret_cast<const u32x4*>(kb + (i % 3) * kPlane + (i / 3) * 1024); };
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) ring[i] = at(i);
+#pragma unroll
+        for (int i = 0; i < kScoreSteps; ++i) {
+            if (i + kAhead < kScoreSteps) ring[(i + kAhead) % (kAhead + 1)] = at(i + kAhead);
+            const u32x4 k = ring[i % (kAhead + 1)];
+            const Terms& q = qf[i / 3];
+            if (i % 3 == 0) {
+                s1 = product(k, q.l, i == 0 ? zero : s1);
+                s0 = product(k, q.h, i == 0 ? zero : s0);
+                s1 = product(k, q.m, s1);
+            } else if (i % 3 == 1) {
+                s1 = product(k, q.m, s1);
+                s1 = product(k, q.h, s1);
+            } else {
+                s1 = product(k, q.h, s1);
+            }
+            piece(i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    {
+        f32x16 s0, s1;
+        scores(0, s0, s1, [](int) {});
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = s0[i] + s1[i];
+    }
+
+    // Iteration t: S(t + 1) (matrix) beside the weights P(t) (vector), then O += V(t) . P(t) (matrix) beside the splitting of
+    // K(t + 2) and V(t + 1) (vector), which were fetched at its start: one wave per SIMD at 128 channels, so what overlaps is
+    // what the wave itself interleaves.  One barrier: what is written was last read before the barrier that came before.
+#pragma unroll 1
+    for (int t = 0; t < n_tiles; ++t) {
+        const bool more = t + 1 < n_tiles;                      // uniform
+        if (more) {
+            fetch_v(t + 1, v0, v1);
+            fetch_k(t + 2, k0, k1);
+            v0 = k0;
+            v1 = k1;
+            k0 = id_of(2 * (t + 3));
+            k1 = id_of(2 * (t + 3) + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const bool mine = t < wave_tiles, next = t + 1 < wave_tiles;
+        if (mine) {
+            if (t >= first_masked) {                            // the tile straddles this wave's diagonal
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int kk = t * BN + (i >> 2) * 8 + hi * 4 + (i & 3);
+                    x[i] = kk <= qpos ? x[i] : -INFINITY;
+                }
+            }
+            float mx = fmaxf(fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7]))),
+                             fmaxf(fmaxf(fmaxf(x[8], x[9]), fmaxf(x[10], x[11])), fmaxf(fmaxf(x[12], x[13]), fmaxf(x[14], x[15]))));
+            mx *= a.scale;                                      // scale > 0: max and scaling commute
+            // m is shared by the two lanes of a column: if either lane's own maximum outgrew it, combine them
+            if (__builtin_amdgcn_ballot_w64(mx > m + kSlack) != 0) {
+                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                const float m_new = fmaxf(m, mx);
+                const float alpha = m_new == -INFINITY ? 1.f : expf(m - m_new);
+                lsum *= alpha;
+#pragma unroll
+                for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) o[mb][i] *= alpha;
+                m = m_new;
+            }
+            const float m_ref = m == -INFINITY ? 0.f : m;
+            float psum[2] = {0.f, 0.f};
+            auto weigh = [&](int j) {                           // pair j of eight
+                const int i = 2 * j;
+                const float p0 = exp_near(fmaf(x[i], a.scale, -m_ref)), p1 = exp_near(fmaf(x[i + 1], a.scale, -m_ref));
+                psum[0] += p0;
+                psum[1] += p1;
+                uint32_t h, mm, l;
+                split_pair(p0, p1, h, mm, l);
+                pf[i >> 3].h[(i & 7) >> 1] = h;
+                pf[i >> 3].m[(i & 7) >> 1] = mm;
+                pf[i >> 3].l[(i & 7) >> 1] = l;
+            };
+            if (next) {
+                f32x16 s0, s1;
+                scores(t + 1, s0, s1, [&](int i) {              // eight pairs over the score product's steps
+                    constexpr int kPer = kScoreSteps / 8 > 0 ? kScoreSteps / 8 : 1;
+                    if constexpr (kScoreSteps >= 16) {
+                        if (i % kPer == 0 && i / kPer < 8) weigh(i / kPer);
+                    } else {
+                        if (i < 8) weigh(i);
+                    }
+                });
+#pragma unroll
+                for (int i = 0; i < 16; ++i) x[i] = s0[i] + s1[i];
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) weigh(j);
+            }
+            lsum += psum[0] + psum[1];
+        }
+        unsigned char* const k_to = k_lds + (t & 1) * 3 * kPlane;
+        unsigned char* const v_to = v_lds + ((t + 1) & 1) * 3 * kPlane;
+        if (more) scrub(t + 1);
+        if (mine) {
+            const unsigned char* vb = v_lds + (t & 1) * 3 * kPlane + hi * DT * 16 + n * 16;
+            constexpr int kN = 6 * kMb;                         // operand i: k-step, term, channel block
+            u32x4 ring[kAhead + 1];
+            auto at = [&](int i) {
+                return *reinterpret_cast<const u32x4*>(vb + ((i / kMb) % 3) * kPlane + (i / (3 * kMb)) * DT * 32 + (i % kMb) * 512);
+            };
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) ring[i] = at(i);
+#pragma unroll
+            for (int i = 0; i < kN; ++i) {
+                if (i + kAhead < kN) ring[(i + kAhead) % (kAhead + 1)] = at(i + kAhead);
+                const u32x4 v = ring[i % (kAhead + 1)];
+                const Terms& p = pf[i / (3 * kMb)];
+                f32x16& acc = o[i % kMb];
+                const int term = (i / kMb) % 3;
+                if (term == 0) acc = product(v, p.l, acc);
+                if (term <= 1) acc = product(v, p.m, acc);
+                acc = product(v, p.h, acc);
+                if (i < kPairs) store_pair(i, k_to, v_to);      // (past the last tile: what is there once more, never read)
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            static_assert(kPairs <= kN, "the value product's steps cover the pairs");
+        } else if (more) {
+#pragma unroll
+            for (int c = 0; c < kPairs; ++c) store_pair(c, k_to, v_to);
+        }
+        __syncthreads();
+    }
+
+    // o[mb][q4 * 4 + e] is O^T[channel mb * 32 + q4 * 8 + hi * 4 + e][column n]
+    lsum += __shfl_xor(lsum, 32);
+    const float inv = 1.0f / lsum;
+    // Infinities among Q, K and V come out of the split products as NaN, whatever they would have given; and the products
+    // take terms below 2^-126 as zero: values under 2^-110 or so lose their low terms (1e-36: 3e-5 of them).
+    float trouble = general::trouble_of(inv), top = 0.f;
+#pragma unroll
+    for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            trouble = general::trouble_of(o[mb][i], trouble);
+            top = fmaxf(top, fabsf(o[mb][i] * inv));
+        }
+    top = fmaxf(top, __shfl_xor(top, 32));
+    const bool tiny = top > 0.f && top < 0x1p-100f;
+    uint64_t again = __builtin_amdgcn_ballot_w64(n < cols_w && (tiny || !(trouble == 0.f)));
+    again = (again | (again >> 32)) & 0xFFFFFFFFu;              // bit c: column c of this wave
+    if (n < cols_w && !((again >> n) & 1)) {
+        float* out = (float*)a.out + row * DT + hi * 4;
+#pragma unroll
+        for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                f32x4 y;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = o[mb][q4 * 4 + e] * inv;
+                *reinterpret_cast<f32x4*>(out + mb * 32 + q4 * 8) = y;
+            }
+    }
+    general::attend_rows_again<float>(a, again, row, s, row0, P, reinterpret_cast<float*>(lds) + 256 * w);    // (all are past the last tile)
+}
+
+// sum_s ceil(N_s G / 128) <= total G / 128 + batch, and no session has more than ceil(max_new G / 128)
+int64_t tiles_bound(const AttnArgs& a)
+{
+    const int64_t G = a.hq / a.c.hkv;
+    return std::min<int64_t>((int64_t)a.total_rows * G / kColumns + a.batch, (int64_t)a.batch * ((a.max_new * G + kColumns - 1) / kColumns));
+}
+
+template <int DT>
+ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
+{
+    constexpr int lds = lds_bytes(DT);
+    static std::atomic<bool> attr_set{false};
+    if (lds > 64 * 1024 && !attr_set.load()) {      // more dynamic LDS than a kernel may use without being told so
+        ag_status e = hip_check(hipFuncSetAttribute((const void*)prefill_f32_kernel<DT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds),
+                                "hipFuncSetAttribute(prefill)");
+        if (e) return e;
+        attr_set.store(true);
+    }
+    const int64_t tiles_max = tiles_bound(a), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
+    prof_before(st);
+    hipLaunchKernelGGL((prefill_f32_kernel<DT>), dim3((unsigned)(per_xcd * 8)), dim3(256), lds, st, a, (int)tiles_max, (int)per_xcd, (int)total);
+    prof_after(st);
+    return hip_check(hipGetLastError(), "prefill launch");
+}
+
+}  // namespace
+
+bool prefill_f32_supported(const AttnArgs& a)
+{
+    return a.c.dtype == AG_F32 && (a.c.d == 64 || a.c.d == 128) && a.c.ps >= 16 &&
+           (((uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 == 0) &&
+           a.c.hkv * tiles_bound(a) + 8 <= 0x7fffffff && (int64_t)a.total_rows * (a.hq / a.c.hkv) <= 0x7fffffff;
+}
+
+ag_status launch_prefill_f32(const AttnArgs& a, hipStream_t st)
+{
+    return a.c.d == 64 ? launch_kernel<64>(a, st) : launch_kernel<128>(a, st);
+}
+
+}  // namespace ag

@@ -334,18 +334,19 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 }  // namespace
 
 // Whether the batch's query tiles are too few for the other kernels.  Counted in workgroups of 32 columns per CU of the
-// stream (one is resident at a time): up to 2 for the bf16 / 128 / 16 shape, 3 for other bf16 shapes (whose weights cost
-// their kernel half again the products), 10 for fp32 (its products are so slow that the load path does not bind).
+// stream (one is resident at a time): up to 2 for the bf16 / 128 / 16 shape, 3 for the others, whose kernels spend half
+// again (bf16, weights in two terms) to three times (fp32, products in six terms) the matrix work.
 // Measured at 32 / 8 heads on 256 CUs, append included, the other kernel -> this one: bf16 / 128 / 16, one chunk of
 // 5 rows on 6007 tokens (8 workgroups) 114 -> 39 us, 211 rows (216) 119 -> 45, 400 rows (400) 122 -> 80; four chunks of
 // 150 rows on 3000 (608) 70 -> 70, eight of 100 on 2000 (832) 57 -> 71.  bf16 / 64 / 64: eight of 40 on 2000 (320) 49 ->
-// 30, 32 of 20 on 1000 (768) 31 -> 31, two prompts of 1000 (2000) 41 -> 50.  fp32 / 128: one chunk of 211 rows on 6007
-// 873 -> 227, two prompts of 1000 (2000) 276 -> 216, four of 300..1500 (3600) 377 -> 461.
+// 30, 32 of 20 on 1000 (768) 31 -> 31, two prompts of 1000 (2000) 41 -> 50.  fp32 / 128: one chunk of 211 rows on 6000
+// (216) 604 -> 225, one prompt of 600 (600) 71 -> 54, twelve chunks of 10..100 rows on 1000..3000 (700) 299 -> 243; three of
+// 300 on 5000 (912) 528 -> 743, two prompts of 1000 (2000) 137 -> 210.
 bool prefill_split_preferred(const AttnArgs& a, hipStream_t st)
 {
     if ((a.c.d != 64 && a.c.d != 128) || a.c.ps < 16 || (int64_t)a.total_rows * (a.hq / a.c.hkv) > 0x7fffffff ||
         ((uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 != 0) return false;
-    const int per_cu = a.c.dtype == AG_F32 ? 10 : a.c.d == 128 && a.c.ps == 16 ? 2 : 3;
+    const int per_cu = a.c.dtype == AG_BF16 && a.c.d == 128 && a.c.ps == 16 ? 2 : 3;
     return a.c.hkv * tiles_bound(a, kColumns) <= (int64_t)per_cu * stream_cus(st);
 }
 

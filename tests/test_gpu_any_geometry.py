@@ -234,3 +234,21 @@ def test_an_infinite_value_stays_with_the_rows_that_see_it(dtype, d, ps, hq, hkv
         assert np.isfinite(seen[plus]).all() and np.isnan(seen[~plus]).all()
         seen[...] = want
         check_close(x, r, dtype, f"D={d} page={ps} {hq}/{hkv} on {cus_per_xcd} CUs per XCD")
+
+
+@pytest.mark.parametrize("sigma_v", [1e-36, 1e-33, 1e37])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_keeps_its_precision_at_the_ends_of_its_range(d, sigma_v):
+    """fp32 numbers taken as three bf16 terms (many columns per CU): the terms of tiny values leave the products' range."""
+    g = I.Geometry(8, 2, d, 16, 40, I.F32)
+    b = make_batch(g, [0, 0], [150, 290], seed=59, sigma_v=sigma_v)
+    stream = B.ag_stream_create_cumask(B.ag_cumask_build(B.ag_device_info()["num_cus"], 8, 0, 1))
+    try:
+        cache = make_cache(g)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(torch.cuda.ExternalStream(stream)):
+            got, ref = run_phase(cache, *fresh_pools(g), b, "cold")
+    finally:
+        torch.cuda.synchronize()
+        B.ag_stream_destroy(stream)
+    check_close(got / sigma_v, ref / sigma_v, I.F32, f"cold D={d}, values of {sigma_v}")
