@@ -51,9 +51,11 @@
  *     pools, so the ag_kv_append that writes a token must precede, on the
  *     same stream or through an event, any attention call that covers it.
  *   - Supported: dtype AG_F32 or AG_BF16; head_dim a multiple of 8, <= 256;
- *     page_size a power of two in [1, 256].  bf16 with head_dim 128 and page_size 16
- *     runs on the matrix-core kernels; every other supported combination
- *     runs on the general fp32-arithmetic kernels.
+ *     page_size a power of two in [1, 256].  With pages of 16 tokens or more and
+ *     16-byte aligned pointers everything runs on matrix-core kernels: bf16 with
+ *     head_dim 128 and page_size 16 rounds softmax weights to bf16; other bf16
+ *     caches keep them to 16 bits of mantissa, fp32 caches to fp32.  Smaller
+ *     pages and unaligned pointers run on a general fp32-arithmetic kernel.
  */
 #ifndef AG_H
 #define AG_H
@@ -145,7 +147,8 @@ AG_API ag_status ag_attn_resume(const ag_kv_cache* cache, const void* q, void* o
  * equal shares, one per workgroup (a share may end one context and start
  * the next); their partial (max, sum, weighted values) triples go through
  * `workspace`, whose previous contents do not matter, and are merged in a
- * fixed order, so results are reproducible.
+ * fixed order, so results are reproducible.  A batch of few, short contexts
+ * takes one workgroup per pair instead, which writes its result itself.
  * workspace_bytes >= ag_attn_decode_workspace_bytes(batch, num_q_heads, head_dim, max_ctx),
  * 16-byte aligned.  Calls sharing a workspace must be ordered on one stream.
  * batch * num_kv_heads * ceil(max_ctx / 32) may not exceed 2^30 (AG_ERR_INVALID_ARG).
