@@ -250,10 +250,12 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
 #pragma unroll
         for (int i = 0; i < 16; ++i) x[i] = s0[i] + s1[i];
     }
+    __syncthreads();                                            // every wave has read K(0): iteration 0 writes K(2) in its place
 
     // Iteration t: S(t + 1) (matrix) beside the weights P(t) (vector), then O += V(t) . P(t) (matrix) beside the splitting of
     // K(t + 2) and V(t + 1) (vector), which were fetched at its start: one wave per SIMD at 128 channels, so what overlaps is
-    // what the wave itself interleaves.  One barrier: what is written was last read before the barrier that came before.
+    // what the wave itself interleaves.  One barrier an iteration: the places it writes, of K(t) and V(t - 1), were last read
+    // in iteration t - 1 (K(0) above), before that iteration's barrier.
 #pragma unroll 1
     for (int t = 0; t < n_tiles; ++t) {
         const bool more = t + 1 < n_tiles;                      // uniform
