@@ -8,7 +8,7 @@
 // of 16, each a pair of its own.  What differs:
 //   - Arithmetic keeps 32 bits where the caches do: fp32 runs on 16x16x4 fp32 products (256 flop per clock and CU:
 //     a step of 16 tokens takes a third of the time its bytes take), with expf on unscaled exponents; bf16 caches
-//     multiply the weights as two bf16 terms (hi + lo, 16 bits of mantissa), so no weight is cut to 8 bits.
+//     multiply the weights as three bf16 terms (bf16_terms.h), so that they stay in 32 bits.
 //   - The 16-token group is the unit of addressing: group i of a context lies in page i / (page_size / 16), and a
 //     group's keys and values sit in the page as in a 16-token page, only with a larger chunk stride for K.
 //   - Two sub-steps of loads are in flight per wave where a sub-step is 16 KiB or less (head_dim 64 and 128):
@@ -192,21 +192,16 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, int s, int g, in
             }
         }
         if constexpr (kBf16) {
-            bf16x8 hi, lo;
+            Terms w;
 #pragma unroll
-            for (int j = 0; j < 8; j += 2) {
-                const bf16_pair h = {(__bf16)p[j], (__bf16)p[j + 1]}, l = low_terms(p[j], p[j + 1], h);
-                hi[j] = h[0];
-                hi[j + 1] = h[1];
-                lo[j] = l[0];
-                lo[j + 1] = l[1];
-            }
+            for (int j = 0; j < 4; ++j) w.set_pair(j, p[2 * j], p[2 * j + 1]);
 #pragma unroll
             for (int mb = 0; mb < X::kV; ++mb) {
                 const bf16x8 v = __builtin_bit_cast(bf16x8, x.v[mb]);
                 o[mb] *= alpha;
-                o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, lo, o[mb], 0, 0, 0);
-                o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, hi, o[mb], 0, 0, 0);
+                o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, __builtin_bit_cast(bf16x8, w.l), o[mb], 0, 0, 0);
+                o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, __builtin_bit_cast(bf16x8, w.m), o[mb], 0, 0, 0);
+                o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, __builtin_bit_cast(bf16x8, w.h), o[mb], 0, 0, 0);
             }
         } else {
 #pragma unroll
@@ -399,7 +394,7 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
             if (!(general::trouble_of(y) == 0.f)) atomicOr(&s_again, 1u << head);
         }
     }
-    __syncthreads();                                             // (two-term weights turn an infinite sum into NaN)
+    __syncthreads();                                             // (weights in terms turn an infinite sum into NaN)
     const uint32_t all = __builtin_amdgcn_readfirstlane(s_again);
     if (all) general::attend_rows_again<E>(a, all & (0x0101u << w), (int64_t)s * hq + (int64_t)g * G + h0 + r, s, s, ctx - 1, &s_o[w][0][0]);
 }
@@ -427,7 +422,7 @@ __global__ __launch_bounds__(256) void decode_any_merge_kernel(AttnArgs a, const
 #pragma unroll
         for (int e = 0; e < 4; ++e) trouble = general::trouble_of(y[e], trouble);
     }
-    // (two-term weights, and partials taken with a weight of zero, turn an infinite sum into NaN)
+    // (weights in terms, and partials taken with a weight of zero, turn an infinite sum into NaN)
     __shared__ float s_q[4][256];
     uint64_t again = __builtin_amdgcn_ballot_w64(!(trouble == 0.f));
     while (again) {                             // one row at a time: other waves that hold a part of it write the same

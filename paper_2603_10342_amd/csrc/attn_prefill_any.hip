@@ -11,9 +11,10 @@
 // on 32x32x16 (bf16) and 32x32x2 (fp32) products.  The score layout's rows are the keys a lane owns, four in a run,
 // and both pools store those runs contiguously (ag.h), so P stays in registers in both types.
 // Precision: fp32 runs in fp32 throughout (expf, fp32 products: 157 TFLOP/s at most); bf16 caches multiply the weights
-// as two bf16 terms (hi + lo), half again the matrix work, so that no weight is cut to 8 bits.
+// as three bf16 terms (bf16_terms.h), twice the matrix work, so that they stay in 32 bits: two terms, 16 bits, take 268 us
+// instead of 336 for the prompts below, and are off from 64 bits by 1e-6 more of the error that the rounding of outputs makes.
 // Measured, append included (one wave per (row, query head) before -> now): eight bf16 prompts of 2048 rows at 32 / 8 heads
-// x 64, 64-token pages, 57 -> 0.266 ms (517 TFLOP/s of result, 776 of products).
+// x 64, 64-token pages, 57 -> 0.336 ms (410 TFLOP/s of result, 820 of products).
 #include <algorithm>
 #include <atomic>
 
@@ -256,19 +257,14 @@ __global__ __launch_bounds__(256, DT > 128 ? 1 : 2) void prefill_any_kernel(Attn
             lsum += psum;
             constexpr int kMb = DT / 32;
             if constexpr (kBf16) {
-                bf16x8 ph[4], pl[4];                            // weights as two bf16 terms, in k-step order
+                Terms p[4];                                     // the weights, in k-step order
 #pragma unroll
-                for (int i = 0; i < 32; i += 2) {
-                    const bf16_pair h = {(__bf16)x[i], (__bf16)x[i + 1]}, l = low_terms(x[i], x[i + 1], h);
-                    ph[i >> 3][i & 7] = h[0];
-                    ph[i >> 3][(i & 7) + 1] = h[1];
-                    pl[i >> 3][i & 7] = l[0];
-                    pl[i >> 3][(i & 7) + 1] = l[1];
-                }
+                for (int i = 0; i < 16; ++i) p[i >> 2].set_pair(i & 3, x[2 * i], x[2 * i + 1]);
                 with_operands<4 * kMb>([&](int i) { return vb + (i / kMb) * 2 * DT * 16 + (i % kMb) * 512; }, [&](int i, u32x4 v) {
                     const bf16x8 vv = __builtin_bit_cast(bf16x8, v);
-                    o[i % kMb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, pl[i / kMb], o[i % kMb], 0, 0, 0);
-                    o[i % kMb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, ph[i / kMb], o[i % kMb], 0, 0, 0);
+                    o[i % kMb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, __builtin_bit_cast(bf16x8, p[i / kMb].l), o[i % kMb], 0, 0, 0);
+                    o[i % kMb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, __builtin_bit_cast(bf16x8, p[i / kMb].m), o[i % kMb], 0, 0, 0);
+                    o[i % kMb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, __builtin_bit_cast(bf16x8, p[i / kMb].h), o[i % kMb], 0, 0, 0);
                 });
             } else {
                 with_operands<4 * kMb>([&](int i) { return vb + (i / kMb) * 2 * DT * 16 + (i % kMb) * 512; }, [&](int i, u32x4 v) {

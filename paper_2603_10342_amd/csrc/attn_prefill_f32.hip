@@ -23,6 +23,7 @@
 
 #include "ag_internal.h"
 #include "attn_general_row.h"
+#include "bf16_terms.h"
 #include "tile_list.h"
 
 namespace ag {
@@ -30,7 +31,6 @@ namespace ag {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -41,21 +41,6 @@ constexpr float kSlack = 5.5f;          // how far a maximum may outgrow the ref
 
 constexpr int plane_bytes(int dt) { return BN * dt * 2; }           // one term of a tile of keys, or of values
 constexpr int lds_bytes(int dt) { return 12 * plane_bytes(dt); }    // two stages of K h, m, l, then two of V h, m, l
-
-__device__ __forceinline__ float widen_lo(uint32_t p) { return __builtin_bit_cast(float, p << 16); }
-__device__ __forceinline__ float widen_hi(uint32_t p) { return __builtin_bit_cast(float, p & 0xFFFF0000u); }
-__device__ __forceinline__ uint32_t pack(float a, float b) { return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b}); }
-
-// Two numbers as packed terms.  An infinity (or what rounds to one) leaves NaN as its rest.
-__device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l)
-{
-    h = pack(a, b);
-    const float ra = a - widen_lo(h), rb = b - widen_hi(h);
-    m = pack(ra, rb);
-    l = pack(ra - widen_lo(m), rb - widen_hi(m));
-}
-
-struct Terms { u32x4 h, m, l; };        // eight numbers
 
 // e^x for x <= 0 or little above: 2^t with the rounding of t = x log2(e) put back to first order (within 1.5 units in the
 // last place, eight instructions).  -inf gives 0, NaN stays NaN.
@@ -72,13 +57,7 @@ __device__ __forceinline__ Terms split8(const f32x4& a, const f32x4& b)
 {
     Terms t;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        uint32_t h, m, l;
-        split_pair(i < 2 ? a[2 * i] : b[2 * i - 4], i < 2 ? a[2 * i + 1] : b[2 * i - 3], h, m, l);
-        t.h[i] = h;
-        t.m[i] = m;
-        t.l[i] = l;
-    }
+    for (int i = 0; i < 4; ++i) t.set_pair(i, i < 2 ? a[2 * i] : b[2 * i - 4], i < 2 ? a[2 * i + 1] : b[2 * i - 3]);
     return t;
 }
 
@@ -168,11 +147,7 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
         const bool of_v = c >= 4 * kUnits;
         const int i = (c >> 2) % kUnits, e = c & 3;
         const f32x4& src = of_v ? vx[i][e >> 1] : kx[i][e >> 1];
-        uint32_t h, m, l;
-        split_pair(src[2 * (e & 1)], src[2 * (e & 1) + 1], h, m, l);
-        run_terms.h[e] = h;
-        run_terms.m[e] = m;
-        run_terms.l[e] = l;
+        run_terms.set_pair(e, src[2 * (e & 1)], src[2 * (e & 1) + 1]);
         if (e == 3) {
             unsigned char* at = (of_v ? v_stage : k_stage) + (tid + 256 * i) * 16;
             *reinterpret_cast<u32x4*>(at) = run_terms.h;
@@ -299,11 +274,7 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
                 const float p0 = exp_near(fmaf(x[i], a.scale, -m_ref)), p1 = exp_near(fmaf(x[i + 1], a.scale, -m_ref));
                 psum[0] += p0;
                 psum[1] += p1;
-                uint32_t h, mm, l;
-                split_pair(p0, p1, h, mm, l);
-                pf[i >> 3].h[(i & 7) >> 1] = h;
-                pf[i >> 3].m[(i & 7) >> 1] = mm;
-                pf[i >> 3].l[(i & 7) >> 1] = l;
+                pf[i >> 3].set_pair((i & 7) >> 1, p0, p1);
             };
             if (next) {
                 f32x16 s0, s1;

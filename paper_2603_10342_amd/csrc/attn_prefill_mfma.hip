@@ -68,7 +68,7 @@ constexpr bool ids_in_lds(int nw) { return nw == 8; }
 constexpr int lds_bytes(int nw, int dt) { return (kKStages + kVStages) * tile_bytes(dt) + (ids_in_lds(nw) ? 2 * kIdWindow * 4 : 0); }
 
 // NW waves per workgroup (4 or 8), 32 columns each.  Eight waves halve the K/V bytes moved per flop (a tile
-// is shared by twice the columns) at the price of coarser query tiles.  kLo: weights as two bf16 terms
+// is shared by twice the columns) at the price of coarser query tiles.  kLo: weights as three bf16 terms
 // (attn_tile32.h); the bf16 / 128 / 16 shape runs without.  kPage16: pages of 16 tokens, whose groups need no place
 // inside the page.
 template <int NW, int DT, bool kLo, bool kPage16>
@@ -352,9 +352,12 @@ static int64_t tiles_bound(const AttnArgs& a, int cols)
 }
 
 // Other bf16 shapes that take this kernel: head_dim 128 (32-token pages, append included, the general tiles -> this one:
-// eight chunks of 40..500 rows on 500..4000 tokens 146 -> 133 us, eight prompts of 2048 428 -> 413), and head_dim 64 when
-// contexts are over twice the chunks (the same chunks, 64-token pages 102 -> 94 us; the prompts 266 -> 273: there the
-// longer start of a tile's pipeline and the lower occupancy cost more than the interleaved softmax gains).
+// eight chunks of 40..500 rows on 500..4000 tokens 210 -> 199 us, eight prompts of 2048 528 -> 523), and head_dim 64 when
+// contexts are over twice the chunks.  There the interleaved softmax shortens a workgroup's chain of tiles, and the longer
+// start of its pipeline and the lower occupancy lengthen a launch of many workgroups.  64-token pages, general tiles -> this
+// one: the same chunks 144 -> 129 us (a launch as long as its longest chain); 32 chunks of 300 rows on 150 tokens 89 ->
+// 97, on 300 114 -> 118, on 600 161 -> 166, on 2000 381 -> 387; eight of 2000 on 0, 500, 1000 336 -> 336, 445 -> 444, 567
+// -> 563, on 1900, 2100, 3000 787 -> 778, 832 -> 825, 1060 -> 1051.  Around the line the two are within 3 %.
 bool prefill_mfma_lo_supported(const AttnArgs& a)
 {
     return a.c.dtype == AG_BF16 && (a.c.d == 128 || (a.c.d == 64 && a.max_ctx > 2 * (int64_t)a.max_new)) && a.c.ps >= 16 && aligned16(a) &&

@@ -38,7 +38,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr int o_row(int dt) { return dt + 4; }          // floats of a column's partial in LDS, padded
 constexpr int lds_bytes(int dt) { return kWaves * kColumns * (o_row(dt) + 2) * 4 + 16; }
 
-// kLo: bf16 weights as two terms (hi + lo); false keeps the rounded weights of the bf16 / 128 / 16 kernels.
+// kLo: bf16 weights as three terms (bf16_terms.h); false keeps the rounded weights of the bf16 / 128 / 16 kernels.
 template <typename E, int DT, bool kLo>
 __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs a, int tiles_max, int per_xcd, int total_work)
 {
@@ -207,21 +207,16 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
             }
         }
         if constexpr (kBf16) {
-            bf16x8 ph[2], pl[2];
+            Terms p[2];                                         // (of which only h without kLo)
 #pragma unroll
             for (int e = 0; e < 16; e += 2) {
                 const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[e], unit, -m_ref)), p1 = __builtin_amdgcn_exp2f(fmaf(sc[e + 1], unit, -m_ref));
-                const bf16x2 pr = {(__bf16)p0, (__bf16)p1};
-                ph[e >> 3][e & 7] = pr[0];
-                ph[e >> 3][(e & 7) + 1] = pr[1];
+                p[e >> 3].set_pair((e & 7) >> 1, p0, p1);
                 if constexpr (kLo) {
-                    const bf16x2 rest = low_terms(p0, p1, pr);
-                    pl[e >> 3][e & 7] = rest[0];
-                    pl[e >> 3][(e & 7) + 1] = rest[1];
                     lsum += p0 + p1;
                 } else {
                     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-                    lsum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum, false);       // the weights as rounded
+                    lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)p[e >> 3].h[(e & 7) >> 1]), ones, lsum, false);       // the weights as rounded
                 }
             }
 #pragma unroll
@@ -229,8 +224,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
 #pragma unroll
                 for (int mb = 0; mb < kMb; ++mb) {
                     const bf16x8 v = __builtin_bit_cast(bf16x8, vx[j * kMb + mb]);
-                    if constexpr (kLo) o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pl[j], o[mb], 0, 0, 0);
-                    o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, ph[j], o[mb], 0, 0, 0);
+                    if constexpr (kLo) {
+                        o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, p[j].l), o[mb], 0, 0, 0);
+                        o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, p[j].m), o[mb], 0, 0, 0);
+                    }
+                    o[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, p[j].h), o[mb], 0, 0, 0);
                 }
         } else {
             float psum = 0.f;
@@ -334,8 +332,8 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 }  // namespace
 
 // Whether the batch's query tiles are too few for the other kernels.  Counted in workgroups of 32 columns per CU of the
-// stream (one is resident at a time): up to 2 for the bf16 / 128 / 16 shape, 3 for the others, whose kernels spend half
-// again (bf16, weights in two terms) to three times (fp32, products in six terms) the matrix work.
+// stream (one is resident at a time): up to 2 for the bf16 / 128 / 16 shape, 3 for the others, whose kernels spend twice
+// (bf16, weights in three terms) to three times (fp32, products in six terms) the matrix work.
 // Measured at 32 / 8 heads on 256 CUs, append included, the other kernel -> this one: bf16 / 128 / 16, one chunk of
 // 5 rows on 6007 tokens (8 workgroups) 114 -> 39 us, 211 rows (216) 119 -> 45, 400 rows (400) 122 -> 80; four chunks of
 // 150 rows on 3000 (608) 70 -> 70, eight of 100 on 2000 (832) 57 -> 71.  bf16 / 64 / 64: eight of 40 on 2000 (320) 49 ->

@@ -2,8 +2,8 @@
 // S^T = K . Q^T and O^T += V^T . P^T on 32x32x16 MFMA with K and V tiles in LDS, and the softmax weights of a
 // tile under a reference maximum.  Shared by the prefill kernel and by the rows items of the merged decode-queue
 // kernel, which walk the same tiles over a part of the keys.  Internal; nothing here is part of the ABI.
-// kLo: weights as two bf16 terms, hi + lo (16 bits of mantissa, twice the value products), for the shapes whose
-// weights are not rounded to 8 bits.
+// kLo: weights as three bf16 terms (24 bits of mantissa, three times the value products), for the shapes whose weights
+// are not rounded to 8 bits.
 #pragma once
 
 #include "ag_internal.h"
@@ -51,8 +51,10 @@ __device__ __forceinline__ u32x4 keep_quads(u32x4 u, int keep_lo, int keep_hi)
 }
 
 // A tile's weights as the B operands of the four k-steps of the second product.
+// Weights taken as three terms are kept in fp32 and split where a k-step uses them: kept as terms they are 48 registers
+// instead of 32, which spills at head_dim 128 (eight prompts of 2048 rows, 32-token pages: 605 instead of 522 us).
 template <bool kLo> struct Weights { bf16x8 hi[4]; };
-template <> struct Weights<true> { bf16x8 hi[4], lo[4]; };
+template <> struct Weights<true> { float p[32]; };
 
 // S^T tile (64 keys x 32 queries) = K tile . Q^T.  kb: this lane's base in a K tile (key n, chunk hi).
 // Operand reads run kAhead matrix instructions ahead of their use; the two key blocks alternate so that
@@ -76,13 +78,23 @@ __device__ __forceinline__ void qk_tile(const unsigned char* kb, const bf16x8 (&
 }
 
 // Operand i of the second product is k-step i / kMb, channel block i % kMb (neighbouring matrix instructions belong to
-// different accumulators); it meets the weights of its k-step, their low terms first.
+// different accumulators); it meets the weights of its k-step, their low terms first.  t: the terms of the k-step.
 template <int DT, bool kLo>
-__device__ __forceinline__ void value_step(int i, const bf16x8& v, const Weights<kLo>& p, f32x16 (&o)[DT / 32])
+__device__ __forceinline__ void value_step(int i, const bf16x8& v, const Weights<kLo>& p, Terms& t, f32x16 (&o)[DT / 32])
 {
     constexpr int kMb = DT / 32;
-    if constexpr (kLo) o[i % kMb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, p.lo[i / kMb], o[i % kMb], 0, 0, 0);
-    o[i % kMb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, p.hi[i / kMb], o[i % kMb], 0, 0, 0);
+    f32x16& acc = o[i % kMb];
+    if constexpr (kLo) {
+        if (i % kMb == 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t.set_pair(e, p.p[(i / kMb) * 8 + 2 * e], p.p[(i / kMb) * 8 + 2 * e + 1]);
+        }
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, t.l), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, t.m), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, __builtin_bit_cast(bf16x8, t.h), acc, 0, 0, 0);
+    } else {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, p.hi[i / kMb], acc, 0, 0, 0);
+    }
 }
 
 // O^T (DT channels x 32 queries) += V^T tile . P^T.  vb: this lane's base in a V tile (channel n, chunk hi).
@@ -95,10 +107,11 @@ __device__ __forceinline__ void pv_tile(const unsigned char* vb, const Weights<k
     auto operand = [&](int i) -> const unsigned char* { return vb + (i % kMb) * 512 + (i / kMb) * DT * 32; };
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) opnd[i] = *reinterpret_cast<const bf16x8*>(operand(i));
+    Terms terms;
 #pragma unroll
     for (int i = 0; i < kN; ++i) {
         if (i + kAhead < kN) opnd[(i + kAhead) % (kAhead + 1)] = *reinterpret_cast<const bf16x8*>(operand(i + kAhead));
-        value_step<DT, kLo>(i, opnd[i % (kAhead + 1)], pb, o);
+        value_step<DT, kLo>(i, opnd[i % (kAhead + 1)], pb, terms, o);
         __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -121,16 +134,17 @@ __device__ __forceinline__ float row_max(const f32x16 (&sc)[2])
 template <bool kLo>
 __device__ __forceinline__ bf16x2 pack_pair(int i, float q0, float q1, Weights<kLo>& p)
 {
-    const bf16x2 pr = {(__bf16)q0, (__bf16)q1};
-    const int e = 2 * i;
-    p.hi[e >> 3][e & 7] = pr[0];
-    p.hi[e >> 3][(e & 7) + 1] = pr[1];
     if constexpr (kLo) {
-        const bf16x2 rest = low_terms(q0, q1, pr);
-        p.lo[e >> 3][e & 7] = rest[0];
-        p.lo[e >> 3][(e & 7) + 1] = rest[1];
+        p.p[2 * i] = q0;
+        p.p[2 * i + 1] = q1;
+        return bf16x2{(__bf16)0.f, (__bf16)0.f};             // (not used)
+    } else {
+        const bf16x2 pr = {(__bf16)q0, (__bf16)q1};
+        const int e = 2 * i;
+        p.hi[e >> 3][e & 7] = pr[0];
+        p.hi[e >> 3][(e & 7) + 1] = pr[1];
+        return pr;
     }
-    return pr;
 }
 
 // P^T = exp2(S^T * sl2 - m) packed as the B operands of the four k-steps of the second product; adds to lsum.
@@ -174,6 +188,7 @@ __device__ __forceinline__ void softmax_and_value_product(bool do_sm, bool do_pv
         for (int i = 0; i < kAhead; ++i) opnd[i] = *reinterpret_cast<const bf16x8*>(operand(i));
         const bf16x2 kOnes = {(__bf16)1.0f, (__bf16)1.0f};
         float psum = 0.f;
+        Terms terms;
         // The vector work of a pair of scores is a chain (scale -> exp -> convert -> sum) whose links cannot
         // issue back to back; it is spread over four steps so that nothing inside a step depends on anything
         // else inside it: step i scales the pairs of step i + 1, takes the exp of its own, converts those of step i - 1
@@ -193,7 +208,7 @@ __device__ __forceinline__ void softmax_and_value_product(bool do_sm, bool do_pv
         for (int i = 0; i < kN + 2; ++i) {
             if (i < kN) {
                 if (i + kAhead < kN) opnd[(i + kAhead) % (kAhead + 1)] = *reinterpret_cast<const bf16x8*>(operand(i + kAhead));
-                value_step<DT, kLo>(i, opnd[i % (kAhead + 1)], p_prev, o);
+                value_step<DT, kLo>(i, opnd[i % (kAhead + 1)], p_prev, terms, o);
             }
 #pragma unroll
             for (int k = 0; k < kPairs; ++k) {

@@ -1,4 +1,5 @@
-// A pair of fp32 weights as two bf16 terms each, hi + lo: 16 bits of mantissa where one term has 8.  Internal.
+// fp32 numbers as three bf16 terms each, x = h + m + l, every term the rounded rest of the ones before it: all 24 bits of
+// the mantissa (each rest is exact).  Internal.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -6,14 +7,36 @@
 
 namespace ag {
 
-typedef __bf16 bf16_pair __attribute__((ext_vector_type(2)));
-
-// What lo leaves of p: p - hi in bf16.  Both halves of the packed hi are widened by one instruction each (left to itself
-// the compiler converts every weight a second time, 64 conversions a tile of 32 weights instead of 32).
-__device__ __forceinline__ bf16_pair low_terms(float p0, float p1, bf16_pair hi)
+__device__ __forceinline__ float widen_lo(uint32_t pair) { return __builtin_bit_cast(float, pair << 16); }
+__device__ __forceinline__ float widen_hi(uint32_t pair) { return __builtin_bit_cast(float, pair & 0xFFFF0000u); }
+__device__ __forceinline__ uint32_t pack(float a, float b)
 {
-    const uint32_t bits = __builtin_bit_cast(uint32_t, hi);
-    return bf16_pair{(__bf16)(p0 - __builtin_bit_cast(float, bits << 16)), (__bf16)(p1 - __builtin_bit_cast(float, bits & 0xFFFF0000u))};
+    typedef __bf16 pair __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, pair{(__bf16)a, (__bf16)b});
 }
+
+// Two numbers as packed terms.  Both halves of a packed term are widened by one instruction each (left to itself the
+// compiler converts every number a second time).  An infinity (or what rounds to one) leaves NaN as its rest.
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l)
+{
+    h = pack(a, b);
+    const float ra = a - widen_lo(h), rb = b - widen_hi(h);
+    m = pack(ra, rb);
+    l = pack(ra - widen_lo(m), rb - widen_hi(m));
+}
+
+// Eight numbers as packed terms: operands of a 16-bit product, smallest terms first when they are summed.
+struct Terms {
+    typedef uint32_t words __attribute__((ext_vector_type(4)));
+    words h, m, l;
+    __device__ __forceinline__ void set_pair(int i, float a, float b)          // numbers 2 i and 2 i + 1
+    {
+        uint32_t hh, mm, ll;
+        split_pair(a, b, hh, mm, ll);
+        h[i] = hh;
+        m[i] = mm;
+        l[i] = ll;
+    }
+};
 
 }  // namespace ag

@@ -1,0 +1,80 @@
+"""What is computed in 32 bits stays in 32 bits: softmax weights of bf16 caches beside the bf16 / 128 / 16 shape."""
+import contextlib
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import DevBatch, gpu_append, gpu_decode, gpu_merged, gpu_prefill, gpu_resume, make_cache
+from helpers import fresh_pools, make_batch, oracle_append, oracle_attn
+from paper_2603_10342_amd import binding as B
+from paper_2603_10342_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@contextlib.contextmanager
+def cus(per_xcd):
+    """A stream of per_xcd CUs of every XCD (0: the whole device): small batches then count as many tiles and pairs."""
+    stream = B.ag_stream_create_cumask(B.ag_cumask_build(B.ag_device_info()["num_cus"], 8, 0, per_xcd)) if per_xcd else None
+    try:
+        torch.cuda.synchronize()
+        with torch.cuda.stream(torch.cuda.ExternalStream(stream) if stream else torch.cuda.current_stream()):
+            yield
+    finally:
+        torch.cuda.synchronize()
+        if stream:
+            B.ag_stream_destroy(stream)
+
+
+def two_opposite_keys(d, ps, hq, hkv, prefix, seed, batch=40):
+    """Every session ends in two keys whose scores differ by 2^-11 to 2^-10 and whose values are +1 and -1, behind `prefix`
+    keys of no weight: the last row is the difference of two nearly equal weights, tanh(difference / 2)."""
+    p, n = np.full(batch, prefix, np.int32), np.full(batch, 2, np.int32)
+    pages = batch * ((prefix + 2 + ps - 1) // ps) + 3
+    g = I.Geometry(hq, hkv, d, ps, pages, I.BF16)
+    rng = np.random.default_rng(seed)
+    bt = I.deal_block_tables(I.rng_for(seed, 0), p + n, ps, pages)
+    k, v = np.zeros((batch * prefix, hkv, d)), np.ones((batch * prefix, hkv, d))
+    k[:, :, 2] = -4096.0
+    fill = make_batch(g, np.zeros_like(p), p, seed=seed, bt=bt, k=k, v=v) if prefix else None
+    k, v = np.zeros((2 * batch, hkv, d)), np.ones((2 * batch, hkv, d))
+    k[:, :, 0] = 1.0
+    k[1::2, :, 1] = -rng.uniform(2.0 ** -8, 2.0 ** -7, size=(batch, hkv))
+    v[1::2] = -1.0
+    q = np.zeros((2 * batch, hq, d))
+    q[:, :, 0] = q[:, :, 2] = 8.0
+    q[:, :, 1] = 1.0
+    return g, fill, make_batch(g, p, n, seed=seed, bt=bt, q=q, k=k, v=v, stream=2), 0.125
+
+
+# A relative error e of one weight is about e 2^10.5 of the result.  Allowed: the result's own rounding to bf16, 2^-9, and as
+# much again for fp32 arithmetic (score, exponential and sums: a few 2^-24, 2^-12 of the result).  Weights cut to 16 bits of
+# mantissa are off by up to 2^-18, up to 2^-7 of the result.
+LIMIT = 2.0 ** -9 + 2.0 ** -10
+
+
+def check_difference(got, ref, what):
+    err = np.abs(got - ref) / np.abs(ref)
+    assert err.max() <= LIMIT, f"{what}: {err.max():.2e} of the result"
+
+
+@pytest.mark.parametrize("cus_per_xcd", [0, 1])
+@pytest.mark.parametrize("prefix", [0, 70])
+@pytest.mark.parametrize("d,ps,hq,hkv", [(64, 64, 8, 2), (64, 16, 4, 4), (128, 32, 8, 2), (72, 32, 5, 1), (256, 16, 6, 2), (128, 64, 40, 2)])
+def test_bf16_caches_keep_their_softmax_weights_in_32_bits(d, ps, hq, hkv, prefix, cus_per_xcd):
+    g, fill, b, scale = two_opposite_keys(d, ps, hq, hkv, prefix, seed=61)
+    cache = make_cache(g)
+    kp, vp = fresh_pools(g)
+    for x in (fill, b):
+        if x is not None:
+            gpu_append(cache, DevBatch(x))
+            oracle_append(kp, vp, x)
+    ref = oracle_attn(kp, vp, b, scale=scale)[1::2]
+    db = DevBatch(b)
+    with cus(cus_per_xcd):
+        got = gpu_resume(cache, db, scale) if prefix else gpu_prefill(cache, db, scale)
+        check_difference(got[1::2], ref, "prefill")
+        check_difference(gpu_merged(cache, db, scale)[1::2], ref, "queue")
+        got = gpu_decode(cache, db.q[1::2].contiguous(), db.bt, db.ctx, db.max_ctx, g, scale)
+        check_difference(got, ref, "decode")
