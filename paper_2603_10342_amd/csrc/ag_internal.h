@@ -63,8 +63,10 @@ ag_status launch_attn_general(const AttnArgs& a, hipStream_t st);
 
 // bf16, head_dim 128, page 16 matrix-core paths
 bool      prefill_mfma_supported(const AttnArgs& a);
-bool      prefill_mfma_lo_supported(const AttnArgs& a);        // other bf16 shapes that launch_prefill_mfma takes
 ag_status launch_prefill_mfma(const AttnArgs& a, hipStream_t st);
+// the same kernel with weights in 32 bits, for the bf16 shapes (and calls) that never rounded them
+bool      prefill_mfma_lo_supported(const AttnArgs& a);
+ag_status launch_prefill_mfma_lo(const AttnArgs& a, hipStream_t st);
 bool      decode_mfma_supported(const AttnArgs& a);
 size_t    decode_workspace_bytes(int batch, int hq, int d, int max_ctx);
 ag_status launch_decode_mfma(const AttnArgs& a, void* ws, hipStream_t st);
@@ -78,9 +80,10 @@ ag_status launch_prefill_any(const AttnArgs& a, hipStream_t st);
 // fp32 at head_dim 64 and 128 on the bf16 matrix cores
 bool      prefill_f32_supported(const AttnArgs& a);
 ag_status launch_prefill_f32(const AttnArgs& a, hipStream_t st);
-// few rows on long contexts: the keys of a query tile split over the waves of one workgroup
-bool      prefill_split_preferred(const AttnArgs& a, hipStream_t st);
-ag_status launch_prefill_split(const AttnArgs& a, hipStream_t st);
+// few rows on long contexts: the keys of a query tile split over the waves of one workgroup (rounded: bf16 weights cut to
+// bf16, as launch_prefill_mfma does)
+bool      prefill_split_preferred(const AttnArgs& a, bool rounded, hipStream_t st);
+ag_status launch_prefill_split(const AttnArgs& a, bool rounded, hipStream_t st);
 // the whole decode step (append + attention + merge) in one launch; same shapes as the matrix-core decode
 size_t    decode_step_workspace_bytes(int batch, int hq, int d, int max_ctx);
 ag_status launch_decode_step(const AttnArgs& a, const void* k_new, const void* v_new, void* ws, hipStream_t st);

@@ -365,8 +365,8 @@ bool prefill_any_supported(const AttnArgs& a)
 
 ag_status launch_prefill_any(const AttnArgs& a, hipStream_t st)
 {
-    if (prefill_mfma_lo_supported(a)) return launch_prefill_mfma(a, st);
-    if (prefill_split_preferred(a, st)) return launch_prefill_split(a, st);
+    if (prefill_mfma_lo_supported(a)) return launch_prefill_mfma_lo(a, st);
+    if (prefill_split_preferred(a, false, st)) return launch_prefill_split(a, false, st);
     if (prefill_f32_supported(a)) return launch_prefill_f32(a, st);
     return a.c.dtype == AG_BF16 ? launch_for_dim<__bf16>(a, st) : launch_for_dim<float>(a, st);
 }

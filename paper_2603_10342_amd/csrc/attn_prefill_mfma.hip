@@ -351,7 +351,7 @@ static int64_t tiles_bound(const AttnArgs& a, int cols)
     return std::min<int64_t>((int64_t)a.total_rows * G / cols + a.batch, (int64_t)a.batch * ((a.max_new * G + cols - 1) / cols));
 }
 
-// Other bf16 shapes that take this kernel: head_dim 128 (32-token pages, append included, the general tiles -> this one:
+// Other bf16 batches that take this kernel, with weights in 32 bits: head_dim 128 (32-token pages, append included, the general tiles -> this one:
 // eight chunks of 40..500 rows on 500..4000 tokens 210 -> 199 us, eight prompts of 2048 528 -> 523), and head_dim 64 when
 // contexts are over twice the chunks.  There the interleaved softmax shortens a workgroup's chain of tiles, and the longer
 // start of its pipeline and the lower occupancy lengthen a launch of many workgroups.  64-token pages, general tiles -> this
@@ -385,17 +385,21 @@ static ag_status launch_prefill_nw(const AttnArgs& a, hipStream_t st)
     return hip_check(hipGetLastError(), "prefill launch");
 }
 
-ag_status launch_prefill_mfma(const AttnArgs& a, hipStream_t st)
+// lo: weights in 32 bits (see kLo)
+static ag_status launch_tiles(const AttnArgs& a, bool lo, hipStream_t st)
 {
-    if (prefill_split_preferred(a, st)) return launch_prefill_split(a, st);
+    if (prefill_split_preferred(a, !lo, st)) return launch_prefill_split(a, !lo, st);
     // 256-column workgroups when chunks are long enough to fill them (a K/V tile then feeds twice the columns);
     // 128-column workgroups keep short, ragged chunks efficient, and spread a batch that the larger ones could not spread
     // over 5/8 of the CUs (one chunk on 6000 tokens, whole call: 600 rows 152 -> 126 us, 1000 rows 167 -> 139; two of 600
     // rows, 160 of the larger workgroups, 159 against 165).
     const bool big = a.max_new >= 512 && 8 * a.c.hkv * tiles_bound(a, 256) >= 5 * (int64_t)stream_cus(st);
-    if (prefill_mfma_supported(a)) return big ? launch_prefill_nw<8, 128, false, true>(a, st) : launch_prefill_nw<4, 128, false, true>(a, st);
+    if (!lo) return big ? launch_prefill_nw<8, 128, false, true>(a, st) : launch_prefill_nw<4, 128, false, true>(a, st);
     if (a.c.d == 128) return big ? launch_prefill_nw<8, 128, true, false>(a, st) : launch_prefill_nw<4, 128, true, false>(a, st);
     return launch_prefill_nw<4, 64, true, false>(a, st);
 }
+
+ag_status launch_prefill_mfma(const AttnArgs& a, hipStream_t st) { return launch_tiles(a, false, st); }
+ag_status launch_prefill_mfma_lo(const AttnArgs& a, hipStream_t st) { return launch_tiles(a, true, st); }
 
 }  // namespace ag

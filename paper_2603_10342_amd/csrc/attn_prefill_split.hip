@@ -340,19 +340,18 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 // 30, 32 of 20 on 1000 (768) 31 -> 31, two prompts of 1000 (2000) 41 -> 50.  fp32 / 128: one chunk of 211 rows on 6000
 // (216) 604 -> 225, one prompt of 600 (600) 71 -> 54, twelve chunks of 10..100 rows on 1000..3000 (700) 299 -> 243; three of
 // 300 on 5000 (912) 528 -> 743, two prompts of 1000 (2000) 137 -> 210.
-bool prefill_split_preferred(const AttnArgs& a, hipStream_t st)
+bool prefill_split_preferred(const AttnArgs& a, bool rounded, hipStream_t st)
 {
     if ((a.c.d != 64 && a.c.d != 128) || a.c.ps < 16 || (int64_t)a.total_rows * (a.hq / a.c.hkv) > 0x7fffffff ||
         ((uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 != 0) return false;
-    const int per_cu = a.c.dtype == AG_BF16 && a.c.d == 128 && a.c.ps == 16 ? 2 : 3;
-    return a.c.hkv * tiles_bound(a, kColumns) <= (int64_t)per_cu * stream_cus(st);
+    return a.c.hkv * tiles_bound(a, kColumns) <= (int64_t)(rounded ? 2 : 3) * stream_cus(st);
 }
 
-ag_status launch_prefill_split(const AttnArgs& a, hipStream_t st)
+ag_status launch_prefill_split(const AttnArgs& a, bool rounded, hipStream_t st)
 {
     if (a.c.dtype == AG_F32) return a.c.d == 64 ? launch_kernel<float, 64, false>(a, st) : launch_kernel<float, 128, false>(a, st);
     if (a.c.d == 64) return launch_kernel<__bf16, 64, true>(a, st);
-    return a.c.ps == 16 ? launch_kernel<__bf16, 128, false>(a, st) : launch_kernel<__bf16, 128, true>(a, st);
+    return rounded ? launch_kernel<__bf16, 128, false>(a, st) : launch_kernel<__bf16, 128, true>(a, st);
 }
 
 }  // namespace ag

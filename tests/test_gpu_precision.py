@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_helpers import DevBatch, gpu_append, gpu_decode, gpu_merged, gpu_prefill, gpu_resume, make_cache
+from gpu_helpers import DevBatch, check_close, gpu_append, gpu_decode, gpu_merged, gpu_prefill, gpu_resume, make_cache
 from helpers import fresh_pools, make_batch, oracle_append, oracle_attn
 from paper_2603_10342_amd import binding as B
 from paper_2603_10342_amd import inputs as I
@@ -80,3 +80,42 @@ def test_bf16_caches_keep_their_softmax_weights_in_32_bits(d, ps, hq, hkv, prefi
         check_difference(gpu_merged(cache, db, scale)[2::3], ref, "queue")
         got = gpu_decode(cache, db.q[2::3].contiguous(), db.bt, db.ctx, db.max_ctx, g, scale)
         check_difference(got, ref, "decode")
+
+
+# bf16 / 128 / 16 with more query heads per KV head than the merged kernel's tiles hold: its queue, like its decode, keeps
+# weights in 32 bits (ag_attn_prefill and ag_attn_resume round them at this shape).
+@pytest.mark.parametrize("cus_per_xcd", [0, 1])
+@pytest.mark.parametrize("prefix", [0, 70])
+def test_queues_of_large_groups_keep_their_softmax_weights_in_32_bits(prefix, cus_per_xcd):
+    g, fill, b, scale = two_opposite_keys(128, 16, 40, 2, prefix, seed=62)
+    cache = make_cache(g)
+    kp, vp = fresh_pools(g)
+    for x in (fill, b):
+        if x is not None:
+            gpu_append(cache, DevBatch(x))
+            oracle_append(kp, vp, x)
+    ref = oracle_attn(kp, vp, b, scale=scale)[2::3]
+    db = DevBatch(b)
+    with cus(cus_per_xcd):
+        check_difference(gpu_merged(cache, db, scale)[2::3], ref, "queue")
+        got = gpu_decode(cache, db.q[2::3].contiguous(), db.bt, db.ctx, db.max_ctx, g, scale)
+        check_difference(got, ref, "decode")
+
+
+@pytest.mark.parametrize("cus_per_xcd", [0, 1])
+def test_an_infinite_value_in_a_queue_of_large_groups_stays_with_the_rows_that_see_it(cus_per_xcd):
+    lens, at, ch, G = [130, 143], 100, 67, 20
+    g = I.Geometry(2 * G, 2, 128, 16, 24, I.BF16)
+    bt = I.deal_block_tables(I.rng_for(63, 0), lens, 16, 24)
+    b = make_batch(g, [0, 0], lens, seed=63, bt=bt)
+    kp, vp = fresh_pools(g)
+    oracle_append(kp, vp, b)
+    ref = oracle_attn(kp, vp, b)
+    cache, db = make_cache(g), DevBatch(b)
+    db.v_new[at, 0, ch] = float("inf")
+    gpu_append(cache, db)
+    with cus(cus_per_xcd):
+        got = gpu_merged(cache, db)
+    assert np.all(got[at:lens[0], :G, ch] == np.inf)
+    got[at:lens[0], :G, ch] = ref[at:lens[0], :G, ch]
+    check_close(got, ref, I.BF16, "queue, 40 / 2 heads")
