@@ -4,10 +4,14 @@
 // bounds the fp32 form of attn_prefill_any.hip.  Here every fp32 number is taken as three bf16 terms, x = h + m + l
 // (each the rounded rest of the ones before: 24 bits and more), and a product as the six of their nine products that
 // reach 2^-24 of it: h h + (h m + m h) + (h l + l h + m m).  What is dropped is below 2^-25, less than the rounding of an
-// fp32 product; sums are fp32 sums as before.  (Published as bf16x3: Henry, Tang and Heinecke, "Leveraging the bfloat16
-// artificial intelligence datatype for higher-precision computations", 2019.)  Relative error against 64 bits: 2.4e-7 over
-// four prompts of 300..1500 rows and 1.2e-6 over 600 rows on 6000 tokens at 32 / 8 heads x 128; one wave per row, in plain
-// fp32 and in the order of the keys, had 3.9e-7 and 1.4e-6.
+// fp32 product; sums are fp32 sums as before.  Terms lie up to 2^-24 below their number and bf16's normal numbers end at
+// 2^-126: a number below 2^-102 is off by up to 2^-126 itself.  Columns where that could show are taken again in plain fp32:
+// a query with so small a channel, a query so large that a small key counts, an output that small.  Weights, the largest of
+// which is about 1, are multiplied by 2^48, so that all down to 2^-126 keep their terms (smaller ones count as zero).
+// (Published as bf16x3: Henry, Tang and Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for
+// higher-precision computations", 2019.)  Relative error against 64 bits: 2.4e-7 over four prompts of 300..1500 rows and
+// 1.2e-6 over 600 rows on 6000 tokens at 32 / 8 heads x 128; one wave per row, in plain fp32 and in the order of the keys,
+// had 3.9e-7 and 1.4e-6.
 //
 // A workgroup of four waves owns 128 (token, head) columns of one (session, KV head), 32 a wave, whose queries lie in
 // registers as terms.  Keys and values are taken 32 at a time: every thread fetches its share of the next tile into
@@ -39,18 +43,31 @@ constexpr int kColumns = 128;           // (token, head) pairs of a workgroup
 constexpr int BN = 32;                  // keys per tile
 constexpr float kSlack = 5.5f;          // how far a maximum may outgrow the reference before O is rescaled
 
+constexpr float kLargeQuery = 0x1p90f;  // scale * |q| up to which what small keys lose (2^-126, times 128 channels) is nothing
+
+// The smallest size among numbers, zero left out because it is exact: of 2 |bits| - 1, where zero comes out largest.
+struct Least {
+    uint32_t u = ~0u;
+    __device__ __forceinline__ void take(float x) { u = min(u, (__builtin_bit_cast(uint32_t, x) << 1) - 1); }
+    __device__ __forceinline__ bool small(float unit = 1.f) const        // (no number but zeros: NaN)
+    {
+        return __builtin_bit_cast(float, u >> 1) * unit < 0x1p-100f;
+    }
+};
+
 constexpr int plane_bytes(int dt) { return BN * dt * 2; }           // one term of a tile of keys, or of values
 constexpr int lds_bytes(int dt) { return 12 * plane_bytes(dt); }    // two stages of K h, m, l, then two of V h, m, l
 
-// e^x for x <= 0 or little above: 2^t with the rounding of t = x log2(e) put back to first order (within 1.5 units in the
+constexpr float kWeightUnit = 0x1p48f;  // what a weight of 1 is multiplied as; their sum is in the same unit
+
+// 2^48 e^x for x <= 0 or little above: 2^t with the rounding of t = x log2(e) put back to first order (within 2 units in the
 // last place, eight instructions).  -inf gives 0, NaN stays NaN.
 __device__ __forceinline__ float exp_near(float x)
 {
     x = x < -200.f ? -200.f : x;
     const float t = x * 1.44269502f;
     const float r = fmaf(x, 1.92596299e-8f, fmaf(x, 1.44269502f, -t));        // log2(e) = 1.44269502 + 1.926e-8
-    const float e = __builtin_amdgcn_exp2f(t);
-    return fmaf(e, r * 0.693147182f, e);
+    return __builtin_amdgcn_exp2f(t) * fmaf(r, 0.693147182f * kWeightUnit, kWeightUnit);
 }
 
 __device__ __forceinline__ Terms split8(const f32x4& a, const f32x4& b)
@@ -330,19 +347,56 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
     // o[mb][q4 * 4 + e] is O^T[channel mb * 32 + q4 * 8 + hi * 4 + e][column n]
     lsum += __shfl_xor(lsum, 32);
     const float inv = 1.0f / lsum;
-    // Infinities among Q, K and V come out of the split products as NaN, whatever they would have given; and the products
-    // take terms below 2^-126 as zero: values under 2^-110 or so lose their low terms (1e-36: 3e-5 of them).
-    float trouble = general::trouble_of(inv), top = 0.f;
+    // Infinities among Q, K and V come out of the split products as NaN, whatever they would have given (weights times large
+    // values may overflow as well); small outputs may have lost terms of theirs.  An output of zero is small too unless its
+    // channel is all zeros, so that where there is one the values are looked at once more.
+    float trouble = general::trouble_of(inv);
+    Least least_o, least_q;
+    float most_q = 0.f;
+    {
+        const float* qp = (const float*)a.q + row * DT + hi * (DT / 2);       // this lane's half of its column's query
+#pragma unroll
+        for (int i = 0; i < DT / 2; i += 4) {
+            const f32x4 q4 = *reinterpret_cast<const f32x4*>(qp + i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                least_q.take(q4[e]);
+                most_q = fmaxf(most_q, fabsf(q4[e]));
+            }
+        }
+    }
+    const bool odd_query = least_q.small() || most_q * a.scale > kLargeQuery;
+    uint32_t zero_o = ~0u;
 #pragma unroll
     for (int mb = 0; mb < kMb; ++mb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             trouble = general::trouble_of(o[mb][i], trouble);
-            top = fmaxf(top, fabsf(o[mb][i] * inv));
+            least_o.take(o[mb][i]);
+            zero_o = min(zero_o, __builtin_bit_cast(uint32_t, o[mb][i]) << 1);
         }
-    top = fmaxf(top, __shfl_xor(top, 32));
-    const bool tiny = top > 0.f && top < 0x1p-100f;
-    uint64_t again = __builtin_amdgcn_ballot_w64(n < cols_w && (tiny || !(trouble == 0.f)));
+    const bool zero_out = zero_o == 0 && n < cols_w;
+    bool small_values = false;
+    uint32_t* const s_any = reinterpret_cast<uint32_t*>(lds + 4096);          // [2][wave], behind what attend_rows_again() uses
+    auto any_of = [&](bool x, uint32_t* at) {                   // of the workgroup
+        const uint64_t lanes = __builtin_amdgcn_ballot_w64(x);
+        if (lane == 0) at[w] = lanes != 0;
+        __syncthreads();
+        return (at[0] | at[1] | at[2] | at[3]) != 0;
+    };
+    if (any_of(zero_out, s_any)) {
+        Least least_v;
+        for (int t = 0; t < n_tiles; ++t) {
+            fetch_v(t, id_of(2 * t), id_of(2 * t + 1));
+            scrub(t);
+#pragma unroll
+            for (int i = 0; i < kUnits; ++i)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) least_v.take(vx[i][e >> 2][e & 3]);
+        }
+        small_values = any_of(least_v.small(), s_any + 4);
+    }
+    uint64_t again = __builtin_amdgcn_ballot_w64(n < cols_w && (odd_query || least_o.small(inv) || (zero_out && small_values) || !(trouble == 0.f)));
     again = (again | (again >> 32)) & 0xFFFFFFFFu;              // bit c: column c of this wave
     if (n < cols_w && !((again >> n) & 1)) {
         float* out = (float*)a.out + row * DT + hi * 4;

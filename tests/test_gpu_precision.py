@@ -119,3 +119,53 @@ def test_an_infinite_value_in_a_queue_of_large_groups_stays_with_the_rows_that_s
     assert np.all(got[at:lens[0], :G, ch] == np.inf)
     got[at:lens[0], :G, ch] = ref[at:lens[0], :G, ch]
     check_close(got, ref, I.BF16, "queue, 40 / 2 heads")
+
+
+# fp32 prefill of many tiles takes numbers as three bf16 terms each, which lie up to 2^-16 below the number: what is too
+# small for its terms has to be noticed, wherever it stands.  Every other value channel, every other key or query, or
+# everything, is scaled down by `small`; the other side of a product is scaled up, so that scores stay as they are.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("what,small", [("channels", 2.0 ** -120), ("channels", 2.0 ** -105), ("values", 2.0 ** -120), ("values", 2.0 ** -140),
+                                        ("keys", 2.0 ** -122), ("queries", 2.0 ** -122), ("weights", 2.0 ** -122)])
+def test_fp32_prefill_keeps_small_numbers_in_32_bits(what, small, d):
+    lens = [150, 290]
+    g = I.Geometry(8, 2, d, 16, 40, I.F32)
+    b = make_batch(g, [0, 0], lens, seed=64)
+    scaled = np.zeros((sum(lens), 1, d), bool)
+    if what == "channels":
+        scaled[:, :, 1::2] = True
+    elif what == "values":
+        scaled[:] = True
+    if what in ("channels", "values"):
+        b.v_new = (b.v_new * np.where(scaled, small, 1.0)).astype(np.float32)
+        b.v_new[:, :, 7] = 0.0                                  # (a channel of zeros is no small number)
+    elif what == "weights":
+        # the first key outweighs the second by 1 / small and up to 8 times that, the others by far more, and only the second
+        # one has values, large ones: the result is its small weight times those
+        first = np.array([0, lens[0]])
+        v = b.v_new[first + 1] * np.float32(2.0 ** 60)
+        b.v_new[:], b.q[:], b.k_new[:] = 0.0, 0.0, 0.0
+        b.v_new[first + 1] = v
+        b.q[:, :, 0] = np.random.default_rng(64).uniform(1.0, 1.0 - np.log(8.0) / np.log(small), size=b.q.shape[:2])
+        b.k_new[:, :, 0] = 2.0 * np.log(small) * np.sqrt(d)
+        b.k_new[first, :, 0], b.k_new[first + 1, :, 0] = 0.0, np.log(small) * np.sqrt(d)
+    else:
+        down, up = (b.k_new, b.q) if what == "keys" else (b.q, b.k_new)
+        down *= np.float32(small)
+        up *= np.float32(1.0 / small)
+    cache = make_cache(g)
+    kp, vp = fresh_pools(g)
+    db = DevBatch(b)
+    with cus(1):
+        gpu_append(cache, db)
+        got = gpu_prefill(cache, db)
+    oracle_append(kp, vp, b)
+    ref = oracle_attn(kp, vp, b)
+    # per channel, so that none hides behind larger ones: the relative gate of fp32, and half a unit of the smallest number
+    # for every term of a sum whose result is as small.  Weights: the exponent of about 85 is rounded to 2^-18 three times
+    # (product, scaled score, difference).
+    gate = 1e-5 + (3 * 2.0 ** -18 if what == "weights" else 0.0)
+    for ch in range(d):
+        err, size = np.linalg.norm(got[:, :, ch] - ref[:, :, ch]), np.linalg.norm(ref[:, :, ch])
+        least = 2.0 ** -150 * np.sqrt(sum(lens) * 8) * max(lens)
+        assert err <= gate * size + least, f"channel {ch}: {err:.2e} of {size:.2e}"
