@@ -396,7 +396,7 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
     }
     __syncthreads();                                             // (weights in terms turn an infinite sum into NaN)
     const uint32_t all = __builtin_amdgcn_readfirstlane(s_again);
-    if (all) general::attend_rows_again<E>(a, all & (0x0101u << w), (int64_t)s * hq + (int64_t)g * G + h0 + r, s, s, ctx - 1, &s_o[w][0][0]);
+    if (all) general::attend_rows_again<E, 2, (DT + 63) / 64>(a, all & (0x0101u << w), (int64_t)s * hq + (int64_t)g * G + h0 + r, ctx - 1, s, g, &s_o[w][0][0]);
 }
 
 template <typename E>
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(256) void decode_any_merge_kernel(AttnArgs a, const
     uint64_t again = __builtin_amdgcn_ballot_w64(!(trouble == 0.f));
     while (again) {                             // one row at a time: other waves that hold a part of it write the same
         const int l = __builtin_ctzll(again), r = __builtin_amdgcn_readlane((int)row, l), rs = __builtin_amdgcn_readlane(s, l);
-        general::attend_rows_again<E>(a, 1ull << l, row, rs, rs, __builtin_amdgcn_readlane(ctx, l) - 1, s_q[threadIdx.x >> 6]);
+        general::attend_rows_again<E, 1, 4>(a, 1ull << l, row, ctx - 1, rs, (r - rs * a.hq) / (a.hq / a.c.hkv), s_q[threadIdx.x >> 6]);
         again &= ~__builtin_amdgcn_ballot_w64((int)row == r);
     }
 }

@@ -93,18 +93,119 @@ __device__ __forceinline__ void attend_row(const AttnArgs& a, int64_t t, int h, 
 
 // For kernels that multiply whole tiles: an infinity or NaN among the values of a tile turns the columns that may not see it
 // into NaN too (0 x inf), and terms of split numbers can turn an infinite result into NaN.  Columns whose result is not
-// finite are therefore taken again, one at a time, in plain arithmetic, and give what they would have given.
-// Bit c of `again` (uniform over the wave): row `rows` of lane c, a row of Q as t * hq + head, of session s, whose first
-// row of Q is row0 at position P.
-template <typename T>
-__device__ __forceinline__ void attend_rows_again(const AttnArgs& a, uint64_t again, int64_t rows, int s, int row0, int P, float* s_q)
+// finite are therefore taken again, in plain arithmetic, and give what they would have given: attend_row()'s numbers bit
+// for bit, for caches with pages of 16 tokens or more and 16-byte aligned pools (whose layout allows 16-byte loads).
+// R rows of one session and KV head share a pass over its keys and values, because whoever sees one value that is not
+// finite is seldom alone: every later row of the session does.
+// s_q: R * D floats of LDS private to this wave; C: 64-channel blocks of head_dim.
+template <typename T, int R, int C>
+__device__ __forceinline__ void attend_rows(const AttnArgs& a, const int64_t (&rows)[R], const int (&pos)[R], int s, int g, float* s_q)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int kVecs = (int)sizeof(T) / 2;             // 16-byte loads of 8 numbers
+    union Eight { u32x4 u[kVecs]; T e[8]; };
+    const int lane = threadIdx.x & 63;
+    const int D = a.c.d, ps = a.c.ps, hkv = a.c.hkv;
+    const int64_t block = (int64_t)D * ps;
+    const T* kp = (const T*)a.c.k;
+    const T* vp = (const T*)a.c.v;
+    const int32_t* bt = a.bt + (int64_t)s * a.max_pages;
+    auto load8 = [](Eight& x, const T* p) {
+#pragma unroll
+        for (int i = 0; i < kVecs; ++i) x.u[i] = reinterpret_cast<const u32x4*>(p)[i];
+    };
+    int last = pos[0];
+#pragma unroll
+    for (int r = 1; r < R; ++r) last = max(last, pos[r]);
+    float m[R], l[R], o[R][C];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        for (int d = lane; d < D; d += 64) s_q[r * D + d] = to_f32(((const T*)a.q)[rows[r] * D + d]);
+        m[r] = -INFINITY;
+        l[r] = 0.f;
+#pragma unroll
+        for (int c = 0; c < C; ++c) o[r][c] = 0.f;
+    }
+    __builtin_amdgcn_wave_barrier();                      // s_q is private to this wave
+
+#pragma unroll 1
+    for (int base = 0; base <= last; base += 64) {
+        const int j = base + lane, at = min(j, last);     // lane = key
+        const int page = bt[at >> a.c.ps_shift];
+        const T* kr = kp + ((int64_t)page * hkv + g) * block + (at & (ps - 1)) * 8;
+        float dot[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) dot[r] = 0.f;
+#pragma unroll 4
+        for (int c = 0; c < D / 8; ++c) {
+            Eight k;
+            load8(k, kr + (int64_t)c * ps * 8);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int r = 0; r < R; ++r) dot[r] = fmaf(s_q[r * D + c * 8 + e], to_f32(k.e[e]), dot[r]);
+        }
+        float p[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            p[r] = 0.f;
+            if (base > pos[r]) continue;                  // uniform: the row has ended
+            const float x = j <= pos[r] ? a.scale * dot[r] : -INFINITY;
+            const float m_new = fmaxf(m[r], wave_max(x));
+            const float alpha = expf(m[r] - m_new);
+            p[r] = j <= pos[r] ? expf(x - m_new) : 0.f;
+            l[r] = l[r] * alpha + wave_sum(p[r]);
+#pragma unroll
+            for (int c = 0; c < C; ++c) o[r][c] *= alpha;
+            m[r] = m_new;
+        }
+#pragma unroll 1
+        for (int first = base; first < base + 64 && first <= last; first += 16) {       // lane = channel, a 16-token group at a time
+            const int64_t pg = __builtin_amdgcn_readlane(page, first - base);
+            const T* vr = vp + (pg * hkv + g) * block + (int64_t)((first & (ps - 1)) >> 4) * 16 * D;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                if (64 * c >= D) break;                   // uniform
+                Eight v[2];                               // keys 0..3 and 8..11 of the group, keys 4..7 and 12..15 (v_offset)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) load8(v[h], vr + (h * D + min(lane + 64 * c, D - 1)) * 8);
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        if (first + i > pos[r]) continue; // uniform
+                        const float w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, p[r]), first - base + i));
+                        o[r][c] = fmaf(w, to_f32(v[(i >> 2) & 1].e[(i & 3) + (i >> 3) * 4]), o[r][c]);
+                    }
+                __builtin_amdgcn_sched_barrier(0);        // one block of channels at a time: registers, of which the callers have few
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const float inv = 1.0f / l[r];
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            if (lane + 64 * c < D) store_out((T*)a.out + rows[r] * D + lane + 64 * c, o[r][c] * inv);
+    }
+}
+
+// Bit c of `again` (uniform over the wave): row `row` of lane c, a row of Q as t * hq + head, of session s and KV head g, at
+// position `pos` of lane c.
+template <typename T, int R, int C>
+__device__ __forceinline__ void attend_rows_again(const AttnArgs& a, uint64_t again, int64_t row, int pos, int s, int g, float* s_q)
 {
     while (again) {
-        const int c = __builtin_ctzll(again);
-        again &= again - 1;
-        const int64_t row = ((int64_t)__builtin_amdgcn_readlane((int)(rows >> 32), c) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)rows, c);
-        const int64_t t = row / a.hq;
-        attend_row<T>(a, t, (int)(row - t * a.hq), s, P + (int)(t - row0), s_q);
+        int64_t rows[R];
+        int at[R], c = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {                     // (fewer than R are left: the last one once more)
+            if (again) c = __builtin_ctzll(again);
+            again &= again - 1;
+            rows[r] = ((int64_t)__builtin_amdgcn_readlane((int)(row >> 32), c) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)row, c);
+            at[r] = __builtin_amdgcn_readlane(pos, c);
+        }
+        attend_rows<T, R, C>(a, rows, at, s, g, s_q);
     }
 }
 

@@ -36,6 +36,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kColumns = 128;           // (token, head) pairs of a workgroup
 constexpr float kLog2e = 1.4426950408889634f;
+// rows taken again together (attn_general_row.h); 256 channels have no registers to spare (2 % of the kernel)
+constexpr int rows_again(int dt) { return dt > 128 ? 1 : 4; }
 constexpr int kAhead = 3;               // LDS operand reads run this many operands ahead of their use
 
 // use(i, operand i) for i = 0 .. N - 1, operand i read from at(i) kAhead operands before its use
@@ -310,7 +312,7 @@ __global__ __launch_bounds__(256, DT > 128 ? 1 : 2) void prefill_any_kernel(Attn
                 }
             }
     }
-    general::attend_rows_again<E>(a, again, row, s, row0, P, reinterpret_cast<float*>(lds) + 256 * wu);       // (all are past the last tile)
+    general::attend_rows_again<E, rows_again(DT), DT / 64>(a, again, row, qpos, s, g, reinterpret_cast<float*>(lds) + rows_again(DT) * DT * wu);       // (all are past the last tile)
 }
 
 // sum_s ceil(N_s G / 128) <= total G / 128 + batch, and no session has more than ceil(max_new G / 128)

@@ -41,6 +41,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kColumns = 128;           // (token, head) pairs of a workgroup
 constexpr int BN = 32;                  // keys per tile
+constexpr int kRowsAgain = 4;           // rows taken again together (attn_general_row.h)
 constexpr float kSlack = 5.5f;          // how far a maximum may outgrow the reference before O is rescaled
 
 constexpr float kLargeQuery = 0x1p90f;  // scale * |q| up to which what small keys lose (2^-126, times 128 channels) is nothing
@@ -288,7 +289,9 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
             float psum[2] = {0.f, 0.f};
             auto weigh = [&](int j) {                           // pair j of eight
                 const int i = 2 * j;
-                const float p0 = exp_near(fmaf(x[i], a.scale, -m_ref)), p1 = exp_near(fmaf(x[i + 1], a.scale, -m_ref));
+                float scale = a.scale;
+                asm volatile("" : "+s"(scale));                 // (here, not all pairs ahead of the products: 4 % of the kernel)
+                const float p0 = exp_near(fmaf(x[i], scale, -m_ref)), p1 = exp_near(fmaf(x[i + 1], scale, -m_ref));
                 psum[0] += p0;
                 psum[1] += p1;
                 pf[i >> 3].set_pair((i & 7) >> 1, p0, p1);
@@ -377,7 +380,7 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
         }
     const bool zero_out = zero_o == 0 && n < cols_w;
     bool small_values = false;
-    uint32_t* const s_any = reinterpret_cast<uint32_t*>(lds + 4096);          // [2][wave], behind what attend_rows_again() uses
+    uint32_t* const s_any = reinterpret_cast<uint32_t*>(lds + 16 * kRowsAgain * DT);          // [2][wave], behind what attend_rows_again() uses
     auto any_of = [&](bool x, uint32_t* at) {                   // of the workgroup
         const uint64_t lanes = __builtin_amdgcn_ballot_w64(x);
         if (lane == 0) at[w] = lanes != 0;
@@ -410,7 +413,7 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
                 *reinterpret_cast<f32x4*>(out + mb * 32 + q4 * 8) = y;
             }
     }
-    general::attend_rows_again<float>(a, again, row, s, row0, P, reinterpret_cast<float*>(lds) + 256 * w);    // (all are past the last tile)
+    general::attend_rows_again<float, kRowsAgain, DT / 64>(a, again, row, qpos, s, g, reinterpret_cast<float*>(lds) + kRowsAgain * DT * w);    // (all are past the last tile)
 }
 
 // sum_s ceil(N_s G / 128) <= total G / 128 + batch, and no session has more than ceil(max_new G / 128)

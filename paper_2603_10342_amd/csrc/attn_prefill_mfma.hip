@@ -327,7 +327,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, in
     }
     if constexpr (kLo) {
         again = (again | (again >> 32)) & 0xFFFFFFFFu;          // bit c: column c of this wave
-        general::attend_rows_again<__bf16>(a, again, (int64_t)base_row + (unsigned)my_row, s, row0, P, reinterpret_cast<float*>(ob));
+        general::attend_rows_again<__bf16, 4, DT / 64>(a, again, (int64_t)base_row + (unsigned)my_row, qpos, s, g, reinterpret_cast<float*>(ob));
     }
 }
 

@@ -32,6 +32,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kColumns = 32;            // (token, head) pairs of a workgroup
 constexpr int kWaves = 8;               // which share its keys
+constexpr int kRowsAgain = 4;           // rows taken again together (attn_general_row.h): a wave's share of the columns
 constexpr int kStep = 32;               // keys of a wave's step
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -300,7 +301,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
         __syncthreads();                                        // what the waves write once more is behind what is there
         const uint32_t all = __builtin_amdgcn_readfirstlane(*s_again);
         int t;
-        if (all) general::attend_rows_again<E>(a, all & (0x01010101u << w), row_of(min(n, cols - 1), t), s, row0, P, s_o + 256 * w);
+        if (all) general::attend_rows_again<E, kRowsAgain, DT / 64>(a, all & (0x01010101u << w), row_of(min(n, cols - 1), t), qpos, s, g, s_o + kRowsAgain * DT * w);
     }
 }
 

@@ -169,3 +169,90 @@ def test_fp32_prefill_keeps_small_numbers_in_32_bits(what, small, d):
         err, size = np.linalg.norm(got[:, :, ch] - ref[:, :, ch]), np.linalg.norm(ref[:, :, ch])
         least = 2.0 ** -150 * np.sqrt(sum(lens) * 8) * max(lens)
         assert err <= gate * size + least, f"channel {ch}: {err:.2e} of {size:.2e}"
+
+
+def off_16_bytes(t):
+    """A copy whose address is no multiple of 16: such calls run row by row in plain fp32."""
+    x = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)[1:].view(t.shape)
+    x.copy_(t)
+    assert x.data_ptr() % 16
+    return x
+
+
+# Rows that are not finite are taken again in plain arithmetic: bit for bit what the row-by-row kernel gives, whichever
+# rows share the pass, and the same every time.  head_dim 72 and 200: a merge workgroup's waves would hold parts of a row.
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("cus_per_xcd", [0, 1])
+@pytest.mark.parametrize("dtype,d,ps,hq,hkv", [(I.BF16, 64, 64, 8, 2), (I.BF16, 128, 32, 8, 2), (I.BF16, 72, 16, 7, 1), (I.BF16, 200, 32, 6, 2),
+                                               (I.BF16, 256, 16, 40, 2), (I.F32, 64, 16, 8, 2), (I.F32, 128, 256, 4, 4), (I.F32, 72, 32, 5, 1),
+                                               (I.F32, 256, 16, 17, 1)])
+def test_rows_taken_again_are_the_row_by_row_kernels(dtype, d, ps, hq, hkv, cus_per_xcd, bad):
+    lens = [150, 290, 1]
+    ctx = [n + 700 for n in lens]
+    pages = sum((c + ps - 1) // ps for c in ctx) + 3
+    g = I.Geometry(hq, hkv, d, ps, pages, dtype)
+    bt = I.deal_block_tables(I.rng_for(65, 0), ctx, ps, pages)
+    fill = make_batch(g, [0] * 3, [700] * 3, seed=65, bt=bt)
+    b = make_batch(g, [700] * 3, lens, seed=65, bt=bt, stream=2)
+    cache, df, db = make_cache(g), DevBatch(fill), DevBatch(b)
+    db.v_new[100, 0, 3] = bad                              # session 0: rows before and after it
+    df.v_new[700 + 5, hkv - 1, d - 1] = bad                # session 1: every row
+    gpu_append(cache, df)
+    gpu_append(cache, db)
+    last = torch.tensor([149, 439, 440], device="cuda")
+
+    def run(q):
+        db.q, db.out = q, torch.zeros_like(q)
+        out = gpu_resume(cache, db)
+        return out, gpu_decode(cache, q[last].contiguous() if q.data_ptr() % 16 == 0 else off_16_bytes(q[last]), db.bt, db.ctx, db.max_ctx, g)
+
+    q = db.q
+    with cus(cus_per_xcd):
+        one, two = run(q), run(q)
+    db.q = off_16_bytes(q)
+    db.out = off_16_bytes(torch.zeros_like(q))
+    rows = run(db.q)
+    for x, again, want in zip(one, two, rows):
+        assert np.array_equal(x, again, equal_nan=True)
+        odd = ~np.isfinite(want).all(axis=-1)              # (row, head)
+        assert odd.any() and not odd.all()
+        np.testing.assert_array_equal(x[odd], want[odd])
+        assert np.isfinite(x[~odd]).all()
+
+
+@pytest.mark.parametrize("dtype,d,ps", [(I.BF16, 64, 64), (I.F32, 128, 16)])
+def test_a_batch_with_a_value_that_is_not_finite_is_no_slower_than_row_by_row(dtype, d, ps):
+    """Eight chunks on cached tokens, and a decode step, one session of which holds a NaN every row of it sees: against the
+    same calls on a q off 16 bytes, which run row by row throughout (measured 4 times as long; one row after another in one
+    wave, as it was, half as long)."""
+    p, n = np.full(8, 1500, np.int32), np.full(8, 120, np.int32)
+    g = I.Geometry(32, 8, d, ps, 8 * ((1620 + ps - 1) // ps), dtype)
+    bt = I.deal_block_tables(I.rng_for(66, 0), p + n, ps, g.num_pages)
+    fill, b = make_batch(g, np.zeros_like(p), p, seed=66, bt=bt), make_batch(g, p, n, seed=66, bt=bt, stream=2)
+    cache, df, db = make_cache(g), DevBatch(fill), DevBatch(b)
+    df.v_new[1, 0, 3] = float("nan")
+    gpu_append(cache, df)
+    gpu_append(cache, db)
+
+    def shortest(call):
+        call()
+        times = []
+        for _ in range(3):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            call()
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end))
+        return min(times)
+
+    ws = torch.empty(B.ag_attn_decode_workspace_bytes(8, 32, d, db.max_ctx) // 4, dtype=torch.float32, device="cuda")
+    last = torch.arange(8, device="cuda") * 120 + 119
+    q, q1 = db.q, db.q[last].contiguous()
+    out, out1 = torch.empty_like(q), torch.empty_like(q1)
+    for q_, o_, q1_, o1_ in ((q, out, q1, out1), (off_16_bytes(q), off_16_bytes(out), off_16_bytes(q1), off_16_bytes(out1))):
+        t = (shortest(lambda: B.ag_attn_resume(cache, q_, o_, db.bt, db.prefix, db.new, db.cu, db.total, db.max_new, db.max_ctx, 32, g.scale)),
+             shortest(lambda: B.ag_attn_decode(cache, q1_, o1_, db.bt, db.ctx, db.max_ctx, 32, g.scale, ws)))
+        if q_ is q:
+            mended = t
+    assert mended[0] <= t[0] and mended[1] <= t[1], (mended, t)
