@@ -399,15 +399,19 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
     if (all) general::attend_rows_again<E, 2, (DT + 63) / 64>(a, all & (0x0101u << w), (int64_t)s * hq + (int64_t)g * G + h0 + r, ctx - 1, s, g, &s_o[w][0][0]);
 }
 
+// Four channels a lane; a row's lanes lie in one wave, so that a row taken again below is this wave's alone.
+__host__ __device__ inline int merge_rows_of_wave(int d) { return 64 / (d >> 2); }
+
 template <typename E>
 __global__ __launch_bounds__(256) void decode_any_merge_kernel(AttnArgs a, const int32_t* __restrict__ hdr,
                                                                const float* __restrict__ ws_o,
                                                                const float* __restrict__ ws_ml, int pmax, int head_blocks)
 {
-    const int D = a.c.d, quads = D >> 2;        // lanes of a row
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x, row = idx / quads;      // s * hq + h
-    const int s = (int)(row / a.hq), h = (int)(row - (int64_t)s * a.hq), d = (int)(idx - row * quads) * 4;
-    const int ctx = row < (int64_t)a.batch * a.hq ? max(a.ctx_lens[s], 0) : -1;      // -1: no row
+    const int D = a.c.d, quads = D >> 2, per_wave = merge_rows_of_wave(D), lane = threadIdx.x & 63;
+    const int mine = lane / quads;              // row of the wave; lanes behind the last one have none
+    const int64_t row = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * per_wave + mine;        // s * hq + h
+    const int s = (int)(row / a.hq), h = (int)(row - (int64_t)s * a.hq), d = (lane - mine * quads) * 4;
+    const int ctx = mine < per_wave && row < (int64_t)a.batch * a.hq ? max(a.ctx_lens[s], 0) : -1;      // -1: no row
     E* out = (E*)a.out + row * D;
     float trouble = 0.f;
     if (ctx == 0) {
@@ -425,7 +429,7 @@ __global__ __launch_bounds__(256) void decode_any_merge_kernel(AttnArgs a, const
     // (weights in terms, and partials taken with a weight of zero, turn an infinite sum into NaN)
     __shared__ float s_q[4][256];
     uint64_t again = __builtin_amdgcn_ballot_w64(!(trouble == 0.f));
-    while (again) {                             // one row at a time: other waves that hold a part of it write the same
+    while (again) {                             // one row at a time
         const int l = __builtin_ctzll(again), r = __builtin_amdgcn_readlane((int)row, l), rs = __builtin_amdgcn_readlane(s, l);
         general::attend_rows_again<E, 1, 4>(a, 1ull << l, row, ctx - 1, rs, (r - rs * a.hq) / (a.hq / a.c.hkv), s_q[threadIdx.x >> 6]);
         again &= ~__builtin_amdgcn_ballot_w64((int)row == r);
@@ -463,7 +467,8 @@ ag_status launch(const AttnArgs& a, hipStream_t st)
         ag_status e = hip_check(hipGetLastError(), "decode split launch");
         if (e) return e;
     }
-    hipLaunchKernelGGL(decode_any_merge_kernel<E>, dim3((unsigned)(((int64_t)a.batch * a.hq * (a.c.d / 4) + 255) / 256)), dim3(256), 0, st, a, hdr, ws_o, ws_ml, pmax, blocks);
+    const int merge_rows = 4 * merge_rows_of_wave(a.c.d);
+    hipLaunchKernelGGL(decode_any_merge_kernel<E>, dim3((unsigned)(((int64_t)a.batch * a.hq + merge_rows - 1) / merge_rows)), dim3(256), 0, st, a, hdr, ws_o, ws_ml, pmax, blocks);
     prof_after(st);
     return hip_check(hipGetLastError(), "decode merge launch");
 }
