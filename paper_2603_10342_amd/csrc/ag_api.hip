@@ -27,6 +27,18 @@ ag_status hip_check(hipError_t e, const char* what)
     return AG_ERR_HIP;
 }
 
+ag_status allow_dynamic_lds(const void* kernel, int bytes, std::atomic<uint64_t>& devices)
+{
+    int dev = 0;
+    ag_status st = hip_check(hipGetDevice(&dev), "hipGetDevice");
+    if (st) return st;
+    const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;         // (devices beyond the table are told every time)
+    if (devices.load() & bit) return AG_OK;
+    if ((st = hip_check(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes), "hipFuncSetAttribute"))) return st;
+    devices.fetch_or(bit);
+    return AG_OK;
+}
+
 struct Prof {
     bool on = false;
     int cap = 0, n = 0;

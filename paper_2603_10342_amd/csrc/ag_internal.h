@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "ag.h"
 
 namespace ag {
@@ -49,6 +51,10 @@ struct AttnArgs {
 
 void set_error(const char* fmt, ...);
 ag_status hip_check(hipError_t e, const char* what);
+
+// Lets `kernel` be launched on the current device with `bytes` of dynamic LDS, more than the 64 KiB a kernel may use
+// without being told so.  The attribute belongs to a device: `devices` keeps the ones it has been set on.
+ag_status allow_dynamic_lds(const void* kernel, int bytes, std::atomic<uint64_t>& devices);
 
 // Event bracket around a main-kernel launch; no-ops unless ag_prof_enable() is active on this thread.
 void prof_before(hipStream_t st);

@@ -494,14 +494,11 @@ static bool takes_direct(const AttnArgs& a, hipStream_t st)
 template <bool kStep>
 static ag_status launch_direct(const AttnArgs& a, const StepArgs& sa, hipStream_t st)
 {
-    static std::atomic<bool> attr_set{false};
+    static std::atomic<uint64_t> told{0};
     const size_t lds = direct_lds(a.hq / a.c.hkv);
-    if (lds > 64 * 1024 && !attr_set.load()) {      // (groups of 8 heads and more) beyond what a kernel may use without being told so
-        ag_status e = hip_check(hipFuncSetAttribute((const void*)decode_direct_kernel<kStep>,
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)direct_lds(16)),
-                                "hipFuncSetAttribute(decode direct)");
+    if (lds > 64 * 1024) {                          // (groups of 8 heads and more)
+        ag_status e = allow_dynamic_lds((const void*)decode_direct_kernel<kStep>, (int)direct_lds(16), told);
         if (e) return e;
-        attr_set.store(true);
     }
     prof_before(st);
     hipLaunchKernelGGL(decode_direct_kernel<kStep>, dim3(a.batch * a.c.hkv), dim3(64 * kDirectWaves), lds, st, a, sa);

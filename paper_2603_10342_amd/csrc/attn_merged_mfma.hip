@@ -653,15 +653,10 @@ ag_status launch_split(int n_wgs, hipStream_t st, const AttnArgs& a, int32_t* hd
                        float* ws_ml, int pmax, int tq, int rk, int rw, float steps_per_us)
 {
     constexpr int lds = kRows ? kRowsLds : kSmemBytes;
-    if constexpr (kRows) {                  // more dynamic LDS than a kernel may use without being told so
-        static std::atomic<bool> attr_set{false};
-        if (!attr_set.load()) {
-            ag_status e = hip_check(hipFuncSetAttribute((const void*)merged_split_kernel<kRows>,
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds),
-                                    "hipFuncSetAttribute(merged split)");
-            if (e) return e;
-            attr_set.store(true);
-        }
+    if constexpr (kRows) {
+        static std::atomic<uint64_t> told{0};
+        ag_status e = allow_dynamic_lds((const void*)merged_split_kernel<kRows>, lds, told);
+        if (e) return e;
     }
     hipLaunchKernelGGL((merged_split_kernel<kRows>), dim3((unsigned)n_wgs), dim3(256), lds, st, a, hdr, row_info, ws_o,
                        ws_ml, pmax, tq, rk, rw, steps_per_us);

@@ -326,15 +326,10 @@ template <typename E, int DT, bool kExact>
 ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 {
     constexpr int lds = 512 * DT;
-    if constexpr (lds > 64 * 1024) {                // more dynamic LDS than a kernel may use without being told so
-        static std::atomic<bool> attr_set{false};
-        if (!attr_set.load()) {
-            ag_status e = hip_check(hipFuncSetAttribute((const void*)prefill_any_kernel<E, DT, kExact>,
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds),
-                                    "hipFuncSetAttribute(prefill)");
-            if (e) return e;
-            attr_set.store(true);
-        }
+    if constexpr (lds > 64 * 1024) {
+        static std::atomic<uint64_t> told{0};
+        ag_status e = allow_dynamic_lds((const void*)prefill_any_kernel<E, DT, kExact>, lds, told);
+        if (e) return e;
     }
     const int64_t tiles_max = tiles_bound(a), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
     prof_before(st);

@@ -427,12 +427,10 @@ template <int DT>
 ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 {
     constexpr int lds = lds_bytes(DT);
-    static std::atomic<bool> attr_set{false};
-    if (lds > 64 * 1024 && !attr_set.load()) {      // more dynamic LDS than a kernel may use without being told so
-        ag_status e = hip_check(hipFuncSetAttribute((const void*)prefill_f32_kernel<DT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds),
-                                "hipFuncSetAttribute(prefill)");
+    if constexpr (lds > 64 * 1024) {
+        static std::atomic<uint64_t> told{0};
+        ag_status e = allow_dynamic_lds((const void*)prefill_f32_kernel<DT>, lds, told);
         if (e) return e;
-        attr_set.store(true);
     }
     const int64_t tiles_max = tiles_bound(a), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
     prof_before(st);

@@ -368,13 +368,10 @@ template <int NW, int DT, bool kLo, bool kPage16>
 static ag_status launch_prefill_nw(const AttnArgs& a, hipStream_t st)
 {
     constexpr int lds = lds_bytes(NW, DT);
-    static std::atomic<bool> attr_set{false};
-    if (lds > 64 * 1024 && !attr_set.load()) {
-        ag_status e = hip_check(hipFuncSetAttribute((const void*)prefill_mfma_kernel<NW, DT, kLo, kPage16>,
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, lds),
-                                "hipFuncSetAttribute(prefill)");
+    if constexpr (lds > 64 * 1024) {
+        static std::atomic<uint64_t> told{0};
+        ag_status e = allow_dynamic_lds((const void*)prefill_mfma_kernel<NW, DT, kLo, kPage16>, lds, told);
         if (e) return e;
-        attr_set.store(true);
     }
     const int64_t tiles_max = tiles_bound(a, 32 * NW), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
     if (per_xcd * 8 > 0x7fffffff) { set_error("too many query tiles for one launch"); return AG_ERR_INVALID_ARG; }

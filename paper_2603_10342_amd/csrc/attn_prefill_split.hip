@@ -314,14 +314,9 @@ int64_t tiles_bound(const AttnArgs& a, int columns)
 template <typename E, int DT, bool kLo>
 ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 {
-    static std::atomic<bool> attr_set{false};
-    if (!attr_set.load()) {
-        ag_status e = hip_check(hipFuncSetAttribute((const void*)prefill_split_kernel<E, DT, kLo>,
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(DT)),
-                                "hipFuncSetAttribute(prefill split)");
-        if (e) return e;
-        attr_set.store(true);
-    }
+    static std::atomic<uint64_t> told{0};
+    ag_status e = allow_dynamic_lds((const void*)prefill_split_kernel<E, DT, kLo>, lds_bytes(DT), told);
+    if (e) return e;
     const int64_t tiles_max = tiles_bound(a, kColumns), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
     prof_before(st);
     hipLaunchKernelGGL((prefill_split_kernel<E, DT, kLo>), dim3((unsigned)(per_xcd * 8)), dim3(64 * kWaves), lds_bytes(DT), st, a,

@@ -25,6 +25,7 @@ typedef enum { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorNotReady = 600 
 typedef enum { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost = 2 } hipMemcpyKind;
 typedef enum { hipDeviceAttributeNumberOfXccs = 1, hipDeviceAttributeMultiprocessorCount = 2 } hipDeviceAttribute_t;
 enum { hipEventDisableTiming = 2 };
+typedef enum { hipFuncAttributeMaxDynamicSharedMemorySize = 8 } hipFuncAttribute;
 
 struct fake_stream { uint64_t enqueued = 0, done = 0; std::vector<uint32_t> mask; bool alive = true; };
 struct fake_event { fake_stream* stream = nullptr; uint64_t ticket = 0; bool recorded = false; bool alive = true; };
@@ -45,6 +46,8 @@ struct Runtime {
     std::vector<Wait> stream_waits;                      // every hipStreamWaitEvent, in order
     std::vector<hipEvent_t> host_waits;                  // every hipEventSynchronize, in order
     int live_events = 0, live_streams = 0;
+    struct Attribute { int device; const void* kernel; int value; };
+    std::vector<Attribute> attributes;                   // every hipFuncSetAttribute, in order
     ~Runtime()                                           // destroyed objects are kept until here, so that a use
     {                                                    // after destroy is an error code, not a dangling pointer
         for (fake_stream* s : streams) delete s;
@@ -52,6 +55,7 @@ struct Runtime {
     }
 };
 inline Runtime& rt() { static Runtime r; return r; }
+inline int& current_device() { static thread_local int d = 0; return d; }
 inline fake_stream* real(hipStream_t s) { return s ? s : &rt().null_stream; }
 // the stream's work up to now has finished
 inline void finish(hipStream_t s) { std::lock_guard<std::recursive_mutex> lk(rt().mu); real(s)->done = real(s)->enqueued; }
@@ -61,7 +65,14 @@ inline void reset_logs() { std::lock_guard<std::recursive_mutex> lk(rt().mu); rt
 
 inline const char* hipGetErrorString(hipError_t e) { return e == hipSuccess ? "hipSuccess" : e == hipErrorNotReady ? "hipErrorNotReady" : "hipErrorInvalidValue"; }
 inline hipError_t hipGetLastError() { return hipSuccess; }
-inline hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+inline hipError_t hipGetDevice(int* d) { *d = fakehip::current_device(); return hipSuccess; }
+inline hipError_t hipSetDevice(int d) { fakehip::current_device() = d; return hipSuccess; }
+inline hipError_t hipFuncSetAttribute(const void* kernel, hipFuncAttribute, int value)
+{
+    std::lock_guard<std::recursive_mutex> lk(fakehip::rt().mu);
+    fakehip::rt().attributes.push_back({fakehip::current_device(), kernel, value});
+    return kernel ? hipSuccess : hipErrorInvalidValue;
+}
 inline hipError_t hipGetDeviceProperties(hipDeviceProp_t* p, int) { memset(p, 0, sizeof(*p)); p->multiProcessorCount = 256; p->warpSize = 64; strcpy(p->gcnArchName, "gfx950:hostbuild"); return hipSuccess; }
 inline hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) { *v = a == hipDeviceAttributeNumberOfXccs ? 8 : 256; return hipSuccess; }
 inline hipError_t hipMemcpy(void* dst, const void* src, size_t n, hipMemcpyKind) { memcpy(dst, src, n); return hipSuccess; }

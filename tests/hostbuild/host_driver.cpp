@@ -341,12 +341,49 @@ static void test_pager_threads()
     CHECK(ag_pager_destroy(p) == AG_OK);
 }
 
+// ---- 5. kernels with more dynamic LDS than 64 KiB are announced on every device they run on ------------
+static void test_lds_limit_per_device()
+{
+    auto& log = fakehip::rt().attributes;
+    log.clear();
+    static int kernel_a, kernel_b;
+    std::atomic<uint64_t> told_a{0}, told_b{0};
+    for (int round = 0; round < 2; ++round)
+        for (int dev : {0, 1, 7}) {
+            CHECK(hipSetDevice(dev) == hipSuccess);
+            CHECK(ag::allow_dynamic_lds(&kernel_a, 81920, told_a) == AG_OK);
+        }
+    CHECK(log.size() == 3);                               // once per device, not once per process
+    for (size_t i = 0; i < 3; ++i) CHECK(log[i].kernel == &kernel_a && log[i].value == 81920);
+    CHECK(log[0].device == 0 && log[1].device == 1 && log[2].device == 7);
+    CHECK(ag::allow_dynamic_lds(&kernel_b, 133120, told_b) == AG_OK && log.size() == 4 && log[3].kernel == &kernel_b);
+    // a refusal is reported and not remembered as done
+    std::atomic<uint64_t> told_none{0};
+    CHECK(ag::allow_dynamic_lds(nullptr, 1, told_none) == AG_ERR_HIP && ag::allow_dynamic_lds(nullptr, 1, told_none) == AG_ERR_HIP);
+    CHECK(told_none.load() == 0 && log.size() == 6);
+    // a device beyond the table is told every time
+    CHECK(hipSetDevice(64) == hipSuccess);
+    CHECK(ag::allow_dynamic_lds(&kernel_a, 81920, told_a) == AG_OK && ag::allow_dynamic_lds(&kernel_a, 81920, told_a) == AG_OK);
+    CHECK(log.size() == 8);
+    CHECK(hipSetDevice(0) == hipSuccess);
+    std::atomic<uint64_t> told_t{0};
+    std::vector<std::thread> th;
+    for (int t = 0; t < 4; ++t)
+        th.emplace_back([&, t] {
+            CHECK(hipSetDevice(t) == hipSuccess);
+            for (int k = 0; k < 100; ++k) CHECK(ag::allow_dynamic_lds(&kernel_a, 81920, told_t) == AG_OK);
+        });
+    for (auto& t : th) t.join();
+    CHECK(told_t.load() == 0xF && log.size() == 12);
+}
+
 int main()
 {
     test_validation();
     test_sched();
     test_pager_ordering();
     test_pager_threads();
+    test_lds_limit_per_device();
     printf("host driver ok\n");
     return 0;
 }
