@@ -13,9 +13,12 @@
 //     group's keys and values sit in the page as in a 16-token page, only with a larger chunk stride for K.
 //   - Two sub-steps of loads are in flight per wave where a sub-step is 16 KiB or less (head_dim 64 and 128):
 //     with half the bytes per token, one in flight does not cover the latency.
+//   - At 256 channels a sub-step's operands and O^T fill the registers: the fp32 split kernel spills 11, outside its step
+//     loop; the dimensions between 128 and 256, which run as 256 with bounds, spill 44 (bf16: 26), 13 (5) of them read back
+//     in every step.
 // Whole decode step, append included (one wave per (row, query head) before -> now): 16 fp32 sessions of 1024..4096
 // tokens at 32 / 8 heads x 128, 2760 -> 75 us (369 MB, 4.9 TB/s; split kernel 66 us); 48 bf16 sessions of 700..5000 at
-// head_dim 64, 32-token pages, 2238 -> 65 us (333 MB, 5.2 TB/s); two fp32 sessions of 300, 4 / 2 heads x 64, 106 -> 12 us.
+// head_dim 64, 32-token pages, 2238 -> 63.5 us (333 MB, 5.2 TB/s; 62.8 with weights in two terms); two fp32 sessions of 300, 4 / 2 heads x 64, 106 -> 12 us.
 // head_dim below its template's DT: loads beyond head_dim repeat its last channels; keys become zeros (as the query
 // does), values land in rows that are not stored.
 #include "attn_general_row.h"

@@ -1,5 +1,5 @@
-// One (row, query head) of paged attention by one wave, in fp32 arithmetic: the general kernel's work, and what kernels for
-// the same shapes fall back on where their result is not finite.  Internal.
+// One (row, query head) of paged attention by one wave, in fp32 arithmetic: the general kernel's work; and the same for
+// several rows at once, which kernels for the same shapes fall back on where their result is not finite.  Internal.
 #pragma once
 
 #include "ag_internal.h"

@@ -19,9 +19,10 @@
 // the layouts of the bf16 kernels, [chunk of 8 channels][key][8] and [chunk of 8 keys][channel][8], two stages.
 // Weights are split in registers.  What bounds it is matrix and vector work one after the other: 96 products of 32 clocks a
 // tile and wave at 128 channels against 128 of 64, and about as much in softmax, splitting and operand reads.
-// Measured, append included, 32 / 8 heads, fp32 products -> terms: four prompts of 300..1500 rows, 128 channels 377 -> 296
-// us (120 TFLOP/s of result), 64 channels 208 -> 139; eight of 2048, 2430 -> 1828; eight chunks of 40..500 on 500..4000
-// tokens 811 -> 638; 32 of 10..60, 235 -> 193.  Scores in three accumulators and value products grouped by term: 3..5 % slower.
+// Measured, append included, 32 / 8 heads, fp32 products -> terms: four prompts of 300..1500 rows, 128 channels 384 -> 306
+// us (117 TFLOP/s of result), 64 channels 208 -> 142; eight of 2048, 2510 -> 1848; eight chunks of 40..500 on 500..4000
+// tokens 1020 -> 680; 32 of 10..60 on 1000, 309 -> 231.  Scores in three accumulators and value products grouped by term:
+// 3..5 % slower.  The watch on small numbers is 0.4..1.6 % of it, all in the epilogue.
 #include <algorithm>
 #include <atomic>
 

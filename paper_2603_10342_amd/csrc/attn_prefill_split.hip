@@ -333,9 +333,9 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 // Measured at 32 / 8 heads on 256 CUs, append included, the other kernel -> this one: bf16 / 128 / 16, one chunk of
 // 5 rows on 6007 tokens (8 workgroups) 114 -> 39 us, 211 rows (216) 119 -> 45, 400 rows (400) 122 -> 80; four chunks of
 // 150 rows on 3000 (608) 70 -> 70, eight of 100 on 2000 (832) 57 -> 71.  bf16 / 64 / 64: eight of 40 on 2000 (320) 49 ->
-// 30, 32 of 20 on 1000 (768) 31 -> 31, two prompts of 1000 (2000) 41 -> 50.  fp32 / 128: one chunk of 211 rows on 6000
-// (216) 604 -> 225, one prompt of 600 (600) 71 -> 54, twelve chunks of 10..100 rows on 1000..3000 (700) 299 -> 243; three of
-// 300 on 5000 (912) 528 -> 743, two prompts of 1000 (2000) 137 -> 210.
+// 32, 32 of 20 on 1000 (768) 32 -> 32, eight of 100 on 2000 (832) 55 -> 58, two prompts of 1000 (2000) 48 -> 54.  fp32 / 128:
+// one chunk of 211 rows on 6000 (216) 589 -> 233, one prompt of 600 (600) 73 -> 57, twelve chunks of 10..100 rows on
+// 1000..3000 (700) 295 -> 249; three of 300 on 5000 (912) 513 -> 762, two prompts of 1000 (2000) 139 -> 215.
 bool prefill_split_preferred(const AttnArgs& a, bool rounded, hipStream_t st)
 {
     if ((a.c.d != 64 && a.c.d != 128) || a.c.ps < 16 || (int64_t)a.total_rows * (a.hq / a.c.hkv) > 0x7fffffff ||

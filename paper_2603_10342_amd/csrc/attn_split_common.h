@@ -1,5 +1,6 @@
-// Pieces shared by the two split-K kernels over a paged KV cache (bf16, head_dim 128, page 16): the decode
-// step and the merged decode + short-resume batch.  Internal; nothing here is part of the ABI.
+// Pieces shared by the kernels that deal a batch's contexts in equal shares and merge partials: the decode step and
+// the merged decode + short-resume batch (bf16, head_dim 128, page 16: D and PS below), and the decode step of every other
+// geometry (attn_decode_any.hip), which takes the plan, the merge and the choice rules.  Internal; not part of the ABI.
 #pragma once
 
 #include "ag_internal.h"
@@ -42,9 +43,7 @@ struct StepRegs {       // one wave's K and V operands for 32 tokens (two pages)
 };
 
 
-// The partials (m, l, O[D]) of one (row, head) lie at slots base .. base + n - 1 (n >= 1, the first of them with a
-// finite m); combine them in slot order - reproducible - four at a time, so that a group's loads are in flight
-// together instead of one dependent round trip per partial.
+// Partials that another workgroup of the same launch reads go past this XCD's caches.
 __device__ __forceinline__ float load_coherent(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void store_coherent(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
@@ -52,7 +51,9 @@ __device__ __forceinline__ void store_coherent(float* p, float v) { __hip_atomic
 template <bool kNatural>
 __device__ __forceinline__ float merge_power(float x) { return kNatural ? expf(x) : exp2f(x); }
 
-// The combination itself, for N neighbouring channels of a pair: load(i, m, l, o) fetches partial i < n.
+// The partials (m, l, O) of one (row, head), n >= 1 of them: combined in slot order - reproducible - four at a time, so that
+// a group's loads are in flight together instead of one dependent round trip per partial.  For N neighbouring channels;
+// load(i, m, l, o) fetches partial i < n.
 template <int N, bool kNatural, class Load>
 __device__ __forceinline__ void merge_channels(int n, Load load, float (&out)[N])
 {
