@@ -8,12 +8,14 @@
 //   V page  [slot/8'][D][8]: transposed in chunks of 8 keys, see v_offset()
 // HBM-bound: 2 * T * 2*Hkv*D*sizeof bytes (read + write).  Two kernels:
 //   kv_append_groups_kernel pages of 16 tokens or more: one workgroup per (touched 16-token group, KV head), rows staged in LDS
-//   kv_append_kernel        smaller pages: one workgroup of 256 threads takes 16 consecutive rows of the
-//                           token-major input and one KV head; 16 neighbouring lanes hold 16 consecutive
-//                           tokens of one chunk of D, so each store instruction writes runs of neighbouring slots.
+//   kv_append_kernel        smaller pages, and many sessions of a few rows: one workgroup of 256 threads takes 16
+//                           consecutive rows of the token-major input and one KV head; 16 neighbouring lanes hold 16
+//                           consecutive tokens of one chunk of D, so each store instruction writes runs of
+//                           neighbouring slots.
 #include <algorithm>
 
 #include "ag_internal.h"
+#include "find_session.h"
 
 namespace ag {
 
@@ -30,6 +32,7 @@ __global__ __launch_bounds__(256) void kv_append_kernel(E* __restrict__ k_pool, 
                                                         const E* __restrict__ k_new, const E* __restrict__ v_new,
                                                         const int32_t* __restrict__ bt, int max_pages,
                                                         const int32_t* __restrict__ prefix_lens,
+                                                        const int32_t* __restrict__ new_lens,
                                                         const int32_t* __restrict__ cu_new, int batch, int total_new,
                                                         int hkv, int d, int ps, int ps_shift)
 {
@@ -51,10 +54,12 @@ __global__ __launch_bounds__(256) void kv_append_kernel(E* __restrict__ k_pool, 
                 const int mid = (lo + hi) >> 1;
                 if (cu_new[mid] <= t) lo = mid; else hi = mid;
             }
-            const int s = lo;
-            const int pos = prefix_lens[s] + (t - cu_new[s]);
-            page = bt[(int64_t)s * max_pages + (pos >> ps_shift)];
-            slot = pos & (ps - 1);
+            const int s = lo, i = t - cu_new[s];
+            const int pos = prefix_lens[s] + i;
+            if (i < new_lens[s]) {                  // total_new may be a bound: a row of nobody's past the last session's
+                page = bt[(int64_t)s * max_pages + (pos >> ps_shift)];
+                slot = pos & (ps - 1);
+            }
         }
         s_page[tid] = page;
         s_slot[tid] = slot;
@@ -88,11 +93,9 @@ __global__ __launch_bounds__(256) void kv_append_kernel(E* __restrict__ k_pool, 
 // in a prefill - as whole 8-key chunks, 2 KiB contiguous per wave.  A partly filled group (the first and last
 // of an appended range, or a decode step's single token) writes V element by element so that slots that
 // already hold older tokens are not touched.
-// Items are numbered session-major; every wave finds the workgroup's (session, group) itself by scanning the
-// per-session group counts, 64 sessions at a time, with the row offsets fetched along: the rows, and the page id,
-// are requested one memory round trip after the kernel starts, which is what bounds an append of few tokens (one
-// token for each of 64 sessions, back to back in a graph: 3.09 us, 3.41 with a scan by one wave whose answers the
-// others read through LDS and memory; for each of 300 sessions 8.1, before 10.3; 32768 tokens 43.7 us, 6.1 TB/s).
+// Items are numbered session-major; every wave finds the workgroup's session itself (find_session()), its lengths fetched
+// along: the rows, and the page id, are requested one memory round trip after the kernel starts for up to 64 sessions, which
+// is what bounds an append of few tokens.
 template <typename E>
 __global__ __launch_bounds__(256) void kv_append_groups_kernel(E* __restrict__ k_pool, E* __restrict__ v_pool,
                                                                const E* __restrict__ k_new, const E* __restrict__ v_new,
@@ -108,36 +111,15 @@ __global__ __launch_bounds__(256) void kv_append_groups_kernel(E* __restrict__ k
     C8* lds_k = reinterpret_cast<C8*>(smem);                       // [16 tokens][d/8]
     C8* lds_v = lds_k + kGroup * (d >> 3);
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int item = blockIdx.x, h = blockIdx.y;
+    const int tid = threadIdx.x, item = blockIdx.x, h = blockIdx.y;
     const int chunks = d >> 3;
 
-    int s = -1, pos0 = 0, n_tok = 0, row0 = 0;                      // uniform: session, first position, token count, first row
-    for (int base = 0, acc = 0; base < batch && s < 0; base += 64) {
-        const int ss = base + lane;
-        int p = 0, n = 0, cu = 0;
-        if (ss < batch) { p = prefix_lens[ss]; n = new_lens[ss]; cu = cu_new[ss]; }
-        const int groups = n > 0 ? ((p + n - 1) >> 4) - (p >> 4) + 1 : 0;
-        int scan = groups;                                           // inclusive scan over the 64 lanes
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int up = __shfl_up(scan, o);
-            if (lane >= o) scan += up;
-        }
-        const uint64_t hit = __builtin_amdgcn_ballot_w64(acc + scan > item);
-        if (hit) {
-            const int l = __builtin_ctzll(hit);                      // first session whose groups reach the item
-            const int before = acc + __builtin_amdgcn_readlane(scan, l) - __builtin_amdgcn_readlane(groups, l);
-            const int pl = __builtin_amdgcn_readlane(p, l), nl = __builtin_amdgcn_readlane(n, l);
-            const int grp = (pl >> 4) + (item - before);
-            s = base + l;
-            pos0 = max(pl, grp << 4);
-            n_tok = min(pl + nl, (grp + 1) << 4) - pos0;
-            row0 = __builtin_amdgcn_readlane(cu, l) + (pos0 - pl);
-        }
-        acc += __builtin_amdgcn_readlane(scan, 63);
-    }
-    if (s < 0) return;                                               // beyond the last touched group
+    // a session has at most as many groups as tokens, and at most N / 16 + 2: both summed over the sessions before
+    const Session f = find_session(new_lens, prefix_lens, cu_new, batch, item, [](int ss, int cu) { return min(cu, (cu >> 4) + 2 * ss); });
+    const int s = f.s, last_pos = f.prefix + f.new_len - 1, grp = (f.prefix >> 4) + (item - f.first);
+    if (f.new_len <= 0 || grp > last_pos >> 4) return;               // nobody's item
+    const int pos0 = max(f.prefix, grp << 4), n_tok = min(last_pos, (grp << 4) + 15) - pos0 + 1;     // uniform
+    const int row0 = f.row0 + (pos0 - f.prefix);
     const int64_t page = bt[(int64_t)s * max_pages + (pos0 >> ps_shift)];
     const int slot0 = pos0 & (ps - 1);                               // in the page
 
@@ -196,12 +178,19 @@ ag_status launch_kv_append(const CacheView& c, const void* k_new, const void* v_
                            const int32_t* prefix_lens, const int32_t* new_lens, const int32_t* cu_new, int batch,
                            int total_new, hipStream_t st)
 {
-    if (c.ps >= 16) {
-        // every session touches at most N_s / 16 + 2 groups, and every group has a token
-        const int64_t items = std::min<int64_t>(total_new / 16 + 2 * (int64_t)batch, total_new);
-        if (items > 0x7fffffff || c.hkv > 65535) { set_error("append too large for one launch"); return AG_ERR_INVALID_ARG; }
+    // every session touches at most N_s / 16 + 2 groups, and every group has a token
+    const int64_t items = std::min<int64_t>(total_new / 16 + 2 * (int64_t)batch, total_new);
+    if (c.ps >= 16 && (items > 0x7fffffff || c.hkv > 65535)) { set_error("append too large for one launch"); return AG_ERR_INVALID_ARG; }
+    const size_t row_bytes = (size_t)c.d * (c.dtype == AG_BF16 ? 2 : 4);
+    // More groups than the chip holds at once (256 CUs of eight workgroups), each mostly empty: a workgroup that takes 16 rows of
+    // whatever sessions comes to fewer.  It is the slower one per byte: rows up to 256 bytes, 2 KiB of them a session.  Sessions
+    // x rows each, 8 KV heads, us by groups -> by rows.  128 bytes a row: 100x4 (1800 groups) 4.6 -> 4.9, 300x4 (5400) 7.9 ->
+    // 6.5, 300x15 12.0 -> 12.2, 2048x4 37 -> 22.  256: 300x1 6.4 -> 7.1, 300x2 9.5 -> 8.0, 300x8 12.1 -> 11.9, 300x15 16.1 -> 17.7,
+    // 1000x4 23.7 -> 19.5.  512: 300x2 11.4 -> 12.3, 300x4 12.2 -> 14.9, 1000x1 16.1 -> 19.6.
+    const bool by_rows = items * c.hkv > 2048 && row_bytes <= 256 && (int64_t)total_new * (int64_t)row_bytes <= 2048 * (int64_t)batch;
+    if (c.ps >= 16 && !by_rows) {
         const dim3 grid((unsigned)items, c.hkv);
-        const size_t lds = 2 * 16 * (size_t)c.d * (c.dtype == AG_BF16 ? 2 : 4);
+        const size_t lds = 2 * 16 * row_bytes;
         if (c.dtype == AG_BF16)
             hipLaunchKernelGGL(kv_append_groups_kernel<uint16_t>, grid, dim3(256), lds, st, (uint16_t*)c.k, (uint16_t*)c.v,
                                (const uint16_t*)k_new, (const uint16_t*)v_new, bt, max_pages, prefix_lens, new_lens,
@@ -215,11 +204,11 @@ ag_status launch_kv_append(const CacheView& c, const void* k_new, const void* v_
     const dim3 grid((total_new + kTok - 1) / kTok, c.hkv);
     if (c.dtype == AG_BF16) {
         hipLaunchKernelGGL(kv_append_kernel<uint16_t>, grid, dim3(256), 0, st, (uint16_t*)c.k, (uint16_t*)c.v,
-                           (const uint16_t*)k_new, (const uint16_t*)v_new, bt, max_pages, prefix_lens, cu_new, batch,
+                           (const uint16_t*)k_new, (const uint16_t*)v_new, bt, max_pages, prefix_lens, new_lens, cu_new, batch,
                            total_new, c.hkv, c.d, c.ps, c.ps_shift);
     } else {
         hipLaunchKernelGGL(kv_append_kernel<uint32_t>, grid, dim3(256), 0, st, (uint32_t*)c.k, (uint32_t*)c.v,
-                           (const uint32_t*)k_new, (const uint32_t*)v_new, bt, max_pages, prefix_lens, cu_new, batch,
+                           (const uint32_t*)k_new, (const uint32_t*)v_new, bt, max_pages, prefix_lens, new_lens, cu_new, batch,
                            total_new, c.hkv, c.d, c.ps, c.ps_shift);
     }
     return hip_check(hipGetLastError(), "kv_append launch");
