@@ -92,7 +92,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, in
     // an XCD most of a microsecond, whether it has work or not.
     const int g = (int)(wk / (unsigned)tiles_max);
     int s = -1, qt = 0, N = 0, P = 0, row0 = 0;
-    find_tile(a, (int)(wk - (unsigned)g * (unsigned)tiles_max), [G](int len) { return (int)(((int64_t)len * G + kCols - 1) / kCols); }, s, qt, N, P, row0);
+    find_tile<kCols>(a, (int)(wk - (unsigned)g * (unsigned)tiles_max), G, s, qt, N, P, row0);
     if (s < 0) return;                              // beyond the batch's tiles
     const int ctx = P + N;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
     const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv, ps = a.c.ps;
     const int g = (int)(wk / (unsigned)tiles_max);
     int s = -1, qt = 0, N = 0, P = 0, row0 = 0;
-    find_tile(a, (int)(wk - (unsigned)g * (unsigned)tiles_max), [G](int len) { return (int)(((int64_t)len * G + kColumns - 1) / kColumns); }, s, qt, N, P, row0);
+    find_tile<kColumns>(a, (int)(wk - (unsigned)g * (unsigned)tiles_max), G, s, qt, N, P, row0);
     if (s < 0) return;                              // beyond the batch's tiles
     const int ctx = P + N;
     const int col0 = qt * kColumns, cols = min(N * G - col0, kColumns);

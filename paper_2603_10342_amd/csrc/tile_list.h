@@ -2,72 +2,70 @@
 #pragma once
 
 #include "ag_internal.h"
+#include "find_session.h"
 
 namespace ag {
 
-// Every wave scans the batch's lengths for itself (lane l of a pass holds session 64 * pass + l); tiles_of(len) is the
-// number of tiles a chunk of len rows is cut into.  s stays -1 when j lies beyond the batch's tiles; otherwise s, its
-// tile qt (the session's tiles count down: longest context first), its lengths N and P and its first row row0.
-template <class TilesOf>
-__device__ __forceinline__ void find_tile(const AttnArgs& a, int j, TilesOf tiles_of, int& s, int& qt, int& N, int& P, int& row0)
+// Tiles of C columns, G columns a row.  s stays -1 when tile j is nobody's; otherwise s, its tile qt (the session's tiles
+// count down: longest context first), its lengths N and P and its first row row0.
+// Up to 64 sessions: every wave scans the lengths for itself, and the tiles are numbered without gaps.  More: find_session().
+template <int C>
+__device__ __forceinline__ void find_tile(const AttnArgs& a, int j, int G, int& s, int& qt, int& N, int& P, int& row0)
 {
+    auto tiles_of = [G](int len) { return (int)(((int64_t)len * G + C - 1) / C); };
+    if (a.batch > 64) {
+        // the host's two bounds on the tiles of a batch (tiles_bound() in the kernels' files), for the sessions before s
+        const int most = tiles_of(a.max_new);
+        const Session f = find_session(a.new_lens, a.prefix_lens, a.cu_new, a.batch, j, [G, most](int ss, int cu) {
+            return (int)min((int64_t)cu * G / C + ss, (int64_t)ss * most);
+        });
+        const int tiles = tiles_of(f.new_len), k = j - f.first;
+        if (k >= tiles) return;                 // uniform
+        // Put into scalar registers by hand: the compiler does not see that the search is uniform, and what it then keeps per
+        // lane spilled 4 VGPRs in the widened 8-wave kernel of 128 channels (8 chunks of 2048, pages of 32: 524 -> 565 us).
+        s = __builtin_amdgcn_readfirstlane(f.s);
+        N = __builtin_amdgcn_readfirstlane(f.new_len);
+        P = __builtin_amdgcn_readfirstlane(f.prefix);
+        row0 = __builtin_amdgcn_readfirstlane(f.row0);
+        qt = __builtin_amdgcn_readfirstlane(tiles - 1 - k);
+        return;
+    }
+    // the lengths are fetched together with the prefix length and the row offset of every session: whichever session the
+    // tile turns out to belong to, no second round trip follows
     const int ln = threadIdx.x & 63;
-    int before = 0;                             // tiles of the sessions of earlier passes
-    for (int s0 = 0; s0 < a.batch && s < 0; s0 += 256) {
-        // four passes' lengths are fetched together, and with them the prefix length and the row offset of
-        // every session: whichever session the tile turns out to belong to, no second round trip follows
-        int lens[4], pre[4], cu[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int ss = s0 + 64 * k + ln;
-            const bool in = ss < a.batch;
-            lens[k] = in ? a.new_lens[ss] : 0;
-            pre[k] = in && a.prefix_lens ? a.prefix_lens[ss] : 0;
-            cu[k] = in ? a.cu_new[ss] : 0;
+    const bool in = ln < a.batch;
+    int len = in ? a.new_lens[ln] : 0, pre = in && a.prefix_lens ? a.prefix_lens[ln] : 0, cu = in ? a.cu_new[ln] : 0;
+    // The batch is walked longest context first: workgroups start in list order, and a launch ends sooner when the tiles
+    // left for its end are the short ones (each has P + position keys to go through).  Every wave ranks the sessions
+    // itself; equal contexts keep the given order.
+    int sess = ln;                              // the session this lane's entry describes
+    const int key = in ? pre + len : -1;
+    const int key0 = __builtin_amdgcn_readlane(key, 0);
+    if (__builtin_amdgcn_ballot_w64(in && key != key0) != 0) {       // uniform
+        int rank = 0;                           // sessions ahead of this one: longer, or as long and earlier
+        for (int o = 0; o < a.batch; ++o) {
+            const int ko = __builtin_amdgcn_readlane(key, o);
+            rank += (ko > key || (ko == key && o < ln)) ? 1 : 0;
         }
-        // A batch that fits one pass is walked longest context first: workgroups start in list order, and a
-        // launch ends sooner when the tiles left for its end are the short ones (each has P + position keys
-        // to go through).  Every wave ranks the sessions itself; equal contexts keep the given order.
-        int sess = ln;                          // the session this lane's entry describes
-        if (a.batch <= 64) {
-            const int key = ln < a.batch ? pre[0] + lens[0] : -1;
-            const int key0 = __builtin_amdgcn_readlane(key, 0);
-            if (__builtin_amdgcn_ballot_w64(ln < a.batch && key != key0) != 0) {       // uniform
-                int rank = 0;                   // sessions ahead of this one: longer, or as long and earlier
-                for (int o = 0; o < a.batch; ++o) {
-                    const int ko = __builtin_amdgcn_readlane(key, o);
-                    rank += (ko > key || (ko == key && o < ln)) ? 1 : 0;
-                }
-                if (ln >= a.batch) rank = ln;   // entries without a session stay where they are
-                sess = __builtin_amdgcn_ds_permute(rank << 2, sess);
-                lens[0] = __builtin_amdgcn_ds_permute(rank << 2, lens[0]);
-                pre[0] = __builtin_amdgcn_ds_permute(rank << 2, pre[0]);
-                cu[0] = __builtin_amdgcn_ds_permute(rank << 2, cu[0]);
-            }
-        }
+        if (!in) rank = ln;                     // entries without a session stay where they are
+        sess = __builtin_amdgcn_ds_permute(rank << 2, sess);
+        len = __builtin_amdgcn_ds_permute(rank << 2, len);
+        pre = __builtin_amdgcn_ds_permute(rank << 2, pre);
+        cu = __builtin_amdgcn_ds_permute(rank << 2, cu);
+    }
+    int incl = tiles_of(len);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (s >= 0) break;                  // uniform
-            const int len = lens[k];
-            const int cnt = tiles_of(len);
-            int incl = cnt;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int t = __shfl_up(incl, d);
-                if (ln >= d) incl += t;
-            }
-            const int pass_total = __builtin_amdgcn_readlane(incl, 63);
-            if (j < before + pass_total) {      // uniform
-                const unsigned long long hit = __builtin_amdgcn_ballot_w64(j < before + incl);
-                const int l = __builtin_ctzll(hit);              // first session whose tiles reach past j
-                s = s0 + 64 * k + (k == 0 ? __builtin_amdgcn_readlane(sess, l) : l);
-                N = __builtin_amdgcn_readlane(len, l);
-                P = __builtin_amdgcn_readlane(pre[k], l);
-                row0 = __builtin_amdgcn_readlane(cu[k], l);
-                qt = before + __builtin_amdgcn_readlane(incl, l) - 1 - j;   // the session's tiles, longest first
-            }
-            before += pass_total;
-        }
+    for (int d = 1; d < 64; d <<= 1) {
+        const int t = __shfl_up(incl, d);
+        if (ln >= d) incl += t;
+    }
+    if (j < __builtin_amdgcn_readlane(incl, 63)) {                   // uniform
+        const int l = __builtin_ctzll(__builtin_amdgcn_ballot_w64(j < incl));    // first session whose tiles reach past j
+        s = __builtin_amdgcn_readlane(sess, l);
+        N = __builtin_amdgcn_readlane(len, l);
+        P = __builtin_amdgcn_readlane(pre, l);
+        row0 = __builtin_amdgcn_readlane(cu, l);
+        qt = __builtin_amdgcn_readlane(incl, l) - 1 - j;             // the session's tiles, longest first
     }
 }
 
