@@ -118,3 +118,51 @@ def test_the_lookup_of_thousands_of_sessions_costs_less_than_their_rows():
     head) (0.5 of its time measured; 1.4 where every workgroup added the lengths up, 256 sessions at a time)."""
     tiles, row_by_row = resume_times(2048, I.Geometry(16, 1, 64, 16, 2051, I.BF16), 3, 1)
     assert tiles <= 0.9 * row_by_row
+
+
+# rows of a pair times (8 + keys) on both sides of the line between one wave per (row, head) and tiles (80) or shares (48)
+@pytest.mark.parametrize("dtype,d,ps,hq,hkv", [(I.BF16, 64, 32, 4, 4), (I.BF16, 128, 32, 4, 4), (I.F32, 128, 16, 4, 4), (I.BF16, 256, 16, 4, 4)])
+@pytest.mark.parametrize("ctx", [12, 40, 41, 72, 73])
+def test_crowds_at_the_line_to_row_by_row(ctx, dtype, d, ps, hq, hkv):
+    """300 sessions of one row, one of them of one token, one empty."""
+    c = np.full(300, ctx, np.int32)
+    c[[0, 7, 299]] = [1, ctx // 2, 0]
+    g = I.Geometry(hq, hkv, d, ps, table_pages(c, ps), dtype)
+    bt = I.deal_block_tables(I.rng_for(74, 0), np.maximum(c, 1), ps, g.num_pages)
+    n = np.minimum(c, 1).astype(np.int32)
+    fill, last = make_batch(g, np.zeros_like(c), c - n, seed=74, bt=bt), make_batch(g, c - n, n, seed=74, bt=bt, stream=2)
+    cache = make_cache(g)
+    kp, vp = fresh_pools(g)
+    df, dl = DevBatch(fill), DevBatch(last)
+    gpu_append(cache, df)
+    oracle_append(kp, vp, fill)
+    gpu_append(cache, dl)
+    oracle_append(kp, vp, last)
+    ref = oracle_attn(kp, vp, last)
+    check_close(gpu_resume(cache, dl), ref, dtype, f"resume of one row on {ctx}")
+    q = torch.zeros((300, hq, d), dtype=dl.q.dtype, device="cuda")
+    q[torch.from_numpy(np.nonzero(c > 0)[0]).cuda()] = dl.q
+    got = gpu_decode(cache, q, dl.bt, dl.ctx, ctx, g)
+    assert np.all(got[c == 0] == 0)
+    check_close(got[c > 0], ref, dtype, f"decode of {ctx}")
+
+
+def test_chunks_of_a_few_tokens_are_no_slower_than_row_by_row():
+    """2048 sessions of one row on three tokens, 32 / 8 heads (1.0 measured; by tiles 1.7, and 3.4 where every workgroup added the lengths up)."""
+    now, row_by_row = resume_times(2048, I.Geometry(32, 8, 64, 32, 2051, I.BF16), 3, 1)
+    assert now <= 1.3 * row_by_row
+
+
+@pytest.mark.parametrize("ctx", [4])
+def test_decode_of_short_sessions_is_no_slower_than_row_by_row(ctx):
+    """64 sessions (the start of as many conversations) at 32 / 8 heads, by shares of 256 tokens: 2.7 at four tokens (1.0 measured)."""
+    c = np.full(64, ctx, np.int32)
+    g = I.Geometry(32, 8, 64, 32, table_pages(c, 32), I.BF16)
+    bt = I.deal_block_tables(I.rng_for(75, 0), c, 32, g.num_pages)
+    cache, b = make_cache(g), DevBatch(make_batch(g, np.zeros_like(c), c, seed=75, bt=bt))
+    gpu_append(cache, b)
+    ws = torch.empty(B.ag_attn_decode_workspace_bytes(64, 32, 64, ctx) // 4, dtype=torch.float32, device="cuda")
+    q = b.q[ctx - 1::ctx].contiguous()
+    out = torch.empty_like(q)
+    now, row_by_row = [graph_time(lambda: B.ag_attn_decode(cache, x, out, b.bt, b.ctx, ctx, 32, g.scale, ws)) for x in (q, off_16_bytes(q))]
+    assert now <= 1.1 * row_by_row
