@@ -439,6 +439,16 @@ __global__ __launch_bounds__(256) void decode_any_merge_kernel(AttnArgs a, const
     }
 }
 
+// Whether all contexts together come to no more than a share of 256 tokens a CU: shares would leave CUs idle, and walk
+// many short contexts one behind the other, where one workgroup per pair (up to eight a CU) takes them side by side.  Measured at
+// 256 CUs, shares -> direct, us: 64 sessions at 32 / 8 heads (two pairs a CU) of 32 tokens, bf16 64 21 -> 6.9, bf16 128 27 -> 10.5,
+// fp32 128 48 -> 16; of 120 tokens 11.2 -> 7.7, 14.5 -> 12.7, 22.7 -> 20.5; 128 sessions of 60 tokens 15.3 -> 12.8, 19.7 -> 19.7, 33.3 ->
+// 33.9, of 120 tokens 13.5 -> 13.4, 18.9 -> 23.7, 32.4 -> 42; 512 sessions of 32 tokens at 4 / 4 heads x 64, 24.8 -> 23.
+inline bool few_tokens(int64_t pairs, int max_ctx, int cus)
+{
+    return pairs <= 8 * cus && max_ctx <= 128 && pairs * max_ctx <= 256 * (int64_t)cus;
+}
+
 inline int head_blocks_of(const AttnArgs& a) { return (a.hq / a.c.hkv + kCols - 1) / kCols; }
 inline int64_t steps_bound(const AttnArgs& a)
 {
@@ -451,8 +461,10 @@ ag_status launch(const AttnArgs& a, hipStream_t st)
     const int pmax = splitk::pieces_max(a.max_ctx), blocks = head_blocks_of(a);
     const int64_t pair_bytes = (int64_t)a.max_ctx * 2 * DT * (int64_t)sizeof(E);
     static_assert((512 << 10) / (2 * DT * (int)sizeof(E)) <= kDirectMaxTokens, "a wave's page ids fit its lanes");
-    if (a.max_ctx > 0 && splitk::direct_preferred((int64_t)a.batch * a.c.hkv * blocks, pair_bytes, stream_cus(st))) {
-        const dim3 grid(a.batch * a.c.hkv * blocks), wg(64 * kDirectWaves);
+    const int64_t pairs = (int64_t)a.batch * a.c.hkv * blocks;
+    const int cus = stream_cus(st);
+    if (a.max_ctx > 0 && (splitk::direct_preferred(pairs, pair_bytes, cus) || few_tokens(pairs, a.max_ctx, cus))) {
+        const dim3 grid((unsigned)pairs), wg(64 * kDirectWaves);
         prof_before(st);
         if (a.c.d == DT) hipLaunchKernelGGL((decode_any_direct_kernel<E, DT, true>), grid, wg, 0, st, a, blocks);
         else hipLaunchKernelGGL((decode_any_direct_kernel<E, DT, false>), grid, wg, 0, st, a, blocks);

@@ -120,9 +120,10 @@ def test_the_lookup_of_thousands_of_sessions_costs_less_than_their_rows():
     assert tiles <= 0.9 * row_by_row
 
 
-# rows of a pair times (8 + keys) on both sides of the line between one wave per (row, head) and tiles (80) or shares (48)
+# rows of a pair times (8 + keys) on both sides of the line between one wave per (row, head) and tiles (80) or shares (48),
+# and on both sides of 256 tokens a CU
 @pytest.mark.parametrize("dtype,d,ps,hq,hkv", [(I.BF16, 64, 32, 4, 4), (I.BF16, 128, 32, 4, 4), (I.F32, 128, 16, 4, 4), (I.BF16, 256, 16, 4, 4)])
-@pytest.mark.parametrize("ctx", [12, 40, 41, 72, 73])
+@pytest.mark.parametrize("ctx", [12, 40, 41, 54, 55, 72, 73])
 def test_crowds_at_the_line_to_row_by_row(ctx, dtype, d, ps, hq, hkv):
     """300 sessions of one row, one of them of one token, one empty."""
     c = np.full(300, ctx, np.int32)
@@ -153,9 +154,9 @@ def test_chunks_of_a_few_tokens_are_no_slower_than_row_by_row():
     assert now <= 1.3 * row_by_row
 
 
-@pytest.mark.parametrize("ctx", [4])
+@pytest.mark.parametrize("ctx", [4, 31])
 def test_decode_of_short_sessions_is_no_slower_than_row_by_row(ctx):
-    """64 sessions (the start of as many conversations) at 32 / 8 heads, by shares of 256 tokens: 2.7 at four tokens (1.0 measured)."""
+    """64 sessions (the start of as many conversations) at 32 / 8 heads, by shares of 256 tokens: 2.7 at four tokens and 1.3 at 31 (1.0 and 0.4 measured)."""
     c = np.full(64, ctx, np.int32)
     g = I.Geometry(32, 8, 64, 32, table_pages(c, 32), I.BF16)
     bt = I.deal_block_tables(I.rng_for(75, 0), c, 32, g.num_pages)
