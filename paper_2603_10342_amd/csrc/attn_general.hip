@@ -42,18 +42,34 @@ __global__ __launch_bounds__(256) void attn_general_kernel(AttnArgs a)
 
 }  // namespace
 
-// More (session, KV head) pairs than CUs, each with so few keys and rows that a workgroup's start is most of what a pair costs
-// the other kernels (11 to 37 ns a pair on a full chip, by dtype and head_dim), while one wave per (row, head) takes 1 to 4 ns
-// and 0.1 to 0.4 a key: rows of a pair times (8 + keys) is the row's time in units of a key's.  Measured, 2048 sessions, the
-// other kernel -> this one, us.  Chunks: bf16 64, 4 / 4 heads, 3 rows on 8 tokens (57) 92 -> 57, 4 on 28 (160) 90 -> 140;
-// 32 / 8 heads, 1 on 3 (48), bf16 64 181 -> 107, bf16 128 234 -> 169, bf16 256 567 -> 306, fp32 128 614 -> 191; 3 on 8 (228) 182 -> 368,
-// 240 -> 710, 580 -> 1354, 636 -> 1026; fp32 64, 4 / 2 heads, 3 on 8 (114) 58 -> 75.  Decode: 32 / 8 heads, 4 tokens (48),
-// bf16 64 112 -> 87, bf16 128 155 -> 148, fp32 128 253 -> 184; 11 tokens (76) 112 -> 126, 154 -> 248, 252 -> 365; 64 sessions of 4
-// tokens 21 -> 8, 26 -> 12, 47 -> 12.
+// Calls of so few keys and rows that starting a workgroup per (session, KV head) pair, which is what the other kernels do, takes
+// longer than one wave per (row, head).  Two things have to hold.  Throughput: rows of a pair times (8 + keys), a row's time in
+// units of a key's, at most `rows`.  Latency: a wave goes through its keys one after another, so `key` pairs a key after the
+// first `pairs` of them (on 256 CUs; others in proportion).  Kernels padded to 64, 128 or 256 channels pay for the padding, fp32 at
+// 256 for spilled registers too, and lose to rows earlier: below 0 pairs even with one session.  One fp32 row a pair leaves most of a
+// padded tile empty at any context; there latency alone decides.
+// Both sides were measured at 1560 decode and 3120 resume batches (1 to 2048 sessions, 1 to 201 keys, 1 to 4 rows, groups of 1, 4 and
+// 16, bf16 and fp32 at 8, 64, 128, 136 and 256 channels).  What the lines choose is on average within 0.3 % (bf16 unpadded) to 2.4 %
+// (fp32 padded) of the faster side.  The other kernel | this one, us.  Decode, 32 / 8 heads: 64 sessions of 4 tokens, bf16 64 7.1 |
+// 7.6, fp32 128 16 | 12; 256 of 16, bf16 64 23 | 22, bf16 128 34 | 38; 64 of 8, fp32 136 36 | 16, bf16 8 8.0 | 6.5; one of one token,
+// fp32 136 16 | 9.  Resume of one row, 32 / 32 heads: 16 sessions of 61 tokens, bf16 64 8.7 | 23, bf16 256 19 | 67; 256 of 32, bf16
+// 128 115 | 70; 256 of 501, fp32 136 4533 | 2189, fp32 72 1402 | 1097.
+namespace {
+struct Line { int rows, key, pairs; };
+constexpr Line kLines[2][2][2] = {   // [decode][padded][fp32]
+    {{{80, 32, 512}, {112, 20, 0}}, {{144, 32, -128}, {208, 16, -128}}},
+    {{{64, 24, 512}, {64, 20, 128}}, {{208, 32, -128}, {256, 16, -128}}},
+};
+}  // namespace
+
 static bool rows_preferred(const AttnArgs& a, hipStream_t st)
 {
+    const bool padded = a.c.d != 64 && a.c.d != 128 && a.c.d != 256, f32 = a.c.dtype == AG_F32;
+    const Line& line = kLines[a.ctx_lens ? 1 : 0][padded ? 1 : 0][f32 ? 1 : 0];
     const int64_t pair_rows = (int64_t)a.total_rows * (a.hq / a.c.hkv);          // rows of all sessions' pairs with one KV head
-    return pair_rows * (8 + (int64_t)a.max_ctx) <= (int64_t)(a.ctx_lens ? 48 : 80) * a.batch && (int64_t)a.batch * a.c.hkv > stream_cus(st);
+    const bool one_row = !a.ctx_lens && padded && f32 && pair_rows <= a.batch;
+    if (!one_row && pair_rows * (8 + (int64_t)a.max_ctx) > (int64_t)line.rows * a.batch) return false;
+    return (int64_t)line.key * a.max_ctx <= (int64_t)a.batch * a.c.hkv * 256 / stream_cus(st) - line.pairs;
 }
 
 ag_status launch_attn_general(const AttnArgs& a, hipStream_t st)
