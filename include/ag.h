@@ -54,8 +54,9 @@
  *     page_size a power of two in [1, 256].  With pages of 16 tokens or more and
  *     16-byte aligned pointers everything runs on matrix-core kernels: bf16 with
  *     head_dim 128 and page_size 16 rounds softmax weights to bf16; other bf16
- *     caches and fp32 caches keep them in 32 bits.  Smaller pages and unaligned
- *     pointers run on a general fp32-arithmetic kernel.
+ *     caches and fp32 caches keep them in 32 bits.  Smaller pages, unaligned
+ *     pointers and, beside that shape, calls of few keys and rows a session run
+ *     on a general fp32-arithmetic kernel.
  */
 #ifndef AG_H
 #define AG_H

@@ -7,8 +7,8 @@
 // lane (score = scale * q.k in fp32, then a streaming softmax: running max m,
 // running sum l, accumulator rescaled when m grows); values are accumulated
 // with lane = channel.  It is the path for what the other kernels do not
-// cover (pages below 16 tokens, pointers off 16 bytes) and for crowds of sessions
-// of a few tokens; it is not tuned.
+// cover (pages below 16 tokens, pointers off 16 bytes) and for calls of few keys
+// and rows (rows_preferred()); it is not tuned.
 #include "ag_internal.h"
 #include "attn_general_row.h"
 

@@ -150,9 +150,11 @@ def test_crowds_at_the_line_to_row_by_row(ctx, dtype, d, ps, hq, hkv):
 
 
 # 2048 sessions on three tokens: by tiles 1.7 of the time, and 3.4 where every workgroup added the lengths up.  One session of one
-# token, fp32 padded to 256 channels: 1.5; 128 of 33 tokens with a head of keys for each of the queries': 2.9.  The last two are for the tiles: one wave would go through its keys alone (3 times as long)
+# token, fp32 padded to 256 channels: 1.5; 128 of 32 with a KV head for each query head: 2.9.  The last two are for the tiles: one
+# wave would go through its keys alone (3 times as long)
 @pytest.mark.parametrize("batch,dtype,d,hq,hkv,prefix,share", [(2048, I.BF16, 64, 32, 8, 3, 1.3), (1, I.F32, 136, 32, 8, 1, 1.2),
-                                                               (128, I.F32, 136, 32, 32, 32, 1.2), (16, I.BF16, 64, 32, 32, 60, 0.7), (128, I.BF16, 128, 4, 4, 60, 0.7)])
+                                                               (128, I.F32, 136, 32, 32, 32, 1.2), (16, I.BF16, 64, 32, 32, 60, 0.7),
+                                                               (128, I.BF16, 128, 4, 4, 60, 0.7)])
 def test_one_row_on_a_few_tokens_against_row_by_row(batch, dtype, d, hq, hkv, prefix, share):
     now, row_by_row = resume_times(batch, I.Geometry(hq, hkv, d, 32, 3 + batch * ((prefix + 32) // 32), dtype), prefix, 1)
     assert now <= share * row_by_row

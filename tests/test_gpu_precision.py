@@ -1,4 +1,6 @@
-"""What is computed in 32 bits stays in 32 bits: softmax weights of bf16 caches beside the bf16 / 128 / 16 shape."""
+"""What is computed in 32 bits stays in 32 bits: softmax weights of bf16 caches beside the bf16 / 128 / 16 shape (more than 16
+heads a group included), and fp32 numbers so small that bf16 terms lose them.  Rows that are not finite are the row-by-row
+kernel's bit for bit, and take no longer than there."""
 import contextlib
 
 import numpy as np
