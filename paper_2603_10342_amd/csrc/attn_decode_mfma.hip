@@ -268,28 +268,33 @@ __global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_
         const int pieces = (base + g * n + n - 1) / q - first_wg + 1;
         const bool direct = kStep && pieces == 1;        // the pair lies inside this share: no partial, no merge
         if (piece < pmax) {
-            for (int idx = tid_e; idx < G * D; idx += 256) {
-                const int head = idx >> 7, d = idx & (D - 1);
+            for (int idx = tid_e; idx < G * (D / 4); idx += 256) {             // four channels a thread
+                const int head = idx >> 5, d = (idx & (D / 4 - 1)) * 4;
                 float ms = s_m[0][head];               // wave 0 always has a step: finite
 #pragma unroll
                 for (int ww = 1; ww < 4; ++ww) ms = fmaxf(ms, s_m[ww][head]);
-                float acc = 0.f, l = 0.f;
+                float l = 0.f;
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int ww = 0; ww < 4; ++ww) {
                     const float fw = exp2f(s_m[ww][head] - ms);   // a wave without steps has m = -inf -> 0
-                    acc += fw * s_o[ww][head][d];
+                    const f32x4 x = *reinterpret_cast<const f32x4*>(&s_o[ww][head][d]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[e] += fw * x[e];
                     l += fw * s_l[ww][head];
                 }
                 const int64_t row = (int64_t)s * hq + (int64_t)g * G + head;
                 if (direct) {
-                    ((__bf16*)a.out)[row * D + d] = (__bf16)(acc / l);
+                    const float y[4] = {acc[0] / l, acc[1] / l, acc[2] / l, acc[3] / l};
+                    store_quad((__bf16*)a.out + row * D + d, y);
                 } else {
                     const int64_t slot = row * pmax + piece;
                     if (kStep) {                       // read by another workgroup of this launch: device-scope stores
-                        store_coherent(ws_o + slot * D + d, acc);
-                        if (d == 0) { store_coherent(ws_ml + slot * 2, ms); store_coherent(ws_ml + slot * 2 + 1, l); }
+                        store_coherent(ws_o + slot * D + d, acc[0], acc[1]);
+                        store_coherent(ws_o + slot * D + d + 2, acc[2], acc[3]);
+                        if (d == 0) store_coherent(ws_ml + slot * 2, ms, l);
                     } else {
-                        ws_o[slot * D + d] = acc;
+                        *reinterpret_cast<f32x4*>(ws_o + slot * D + d) = acc;
                         if (d == 0) { ws_ml[slot * 2] = ms; ws_ml[slot * 2 + 1] = l; }
                     }
                 }
@@ -305,10 +310,12 @@ __global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_
             if (tid_e == 0) s_arrived = __hip_atomic_fetch_add(&sa.counters[s * hkv + g], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
             if (s_arrived == pieces - 1) {
-                for (int idx = tid_e; idx < G * D; idx += 256) {
-                    const int head = idx >> 7, d = idx & (D - 1);
+                for (int idx = tid_e; idx < G * (D / 4); idx += 256) {
+                    const int head = idx >> 5, d = (idx & (D / 4 - 1)) * 4;
                     const int64_t row = (int64_t)s * hq + (int64_t)g * G + head;
-                    ((__bf16*)a.out)[row * D + d] = (__bf16)merge_coherent(ws_o, ws_ml, row * pmax, min(pieces, pmax), d);
+                    float y[4];
+                    merge_coherent<false>(ws_o, ws_ml, row * pmax, min(pieces, pmax), d, D, y);
+                    store_quad((__bf16*)a.out + row * D + d, y);
                 }
                 if (tid_e == 0) sa.counters[s * hkv + g] = 0;      // as the next call expects it
             }

@@ -43,59 +43,95 @@ struct StepRegs {       // one wave's K and V operands for 32 tokens (two pages)
 };
 
 
-// Partials that another workgroup of the same launch reads go past this XCD's caches.
-__device__ __forceinline__ float load_coherent(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void store_coherent(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Partials that another workgroup of the same launch reads go past this XCD's caches, two floats at a time.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ f32x2 load_coherent(const float* p)
+{
+    return __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ void store_coherent(float* p, float x, float y)
+{
+    __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, f32x2{x, y}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // kNatural: the partials' maxima are in natural units (fp32 caches), not in powers of two.
 template <bool kNatural>
 __device__ __forceinline__ float merge_power(float x) { return kNatural ? expf(x) : exp2f(x); }
 
-// The partials (m, l, O) of one (row, head), n >= 1 of them: combined in slot order - reproducible - four at a time, so that
-// a group's loads are in flight together instead of one dependent round trip per partial.  For N neighbouring channels;
+// The partials (m, l, O) of one (row, head), n >= 1 of them: combined in slot order - reproducible - four at a time, with the
+// loads of kFlight (4 or 8) in flight together instead of one dependent round trip per partial.  For N neighbouring channels;
 // load(i, m, l, o) fetches partial i < n.
-template <int N, bool kNatural, class Load>
+template <int N, bool kNatural, int kFlight, class Load>
 __device__ __forceinline__ void merge_channels(int n, Load load, float (&out)[N])
 {
     float ms = -INFINITY, l = 0.f, acc[N];
 #pragma unroll
     for (int e = 0; e < N; ++e) acc[e] = 0.f;
-    for (int i0 = 0; i0 < n; i0 += 4) {
-        float mi[4], li[4], oi[4][N];
+    for (int i0 = 0; i0 < n; i0 += kFlight) {
+        float mi[kFlight], li[kFlight], oi[kFlight][N];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            load(min(i0 + j, n - 1), mi[j], li[j], oi[j]);
-            if (i0 + j >= n) mi[j] = -INFINITY;
+        for (int h = 0; h < kFlight; h += 4) {
+            if (h > 0 && i0 + h >= n) break;
+#pragma unroll
+            for (int j = h; j < h + 4; ++j) load(min(i0 + j, n - 1), mi[j], li[j], oi[j]);
         }
-        const float m_new = fmaxf(fmaxf(ms, fmaxf(mi[0], mi[1])), fmaxf(mi[2], mi[3]));
-        const float keep = ms == -INFINITY ? 0.f : merge_power<kNatural>(ms - m_new);
-        l *= keep;
 #pragma unroll
-        for (int e = 0; e < N; ++e) acc[e] *= keep;
+        for (int h = 0; h < kFlight; h += 4) {
+            if (h > 0 && i0 + h >= n) break;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float f = mi[j] == -INFINITY ? 0.f : merge_power<kNatural>(mi[j] - m_new);     // a partial that saw no key
-            l += f * li[j];
+            for (int j = h; j < h + 4; ++j)
+                if (i0 + j >= n) mi[j] = -INFINITY;
+            const float m_new = fmaxf(fmaxf(ms, fmaxf(mi[h], mi[h + 1])), fmaxf(mi[h + 2], mi[h + 3]));
+            const float keep = ms == -INFINITY ? 0.f : merge_power<kNatural>(ms - m_new);
+            l *= keep;
 #pragma unroll
-            for (int e = 0; e < N; ++e) acc[e] += f * oi[j][e];
+            for (int e = 0; e < N; ++e) acc[e] *= keep;
+#pragma unroll
+            for (int j = h; j < h + 4; ++j) {
+                const float f = mi[j] == -INFINITY ? 0.f : merge_power<kNatural>(mi[j] - m_new);     // a partial that saw no key
+                l += f * li[j];
+#pragma unroll
+                for (int e = 0; e < N; ++e) acc[e] += f * oi[j][e];
+            }
+            ms = m_new;
         }
-        ms = m_new;
     }
 #pragma unroll
     for (int e = 0; e < N; ++e) out[e] = acc[e] / l;
 }
 
-// Channel d, from partials that other workgroups of the SAME launch wrote (device-scope stores, see store_coherent): read
-// with device-scope loads, which do not hit in this XCD's caches.
-__device__ __forceinline__ float merge_coherent(const float* __restrict__ ws_o, const float* __restrict__ ws_ml, int64_t base, int n, int d)
+// Four neighbouring channels of a row as E, in one store where the row is aligned for it (uniform: rows are multiples of it apart).
+template <typename E>
+__device__ __forceinline__ void store_quad(E* out, const float (&y)[4])
 {
-    float y[1];
-    merge_channels<1, false>(n, [&](int i, float& m, float& l, float (&o)[1]) {
-        m = load_coherent(ws_ml + (base + i) * 2);
-        l = load_coherent(ws_ml + (base + i) * 2 + 1);
-        o[0] = load_coherent(ws_o + (base + i) * D + d);
+    typedef E quad __attribute__((ext_vector_type(4)));
+    const quad q = {(E)y[0], (E)y[1], (E)y[2], (E)y[3]};
+    if ((uintptr_t)out % sizeof(quad) == 0) {
+        *reinterpret_cast<quad*>(out) = q;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) out[e] = q[e];
+    }
+}
+
+// Channels d .. d + 3 of a (row, head) with D_ channels, from partials that other workgroups of the SAME launch wrote
+// (store_coherent): read with device-scope loads, which do not hit in this XCD's caches.  Four channels a thread, 16 bytes of
+// a partial in two loads: with one channel a thread a group of 16 heads was eight such chains one after another (step of
+// 53 sessions of 750..3260 tokens at 16 / 1 heads 36.4 -> 23.1 us, one session of 8000 at 32 / 8 20.5 -> 15.7, of 1000 8.0 -> 7.4).
+template <bool kNatural>
+__device__ __forceinline__ void merge_coherent(const float* __restrict__ ws_o, const float* __restrict__ ws_ml, int64_t base, int n,
+                                               int d, int D_, float (&y)[4])
+{
+    merge_channels<4, kNatural, 8>(n, [&](int i, float& m, float& l, float (&o)[4]) {
+        const f32x2 ml = load_coherent(ws_ml + (base + i) * 2);
+        const f32x2 lo = load_coherent(ws_o + (base + i) * D_ + d), hi = load_coherent(ws_o + (base + i) * D_ + d + 2);
+        m = ml[0];
+        l = ml[1];
+        o[0] = lo[0];
+        o[1] = lo[1];
+        o[2] = hi[0];
+        o[3] = hi[1];
     }, y);
-    return y[0];
 }
 
 // Channels d .. d + 3 of a pair with D_ channels, by the merge kernels: four channels a thread, so that a (row, head) takes
@@ -105,21 +141,14 @@ __device__ __forceinline__ f32x4 merge_quad(const float* __restrict__ ws_o, cons
                                            int d, int D_, E* __restrict__ out)
 {
     float y[4];
-    merge_channels<4, kNatural>(n, [&](int i, float& m, float& l, float (&o)[4]) {
+    merge_channels<4, kNatural, 4>(n, [&](int i, float& m, float& l, float (&o)[4]) {
         m = ws_ml[(base + i) * 2];
         l = ws_ml[(base + i) * 2 + 1];
         const f32x4 x = *reinterpret_cast<const f32x4*>(ws_o + (base + i) * D_ + d);
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = x[e];
     }, y);
-    typedef E quad __attribute__((ext_vector_type(4)));
-    const quad q = {(E)y[0], (E)y[1], (E)y[2], (E)y[3]};
-    if ((uintptr_t)out % sizeof(quad) == 0) {            // (uniform: rows are multiples of it apart)
-        *reinterpret_cast<quad*>(out + d) = q;
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) out[d + e] = q[e];
-    }
+    store_quad(out + d, y);
     return f32x4{y[0], y[1], y[2], y[3]};
 }
 
