@@ -1,17 +1,20 @@
 // Prefill of few rows on long contexts (a tool output appended to one agent's session, a handful of short prompts):
-// the keys of a query tile are split over the waves of one workgroup.  bf16 and fp32, head_dim 64 and 128, pages of 16
-// tokens or more.
+// the keys of a query tile are split over the waves of one workgroup.  bf16 and fp32, head_dim 64 and 128, and bf16 at 256;
+// pages of 16 tokens or more.
 //
 // With few rows the other prefill kernels leave the chip idle: a workgroup of 128 columns walks all its keys alone
 // (211 rows at 32 / 8 heads are 56 workgroups of 98 key tiles each on 256 CUs).  Here a workgroup owns 32 columns - a
-// column is a (token, query head of the group) pair, numbered token * G + head - and its eight waves take every
-// eighth step of 32 keys, each with its own (m, l, O), which are merged through LDS at the end: four times the
+// column is a (token, query head of the group) pair, numbered token * G + head - and its eight waves (four at 256 channels,
+// where O^T alone is 128 registers) take every eighth step of 32 keys, each with its own (m, l, O), which are merged through LDS at the end: four times the
 // workgroups, each an eighth as long.  Nothing goes through memory between them, so the entry point needs no workspace.
 // No wave shares its keys with another, so K and V go straight from the pages into the registers of the matrix
 // operands (no LDS stage, no barrier in the loop); K of the next step is requested as soon as the score product has
-// read this one's, V after the value product.  What bounds it is the load path of a CU (64 bytes per clock from L2: 16
-// KiB per wave and step against 512 clocks of products), about half the matrix rate; the line to the other kernels
-// is at prefill_split_preferred().
+// read this one's, V after the value product.  What bounds it is the load path of a CU, 64 bytes per clock: a round of
+// eight steps at 128 channels, 128 KiB, takes 1.0 us where the same loads alone take 0.9 from L2; scores of the next step
+// beside the weights of this one, a second step's keys in flight, or neighbours starting at other steps of a ring of 4 to 16
+// all measured slower.  Rest of a call on 6000 tokens (35 us): the append, 8 us of start, merge and launch.  Locating a
+// step's pages once for K and V: 36.8 -> 35.1 us there, eight chunks of 50 rows on 2000 tokens 29.0 -> 28.5.  The line to the
+// other kernels is at prefill_split_preferred().
 #include <algorithm>
 #include <atomic>
 
@@ -31,18 +34,22 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kColumns = 32;            // (token, head) pairs of a workgroup
-constexpr int kWaves = 8;               // which share its keys
-constexpr int kRowsAgain = 4;           // rows taken again together (attn_general_row.h): a wave's share of the columns
 constexpr int kStep = 32;               // keys of a wave's step
 constexpr float kLog2e = 1.4426950408889634f;
 
-constexpr int o_row(int dt) { return dt + 4; }          // floats of a column's partial in LDS, padded
-constexpr int lds_bytes(int dt) { return kWaves * kColumns * (o_row(dt) + 2) * 4 + 16; }
+template <int DT>
+struct Shape {
+    static constexpr int waves = DT > 128 ? 4 : 8;          // which share the columns' keys; 512 registers a lane, or 256
+    static constexpr int rows_again = DT > 128 ? 1 : 4;     // rows taken again together (attn_general_row.h)
+    static constexpr int o_row = DT + 4;                    // floats of a column's partial in LDS, padded
+    static constexpr int lds = waves * kColumns * (o_row + 2) * 4 + 16;
+};
 
 // kLo: bf16 weights as three terms (bf16_terms.h); false keeps the rounded weights of the bf16 / 128 / 16 kernels.
 template <typename E, int DT, bool kLo>
-__global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs a, int tiles_max, int per_xcd, int total_work)
+__global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void prefill_split_kernel(AttnArgs a, int tiles_max, int per_xcd, int total_work)
 {
+    constexpr int kWaves = Shape<DT>::waves, kORow = Shape<DT>::o_row, kRowsAgain = Shape<DT>::rows_again;
     constexpr bool kBf16 = sizeof(E) == 2;
     constexpr int kK = DT * (int)sizeof(E) / 32;    // 16-byte loads of a lane per step: keys
     constexpr int kMb = DT / 32;
@@ -107,23 +114,25 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
 
     const int64_t block = (int64_t)DT * ps;                     // elements of one (page, head)
     u32x4 kx[kK], vx[kRuns * kMb];
-    // the two groups' (page, head) blocks of own step i, with the groups' places inside them
-    auto group_at = [&](int i, int half, int& gi) -> int64_t {
-        gi = min(2 * (w + kWaves * i) + half, last_grp) & gmask;
-        return ((int64_t)__builtin_amdgcn_readlane(my_pid, 2 * (i & 31) + half) * hkv + g) * block;
+    // a step's two groups: elements from a pool's start to their (page, head) blocks, and their places inside them
+    struct Groups { int64_t a, b; int ga, gb; };
+    auto locate = [&](int i) {                                  // own step i; the steps are located in order
+        if ((i & 31) == 0 && i > 0) fetch_ids(i);
+        Groups p;
+        p.a = ((int64_t)__builtin_amdgcn_readlane(my_pid, 2 * (i & 31)) * hkv + g) * block;
+        p.b = ((int64_t)__builtin_amdgcn_readlane(my_pid, 2 * (i & 31) + 1) * hkv + g) * block;
+        p.ga = min(2 * (w + kWaves * i), last_grp) & gmask;
+        p.gb = min(2 * (w + kWaves * i) + 1, last_grp) & gmask;
+        return p;
     };
-    auto load_k = [&](int i) {
-        int gA, gB;
-        const int64_t bA = group_at(i, 0, gA), bB = group_at(i, 1, gB);
-        const E* kp = (const E*)a.c.k + (n >> 4 ? bB + gB * 128 : bA + gA * 128) + (n & 15) * 8 + (kBf16 ? hi * ps * 8 : hi * 4);
+    auto load_k = [&](const Groups& p) {
+        const E* kp = (const E*)a.c.k + (n >> 4 ? p.b + p.gb * 128 : p.a + p.ga * 128) + (n & 15) * 8 + (kBf16 ? hi * ps * 8 : hi * 4);
 #pragma unroll
         for (int j = 0; j < kK; ++j) kx[j] = *reinterpret_cast<const u32x4*>(kp + (int64_t)(kBf16 ? 2 * j : j) * ps * 8);
     };
-    auto load_v = [&](int i) {
-        int gA, gB;
-        const int64_t bA = group_at(i, 0, gA), bB = group_at(i, 1, gB);
-        const E* vA = (const E*)a.c.v + bA + gA * 16 * DT + (hi * DT + n) * 8;
-        const E* vB = (const E*)a.c.v + bB + gB * 16 * DT + (hi * DT + n) * 8;
+    auto load_v = [&](const Groups& p) {
+        const E* vA = (const E*)a.c.v + p.a + p.ga * 16 * DT + (hi * DT + n) * 8;
+        const E* vB = (const E*)a.c.v + p.b + p.gb * 16 * DT + (hi * DT + n) * 8;
 #pragma unroll
         for (int j = 0; j < kRuns; ++j)
 #pragma unroll
@@ -139,7 +148,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[mb][i] = 0.f;
     if (kQInLds) __syncthreads();
-    if (my_n > 0) { load_k(0); load_v(0); }
+    Groups at = {};                                             // the step requested last
+    if (my_n > 0) {
+        at = locate(0);
+        load_k(at);
+        load_v(at);
+    }
 
 #pragma unroll 1
     for (int i = 0; i < my_n; ++i) {
@@ -159,8 +173,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
             }
         }
         if (i + 1 < my_n) {
-            if (((i + 1) & 31) == 0) fetch_ids(i + 1);
-            load_k(i + 1);
+            at = locate(i + 1);
+            load_k(at);
         }
         __builtin_amdgcn_sched_barrier(0);
         if (st >= first_masked) {
@@ -247,7 +261,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
                     for (int mb = 0; mb < kMb; ++mb)
                         o[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(f32x4, vx[j * kMb + mb])[e], sc[j * 4 + e], o[mb], 0, 0, 0);
         }
-        if (i + 1 < my_n) load_v(i + 1);
+        if (i + 1 < my_n) load_v(at);
         __builtin_amdgcn_sched_barrier(0);
     }
 
@@ -255,14 +269,14 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
     lsum += __shfl_xor(lsum, 32);
     if (kQInLds) __syncthreads();                               // Q has been read
     float* const s_o = reinterpret_cast<float*>(lds);           // [wave][column][o_row]
-    float* const s_m = s_o + kWaves * kColumns * o_row(DT);
+    float* const s_m = s_o + kWaves * kColumns * kORow;
     float* const s_l = s_m + kWaves * kColumns;
 #pragma unroll
     for (int mb = 0; mb < kMb; ++mb)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
             const f32x4 x = {o[mb][q4 * 4], o[mb][q4 * 4 + 1], o[mb][q4 * 4 + 2], o[mb][q4 * 4 + 3]};
-            *reinterpret_cast<f32x4*>(s_o + (w * kColumns + n) * o_row(DT) + mb * 32 + q4 * 8 + hi * 4) = x;
+            *reinterpret_cast<f32x4*>(s_o + (w * kColumns + n) * kORow + mb * 32 + q4 * 8 + hi * 4) = x;
         }
     uint32_t* const s_again = reinterpret_cast<uint32_t*>(s_l + kWaves * kColumns);       // bit c: column c is not finite
     if (hi == 0) { s_m[w * kColumns + n] = m; s_l[w * kColumns + n] = lsum; }
@@ -280,7 +294,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
             const float f = power(s_m[ww * kColumns + c] - ms);       // a wave that saw no key has m = -inf -> 0
             l += f * s_l[ww * kColumns + c];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] += f * s_o[(ww * kColumns + c) * o_row(DT) + d + e];
+            for (int e = 0; e < 8; ++e) acc[e] += f * s_o[(ww * kColumns + c) * kORow + d + e];
         }
         const float inv = 1.0f / l;
         int t;
@@ -300,8 +314,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_split_kernel(AttnArgs 
     if constexpr (kTakeAgain) {
         __syncthreads();                                        // what the waves write once more is behind what is there
         const uint32_t all = __builtin_amdgcn_readfirstlane(*s_again);
+        constexpr uint32_t kMine = kWaves == 8 ? 0x01010101u : 0x11111111u;       // columns w, w + kWaves, ...
         int t;
-        if (all) general::attend_rows_again<E, kRowsAgain, DT / 64>(a, all & (0x01010101u << w), row_of(min(n, cols - 1), t), qpos, s, g, s_o + kRowsAgain * DT * w);
+        if (all) general::attend_rows_again<E, kRowsAgain, DT / 64>(a, all & (kMine << w), row_of(min(n, cols - 1), t), qpos, s, g, s_o + kRowsAgain * DT * w);
     }
 }
 
@@ -314,12 +329,13 @@ int64_t tiles_bound(const AttnArgs& a, int columns)
 template <typename E, int DT, bool kLo>
 ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 {
+    constexpr int lds = Shape<DT>::lds;
     static std::atomic<uint64_t> told{0};
-    ag_status e = allow_dynamic_lds((const void*)prefill_split_kernel<E, DT, kLo>, lds_bytes(DT), told);
+    ag_status e = allow_dynamic_lds((const void*)prefill_split_kernel<E, DT, kLo>, lds, told);
     if (e) return e;
     const int64_t tiles_max = tiles_bound(a, kColumns), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
     prof_before(st);
-    hipLaunchKernelGGL((prefill_split_kernel<E, DT, kLo>), dim3((unsigned)(per_xcd * 8)), dim3(64 * kWaves), lds_bytes(DT), st, a,
+    hipLaunchKernelGGL((prefill_split_kernel<E, DT, kLo>), dim3((unsigned)(per_xcd * 8)), dim3(64 * Shape<DT>::waves), lds, st, a,
                        (int)tiles_max, (int)per_xcd, (int)total);
     prof_after(st);
     return hip_check(hipGetLastError(), "prefill launch");
@@ -328,17 +344,18 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 }  // namespace
 
 // Whether the batch's query tiles are too few for the other kernels.  Counted in workgroups of 32 columns per CU of the
-// stream (one is resident at a time): up to 2 for the bf16 / 128 / 16 shape, 3 for the others, whose kernels spend twice
-// (bf16, weights in three terms) to three times (fp32, products in six terms) the matrix work.
+// stream (one is resident at a time): up to 2 for the bf16 / 128 / 16 shape, 3 for the others, whose kernels
+// spend twice (bf16, weights in three terms) to three times (fp32, products in six terms) the matrix work.
 // Measured at 32 / 8 heads on 256 CUs, append included, the other kernel -> this one: bf16 / 128 / 16, one chunk of
-// 5 rows on 6007 tokens (8 workgroups) 114 -> 39 us, 211 rows (216) 119 -> 45, 400 rows (400) 122 -> 80; four chunks of
+// 5 rows on 6007 tokens (8 workgroups) 114 -> 37 us, 211 rows (216) 119 -> 43, 400 rows (400) 122 -> 77; four chunks of
 // 150 rows on 3000 (608) 70 -> 70, eight of 100 on 2000 (832) 57 -> 71.  bf16 / 64 / 64: eight of 40 on 2000 (320) 49 ->
 // 32, 32 of 20 on 1000 (768) 32 -> 32, eight of 100 on 2000 (832) 55 -> 58, two prompts of 1000 (2000) 48 -> 54.  fp32 / 128:
 // one chunk of 211 rows on 6000 (216) 589 -> 233, one prompt of 600 (600) 73 -> 57, twelve chunks of 10..100 rows on
-// 1000..3000 (700) 295 -> 249; three of 300 on 5000 (912) 513 -> 762, two prompts of 1000 (2000) 139 -> 215.
+// 1000..3000 (700) 295 -> 249; three of 300 on 5000 (912) 513 -> 762, two prompts of 1000 (2000) 139 -> 215.  bf16 / 256 (graph
+// replay): six of 13 rows on 2200 (112) 120 -> 40, eight of 120 on 2000 (784) 119 -> 100, of 160 on 1500 (1024) 100 -> 107.
 bool prefill_split_preferred(const AttnArgs& a, bool rounded, hipStream_t st)
 {
-    if ((a.c.d != 64 && a.c.d != 128) || a.c.ps < 16 || (int64_t)a.total_rows * (a.hq / a.c.hkv) > 0x7fffffff ||
+    if ((a.c.d != 64 && a.c.d != 128 && (a.c.d != 256 || a.c.dtype == AG_F32)) || a.c.ps < 16 || (int64_t)a.total_rows * (a.hq / a.c.hkv) > 0x7fffffff ||
         ((uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 != 0) return false;
     return a.c.hkv * tiles_bound(a, kColumns) <= (int64_t)(rounded ? 2 : 3) * stream_cus(st);
 }
@@ -346,6 +363,7 @@ bool prefill_split_preferred(const AttnArgs& a, bool rounded, hipStream_t st)
 ag_status launch_prefill_split(const AttnArgs& a, bool rounded, hipStream_t st)
 {
     if (a.c.dtype == AG_F32) return a.c.d == 64 ? launch_kernel<float, 64, false>(a, st) : launch_kernel<float, 128, false>(a, st);
+    if (a.c.d == 256) return launch_kernel<__bf16, 256, true>(a, st);
     if (a.c.d == 64) return launch_kernel<__bf16, 64, true>(a, st);
     return rounded ? launch_kernel<__bf16, 128, false>(a, st) : launch_kernel<__bf16, 128, true>(a, st);
 }
