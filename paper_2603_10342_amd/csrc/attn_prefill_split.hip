@@ -344,7 +344,7 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 }  // namespace
 
 // Whether the batch's query tiles are too few for the other kernels.  Counted in workgroups of 32 columns per CU of the
-// stream (one is resident at a time): up to 2 for the bf16 / 128 / 16 shape, 3 for the others, whose kernels
+// stream (one is resident at a time): on long contexts up to 2 for the bf16 / 128 / 16 shape, 3 for the others, whose kernels
 // spend twice (bf16, weights in three terms) to three times (fp32, products in six terms) the matrix work.
 // Measured at 32 / 8 heads on 256 CUs, append included, the other kernel -> this one: bf16 / 128 / 16, one chunk of
 // 5 rows on 6007 tokens (8 workgroups) 114 -> 37 us, 211 rows (216) 119 -> 43, 400 rows (400) 122 -> 77; four chunks of
@@ -353,11 +353,21 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 // one chunk of 211 rows on 6000 (216) 589 -> 233, one prompt of 600 (600) 73 -> 57, twelve chunks of 10..100 rows on
 // 1000..3000 (700) 295 -> 249; three of 300 on 5000 (912) 513 -> 762, two prompts of 1000 (2000) 139 -> 215.  bf16 / 256 (graph
 // replay): six of 13 rows on 2200 (112) 120 -> 40, eight of 120 on 2000 (784) 119 -> 100, of 160 on 1500 (1024) 100 -> 107.
+// A workgroup's start and merge cost it about 8 us whatever its keys, so a second one on a CU pays only where there are keys to
+// go through: the line falls to little more than one a CU for the shortest contexts.  Graph replay, this one -> the other: 16 prompts of
+// 50 rows (700 workgroups) bf16 / 64 16.1 -> 10.2 us, fp32 / 64 25.9 -> 14.8, fp32 / 128 36.9 -> 23.0; eight of 100 (660) bf16 / 64
+// 15.7 -> 11.6, bf16 / 128 on pages of 32 19.3 -> 15.2, bf16 / 256 29.9 -> 25.4; eight of 50 (360) bf16 / 128 / 16 12.5 -> 11.4,
+// fp32 / 64 17.6 -> 13.3; four of 200 rows on 300 (630) bf16 / 128 on pages of 32 26.4 -> 23.4; but eight of 60 on 300 (420) bf16 / 64 13.7 ->
+// 15.1, 16 of 30 on 600 (490) 16.7 -> 21.2, five of 60 (200) bf16 / 128 / 16 9.3 -> 10.9, twelve of 40 on 150 (456) fp32 / 128 30 -> 33.
 bool prefill_split_preferred(const AttnArgs& a, bool rounded, hipStream_t st)
 {
     if ((a.c.d != 64 && a.c.d != 128 && (a.c.d != 256 || a.c.dtype == AG_F32)) || a.c.ps < 16 || (int64_t)a.total_rows * (a.hq / a.c.hkv) > 0x7fffffff ||
         ((uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 != 0) return false;
-    return a.c.hkv * tiles_bound(a, kColumns) <= (int64_t)(rounded ? 2 : 3) * stream_cus(st);
+    const int64_t ctx = a.max_ctx;                  // in thousandths of a workgroup per CU:
+    const bool wide = a.c.d * (a.c.dtype == AG_F32 ? 4 : 2) >= 512;
+    const int64_t line = rounded ? std::max<int64_t>(1125, std::min<int64_t>(875 + 2 * ctx, 2000))
+                                 : std::min<int64_t>(wide ? 1125 + ctx * 11 / 2 : 1250 + 3 * ctx, 3000);
+    return 1000 * a.c.hkv * tiles_bound(a, kColumns) <= line * stream_cus(st);
 }
 
 ag_status launch_prefill_split(const AttnArgs& a, bool rounded, hipStream_t st)

@@ -1,5 +1,5 @@
-"""Prefill of few rows at 256 channels (the keys of a query tile split over four waves):
-edges of steps, of the waves' shares, of tiles, against the oracle."""
+"""Prefill of few rows at 256 channels (the keys of a query tile split over four waves) and both sides of the line between that
+kernel and the others, which depends on the contexts: edges of steps, of the waves' shares, of tiles, against the oracle."""
 import numpy as np
 import pytest
 
@@ -28,3 +28,9 @@ def test_256_channels(ps, hq, hkv):
     # rows that end a tile of 32 columns and do not
     fill_and_resume(g, [0, 31, 95, 127, 128, 500, 1, 4200], [1, 1, 33, 8, 9, 16, 40, 5], seed=61)
 
+
+@pytest.mark.parametrize("dtype,d,ps", [(I.BF16, 128, 16), (I.BF16, 64, 32), (I.F32, 64, 16), (I.F32, 128, 16), (I.BF16, 256, 16)])
+@pytest.mark.parametrize("sessions,rows,prefix", [(9, 13, 0), (9, 13, 700), (16, 50, 0)])
+def test_around_the_line(dtype, d, ps, sessions, rows, prefix):
+    g = I.Geometry(32, 8, d, ps, 1024, dtype)
+    fill_and_resume(g, [prefix] * sessions, [rows - s % 3 for s in range(sessions)], seed=62)
