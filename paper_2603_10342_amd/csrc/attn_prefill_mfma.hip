@@ -386,11 +386,20 @@ static ag_status launch_prefill_nw(const AttnArgs& a, hipStream_t st)
 static ag_status launch_tiles(const AttnArgs& a, bool lo, hipStream_t st)
 {
     if (prefill_split_preferred(a, !lo, st)) return launch_prefill_split(a, !lo, st);
-    // 256-column workgroups when chunks are long enough to fill them (a K/V tile then feeds twice the columns);
-    // 128-column workgroups keep short, ragged chunks efficient, and spread a batch that the larger ones could not spread
-    // over 5/8 of the CUs (one chunk on 6000 tokens, whole call: 600 rows 152 -> 126 us, 1000 rows 167 -> 139; two of 600
-    // rows, 160 of the larger workgroups, 159 against 165).
-    const bool big = a.max_new >= 512 && 8 * a.c.hkv * tiles_bound(a, 256) >= 5 * (int64_t)stream_cus(st);
+    // 256-column workgroups (a K/V tile then feeds twice the columns) when chunks are long enough to fill them and the batch
+    // spreads over at least 5/8 of the CUs.  128-column workgroups keep short, ragged chunks efficient and spread small batches (one
+    // chunk on 6000 tokens, whole call: 600 rows 152 -> 126 us, 1000 rows 167 -> 139).  They also end a launch better: 256 columns
+    // are one workgroup a CU, whose start (4 us) and end nothing else hides and of which a last one a CU is a long one, so that
+    // two workgroups of 128 columns a CU win on contexts up to 1536 unless all of the larger ones run at once, and on longer ones
+    // while the larger ones come to few a CU.  Graph replay, append included, 256 -> 128 columns, us (of the larger a CU):
+    // rounded weights, four prompts of 600 (1.3) 37.8 -> 32.5, seven of 700..912 at 16 / 2 heads (1.4) 52 -> 47, eight of 1000 (4) 108 -> 105,
+    // two of 1000 (1) 38.9 -> 40.3, one of 2048 (1) 62.5 -> 58.2, two of 2048 (2) 84 -> 86, one of 4096 (2) 143 -> 148, 16 of 300..2000
+    // at 8 / 2 (2.2) 97 -> 88, eight of 512..600 on 2000..4000 (2.2) 261 -> 268; weights in 32 bits, one of 2048 (1) 101 -> 85, two of
+    // 1000 (1) 58.5 -> 62.5, eight of 512..600 on 1000..2000 (2.2) 258 -> 241, four of 2048 (4) 265 -> 274.
+    const int64_t cus = stream_cus(st), large = a.c.hkv * tiles_bound(a, 256);         // workgroups of 256 columns
+    const bool ragged = 5 * (int64_t)a.total_rows < 4 * (int64_t)a.batch * a.max_new;
+    const bool pays = large <= cus ? a.max_ctx <= 1536 : a.max_ctx > 1536 && 4 * large >= (lo || ragged ? 10 : 7) * cus;
+    const bool big = a.max_new >= 512 && 8 * large >= 5 * cus && pays;
     if (!lo) return big ? launch_prefill_nw<8, 128, false, true>(a, st) : launch_prefill_nw<4, 128, false, true>(a, st);
     if (a.c.d == 128) return big ? launch_prefill_nw<8, 128, true, false>(a, st) : launch_prefill_nw<4, 128, true, false>(a, st);
     return launch_prefill_nw<4, 64, true, false>(a, st);
