@@ -55,24 +55,39 @@ struct SubStep {
 template <typename E, int DT>
 constexpr int q_row() { return DT * (int)sizeof(E) + 16; }      // bytes of a query row in LDS, padded
 
-// One wave's part of a segment - steps my_u .. my_u + my_n - 1 (at most 32) of (session s, KV head g, heads h0 .. h0 + nh - 1
-// of its group), whose context has ctx tokens: running maximum, sum and O^T of the heads.  Contains one workgroup barrier (Q
-// goes through LDS).
+// The queries of a pair (heads h0 .. h0 + nh - 1 of a group) into LDS, rows padded and zero behind the last head and channel.
 template <typename E, int DT, bool kExact, int kThreads>
-__device__ __forceinline__ void attend_steps(const AttnArgs& a, int s, int g, int h0, int nh, int ctx, int my_u, int my_n,
-                                             unsigned char* s_q, float& m, float& lsum, f32x4 (&o)[DT / 16])
+__device__ __forceinline__ void queries_to_lds(const AttnArgs& a, int s, int g, int h0, int nh, unsigned char* s_q)
+{
+    constexpr int kPieces = DT * (int)sizeof(E) / 16;            // of a query row
+    const int D = kExact ? DT : a.c.d, pieces = D * (int)sizeof(E) / 16, G = a.hq / a.c.hkv;
+    const unsigned char* qs = (const unsigned char*)a.q + ((int64_t)s * a.hq + (int64_t)g * G + h0) * D * (int)sizeof(E);
+    for (int idx = threadIdx.x; idx < kCols * kPieces; idx += kThreads) {
+        const int head = idx / kPieces, p = idx - head * kPieces;
+        u32x4 x = {0, 0, 0, 0};
+        if (head < nh && p < pieces) x = *reinterpret_cast<const u32x4*>(qs + ((int64_t)head * pieces + p) * 16);
+        *reinterpret_cast<u32x4*>(s_q + head * q_row<E, DT>() + p * 16) = x;
+    }
+}
+
+// One wave's part of a pair's keys - sub-steps first, first + kStride, ... , `subs` of them - of (session s, KV head g, heads h0 ..
+// h0 + nh - 1 of its group), whose context has ctx tokens: running maximum, sum and O^T of the heads.  my_pid: lane i holds
+// the page of the i-th 16-token group of these sub-steps (of a group behind the last one, anything).  Contains one workgroup barrier
+// (the queries are in LDS behind it).
+template <typename E, int DT, bool kExact, int kStride>
+__device__ __forceinline__ void attend_steps(const AttnArgs& a, int g, int ctx, int first, int subs, int my_pid,
+                                             const unsigned char* s_q, float& m, float& lsum, f32x4 (&o)[DT / 16])
 {
     using X = SubStep<E, DT>;
     constexpr bool kBf16 = X::kBf16;
-    constexpr int kSub = 32 / X::kTok;                           // sub-steps of a step
     constexpr bool kTwoInFlight = X::kK + X::kV <= 16;
     constexpr int kQRow = q_row<E, DT>();
-    const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv;
+    const int hkv = a.c.hkv;
     const int D = kExact ? DT : a.c.d, ps = a.c.ps;
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int lane = threadIdx.x & 63;
 
     const int r = lane & 15, c = lane >> 4;
-    const int gshift = a.c.ps_shift - 4, gmask = (1 << gshift) - 1;       // 16-token groups of a page
+    const int gmask = (1 << (a.c.ps_shift - 4)) - 1;            // 16-token groups of a page
     const int64_t block = (int64_t)D * ps;                       // elements of one (page, head)
     // bf16: score row r is slot r & 7 of group r >> 3, the second product takes slots 8..15, so that lane group c owns
     // the 8 tokens of value chunk c & 1 of group c >> 1.  fp32: score row r is slot r, lane group c owns tokens
@@ -84,25 +99,13 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, int s, int g, in
     auto power = [](float x) { return kBf16 ? __builtin_amdgcn_exp2f(x) : expf(x); };
 
     const int last_grp = (ctx - 1) >> 4;
-    int my_pid = 0;                                          // lane i: page of the wave's group i
-    if (my_n > 0) my_pid = a.bt[(int64_t)s * a.max_pages + (min(2 * my_u + lane, last_grp) >> gshift)];
-    {
-        constexpr int kPieces = DT * (int)sizeof(E) / 16;    // of a query row
-        const int pieces = D * (int)sizeof(E) / 16;
-        const unsigned char* qs = (const unsigned char*)a.q + ((int64_t)s * hq + (int64_t)g * G + h0) * D * (int)sizeof(E);
-        for (int idx = tid; idx < kCols * kPieces; idx += kThreads) {
-            const int head = idx / kPieces, p = idx - head * kPieces;
-            u32x4 x = {0, 0, 0, 0};
-            if (head < nh && p < pieces) x = *reinterpret_cast<const u32x4*>(qs + ((int64_t)head * pieces + p) * 16);
-            *reinterpret_cast<u32x4*>(s_q + head * kQRow + p * 16) = x;
-        }
-    }
     const E* kpool = (const E*)a.c.k;
     const E* vpool = (const E*)a.c.v;
     auto load = [&](X& x, int i) {                           // sub-step i of the wave
         if constexpr (kBf16) {
-            const int64_t pA = __builtin_amdgcn_readlane(my_pid, 2 * i), pB = __builtin_amdgcn_readlane(my_pid, 2 * i + 1);
-            const int gA = min(2 * (my_u + i), last_grp) & gmask, gB = min(2 * (my_u + i) + 1, last_grp) & gmask;
+            const int grp = 2 * (first + kStride * i);       // (the second group may lie behind the last one)
+            const int64_t pA = __builtin_amdgcn_readlane(my_pid, 2 * i), pB = grp < last_grp ? __builtin_amdgcn_readlane(my_pid, 2 * i + 1) : pA;
+            const int gA = grp & gmask, gB = min(grp + 1, last_grp) & gmask;
             const int64_t baseA = (pA * hkv + g) * block, baseB = (pB * hkv + g) * block;
             const E* kp = kpool + (r >> 3 ? baseB + gB * 128 : baseA + gA * 128) + k_slot;
             const E* vp = vpool + (c >> 1 ? baseB + gB * 16 * D : baseA + gA * 16 * D) + v_lane;
@@ -117,7 +120,7 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, int s, int g, in
             for (int mb = 0; mb < X::kV; ++mb) x.v[mb] = load16(vp + (kExact ? mb * 16 + r : min(mb * 16 + r, D - 1)) * 8);
         } else {
             const int64_t p = __builtin_amdgcn_readlane(my_pid, i);
-            const int gi = min(2 * my_u + i, last_grp) & gmask;
+            const int gi = min(first + kStride * i, last_grp) & gmask;
             const int64_t at = (p * hkv + g) * block;
             const E* kp = kpool + at + gi * 128 + k_slot;
             const E* vp = vpool + at + gi * 16 * D + v_lane;
@@ -140,7 +143,7 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, int s, int g, in
 
     auto compute = [&](X& x, int i) {
         constexpr int kScores = kBf16 ? 8 : 4;
-        const int tok0 = my_u * 32 + i * X::kTok;
+        const int tok0 = (first + kStride * i) * X::kTok;
         const int tokb = kBf16 ? tok0 + (c >> 1) * 16 + (c & 1) * 4 : tok0 + c * 4;
         const int keep = ctx - tokb;                         // token tokb + j exists iff j < keep
         f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
@@ -217,7 +220,6 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, int s, int g, in
         }
     };
 
-    const int subs = my_n * kSub;
     if constexpr (kTwoInFlight) {
         X x0, x1;
         if (subs > 0) load(x0, 0);
@@ -285,7 +287,11 @@ __global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, in
 
         float m, lsum;
         f32x4 o[DT / 16];
-        attend_steps<E, DT, kExact, 256>(a, s, g, h0, nh, ctx, my_u, my_n, s_q, m, lsum, o);
+        constexpr int kSub = 32 / SubStep<E, DT>::kTok;          // sub-steps of a step
+        int my_pid = 0;
+        if (my_n > 0) my_pid = a.bt[(int64_t)s * a.max_pages + (min(2 * my_u + lane, (ctx - 1) >> 4) >> (a.c.ps_shift - 4))];
+        queries_to_lds<E, DT, kExact, 256>(a, s, g, h0, nh, s_q);
+        attend_steps<E, DT, kExact, 1>(a, g, ctx, my_u * kSub, my_n * kSub, my_pid, s_q, m, lsum, o);
 
         // o[mb][i] is O^T[channel mb * 16 + c * 4 + i][head r]; the four waves are merged in LDS, kChan channels at a time
         const int first_wg = (base + pair * n) / sh.q;           // the pair's segments are numbered from this workgroup
@@ -338,7 +344,7 @@ __global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, in
 // A batch of few, short contexts: one workgroup of eight waves per pair, which shares the pair's steps and writes the
 // result itself - no plan, no partials, no merge launch (see direct_preferred()).
 constexpr int kDirectWaves = 8;
-constexpr int kDirectMaxTokens = kDirectWaves * 32 * 32;         // page ids of a wave's steps: two per step, one per lane
+constexpr int kDirectMaxTokens = kDirectWaves * 32 * 32;
 
 template <typename E, int DT, bool kExact>
 __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel(AttnArgs a, int head_blocks)
@@ -357,17 +363,20 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
     const int s = blockIdx.x / heads, pair = blockIdx.x - s * heads;
     const int g = pair / head_blocks, h0 = (pair - g * head_blocks) * kCols;
     const int nh = min(kCols, G - h0);
-    const int ctx = min(a.ctx_lens[s], kDirectMaxTokens);
+    // The wave's sub-steps are every eighth, so that none has more than one over the others (runs of whole steps gave one wave
+    // four sub-steps of 16 tokens where three are the most: two fp32 sessions of 300 tokens, 4 / 2 heads x 64, append included, 11.3 ->
+    // 9.5 us; 64 of 60 at 32 / 8 x 128 19.8 -> 17.0; bf16 within 1 %), and which they are does not follow from the length: the page ids are fetched beside it.
+    constexpr int kTok = SubStep<E, DT>::kTok, kGroups = kTok / 16;
+    static_assert(kDirectMaxTokens <= kDirectWaves * (64 / kGroups) * kTok, "the page ids of a wave's sub-steps fit its lanes");
+    const int my_pid = a.bt[(int64_t)s * a.max_pages +
+                            min((kGroups * (w + kDirectWaves * (lane / kGroups)) + lane % kGroups) >> (a.c.ps_shift - 4), a.max_pages - 1)];
+    const int ctx = max(0, min(a.ctx_lens[s], kDirectMaxTokens));
+    queries_to_lds<E, DT, kExact, kThreads>(a, s, g, h0, nh, s_q);
+    const int n = (ctx + kTok - 1) / kTok, subs = w < n ? (n - w - 1) / kDirectWaves + 1 : 0;
     E* out = (E*)a.out + ((int64_t)s * hq + (int64_t)g * G + h0) * D;
-    if (ctx <= 0) {                     // uniform over the workgroup
-        for (int idx = tid; idx < nh * D; idx += kThreads) out[idx] = (E)0.0f;
-        return;
-    }
-    const int n = steps_of(ctx), per = (n + kDirectWaves - 1) / kDirectWaves;
-    const int my_u = w * per, my_n = max(0, min(per, n - my_u));
     float m, lsum;
     f32x4 o[DT / 16];
-    attend_steps<E, DT, kExact, kThreads>(a, s, g, h0, nh, ctx, my_u, my_n, s_q, m, lsum, o);
+    attend_steps<E, DT, kExact, kDirectWaves>(a, g, ctx, w, subs, my_pid, s_q, m, lsum, o);
 
     const int r = lane & 15, c = lane >> 4;
     auto power = [](float x) { return kBf16 ? __builtin_amdgcn_exp2f(x) : expf(x); };
@@ -382,7 +391,7 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
         for (int idx = tid; idx < nh * kChan; idx += kThreads) {
             const int head = idx / kChan, dl = idx - head * kChan;
             if (d0 + dl >= D) continue;
-            float ms = s_m[0][head];                             // wave 0 always has a step
+            float ms = s_m[0][head];                             // wave 0 has a step, if there is one
 #pragma unroll
             for (int ww = 1; ww < kDirectWaves; ++ww) ms = fmaxf(ms, s_m[ww][head]);
             float acc = 0.f, l = 0.f;
@@ -392,7 +401,7 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
                 acc += fw * s_o[ww][head][dl];
                 l += fw * s_l[ww][head];
             }
-            const float y = acc / l;
+            const float y = ctx > 0 ? acc / l : 0.f;
             out[head * D + d0 + dl] = (E)y;
             if (!(general::trouble_of(y) == 0.f)) atomicOr(&s_again, 1u << head);
         }
