@@ -1,9 +1,14 @@
-"""ctypes binding of libagattn.so: same names as include/ag.h, argument
+"""Binding of libagattn.so: same names as include/ag.h, argument
 marshalling only.  Every step of the path runs in the HIP kernels behind the
 C ABI; tensors are torch CUDA (ROCm) tensors used as device memory.
 
-There is no fallback: if the library is missing or was not built, importing
-`lib()` raises.
+The calls of a serving loop go through agcall.so (csrc/py_call.cpp), which takes
+plain arguments - contiguous GPU tensors of the right dtypes, ints, floats - at a
+fraction of what ctypes costs; what it does not take, and every other entry point,
+goes through ctypes.
+
+There is no fallback: if the library or the module is missing or was not built,
+using it raises.
 """
 from __future__ import annotations
 
@@ -15,6 +20,7 @@ import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libagattn.so")
+CALL_PATH = os.path.join(HERE, "agcall.so")
 
 AG_OK, AG_ERR_INVALID_ARG, AG_ERR_UNSUPPORTED, AG_ERR_WORKSPACE, AG_ERR_HIP, AG_ERR_NO_SPACE = 0, -1, -2, -3, -4, -5
 AG_F32, AG_BF16 = 0, 1
@@ -146,6 +152,30 @@ def lib():
     return l
 
 
+_native = None
+
+
+def _calls():
+    """The module the calls of a serving loop go through, bound to the library."""
+    global _native
+    if _native is None:
+        from importlib.machinery import ExtensionFileLoader
+        from importlib.util import module_from_spec, spec_from_file_location
+        l = lib()
+        if not os.path.exists(CALL_PATH):
+            raise ImportError(f"{CALL_PATH} is missing: build it with `python -m paper_2603_10342_amd.build` "
+                              "(or __graft_entry__.build())")
+        spec = spec_from_file_location("agcall", CALL_PATH, loader=ExtensionFileLoader("agcall", CALL_PATH))
+        m = module_from_spec(spec)
+        spec.loader.exec_module(m)
+        m.setup(KVCache, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream,
+                *(C.cast(getattr(l, name), C.c_void_p).value
+                  for name in ("ag_kv_append", "ag_attn_prefill", "ag_attn_resume", "ag_attn_decode",
+                               "ag_attn_decode_static", "ag_decode_step", "ag_attn_merged")))
+        _native = m
+    return _native
+
+
 def _check(status: int):
     if status != AG_OK:
         raise AgError(status, lib().ag_last_error().decode())
@@ -218,6 +248,9 @@ class KVCache:
 
 def ag_kv_append(cache: KVCache, k_new, v_new, block_tables, prefix_lens, new_lens, cu_new, total_new: int,
                  stream=None):
+    st = (_native or _calls()).kv_append(cache, k_new, v_new, block_tables, prefix_lens, new_lens, cu_new, total_new, stream)
+    if st is not None:
+        return _check(st)
     c = cache.c_struct()
     _check(lib().ag_kv_append(C.byref(c), _ptr(k_new), _ptr(v_new), _i32(block_tables), block_tables.shape[1],
                               _i32(prefix_lens), _i32(new_lens), _i32(cu_new), new_lens.shape[0], total_new,
@@ -226,6 +259,10 @@ def ag_kv_append(cache: KVCache, k_new, v_new, block_tables, prefix_lens, new_le
 
 def ag_attn_prefill(cache: KVCache, q, out, block_tables, new_lens, cu_new, total_new: int, max_new: int,
                     num_q_heads: int, scale: float, stream=None):
+    st = (_native or _calls()).attn_prefill(cache, q, out, block_tables, new_lens, cu_new, total_new, max_new, num_q_heads,
+                                           scale, stream)
+    if st is not None:
+        return _check(st)
     c = cache.c_struct()
     _check(lib().ag_attn_prefill(C.byref(c), _ptr(q), _ptr(out), _i32(block_tables), block_tables.shape[1],
                                  _i32(new_lens), _i32(cu_new), new_lens.shape[0], total_new, max_new, num_q_heads,
@@ -234,6 +271,10 @@ def ag_attn_prefill(cache: KVCache, q, out, block_tables, new_lens, cu_new, tota
 
 def ag_attn_resume(cache: KVCache, q, out, block_tables, prefix_lens, new_lens, cu_new, total_new: int,
                    max_new: int, max_ctx: int, num_q_heads: int, scale: float, stream=None):
+    st = (_native or _calls()).attn_resume(cache, q, out, block_tables, prefix_lens, new_lens, cu_new, total_new, max_new,
+                                          max_ctx, num_q_heads, scale, stream)
+    if st is not None:
+        return _check(st)
     c = cache.c_struct()
     _check(lib().ag_attn_resume(C.byref(c), _ptr(q), _ptr(out), _i32(block_tables), block_tables.shape[1],
                                 _i32(prefix_lens), _i32(new_lens), _i32(cu_new), new_lens.shape[0], total_new,
@@ -246,6 +287,10 @@ def ag_attn_decode_workspace_bytes(batch: int, num_q_heads: int, head_dim: int, 
 
 def ag_attn_decode(cache: KVCache, q, out, block_tables, ctx_lens, max_ctx: int, num_q_heads: int, scale: float,
                    workspace: torch.Tensor, stream=None):
+    st = (_native or _calls()).attn_decode(cache, q, out, block_tables, ctx_lens, max_ctx, num_q_heads, scale, workspace,
+                                          stream)
+    if st is not None:
+        return _check(st)
     c = cache.c_struct()
     _check(lib().ag_attn_decode(C.byref(c), _ptr(q), _ptr(out), _i32(block_tables), block_tables.shape[1],
                                 _i32(ctx_lens), ctx_lens.shape[0], max_ctx, num_q_heads, scale, _ptr(workspace),
@@ -257,6 +302,9 @@ AG_DECODE_STATIC_SCRATCH_BYTES = 32 << 20
 
 def ag_attn_decode_static(cache: KVCache, q, out, block_tables, ctx_lens, max_ctx: int, num_q_heads: int, scale: float,
                           stream=None):
+    st = (_native or _calls()).attn_decode_static(cache, q, out, block_tables, ctx_lens, max_ctx, num_q_heads, scale, stream)
+    if st is not None:
+        return _check(st)
     c = cache.c_struct()
     _check(lib().ag_attn_decode_static(C.byref(c), _ptr(q), _ptr(out), _i32(block_tables), block_tables.shape[1],
                                        _i32(ctx_lens), ctx_lens.shape[0], max_ctx, num_q_heads, scale,
@@ -273,6 +321,10 @@ def ag_decode_step_workspace_bytes(batch: int, num_q_heads: int, head_dim: int, 
 def ag_decode_step(cache: KVCache, k_new, v_new, q, out, block_tables, ctx_lens, max_ctx: int, num_q_heads: int,
                    scale: float, workspace: torch.Tensor, stream=None):
     """`workspace` must have been zero-filled once before its first use (every call leaves its counters zero)."""
+    st = (_native or _calls()).decode_step(cache, k_new, v_new, q, out, block_tables, ctx_lens, max_ctx, num_q_heads, scale,
+                                          workspace, stream)
+    if st is not None:
+        return _check(st)
     c = cache.c_struct()
     _check(lib().ag_decode_step(C.byref(c), _ptr(k_new), _ptr(v_new), _ptr(q), _ptr(out), _i32(block_tables),
                                 block_tables.shape[1], _i32(ctx_lens), ctx_lens.shape[0], max_ctx, num_q_heads, scale,
@@ -285,6 +337,10 @@ def ag_attn_merged_workspace_bytes(total_new: int, num_q_heads: int, max_ctx: in
 
 def ag_attn_merged(cache: KVCache, q, out, block_tables, prefix_lens, new_lens, cu_new, total_new: int,
                    max_new: int, max_ctx: int, num_q_heads: int, scale: float, workspace: torch.Tensor, stream=None):
+    st = (_native or _calls()).attn_merged(cache, q, out, block_tables, prefix_lens, new_lens, cu_new, total_new, max_new,
+                                          max_ctx, num_q_heads, scale, workspace, stream)
+    if st is not None:
+        return _check(st)
     c = cache.c_struct()
     _check(lib().ag_attn_merged(C.byref(c), _ptr(q), _ptr(out), _i32(block_tables), block_tables.shape[1],
                                 _i32(prefix_lens), _i32(new_lens), _i32(cu_new), new_lens.shape[0], total_new,

@@ -1,4 +1,5 @@
-"""Builds the HIP library in-tree: paper_2603_10342_amd/libagattn.so (gfx950 only)."""
+"""Builds the HIP library in-tree, paper_2603_10342_amd/libagattn.so (gfx950 only), and the module that calls it from
+Python, paper_2603_10342_amd/agcall.so (host code, against the installed torch)."""
 from __future__ import annotations
 
 import os
@@ -11,6 +12,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libagattn.so")
+CALL = os.path.join(HERE, "agcall.so")
 SOURCES = ["ag_api.hip", "kv_append.hip", "attn_general.hip", "attn_decode_mfma.hip", "attn_decode_any.hip", "attn_prefill_mfma.hip", "attn_prefill_any.hip", "attn_prefill_split.hip", "attn_prefill_f32.hip",
            "attn_merged_mfma.hip",
            "ag_sched.hip", "ag_pager.hip"]
@@ -52,5 +54,28 @@ def build(extra=(), verbose: bool = False, lib: str = LIB, tag: str = "") -> str
     return LIBP
 
 
+def build_call(verbose: bool = False) -> str:
+    """Compile and link the calling module (csrc/py_call.cpp)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = CALL + f".tmp{os.getpid()}"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I" + os.path.join(ROOT, "include"), "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "py_call.cpp"), "-o", tmp,
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode:
+        raise RuntimeError("g++ failed on py_call.cpp:\n" + r.stderr)
+    os.replace(tmp, CALL)
+    if verbose:
+        print("built", CALL)
+    return CALL
+
+
 if __name__ == "__main__":
     build(extra=sys.argv[1:], verbose=True)
+    build_call(verbose=True)

@@ -1,0 +1,74 @@
+"""The calling module (csrc/py_call.cpp) against the ctypes path it stands in front of: what it does not take raises as before,
+and what it takes gives the same bits and the same errors."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_10342_amd import binding as B
+
+
+def small(device, dtype=torch.bfloat16):
+    cache = B.KVCache(8, 16, 2, 128, B.AG_BF16, device, fill=0.0)
+    x = lambda *s: torch.zeros(s, dtype=dtype, device=device)
+    i = lambda *v: torch.tensor(v, dtype=torch.int32, device=device)
+    return cache, x, i
+
+
+def test_the_module_takes_no_host_tensors_and_ctypes_says_why():
+    cache, x, i = small("cpu")
+    bt = i(0, 1).view(1, 2)
+    args = [cache, x(1, 2, 128), x(1, 2, 128), bt, i(0), i(1), i(0, 1), 1, None]
+    assert B._calls().kv_append(*args) is None
+    with pytest.raises(ValueError, match="contiguous CUDA"):
+        B.ag_kv_append(*args)
+    with pytest.raises(TypeError, match="int32"):
+        B.ag_attn_prefill(cache, None, None, bt.long(), i(1), i(0, 1), 1, 1, 4, 0.1)
+    assert B._calls().kv_append(*args[:-1]) is None                    # too few
+
+
+@pytest.mark.gpu
+def test_plain_calls_equal_the_ctypes_path_and_others_are_refused_as_there():
+    torch.manual_seed(5)
+    cache, x, i = small("cuda")
+    n = [20, 1]
+    r = lambda *s: torch.randn(s, dtype=torch.bfloat16, device="cuda")
+    bt, prefix, new, cu, ctx = i(0, 1, 2, 3).view(2, 2), i(0, 0), i(*n), i(0, 20, 21), i(*n)
+    k, v, q = r(21, 2, 128), r(21, 2, 128), r(21, 8, 128)
+    ws = torch.zeros(1 << 16, dtype=torch.float32, device="cuda")
+    outs = []
+    # a torch stream is what the module leaves to ctypes; keywords and positions alike
+    for stream in (None, torch.cuda.current_stream()):
+        c2 = B.KVCache(8, 16, 2, 128, B.AG_BF16, "cuda", fill=0.0)
+        o = [torch.zeros_like(q) for _ in range(3)] + [torch.zeros_like(q[:2])]
+        B.ag_kv_append(c2, k, v, bt, prefix_lens=prefix, new_lens=new, cu_new=cu, total_new=21, stream=stream)
+        B.ag_attn_prefill(c2, q, o[0], bt, new, cu, 21, 20, 8, 0.09, stream=stream)
+        B.ag_attn_resume(c2, q, o[1], bt, prefix, new, cu, 21, 20, 20, 8, 0.09, stream)
+        B.ag_attn_merged(c2, q, o[2], bt, prefix, new, cu, 21, 20, 20, 8, 0.09, ws, stream)
+        B.ag_attn_decode(c2, q[:2], o[3], bt, ctx, 20, 8, 0.09, ws, stream)
+        st, ds = torch.zeros_like(o[3]), torch.zeros_like(o[3])
+        B.ag_attn_decode_static(c2, q[:2], ds, bt, ctx, 20, 8, 0.09, stream)
+        B.ag_decode_step(c2, k[:2], v[:2], q[:2], st, bt, i(21, 2), 21, 8, 0.09, torch.zeros(1 << 20, dtype=torch.float32, device="cuda"), stream)
+        torch.cuda.synchronize()
+        outs.append(o + [st, ds, c2.k_pool, c2.v_pool])
+    for a, b in zip(*outs):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16)) and bool(a.any())
+    plain = [cache, q[:2], x(2, 8, 128), bt, ctx, 20, 8, 0.09, ws, None]
+    call = B._calls().attn_decode
+    assert call(*plain) == B.AG_OK
+    for at, value in [(1, q[:2, ::2]), (1, q[:2].cpu()), (1, None), (1, torch.nn.Parameter(q[:2].float()).as_subclass(type("T", (torch.Tensor,), {}))),
+                      (3, bt.long()), (3, bt[0]), (5, 20.0), (5, np.int32(20)), (5, 1 << 40), (7, 1), (8, None), (9, "s")]:
+        args = list(plain)
+        args[at] = value
+        if at != 3 or value.dim() == 2:
+            assert call(*args) is None, at
+        if value is None and at == 1:
+            with pytest.raises(B.AgError):
+                B.ag_attn_decode(*args)
+        elif isinstance(value, float):
+            with pytest.raises(ctypes.ArgumentError):
+                B.ag_attn_decode(*args)
+    with pytest.raises(B.AgError) as e:                                # a host-side refusal, through the module
+        B.ag_attn_decode(*(plain[:5] + [33] + plain[6:]))
+    assert e.value.status == B.AG_ERR_INVALID_ARG and "max_pages" in str(e.value)
