@@ -21,6 +21,8 @@
 // head_dim 64, 32-token pages, 2238 -> 63.5 us (333 MB, 5.2 TB/s; 62.8 with weights in two terms); two fp32 sessions of 300, 4 / 2 heads x 64, 106 -> 12 us.
 // head_dim below its template's DT: loads beyond head_dim repeat its last channels; keys become zeros (as the query
 // does), values land in rows that are not stored.
+#include <type_traits>
+
 #include "attn_general_row.h"
 #include "attn_split_common.h"
 #include "bf16_terms.h"
@@ -254,7 +256,7 @@ __global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, in
 {
     constexpr bool kBf16 = sizeof(E) == 2;
     constexpr int kChan = DT < 128 ? DT : 128;                   // channels the waves' results go through LDS at a time
-    __shared__ float s_o[4][kCols][kChan];
+    __shared__ __attribute__((aligned(16))) float s_o[4][kCols][kChan];
     __shared__ float s_m[4][kCols];
     __shared__ float s_l[4][kCols];
     __shared__ __attribute__((aligned(16))) unsigned char s_q[kCols * q_row<E, DT>()];
@@ -303,21 +305,24 @@ __global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, in
             for (int mb = 0; mb < kChan / 16; ++mb) *reinterpret_cast<f32x4*>(&s_o[w][r][mb * 16 + c * 4]) = o[d0 / 16 + mb];
             __syncthreads();
             if (piece < pmax) {
-                for (int idx = tid; idx < nh * kChan; idx += 256) {
-                    const int head = idx / kChan, dl = idx - head * kChan, d = d0 + dl;
+                for (int idx = tid; idx < nh * (kChan / 4); idx += 256) {        // four channels a thread
+                    const int head = idx / (kChan / 4), dl = (idx - head * (kChan / 4)) * 4, d = d0 + dl;
                     if (d >= D) continue;
                     float ms = s_m[0][head];                     // wave 0 always has a step: finite unless the scores are not
 #pragma unroll
                     for (int ww = 1; ww < 4; ++ww) ms = fmaxf(ms, s_m[ww][head]);
-                    float acc = 0.f, l = 0.f;
+                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                    float l = 0.f;
 #pragma unroll
                     for (int ww = 0; ww < 4; ++ww) {
                         const float fw = power(s_m[ww][head] - ms);        // a wave without steps has m = -inf -> 0
-                        acc += fw * s_o[ww][head][dl];
+                        const f32x4 x = *reinterpret_cast<const f32x4*>(&s_o[ww][head][dl]);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[e] += fw * x[e];
                         l += fw * s_l[ww][head];
                     }
                     const int64_t slot = ((int64_t)s * hq + (int64_t)g * G + h0 + head) * pmax + piece;
-                    ws_o[slot * D + d] = acc;
+                    *reinterpret_cast<f32x4*>(ws_o + slot * D + d) = acc;
                     if (d == 0) { ws_ml[slot * 2] = ms; ws_ml[slot * 2 + 1] = l; }
                 }
             }
@@ -351,7 +356,7 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
 {
     constexpr bool kBf16 = sizeof(E) == 2;
     constexpr int kChan = 64, kThreads = 64 * kDirectWaves;
-    __shared__ float s_o[kDirectWaves][kCols][kChan];
+    __shared__ __attribute__((aligned(16))) float s_o[kDirectWaves][kCols][kChan];
     __shared__ float s_m[kDirectWaves][kCols];
     __shared__ float s_l[kDirectWaves][kCols];
     __shared__ uint32_t s_again;                                 // bit h: head h has an element that is not finite
@@ -388,23 +393,38 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
 #pragma unroll
         for (int mb = 0; mb < kChan / 16; ++mb) *reinterpret_cast<f32x4*>(&s_o[w][r][mb * 16 + c * 4]) = o[d0 / 16 + mb];
         __syncthreads();
-        for (int idx = tid; idx < nh * kChan; idx += kThreads) {
-            const int head = idx / kChan, dl = idx - head * kChan;
-            if (d0 + dl >= D) continue;
-            float ms = s_m[0][head];                             // wave 0 has a step, if there is one
+        // One channel a thread while that is one each (half the latency), four beyond.
+        auto combine = [&](auto channels) {
+            constexpr int N = decltype(channels)::value;
+            for (int idx = tid; idx < nh * (kChan / N); idx += kThreads) {
+                const int head = idx / (kChan / N), dl = (idx - head * (kChan / N)) * N;
+                if (d0 + dl >= D) continue;
+                float ms = s_m[0][head];                         // wave 0 has a step, if there is one
 #pragma unroll
-            for (int ww = 1; ww < kDirectWaves; ++ww) ms = fmaxf(ms, s_m[ww][head]);
-            float acc = 0.f, l = 0.f;
+                for (int ww = 1; ww < kDirectWaves; ++ww) ms = fmaxf(ms, s_m[ww][head]);
+                float acc[N] = {}, l = 0.f;
 #pragma unroll
-            for (int ww = 0; ww < kDirectWaves; ++ww) {
-                const float fw = power(s_m[ww][head] - ms);      // a wave without steps has m = -inf -> 0
-                acc += fw * s_o[ww][head][dl];
-                l += fw * s_l[ww][head];
+                for (int ww = 0; ww < kDirectWaves; ++ww) {
+                    const float fw = power(s_m[ww][head] - ms);  // a wave without steps has m = -inf -> 0
+                    l += fw * s_l[ww][head];
+                    typedef float numbers __attribute__((ext_vector_type(N)));
+                    const numbers x = *reinterpret_cast<const numbers*>(&s_o[ww][head][dl]);
+#pragma unroll
+                    for (int e = 0; e < N; ++e) acc[e] += fw * x[e];
+                }
+                float trouble = 0.f;
+#pragma unroll
+                for (int e = 0; e < N; ++e) {
+                    acc[e] = ctx > 0 ? acc[e] / l : 0.f;
+                    trouble = general::trouble_of(acc[e], trouble);
+                }
+                if constexpr (N == 4) splitk::store_quad(out + head * D + d0 + dl, acc);
+                else out[head * D + d0 + dl] = (E)acc[0];
+                if (!(trouble == 0.f)) atomicOr(&s_again, 1u << head);
             }
-            const float y = ctx > 0 ? acc / l : 0.f;
-            out[head * D + d0 + dl] = (E)y;
-            if (!(general::trouble_of(y) == 0.f)) atomicOr(&s_again, 1u << head);
-        }
+        };
+        if (nh * kChan <= kThreads) combine(std::integral_constant<int, 1>{});
+        else combine(std::integral_constant<int, 4>{});
     }
     __syncthreads();                                             // (weights in terms turn an infinite sum into NaN)
     const uint32_t all = __builtin_amdgcn_readfirstlane(s_again);

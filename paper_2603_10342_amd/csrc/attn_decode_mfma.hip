@@ -40,6 +40,7 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "attn_split_common.h"
 
@@ -377,20 +378,32 @@ __global__ __launch_bounds__(64 * kDirectWaves, 4) void decode_direct_kernel(Att
         if (c == 0) { s_m[w * G + r] = m; s_l[w * G + r] = lsum; }
     }
     __syncthreads();
-    for (int idx = tid; idx < G * D; idx += 64 * kDirectWaves) {
-        const int head = idx >> 7, d = idx & (D - 1);
-        float ms = s_m[head];                               // wave 0 always has a step: finite
+    // One channel a thread while that is one each (half the latency), four beyond.
+    auto combine = [&](auto channels) {
+        constexpr int N = decltype(channels)::value;
+        for (int idx = tid; idx < G * (D / N); idx += 64 * kDirectWaves) {
+            const int head = idx / (D / N), d = (idx & (D / N - 1)) * N;
+            float ms = s_m[head];                               // wave 0 always has a step: finite
 #pragma unroll
-        for (int ww = 1; ww < kDirectWaves; ++ww) ms = fmaxf(ms, s_m[ww * G + head]);
-        float acc = 0.f, l = 0.f;
+            for (int ww = 1; ww < kDirectWaves; ++ww) ms = fmaxf(ms, s_m[ww * G + head]);
+            float acc[N] = {}, l = 0.f;
 #pragma unroll
-        for (int ww = 0; ww < kDirectWaves; ++ww) {
-            const float fw = exp2f(s_m[ww * G + head] - ms);               // a wave without steps has m = -inf -> 0
-            acc += fw * s_dyn[(ww * G + head) * D + d];
-            l += fw * s_l[ww * G + head];
+            for (int ww = 0; ww < kDirectWaves; ++ww) {
+                const float fw = exp2f(s_m[ww * G + head] - ms);               // a wave without steps has m = -inf -> 0
+                l += fw * s_l[ww * G + head];
+                typedef float numbers __attribute__((ext_vector_type(N)));
+                const numbers x = *reinterpret_cast<const numbers*>(s_dyn + (ww * G + head) * D + d);
+#pragma unroll
+                for (int e = 0; e < N; ++e) acc[e] += fw * x[e];
+            }
+#pragma unroll
+            for (int e = 0; e < N; ++e) acc[e] /= l;
+            if constexpr (N == 4) store_quad(out + head * D + d, acc);
+            else out[idx] = (__bf16)acc[0];
         }
-        out[idx] = (__bf16)(acc / l);
-    }
+    };
+    if (G * D <= 64 * kDirectWaves) combine(std::integral_constant<int, 1>{});
+    else combine(std::integral_constant<int, 4>{});
 }
 
 constexpr int kMergeRows = 8;               // (session, query head) rows of a merge workgroup, 32 lanes each

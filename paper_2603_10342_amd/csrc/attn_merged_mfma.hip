@@ -222,22 +222,25 @@ __device__ __forceinline__ void stream_segment(const AttnArgs& a, float* __restr
     __syncthreads();
     if (sg.piece < pmax) {
         const int n_cols = min(tq, nt) * G;
-        for (int idx = threadIdx.x; idx < n_cols * D; idx += 256) {
-            const int col = idx >> 7, d = idx & (D - 1);
+        for (int idx = threadIdx.x; idx < n_cols * (D / 4); idx += 256) {              // four channels a thread
+            const int col = idx >> 5, d = (idx & (D / 4 - 1)) * 4;
             float ms = s_m[0][col];
 #pragma unroll
             for (int ww = 1; ww < 4; ++ww) ms = fmaxf(ms, s_m[ww][col]);
-            float acc = 0.f, lt = 0.f;
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            float lt = 0.f;
 #pragma unroll
             for (int ww = 0; ww < 4; ++ww) {
                 const float mw = s_m[ww][col];
                 const float f = mw == -INFINITY ? 0.f : exp2f(mw - ms);    // a wave that saw no key of this column
-                acc += f * s_o[ww][col][d];
+                const f32x4 x = *reinterpret_cast<const f32x4*>(&s_o[ww][col][d]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] += f * x[e];
                 lt += f * s_l[ww][col];
             }
             const int crow = col / G, chead = col - crow * G;
             const int64_t slot = (((int64_t)a.cu_new[s] + t0 + crow) * hq + (int64_t)g * G + chead) * pmax + sg.piece;
-            ws_o[slot * D + d] = acc;
+            *reinterpret_cast<f32x4*>(ws_o + slot * D + d) = acc;
             if (d == 0) { ws_ml[slot * 2] = ms; ws_ml[slot * 2 + 1] = lt; }
         }
     }
