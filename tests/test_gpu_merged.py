@@ -55,6 +55,32 @@ def test_merged_batch_matches_oracle(name):
     check_close(got, ref, g.dtype, name)
 
 
+ON_A_PARTITION = [(n, 8, 2) for n in sorted(MIXES)] + [("few_rows", *h) for h in [(4, 4), (32, 8), (16, 2), (16, 1), (6, 2)]]
+
+
+@pytest.mark.parametrize("name,hq,hkv", ON_A_PARTITION)
+def test_both_sides_of_the_line_to_the_split_prefill(name, hq, hkv):
+    """Queues around the rule that hands small ones to the prefill kernel which splits a tile's keys: what is a small queue on the
+    whole device is a large one on 8 CUs, where the merged kernel keeps it.  Both against the oracle."""
+    prefix, new = MIXES.get(name) or ([900, 1500, 31, 0, 2100, 300], [9, 33, 1, 65, 1, 3])
+    g = geom(pages=2048, hq=hq, hkv=hkv)
+    cache, kp, vp, chunk = filled(g, prefix, new, seed=340 + len(name))
+    ref = oracle_attn(kp, vp, chunk)
+    d = DevBatch(chunk)
+    check_close(gpu_merged(cache, d), ref, g.dtype, name)
+    info = B.ag_device_info()
+    stream = B.ag_stream_create_cumask(B.ag_cumask_build(info["num_cus"], info["num_xcd"] or 8, 0, 1))
+    try:
+        ws = torch.full((B.ag_attn_merged_workspace_bytes(d.total, hq, d.max_ctx) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+        out = torch.full_like(d.q, float("nan"))
+        torch.cuda.synchronize()
+        B.ag_attn_merged(cache, d.q, out, d.bt, d.prefix, d.new, d.cu, d.total, d.max_new, d.max_ctx, hq, g.scale, ws, stream)
+        torch.cuda.synchronize()
+        check_close(to_f64(out, g.dtype), ref, g.dtype, name)
+    finally:
+        B.ag_stream_destroy(stream)
+
+
 @pytest.mark.parametrize("hq,hkv", [(4, 4), (8, 4), (32, 8), (16, 2), (16, 1), (6, 2), (40, 8)])
 def test_merged_batch_group_sizes(hq, hkv):
     """G = 1, 2, 4, 8, 16 fill the 16 columns exactly; 3 and 5 leave one unused."""
