@@ -19,10 +19,15 @@
 // the layouts of the bf16 kernels, [chunk of 8 channels][key][8] and [chunk of 8 keys][channel][8], two stages.
 // Weights are split in registers.  What bounds it is matrix and vector work one after the other: 96 products of 32 clocks a
 // tile and wave at 128 channels against 128 of 64, and about as much in softmax, splitting and operand reads.
-// Measured, append included, 32 / 8 heads, fp32 products -> terms: four prompts of 300..1500 rows, 128 channels 384 -> 306
-// us (117 TFLOP/s of result), 64 channels 208 -> 142; eight of 2048, 2510 -> 1848; eight chunks of 40..500 on 500..4000
-// tokens 1020 -> 680; 32 of 10..60 on 1000, 309 -> 231.  Scores in three accumulators and value products grouped by term:
-// 3..5 % slower.  The watch on small numbers is 0.4..1.6 % of it, all in the epilogue.
+// Measured, append included, 32 / 8 heads, fp32 products -> terms: four prompts of 300..1500 rows, 128 channels 384 -> 292
+// us (123 TFLOP/s of result); eight of 2048, 2510 -> 1820.  Scores in three accumulators and value products grouped by
+// term: 3..5 % slower.  The watch on small numbers is 0.4..1.6 % of it, all in the epilogue.
+//
+// A weight is 2^(s scale log2(e) - m): an exp2, the unit, and two fused products that take a score's two accumulators as
+// they are, so that their sum is rounded after m is off it.  Before, e^x as 2^t with the rounding of t put back took seven
+// more instructions on an x that had been rounded where it was large.  Four prompts of 300..1500 rows 306 -> 292 us; eight of
+// 2048, 128 channels 1912 -> 1827, 64 channels 917 -> 874; eight chunks of 120..300 rows 420 -> 395 and 230 -> 216.  Error
+// against 64 bits over 24 batches 0.972 to 0.998 of what it was (with the sum rounded first 0.994 to 1.006).
 #include <algorithm>
 #include <atomic>
 
@@ -43,7 +48,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kColumns = 128;           // (token, head) pairs of a workgroup
 constexpr int BN = 32;                  // keys per tile
 constexpr int kRowsAgain = 4;           // rows taken again together (attn_general_row.h)
-constexpr float kSlack = 5.5f;          // how far a maximum may outgrow the reference before O is rescaled
+constexpr float kSlack = 8.0f;          // how far (in powers of two) a maximum may outgrow the reference before O is rescaled
 
 constexpr float kLargeQuery = 0x1p90f;  // scale * |q| up to which what small keys lose (2^-126, times 128 channels) is nothing
 
@@ -62,16 +67,6 @@ constexpr int lds_bytes(int dt) { return 12 * plane_bytes(dt); }    // two stage
 
 constexpr float kWeightUnit = 0x1p48f;  // what a weight of 1 is multiplied as; their sum is in the same unit
 
-// 2^48 e^x for x <= 0 or little above: 2^t with the rounding of t = x log2(e) put back to first order (within 2 units in the
-// last place, eight instructions).  -inf gives 0, NaN stays NaN.
-__device__ __forceinline__ float exp_near(float x)
-{
-    x = x < -200.f ? -200.f : x;
-    const float t = x * 1.44269502f;
-    const float r = fmaf(x, 1.92596299e-8f, fmaf(x, 1.44269502f, -t));        // log2(e) = 1.44269502 + 1.926e-8
-    return __builtin_amdgcn_exp2f(t) * fmaf(r, 0.693147182f * kWeightUnit, kWeightUnit);
-}
-
 __device__ __forceinline__ Terms split8(const f32x4& a, const f32x4& b)
 {
     Terms t;
@@ -85,8 +80,9 @@ __device__ __forceinline__ f32x16 product(const u32x4& a, const u32x4& b, const 
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// unit: scale log2(e), as weights are taken as powers of two
 template <int DT>
-__global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnArgs a, int tiles_max, int per_xcd, int total_work)
+__global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnArgs a, float unit, int tiles_max, int per_xcd, int total_work)
 {
     constexpr int kPlane = plane_bytes(DT);
     constexpr int kUnits = BN * DT / 8 / 256;       // runs of eight numbers a thread moves of a K tile, and of a V tile
@@ -209,7 +205,7 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
     __syncthreads();
 
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float x[16];                                                // S(t), then what is left to exponentiate
+    float x[16], y[16];                                         // S(t) is x + y
     Terms pf[2];                                                // the weights of tile t
     // S of tile t into s0 + s1 (the h h products, and all smaller ones), with piece(i) of other work behind operand i's products
     constexpr int kScoreSteps = 3 * (DT / 16);                  // operand i: k-step i / 3, term i % 3
@@ -242,7 +238,7 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
         f32x16 s0, s1;
         scores(0, s0, s1, [](int) {});
 #pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = s0[i] + s1[i];
+        for (int i = 0; i < 16; ++i) x[i] = s0[i], y[i] = s1[i];
     }
     __syncthreads();                                            // every wave has read K(0): iteration 0 writes K(2) in its place
 
@@ -271,14 +267,18 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
                     x[i] = kk <= qpos ? x[i] : -INFINITY;
                 }
             }
-            float mx = fmaxf(fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7]))),
-                             fmaxf(fmaxf(fmaxf(x[8], x[9]), fmaxf(x[10], x[11])), fmaxf(fmaxf(x[12], x[13]), fmaxf(x[14], x[15]))));
-            mx *= a.scale;                                      // scale > 0: max and scaling commute
+            float top[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                top[i] = fmaxf(fmaxf(x[i] + y[i], x[i + 4] + y[i + 4]), fmaxf(x[i + 8] + y[i + 8], x[i + 12] + y[i + 12]));
+            }
+            float mx = fmaxf(fmaxf(top[0], top[1]), fmaxf(top[2], top[3]));
+            mx *= unit;                                         // scale > 0: max and scaling commute
             // m is shared by the two lanes of a column: if either lane's own maximum outgrew it, combine them
             if (__builtin_amdgcn_ballot_w64(mx > m + kSlack) != 0) {
                 mx = fmaxf(mx, __shfl_xor(mx, 32));
                 const float m_new = fmaxf(m, mx);
-                const float alpha = m_new == -INFINITY ? 1.f : expf(m - m_new);
+                const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
                 lsum *= alpha;
 #pragma unroll
                 for (int mb = 0; mb < kMb; ++mb)
@@ -290,9 +290,10 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
             float psum[2] = {0.f, 0.f};
             auto weigh = [&](int j) {                           // pair j of eight
                 const int i = 2 * j;
-                float scale = a.scale;
+                float scale = unit;
                 asm volatile("" : "+s"(scale));                 // (here, not all pairs ahead of the products: 4 % of the kernel)
-                const float p0 = exp_near(fmaf(x[i], scale, -m_ref)), p1 = exp_near(fmaf(x[i + 1], scale, -m_ref));
+                const float p0 = __builtin_amdgcn_exp2f(fmaf(y[i], scale, fmaf(x[i], scale, -m_ref))) * kWeightUnit;
+                const float p1 = __builtin_amdgcn_exp2f(fmaf(y[i + 1], scale, fmaf(x[i + 1], scale, -m_ref))) * kWeightUnit;
                 psum[0] += p0;
                 psum[1] += p1;
                 pf[i >> 3].set_pair((i & 7) >> 1, p0, p1);
@@ -308,7 +309,7 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
                     }
                 });
 #pragma unroll
-                for (int i = 0; i < 16; ++i) x[i] = s0[i] + s1[i];
+                for (int i = 0; i < 16; ++i) x[i] = s0[i], y[i] = s1[i];
             } else {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) weigh(j);
@@ -433,9 +434,10 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
         ag_status e = allow_dynamic_lds((const void*)prefill_f32_kernel<DT>, lds, told);
         if (e) return e;
     }
+    const float unit = (float)(a.scale * 1.4426950408889634);
     const int64_t tiles_max = tiles_bound(a), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
     prof_before(st);
-    hipLaunchKernelGGL((prefill_f32_kernel<DT>), dim3((unsigned)(per_xcd * 8)), dim3(256), lds, st, a, (int)tiles_max, (int)per_xcd, (int)total);
+    hipLaunchKernelGGL((prefill_f32_kernel<DT>), dim3((unsigned)(per_xcd * 8)), dim3(256), lds, st, a, unit, (int)tiles_max, (int)per_xcd, (int)total);
     prof_after(st);
     return hip_check(hipGetLastError(), "prefill launch");
 }
