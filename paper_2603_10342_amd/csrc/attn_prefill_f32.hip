@@ -18,10 +18,17 @@
 // registers while the current one is multiplied, splits it - once for all four waves - and writes the terms to LDS in
 // the layouts of the bf16 kernels, [chunk of 8 channels][key][8] and [chunk of 8 keys][channel][8], two stages.
 // Weights are split in registers.  What bounds it is matrix and vector work one after the other: 96 products of 32 clocks a
-// tile and wave at 128 channels against 128 of 64, and about as much in softmax, splitting and operand reads.
-// Measured, append included, 32 / 8 heads, fp32 products -> terms: four prompts of 300..1500 rows, 128 channels 384 -> 292
-// us (123 TFLOP/s of result); eight of 2048, 2510 -> 1820.  Scores in three accumulators and value products grouped by
+// tile and wave at 128 channels against 128 of 64, and less than that in softmax, splitting and operand reads.
+// Measured, append included, 32 / 8 heads, fp32 products -> terms: four prompts of 300..1500 rows, 128 channels 384 -> 264
+// us (136 TFLOP/s of result); eight of 2048, 2510 -> 1640.  Scores in three accumulators and value products grouped by
 // term: 3..5 % slower.  The watch on small numbers is 0.4..1.6 % of it, all in the epilogue.
+//
+// A wave issues in order, and a matrix product behind another holds up the vector work behind it: the weights and the
+// splitting are cut into pieces of a few instructions, one behind each product (a pair at once behind every third operand
+// before), the maximum of S(t + 1) is taken beside the value product of tile t, and rescaling is outside the tile loop (below).
+// 128 channels: 96 products are 46 % of an iteration's clocks, 530 vector instructions 36 %.  Eight prompts of 2048 rows
+// 1790 -> 1640 us, eight chunks of 120..300 rows 390 -> 352, 64 channels 852 -> 815 and 212 -> 203; the results are the same
+// bits.  Page ids in the lanes of a vector, scalar tile addresses, value products two operands at a time: 2..7 % slower each.
 //
 // A weight is 2^(s scale log2(e) - m): an exp2, the unit, and two fused products that take a score's two accumulators as
 // they are, so that their sum is rounded after m is off it.  Before, e^x as 2^t with the rounding of t put back took seven
@@ -142,8 +149,6 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
             vx[i][1] = p[1];
         }
     };
-    // What the fetches brought is split a pair at a time, so that the value product can hide it: pair c of the thread's
-    // 8 kUnits (K first), whose run goes to LDS with its last pair.
     auto scrub = [&](int t) {                                   // slots past the last token may hold anything, NaN included
         if (ctx < (t + 1) * BN) {
 #pragma unroll
@@ -157,18 +162,33 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
             }
         }
     };
+    // What the fetches brought is split a pair at a time, and a pair a term at a time, so that the value product can hide it:
+    // pair c of the thread's 8 kUnits (K first), whose run goes to LDS with its last pair.
     Terms run_terms;
-    auto store_pair = [&](int c, unsigned char* k_stage, unsigned char* v_stage) {
+    float rest0, rest1;
+    auto store_part = [&](int c, int part, unsigned char* k_stage, unsigned char* v_stage) {
         const bool of_v = c >= 4 * kUnits;
         const int i = (c >> 2) % kUnits, e = c & 3;
         const f32x4& src = of_v ? vx[i][e >> 1] : kx[i][e >> 1];
-        run_terms.set_pair(e, src[2 * (e & 1)], src[2 * (e & 1) + 1]);
-        if (e == 3) {
-            unsigned char* at = (of_v ? v_stage : k_stage) + (tid + 256 * i) * 16;
-            *reinterpret_cast<u32x4*>(at) = run_terms.h;
-            *reinterpret_cast<u32x4*>(at + kPlane) = run_terms.m;
-            *reinterpret_cast<u32x4*>(at + 2 * kPlane) = run_terms.l;
+        if (part == 0) {
+            rest0 = src[2 * (e & 1)];
+            rest1 = src[2 * (e & 1) + 1];
+            run_terms.h[e] = take_term(rest0, rest1);
+        } else if (part == 1) {
+            run_terms.m[e] = take_term(rest0, rest1);
+        } else {
+            run_terms.l[e] = pack(rest0, rest1);
+            if (e == 3) {
+                unsigned char* at = (of_v ? v_stage : k_stage) + (tid + 256 * i) * 16;
+                *reinterpret_cast<u32x4*>(at) = run_terms.h;
+                *reinterpret_cast<u32x4*>(at + kPlane) = run_terms.m;
+                *reinterpret_cast<u32x4*>(at + 2 * kPlane) = run_terms.l;
+            }
         }
+    };
+    auto store_pair = [&](int c, unsigned char* k_stage, unsigned char* v_stage) {
+#pragma unroll
+        for (int part = 0; part < 3; ++part) store_part(c, part, k_stage, v_stage);
     };
     constexpr int kPairs = 8 * kUnits;
     unsigned char* const k_lds = lds;                           // K tile t lives at k_lds + (t & 1) * 3 * kPlane
@@ -206,8 +226,11 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
 
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float x[16], y[16];                                         // S(t) is x + y
+    float top[4];                                               // the largest scores of tile t
+    auto look = [&](int i) { top[i & 3] = i < 4 ? x[i] + y[i] : fmaxf(top[i & 3], x[i] + y[i]); };
     Terms pf[2];                                                // the weights of tile t
-    // S of tile t into s0 + s1 (the h h products, and all smaller ones), with piece(i) of other work behind operand i's products
+    // S of tile t into s0 + s1 (the h h products, and all smaller ones), with piece(i) of other work behind product i
+    constexpr int kProducts = 6 * (DT / 16);                    // of a score tile, and of a value tile
     constexpr int kScoreSteps = 3 * (DT / 16);                  // operand i: k-step i / 3, term i % 3
     auto scores = [&](int t, f32x16& s0, f32x16& s1, auto piece) {
         const unsigned char* kb = k_lds + (t & 1) * 3 * kPlane + hi * 512 + n * 16;
@@ -220,25 +243,31 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
             if (i + kAhead < kScoreSteps) ring[(i + kAhead) % (kAhead + 1)] = at(i + kAhead);
             const u32x4 k = ring[i % (kAhead + 1)];
             const Terms& q = qf[i / 3];
+            auto add = [&](f32x16& sum, const u32x4& part, int j) {           // product 6 (i / 3) + j
+                sum = product(k, part, i == 0 && j < 2 ? zero : sum);
+                piece(6 * (i / 3) + j);
+                __builtin_amdgcn_sched_barrier(0);
+            };
             if (i % 3 == 0) {
-                s1 = product(k, q.l, i == 0 ? zero : s1);
-                s0 = product(k, q.h, i == 0 ? zero : s0);
-                s1 = product(k, q.m, s1);
+                add(s1, q.l, 0);
+                add(s0, q.h, 1);
+                add(s1, q.m, 2);
             } else if (i % 3 == 1) {
-                s1 = product(k, q.m, s1);
-                s1 = product(k, q.h, s1);
+                add(s1, q.m, 3);
+                add(s1, q.h, 4);
             } else {
-                s1 = product(k, q.h, s1);
+                add(s1, q.h, 5);
             }
-            piece(i);
-            __builtin_amdgcn_sched_barrier(0);
         }
     };
     {
         f32x16 s0, s1;
         scores(0, s0, s1, [](int) {});
 #pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = s0[i], y[i] = s1[i];
+        for (int i = 0; i < 16; ++i) {
+            x[i] = s0[i], y[i] = s1[i];
+            look(i);
+        }
     }
     __syncthreads();                                            // every wave has read K(0): iteration 0 writes K(2) in its place
 
@@ -246,107 +275,137 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
     // K(t + 2) and V(t + 1) (vector), which were fetched at its start: one wave per SIMD at 128 channels, so what overlaps is
     // what the wave itself interleaves.  One barrier an iteration: the places it writes, of K(t) and V(t - 1), were last read
     // in iteration t - 1 (K(0) above), before that iteration's barrier.
+    // A wave leaves the tile loop where a score outgrew its column's reference maximum, rescales O and enters it again: with
+    // the rescaling in the loop the compiler keeps O where vector instructions reach it, and copied the 64 accumulators of 128
+    // channels (matrix registers) there and S twice in every iteration, 166 copies, now 64.
 #pragma unroll 1
-    for (int t = 0; t < n_tiles; ++t) {
-        const bool more = t + 1 < n_tiles;                      // uniform
-        if (more) {
-            fetch_v(t + 1, v0, v1);
-            fetch_k(t + 2, k0, k1);
-            v0 = k0;
-            v1 = k1;
-            k0 = id_of(2 * (t + 3));
-            k1 = id_of(2 * (t + 3) + 1);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        const bool mine = t < wave_tiles, next = t + 1 < wave_tiles;
-        if (mine) {
-            if (t >= first_masked) {                            // the tile straddles this wave's diagonal
+    for (int t = 0;;) {
+        float mx = 0.f;
+#pragma unroll 1
+        for (; t < n_tiles; ++t) {
+            const bool mine = t < wave_tiles, next = t + 1 < wave_tiles;
+            if (mine) {
+                if (t >= first_masked) {                            // the tile straddles this wave's diagonal
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int kk = t * BN + (i >> 2) * 8 + hi * 4 + (i & 3);
-                    x[i] = kk <= qpos ? x[i] : -INFINITY;
-                }
-            }
-            float top[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                top[i] = fmaxf(fmaxf(x[i] + y[i], x[i + 4] + y[i + 4]), fmaxf(x[i + 8] + y[i + 8], x[i + 12] + y[i + 12]));
-            }
-            float mx = fmaxf(fmaxf(top[0], top[1]), fmaxf(top[2], top[3]));
-            mx *= unit;                                         // scale > 0: max and scaling commute
-            // m is shared by the two lanes of a column: if either lane's own maximum outgrew it, combine them
-            if (__builtin_amdgcn_ballot_w64(mx > m + kSlack) != 0) {
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
-                const float m_new = fmaxf(m, mx);
-                const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
-                lsum *= alpha;
-#pragma unroll
-                for (int mb = 0; mb < kMb; ++mb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) o[mb][i] *= alpha;
-                m = m_new;
-            }
-            const float m_ref = m == -INFINITY ? 0.f : m;
-            float psum[2] = {0.f, 0.f};
-            auto weigh = [&](int j) {                           // pair j of eight
-                const int i = 2 * j;
-                float scale = unit;
-                asm volatile("" : "+s"(scale));                 // (here, not all pairs ahead of the products: 4 % of the kernel)
-                const float p0 = __builtin_amdgcn_exp2f(fmaf(y[i], scale, fmaf(x[i], scale, -m_ref))) * kWeightUnit;
-                const float p1 = __builtin_amdgcn_exp2f(fmaf(y[i + 1], scale, fmaf(x[i + 1], scale, -m_ref))) * kWeightUnit;
-                psum[0] += p0;
-                psum[1] += p1;
-                pf[i >> 3].set_pair((i & 7) >> 1, p0, p1);
-            };
-            if (next) {
-                f32x16 s0, s1;
-                scores(t + 1, s0, s1, [&](int i) {              // eight pairs over the score product's steps
-                    constexpr int kPer = kScoreSteps / 8 > 0 ? kScoreSteps / 8 : 1;
-                    if constexpr (kScoreSteps >= 16) {
-                        if (i % kPer == 0 && i / kPer < 8) weigh(i / kPer);
-                    } else {
-                        if (i < 8) weigh(i);
+                    for (int i = 0; i < 16; ++i) {
+                        const int kk = t * BN + (i >> 2) * 8 + hi * 4 + (i & 3);
+                        x[i] = kk <= qpos ? x[i] : -INFINITY;
+                        look(i);
                     }
-                });
-#pragma unroll
-                for (int i = 0; i < 16; ++i) x[i] = s0[i], y[i] = s1[i];
-            } else {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) weigh(j);
+                }
+                mx = fmaxf(fmaxf(top[0], top[1]), fmaxf(top[2], top[3])) * unit;      // scale > 0: max and scaling commute
+                if (__builtin_amdgcn_ballot_w64(mx > m + kSlack) != 0) break;
             }
-            lsum += psum[0] + psum[1];
-        }
-        unsigned char* const k_to = k_lds + (t & 1) * 3 * kPlane;
-        unsigned char* const v_to = v_lds + ((t + 1) & 1) * 3 * kPlane;
-        if (more) scrub(t + 1);
-        if (mine) {
-            const unsigned char* vb = v_lds + (t & 1) * 3 * kPlane + hi * DT * 16 + n * 16;
-            constexpr int kN = 6 * kMb;                         // operand i: k-step, term, channel block
-            u32x4 ring[kAhead + 1];
-            auto at = [&](int i) {
-                return *reinterpret_cast<const u32x4*>(vb + ((i / kMb) % 3) * kPlane + (i / (3 * kMb)) * DT * 32 + (i % kMb) * 512);
-            };
-#pragma unroll
-            for (int i = 0; i < kAhead; ++i) ring[i] = at(i);
-#pragma unroll
-            for (int i = 0; i < kN; ++i) {
-                if (i + kAhead < kN) ring[(i + kAhead) % (kAhead + 1)] = at(i + kAhead);
-                const u32x4 v = ring[i % (kAhead + 1)];
-                const Terms& p = pf[i / (3 * kMb)];
-                f32x16& acc = o[i % kMb];
-                const int term = (i / kMb) % 3;
-                if (term == 0) acc = product(v, p.l, acc);
-                if (term <= 1) acc = product(v, p.m, acc);
-                acc = product(v, p.h, acc);
-                if (i < kPairs) store_pair(i, k_to, v_to);      // (past the last tile: what is there once more, never read)
-                __builtin_amdgcn_sched_barrier(0);
+            const bool more = t + 1 < n_tiles;                      // uniform
+            if (more) {
+                fetch_v(t + 1, v0, v1);
+                fetch_k(t + 2, k0, k1);
+                v0 = k0;
+                v1 = k1;
+                k0 = id_of(2 * (t + 3));
+                k1 = id_of(2 * (t + 3) + 1);
             }
-            static_assert(kPairs <= kN, "the value product's steps cover the pairs");
-        } else if (more) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (mine) {
+                const float m_ref = m == -INFINITY ? 0.f : m;
+                float psum[2] = {0.f, 0.f};
+                float w0, w1;
+                auto weigh = [&](int j, int part) {                 // a sixth of pair j of eight
+                    const int i = 2 * j;
+                    Terms& to = pf[i >> 3];
+                    const int e = (i & 7) >> 1;
+                    if (part == 0) {
+                        float scale = unit;
+                        asm volatile("" : "+s"(scale));             // (here, not all pairs ahead of the products: 4 % of the kernel)
+                        w0 = fmaf(y[i], scale, fmaf(x[i], scale, -m_ref));
+                        w1 = fmaf(y[i + 1], scale, fmaf(x[i + 1], scale, -m_ref));
+                    } else if (part == 1) {
+                        w0 = __builtin_amdgcn_exp2f(w0);
+                        w1 = __builtin_amdgcn_exp2f(w1);
+                    } else if (part == 2) {
+                        w0 *= kWeightUnit;
+                        w1 *= kWeightUnit;
+                        psum[0] += w0;
+                        psum[1] += w1;
+                    } else if (part == 3) {
+                        to.h[e] = take_term(w0, w1);
+                    } else if (part == 4) {
+                        to.m[e] = take_term(w0, w1);
+                    } else {
+                        to.l[e] = pack(w0, w1);
+                    }
+                };
+                if (next) {
+                    f32x16 s0, s1;
+                    scores(t + 1, s0, s1, [&](int i) {              // eight pairs over the score product's steps
+                        constexpr int kPer = 6 * 8 / kProducts;     // parts a product: 1 or 2
 #pragma unroll
-            for (int c = 0; c < kPairs; ++c) store_pair(c, k_to, v_to);
+                        for (int k = 0; k < kPer; ++k) weigh((i * kPer + k) / 6, (i * kPer + k) % 6);
+                    });
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) x[i] = s0[i], y[i] = s1[i];
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 48; ++j) weigh(j / 6, j % 6);
+                }
+                lsum += psum[0] + psum[1];
+            }
+            unsigned char* const k_to = k_lds + (t & 1) * 3 * kPlane;
+            unsigned char* const v_to = v_lds + ((t + 1) & 1) * 3 * kPlane;
+            if (more) scrub(t + 1);
+            if (mine) {
+                const unsigned char* vb = v_lds + (t & 1) * 3 * kPlane + hi * DT * 16 + n * 16;
+                constexpr int kN = 6 * kMb;                         // operand i: k-step, term, channel block
+                u32x4 ring[kAhead + 1];
+                auto at = [&](int i) {
+                    return *reinterpret_cast<const u32x4*>(vb + ((i / kMb) % 3) * kPlane + (i / (3 * kMb)) * DT * 32 + (i % kMb) * 512);
+                };
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i) ring[i] = at(i);
+#pragma unroll
+                for (int i = 0; i < kN; ++i) {
+                    if (i + kAhead < kN) ring[(i + kAhead) % (kAhead + 1)] = at(i + kAhead);
+                    const u32x4 v = ring[i % (kAhead + 1)];
+                    const Terms& p = pf[i / (3 * kMb)];
+                    f32x16& acc = o[i % kMb];
+                    const int term = (i / kMb) % 3;
+                    auto add = [&](const u32x4& part, int j) {       // product 6 kMb (i / 3 kMb) + j
+                        const int at = 6 * kMb * (i / (3 * kMb)) + j;
+                        acc = product(v, part, acc);
+                        if (at < 3 * kPairs) store_part(at / 3, at % 3, k_to, v_to);   // (past the last tile: what is there once more, never read)
+                        if (at >= 4 && at < 20) look(at - 4);
+                        __builtin_amdgcn_sched_barrier(0);
+                    };
+                    const int b = i % kMb;
+                    if (term == 0) {
+                        add(p.l, 3 * b);
+                        add(p.m, 3 * b + 1);
+                        add(p.h, 3 * b + 2);
+                    } else if (term == 1) {
+                        add(p.m, 3 * kMb + 2 * b);
+                        add(p.h, 3 * kMb + 2 * b + 1);
+                    } else {
+                        add(p.h, 5 * kMb + b);
+                    }
+                }
+                static_assert(3 * kPairs <= kProducts, "the value product's products cover the pairs' parts");
+            } else if (more) {
+#pragma unroll
+                for (int c = 0; c < kPairs; ++c) store_pair(c, k_to, v_to);
+            }
+            __syncthreads();
         }
-        __syncthreads();
+        if (t >= n_tiles) break;
+        // m is shared by the two lanes of a column: combine them (mx <= m afterwards, or unordered)
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m, mx);
+        const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
+        lsum *= alpha;
+#pragma unroll
+        for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[mb][i] *= alpha;
+        m = m_new;
     }
 
     // o[mb][q4 * 4 + e] is O^T[channel mb * 32 + q4 * 8 + hi * 4 + e][column n]

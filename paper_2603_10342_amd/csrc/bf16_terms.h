@@ -15,14 +15,22 @@ __device__ __forceinline__ uint32_t pack(float a, float b)
     return __builtin_bit_cast(uint32_t, pair{(__bf16)a, (__bf16)b});
 }
 
+// The leading terms of two numbers, packed; a and b become their rests.
+__device__ __forceinline__ uint32_t take_term(float& a, float& b)
+{
+    const uint32_t t = pack(a, b);
+    a -= widen_lo(t);
+    b -= widen_hi(t);
+    return t;
+}
+
 // Two numbers as packed terms.  Both halves of a packed term are widened by one instruction each (left to itself the
 // compiler converts every number a second time).  An infinity (or what rounds to one) leaves NaN as its rest.
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l)
 {
-    h = pack(a, b);
-    const float ra = a - widen_lo(h), rb = b - widen_hi(h);
-    m = pack(ra, rb);
-    l = pack(ra - widen_lo(m), rb - widen_hi(m));
+    h = take_term(a, b);
+    m = take_term(a, b);
+    l = pack(a, b);
 }
 
 // Eight numbers as packed terms: operands of a 16-bit product, smallest terms first when they are summed.
