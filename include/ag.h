@@ -219,7 +219,8 @@ AG_API ag_status ag_decode_step(const ag_kv_cache* cache, const void* k_new, con
  * ag_attn_decode (streaming work for decodes and chunks of a few rows, tile work for longer chunks, side by
  * side), which pays when sessions bring few rows (the launch is then bound by reading K and V); when the
  * longest chunk (max_new) has 144 rows or more the call runs ag_attn_resume's kernel instead, which is faster
- * from about there on.  The launch is sized for the CUs `stream` may use (its CU mask, if it has one).
+ * from about there on, and a queue too small to fill the CUs runs the kernel that ag_attn_resume takes for few
+ * rows (the workspace is then checked but not written).  The launch is sized for the CUs `stream` may use (its CU mask, if it has one).
  * Arguments as ag_attn_resume, plus a device workspace of at least
  * ag_attn_merged_workspace_bytes(total_new, num_q_heads, max_ctx) bytes, 16-byte aligned, which the call may
  * overwrite entirely (AG_ERR_WORKSPACE if smaller).  Calls sharing a workspace must be ordered on one stream.
