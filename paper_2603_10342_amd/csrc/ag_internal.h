@@ -89,7 +89,8 @@ ag_status launch_prefill_f32(const AttnArgs& a, hipStream_t st);
 // few rows on long contexts: the keys of a query tile split over the waves of one workgroup (rounded: bf16 weights cut to
 // bf16, as launch_prefill_mfma does)
 bool      prefill_split_preferred(const AttnArgs& a, bool rounded, hipStream_t st);
-ag_status launch_prefill_split(const AttnArgs& a, bool rounded, hipStream_t st);
+// exact: rounded weights stand against the largest score so far, see prefill_split_kernel()
+ag_status launch_prefill_split(const AttnArgs& a, bool rounded, hipStream_t st, bool exact = false);
 // the whole decode step (append + attention + merge) in one launch; same shapes as the matrix-core decode
 size_t    decode_step_workspace_bytes(int batch, int hq, int d, int max_ctx);
 ag_status launch_decode_step(const AttnArgs& a, const void* k_new, const void* v_new, void* ws, hipStream_t st);

@@ -683,14 +683,14 @@ bool merged_mfma_supported(const AttnArgs& a)
 
 // Whether a queue is small enough for the prefill kernel that splits the keys of 32 (row, head) columns over a workgroup's waves: no
 // plan, no partials in memory and no merge, which are 16 us of a small queue here, but a workgroup walks its keys alone, 8 us +
-// 4.8 us per 1000 tokens.  r: its workgroups per CU.  Up to three, on contexts up to 2600 + 4096 r tokens; 1000 fewer where
-// the queue streams: most sessions are decodes, or every chunk is one group of rows.  Measured over 130 queues of 1..8 chunks of 2..128 rows and 1..64 decodes (graph replay, append
-// included; this kernel -> that one, us, at r, longest context): 1.7x at r = 0.05 to 0.3 on 700..2000 (21 -> 10.4, 25 -> 14.8), 33 -> 23 (0.5,
-// 3400), 33 -> 20 (0.7, 2000), 30 -> 16 (0.9, 1800), 39 -> 19 (1, 1600), 63 -> 35 (1.6, 1100), 75 -> 55 (1.8, 6400), 59 -> 41 (2.1, 3500), 137 -> 93
-// (2.6, 3100), 61 -> 51 (2.8, 1700); on the other side 24 -> 36 (0.1, 6000), 23 -> 43 (0.2, 7300), 35 -> 43 (0.2, 6800), 31 -> 35 (0.55,
-// 5000), streaming 16 -> 18 (0.07, 2700), 94 -> 95 (3.4, 1700).  Many decodes on long contexts
-// are bound by HBM, which equal shares of all the keys keep busy to the end: 79 -> 92 (2.2, 5500, 99 rows of 57 sessions), 64 -> 67
-// (64 decodes up to 2000).  The largest losses on the chosen side are 6 to 10 % (28 -> 30 at 0.4, 4060; 40 -> 44 at 1.03, 3600).
+// 5.5 us per 1000 tokens.  r: its workgroups per CU.  Up to three, on contexts up to 2200 + 1500 r tokens; 1000 fewer where
+// the queue streams: most sessions are decodes, or every chunk is one group of rows.  Measured over 44 drawn queues (graph replay,
+// append included; this kernel -> that one, us, at r, longest context): 23 -> 10.6 (0.2, 570), 28 -> 14.4 (0.3, 1390), 22 -> 16.6 (0.3, 2130),
+// 24 -> 18.4 (0.2, 1900), 28 -> 20 (0.2, 2500), 32 -> 20.5 (1.8, 1730), 42 -> 29 (1.6, 1870), 68 -> 51 (2.1, 2200), 32 -> 28.7 (0.6, 2900),
+// 26 -> 23 (0.5, 2580).  On the other side 60 -> 63 (1.5, 4900); with the kernel 1 to 10 % faster than it is with exact references, 24 -> 36
+// (0.1, 6000), 35 -> 43 (0.2, 6800), 31 -> 35 (0.55, 5000), 25.8 -> 27.4 (0.3, 3670), streaming 16 -> 18 (0.07, 2700), 94 -> 95 (3.4, 1700).  Many
+// decodes on long contexts are bound by HBM, which equal shares of all the keys keep busy to the end: 79 -> 92 (2.2, 5500, 99 rows
+// of 57 sessions), 64 -> 67 (64 decodes up to 2000).
 static bool split_preferred(const AttnArgs& a, hipStream_t st)
 {
     const int64_t G = a.hq / a.c.hkv, cus = stream_cus(st);
@@ -698,14 +698,14 @@ static bool split_preferred(const AttnArgs& a, hipStream_t st)
     const int64_t wgs = a.c.hkv * std::min<int64_t>(a.total_rows * G / 32 + a.batch, (int64_t)a.batch * ((a.max_new * G + 31) / 32));
     const bool decodes = (int64_t)a.total_rows < 2 * (int64_t)a.batch;         // most sessions bring one row
     if (decodes && 2 * wgs > 3 * cus && a.max_ctx > 1500) return false;
-    const int64_t ctx = decodes || a.max_new <= rows_per_group(a.hq, a.c.hkv) ? 1600 : 2600;
-    return wgs <= 3 * cus && (a.max_ctx - ctx) * cus <= 4096 * wgs;
+    const int64_t ctx = decodes || a.max_new <= rows_per_group(a.hq, a.c.hkv) ? 1200 : 2200;
+    return wgs <= 3 * cus && (a.max_ctx - ctx) * cus <= 1500 * wgs;
 }
 
 ag_status launch_merged_mfma(const AttnArgs& a, void* ws, hipStream_t st)
 {
     if (a.total_rows <= 0) return AG_OK;
-    if (split_preferred(a, st)) return launch_prefill_split(a, true, st);
+    if (split_preferred(a, st)) return launch_prefill_split(a, true, st, true);
     const int tq = rows_per_group(a.hq, a.c.hkv);
     // Keys items hold one group of rows (tq: a decode, or a chunk that fits the 16 columns with its heads); once
     // some session may bring more, there are rows items of up to 8 groups.  (Keys items of two groups - the

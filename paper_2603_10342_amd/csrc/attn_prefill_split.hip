@@ -46,7 +46,10 @@ struct Shape {
 };
 
 // kLo: bf16 weights as three terms (bf16_terms.h); false keeps the rounded weights of the bf16 / 128 / 16 kernels.
-template <typename E, int DT, bool kLo>
+// kExact: a wave's reference is the largest score so far, so that the largest weights come out as 1 and lose nothing in rounding, as
+// those of the decode queue's own kernels do.  Queues, ten batches: error against 64 bits 0.92 to 0.96 of theirs, where a reference
+// that may be outgrown had 0.99 to 1.05; it costs 1 to 10 % of a small queue (rescaling O in most steps).
+template <typename E, int DT, bool kLo, bool kExact = false>
 __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void prefill_split_kernel(AttnArgs a, int tiles_max, int per_xcd, int total_work)
 {
     constexpr int kWaves = Shape<DT>::waves, kORow = Shape<DT>::o_row, kRowsAgain = Shape<DT>::rows_again;
@@ -56,7 +59,7 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
     constexpr bool kTakeAgain = kLo || !kBf16;      // columns that are not finite, in plain arithmetic (attn_general_row.h)
     constexpr int kRuns = kBf16 ? 2 : 4;            // runs of keys a lane's weights fall into: 8 keys (bf16), 4 (fp32)
     constexpr bool kQInLds = !kBf16;                // fp32 queries are twice the registers and are read a quarter as often
-    constexpr float kSlack = kBf16 ? 8.0f : 5.5f;   // how far a maximum may outgrow the reference before O is rescaled
+    constexpr float kSlack = kExact ? 0.f : kBf16 ? 8.0f : 5.5f;   // how far a maximum may outgrow the reference before O is rescaled
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];       // Q in the loop (fp32), then the waves' partials
 
     // ---- which (KV head, session, tile): the XCD a workgroup lands on owns a contiguous range of KV heads ----
@@ -326,16 +329,16 @@ int64_t tiles_bound(const AttnArgs& a, int columns)
     return std::min<int64_t>((int64_t)a.total_rows * G / columns + a.batch, (int64_t)a.batch * ((a.max_new * G + columns - 1) / columns));
 }
 
-template <typename E, int DT, bool kLo>
+template <typename E, int DT, bool kLo, bool kExact = false>
 ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 {
     constexpr int lds = Shape<DT>::lds;
     static std::atomic<uint64_t> told{0};
-    ag_status e = allow_dynamic_lds((const void*)prefill_split_kernel<E, DT, kLo>, lds, told);
+    ag_status e = allow_dynamic_lds((const void*)prefill_split_kernel<E, DT, kLo, kExact>, lds, told);
     if (e) return e;
     const int64_t tiles_max = tiles_bound(a, kColumns), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
     prof_before(st);
-    hipLaunchKernelGGL((prefill_split_kernel<E, DT, kLo>), dim3((unsigned)(per_xcd * 8)), dim3(64 * Shape<DT>::waves), lds, st, a,
+    hipLaunchKernelGGL((prefill_split_kernel<E, DT, kLo, kExact>), dim3((unsigned)(per_xcd * 8)), dim3(64 * Shape<DT>::waves), lds, st, a,
                        (int)tiles_max, (int)per_xcd, (int)total);
     prof_after(st);
     return hip_check(hipGetLastError(), "prefill launch");
@@ -370,11 +373,12 @@ bool prefill_split_preferred(const AttnArgs& a, bool rounded, hipStream_t st)
     return 1000 * a.c.hkv * tiles_bound(a, kColumns) <= line * stream_cus(st);
 }
 
-ag_status launch_prefill_split(const AttnArgs& a, bool rounded, hipStream_t st)
+ag_status launch_prefill_split(const AttnArgs& a, bool rounded, hipStream_t st, bool exact)
 {
     if (a.c.dtype == AG_F32) return a.c.d == 64 ? launch_kernel<float, 64, false>(a, st) : launch_kernel<float, 128, false>(a, st);
     if (a.c.d == 256) return launch_kernel<__bf16, 256, true>(a, st);
     if (a.c.d == 64) return launch_kernel<__bf16, 64, true>(a, st);
+    if (rounded && exact) return launch_kernel<__bf16, 128, false, true>(a, st);
     return rounded ? launch_kernel<__bf16, 128, false>(a, st) : launch_kernel<__bf16, 128, true>(a, st);
 }
 
