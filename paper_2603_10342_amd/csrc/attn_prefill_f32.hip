@@ -290,6 +290,7 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
                     for (int i = 0; i < 16; ++i) {
                         const int kk = t * BN + (i >> 2) * 8 + hi * 4 + (i & 3);
                         x[i] = kk <= qpos ? x[i] : -INFINITY;
+                        y[i] = kk <= qpos ? y[i] : 0.f;     // (a key not to be seen may be anything, NaN included)
                         look(i);
                     }
                 }
