@@ -390,15 +390,23 @@ static ag_status launch_tiles(const AttnArgs& a, bool lo, hipStream_t st)
     // spreads over at least 5/8 of the CUs.  128-column workgroups keep short, ragged chunks efficient and spread small batches (one
     // chunk on 6000 tokens, whole call: 600 rows 152 -> 126 us, 1000 rows 167 -> 139).  They also end a launch better: 256 columns
     // are one workgroup a CU, whose start (4 us) and end nothing else hides and of which a last one a CU is a long one, so that
-    // two workgroups of 128 columns a CU win on contexts up to 1536 unless all of the larger ones run at once, and on longer ones
-    // while the larger ones come to few a CU.  Graph replay, append included, 256 -> 128 columns, us (of the larger a CU):
-    // rounded weights, four prompts of 600 (1.3) 37.8 -> 32.5, seven of 700..912 at 16 / 2 heads (1.4) 52 -> 47, eight of 1000 (4) 108 -> 105,
-    // two of 1000 (1) 38.9 -> 40.3, one of 2048 (1) 62.5 -> 58.2, two of 2048 (2) 84 -> 86, one of 4096 (2) 143 -> 148, 16 of 300..2000
-    // at 8 / 2 (2.2) 97 -> 88, eight of 512..600 on 2000..4000 (2.2) 261 -> 268; weights in 32 bits, one of 2048 (1) 101 -> 85, two of
-    // 1000 (1) 58.5 -> 62.5, eight of 512..600 on 1000..2000 (2.2) 258 -> 241, four of 2048 (4) 265 -> 274.
+    // two workgroups of 128 columns a CU win on contexts up to 1536 unless all of the larger ones run at once, however many there
+    // are, and on longer ones while the larger ones come to few a CU - unless all of them run at once and are alike, so that there
+    // is nothing to even out: chunks of one length, short beside their contexts (a tile's keys grow over a chunk).
+    // Graph replay, append included, 256 -> 128 columns, us (of the larger a CU).  Rounded weights: four prompts of 600 (1.3) 37.8 ->
+    // 32.5, seven of 700..912 at 16 / 2 heads (1.4) 52 -> 47, one of 2048 (1) 62.5 -> 58.2, three of 700 on 2000 (1.03) 127 -> 118, 16 of
+    // 1500 (12) 401 -> 386, 64 of 600, 1000, 1500 (20, 32, 48) 382 -> 364, 856 -> 803, 1568 -> 1510; but two of 1000 (1) 38.9 -> 40.3,
+    // two of 1000 on 2000 (1) 93 -> 97, four of 512 on 3000 (1) 112 -> 116, six of 1024 on 4000 at 8 / 2 (0.75) 131 -> 139, eight of
+    // 512..600 on 2000..4000 (2.2) 261 -> 268.  Weights in 32 bits: one of 2048 (1) 101 -> 85, three of 700 on 2000 (1.03) 218 -> 189, 64 of
+    // 1000, 1500 (32, 48) 1316 -> 1211, 2567 -> 2392; but two of 600 on 6000 (0.62) 283 -> 310, one of 3000 on 3000 at 16 / 2 (0.73) 264 -> 281, six of 1024 on 4000 at 8 / 2
+    // (0.75) 229 -> 251, two of 1000 on 2000 (1) 160 -> 170, four of 2048 (4) 265 -> 274.  Over 1540 drawn batches of 0.6 to 3.2 a CU, also
+    // on 64 and 160 CUs, this line is 1.04 times faster than 256 columns from 5/8 of the CUs on; it is over 3 % slower at 75, of which 58
+    // are of more than one round, where the order in which unlike workgroups come to a CU decides.
     const int64_t cus = stream_cus(st), large = a.c.hkv * tiles_bound(a, 256);         // workgroups of 256 columns
     const bool ragged = 5 * (int64_t)a.total_rows < 4 * (int64_t)a.batch * a.max_new;
-    const bool pays = large <= cus ? a.max_ctx <= 1536 : a.max_ctx > 1536 && 4 * large >= (lo || ragged ? 10 : 7) * cus;
+    const int64_t rows = a.max_new, ctx = a.max_ctx;
+    const bool alike = !ragged && (lo ? 3 * rows <= ctx || (10 * large > 7 * cus && 5 * rows <= 4 * ctx) : 5 * rows <= 2 * ctx);
+    const bool pays = large <= cus ? a.max_ctx <= 1536 || alike : a.max_ctx > 1536 && 4 * large >= (lo || ragged ? 10 : 7) * cus;
     const bool big = a.max_new >= 512 && 8 * large >= 5 * cus && pays;
     if (!lo) return big ? launch_prefill_nw<8, 128, false, true>(a, st) : launch_prefill_nw<4, 128, false, true>(a, st);
     if (a.c.d == 128) return big ? launch_prefill_nw<8, 128, true, false>(a, st) : launch_prefill_nw<4, 128, true, false>(a, st);

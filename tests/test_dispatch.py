@@ -1,0 +1,31 @@
+"""Which kernel a call takes, at batches where both sides of a line were measured and differ (the figures stand at the lines in
+the sources): seen on the CPU, through a HIP runtime that logs launches."""
+import pytest
+
+from launches import launched
+
+
+@pytest.fixture(scope="module")
+def tmp(tmp_path_factory):
+    return tmp_path_factory.mktemp("launches")
+
+
+def kernels(tmp, *calls):
+    return [[l.split(" ")[0] for l in r] for r in launched(calls, tmp)]
+
+
+H82, H162 = dict(hq=8, hkv=2), dict(hq=16, hkv=2)
+
+
+@pytest.mark.parametrize("page,columns,batches", [
+    (16, 128, [dict(batch=1, new=2048), dict(batch=3, prefix=2000, new=700), dict(batch=16, new=1500), dict(batch=64, new=600), dict(batch=64, new=1500)]),
+    (16, 256, [dict(batch=2, new=1000), dict(batch=2, prefix=2000, new=1000), dict(batch=4, prefix=3000, new=512), dict(batch=6, prefix=4000, new=1024, **H82),
+               dict(batch=8, new=4096)]),
+    (32, 128, [dict(batch=1, new=2048), dict(batch=3, prefix=2000, new=700), dict(batch=64, new=1000)]),
+    (32, 256, [dict(batch=2, prefix=6000, new=600), dict(batch=1, prefix=3000, new=3000, **H162), dict(batch=6, prefix=4000, new=1024, **H82), dict(batch=2, prefix=2000, new=1000),
+               dict(batch=4, new=2048)]),
+])
+def test_columns_of_a_prefill_workgroup(tmp, page, columns, batches):
+    tail = "false,true" if page == 16 else "true,false"
+    for b, k in zip(batches, kernels(tmp, *(dict(call="resume", page=page, **b) for b in batches))):
+        assert k == [f"prefill_mfma_kernel<{columns // 32},128,{tail}>"], b
