@@ -361,16 +361,23 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 // 50 rows (700 workgroups) bf16 / 64 16.1 -> 10.2 us, fp32 / 64 25.9 -> 14.8, fp32 / 128 36.9 -> 23.0; eight of 100 (660) bf16 / 64
 // 15.7 -> 11.6, bf16 / 128 on pages of 32 19.3 -> 15.2, bf16 / 256 29.9 -> 25.4; eight of 50 (360) bf16 / 128 / 16 12.5 -> 11.4,
 // fp32 / 64 17.6 -> 13.3; four of 200 rows on 300 (630) bf16 / 128 on pages of 32 26.4 -> 23.4; but eight of 60 on 300 (420) bf16 / 64 13.7 ->
-// 15.1, 16 of 30 on 600 (490) 16.7 -> 21.2, five of 60 (200) bf16 / 128 / 16 9.3 -> 10.9, twelve of 40 on 150 (456) fp32 / 128 30 -> 33.
+// 15.1, 16 of 30 on 600 (490) 16.7 -> 21.2, five of 60 at 16 / 2 (160) bf16 / 128 / 16 8.2 -> 10.5.
+// Where a row is 512 bytes or more it rises more slowly: 29 of 101 rows on 274 at 8 / 2 heads (755) bf16 / 256 43 -> 39, 21 of 13 on 25
+// (335) 21 -> 17, 19 of 63 on 190 at 16 / 2 (609) fp32 / 128 49 -> 37; but eight of 60 on 300 (512)
+// bf16 / 256 31 -> 37, 16 of 30 on 600 (512) 39 -> 51.  And it does not fall where no chunk has more than 32 columns, so that the
+// other kernel has as many workgroups, three quarters empty: 44 of 3 on 32 (352) fp32 / 128 23 -> 29.  Over 931 drawn batches of these two
+// shapes of 0 to 4 a CU the line costs 1.7 % against the faster side of each.
 bool prefill_split_preferred(const AttnArgs& a, bool rounded, hipStream_t st)
 {
     if ((a.c.d != 64 && a.c.d != 128 && (a.c.d != 256 || a.c.dtype == AG_F32)) || a.c.ps < 16 || (int64_t)a.total_rows * (a.hq / a.c.hkv) > 0x7fffffff ||
         ((uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 != 0) return false;
     const int64_t ctx = a.max_ctx;                  // in thousandths of a workgroup per CU:
     const bool wide = a.c.d * (a.c.dtype == AG_F32 ? 4 : 2) >= 512;
+    const int64_t tiles = tiles_bound(a, kColumns);
+    const bool one_each = wide && tiles == tiles_bound(a, 128);
     const int64_t line = rounded ? std::max<int64_t>(1125, std::min<int64_t>(875 + 2 * ctx, 2000))
-                                 : std::min<int64_t>(wide ? 1125 + ctx * 11 / 2 : 1250 + 3 * ctx, 3000);
-    return 1000 * a.c.hkv * tiles_bound(a, kColumns) <= line * stream_cus(st);
+                                 : std::min<int64_t>(one_each ? 3000 : wide ? 1125 + 4 * ctx : 1250 + 3 * ctx, 3000);
+    return 1000 * a.c.hkv * tiles <= line * stream_cus(st);
 }
 
 ag_status launch_prefill_split(const AttnArgs& a, bool rounded, hipStream_t st, bool exact)

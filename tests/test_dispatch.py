@@ -29,3 +29,22 @@ def test_columns_of_a_prefill_workgroup(tmp, page, columns, batches):
     tail = "false,true" if page == 16 else "true,false"
     for b, k in zip(batches, kernels(tmp, *(dict(call="resume", page=page, **b) for b in batches))):
         assert k == [f"prefill_mfma_kernel<{columns // 32},128,{tail}>"], b
+
+
+SPLIT = "prefill_split_kernel"
+
+
+@pytest.mark.parametrize("shape,split,batches", [
+    (dict(d=256), False, [dict(batch=29, prefix=274, new=101, **H82), dict(batch=21, prefix=25, new=13),
+                          dict(batch=8, new=100), dict(batch=8, prefix=1500, new=160)]),
+    (dict(d=256), True, [dict(batch=8, prefix=300, new=60), dict(batch=16, prefix=600, new=30), dict(batch=6, prefix=2200, new=13), dict(batch=44, prefix=21, new=7)]),
+    (dict(dtype="f32"), False, [dict(batch=19, prefix=190, new=63, **H162), dict(batch=16, new=50), dict(batch=2, new=1000)]),
+    (dict(dtype="f32"), True, [dict(batch=44, prefix=32, new=3), dict(batch=1, prefix=6000, new=211)]),
+    (dict(d=64), False, [dict(batch=16, new=50), dict(batch=8, prefix=2000, new=100)]),
+    (dict(d=64), True, [dict(batch=8, prefix=300, new=60), dict(batch=16, prefix=600, new=30)]),
+    (dict(), False, [dict(batch=8, new=50), dict(batch=8, prefix=2000, new=100)]),
+    (dict(), True, [dict(batch=5, new=60, **H162), dict(batch=1, prefix=6007, new=400)]),
+])
+def test_few_rows_or_whole_tiles(tmp, shape, split, batches):
+    for b, k in zip(batches, kernels(tmp, *(dict(call="resume", **shape, **b) for b in batches))):
+        assert len(k) == 1 and k[0].startswith(SPLIT) == split, (b, k)
