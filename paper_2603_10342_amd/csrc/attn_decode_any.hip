@@ -470,16 +470,19 @@ __global__ __launch_bounds__(256) void decode_any_merge_kernel(AttnArgs a, const
 
 // Whether every pair, each of at most `bytes` of keys and values, takes one workgroup.  Shares and their merge are two launches
 // here (splitk::direct_preferred() weighs the kernel that has a form in one as well), so a workgroup may go through somewhat more: 448
-// KiB, and 1 MiB where the pairs take more than half of the CUs, so that shares are hardly finer.  Measured at 256 CUs, append included
+// KiB (432 of fp32 at 64 channels, where a wave has the most sub-steps one behind another), and 1 MiB where the pairs take more than
+// half of the CUs, so that shares are hardly finer.  Measured at 256 CUs, append included
 // (graph replay), shares -> one workgroup, us, by longest context: one session at 8 / 2 heads, bf16 64 of 1500 tokens 11.8 -> 9.7, of 2200
 // 12.3 -> 11.9, of 3500 12.4 -> 15.6; bf16 128 of 600 13.0 -> 10.1, of 1000 13.6 -> 12.2, of 1500 13.6 -> 15.9; fp32 64 of 600 15.2 ->
 // 12.0, of 1000 15.8 -> 16.5; 16 at 4 / 4, bf16 128 of 600 14.6 -> 12.4, of 1000 15.3 -> 16.6; fp32 128 of 600 22.5 -> 22.6.  30 at 32 / 8
 // (240 pairs): bf16 64 of 2200 24.0 -> 20.6; bf16 128 of 1500 31 -> 28, of 2200 40 -> 37; fp32 128 of 600 33 -> 28, of 1000 43 -> 39,
-// of 2200 75 -> 75; bf16 256 of 1000 41 -> 38.
+// of 2200 75 -> 75; bf16 256 of 1000 41 -> 38.  Around the line, shares / one workgroup: fp32 64, 416 to 432 KiB, 0.97 to 1.16, 1.02 over
+// 11 batches, 432 to 448 KiB 0.84 to 1.09, 0.92 over 15 (one session of 878 at 4 / 4, 14.0 -> 16.4); bf16 64 and 128, 432 to 448 KiB, 0.85
+// to 1.13, 0.98 over 26; rows of 512 bytes and more, 384 to 448 KiB, 1.05 to 1.8.
 constexpr int64_t kDirectMostBytes = 1 << 20;
-inline bool one_workgroup_a_pair(int64_t pairs, int64_t bytes, int cus)
+inline bool one_workgroup_a_pair(int64_t pairs, int64_t bytes, bool fp32_64, int cus)
 {
-    return pairs <= cus && bytes <= (2 * pairs > cus ? kDirectMostBytes : 448 << 10);
+    return pairs <= cus && bytes <= (2 * pairs > cus ? kDirectMostBytes : fp32_64 ? 432 << 10 : 448 << 10);
 }
 
 // Whether all contexts together come to no more than a share of 256 tokens a CU: shares would leave CUs idle, and walk
@@ -506,7 +509,7 @@ ag_status launch(const AttnArgs& a, hipStream_t st)
     static_assert(kDirectMostBytes / (2 * DT * (int)sizeof(E)) <= kDirectMaxTokens, "a wave's page ids fit its lanes");
     const int64_t pairs = (int64_t)a.batch * a.c.hkv * blocks;
     const int cus = stream_cus(st);
-    if (a.max_ctx > 0 && (one_workgroup_a_pair(pairs, pair_bytes, cus) || few_tokens(pairs, a.max_ctx, cus))) {
+    if (a.max_ctx > 0 && (one_workgroup_a_pair(pairs, pair_bytes, DT == 64 && sizeof(E) == 4, cus) || few_tokens(pairs, a.max_ctx, cus))) {
         const dim3 grid((unsigned)pairs), wg(64 * kDirectWaves);
         prof_before(st);
         if (a.c.d == DT) hipLaunchKernelGGL((decode_any_direct_kernel<E, DT, true>), grid, wg, 0, st, a, blocks);

@@ -48,3 +48,16 @@ SPLIT = "prefill_split_kernel"
 def test_few_rows_or_whole_tiles(tmp, shape, split, batches):
     for b, k in zip(batches, kernels(tmp, *(dict(call="resume", **shape, **b) for b in batches))):
         assert len(k) == 1 and k[0].startswith(SPLIT) == split, (b, k)
+
+
+F64, F128 = dict(dtype="f32", d=64), dict(dtype="f32")
+
+
+@pytest.mark.parametrize("alone,batches", [
+    (True, [dict(batch=1, max_ctx=850, hq=4, hkv=4, **F64), dict(batch=1, max_ctx=1770, d=64, **H82), dict(batch=1, max_ctx=440, **F128), dict(batch=1, max_ctx=440, d=256),
+            dict(batch=30, max_ctx=2200, d=64), dict(batch=64, max_ctx=120, **F64)]),
+    (False, [dict(batch=1, max_ctx=878, hq=4, hkv=4, **F64), dict(batch=1, max_ctx=1800, d=64, **H82), dict(batch=1, max_ctx=460, **F128), dict(batch=30, max_ctx=4200, d=64)]),
+])
+def test_decode_one_workgroup_a_pair_or_shares(tmp, alone, batches):
+    for b, k in zip(batches, kernels(tmp, *(dict(call="decode", page=32, **b) for b in batches))):
+        assert [x.split("<")[0] for x in k] == (["decode_any_direct_kernel"] if alone else ["decode_any_split_kernel", "decode_any_merge_kernel"]), b

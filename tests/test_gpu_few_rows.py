@@ -41,9 +41,9 @@ def test_around_the_line(dtype, d, ps, sessions, rows, prefix):
 
 
 @pytest.mark.parametrize("dtype,d,ps,hq,hkv", [(I.BF16, 64, 32, 8, 2), (I.BF16, 256, 16, 6, 2), (I.F32, 64, 16, 16, 1), (I.F32, 72, 32, 4, 2)])
-@pytest.mark.parametrize("kib,cus_per_xcd", [(448, 0), (1024, 1)])
+@pytest.mark.parametrize("kib,cus_per_xcd", [(432, 0), (448, 0), (1024, 1)])
 def test_decode_at_the_lines_of_one_workgroup_a_pair(dtype, d, ps, hq, hkv, kib, cus_per_xcd):
-    """max_ctx at and one past what one workgroup goes through alone: 448 KiB, and 1 MiB where the pairs take more than half of the
+    """max_ctx at and one past what one workgroup goes through alone: 432 or 448 KiB, and 1 MiB where the pairs take more than half of the
     CUs (six or three on 8)."""
     padded = 64 if d <= 64 else 128 if d <= 128 else 256
     line = (kib << 10) // (2 * padded * (4 if dtype == I.F32 else 2))
