@@ -21,7 +21,7 @@
 // head_dim 64, 32-token pages, 2238 -> 63.5 us (333 MB, 5.2 TB/s; 62.8 with weights in two terms); two fp32 sessions of 300, 4 / 2 heads x 64, 106 -> 12 us.
 // head_dim below its template's DT: loads beyond head_dim repeat its last channels; keys become zeros (as the query
 // does), values land in rows that are not stored.
-#include <type_traits>
+#include <algorithm>
 
 #include "attn_general_row.h"
 #include "attn_split_common.h"
@@ -351,7 +351,9 @@ __global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, in
 constexpr int kDirectWaves = 8;
 constexpr int kDirectMaxTokens = kDirectWaves * 32 * 32;
 
-template <typename E, int DT, bool kExact>
+// N: channels a thread takes of the waves' results: one while that is one each (half the latency), four beyond.  (Both in one kernel, chosen
+// by the pair's heads, cost short calls 0.15 us: 16 sessions of 200 tokens, 32 / 8 heads x 128, 9.57 -> 9.73.)
+template <typename E, int DT, bool kExact, int N>
 __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel(AttnArgs a, int head_blocks)
 {
     constexpr bool kBf16 = sizeof(E) == 2;
@@ -393,38 +395,32 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
 #pragma unroll
         for (int mb = 0; mb < kChan / 16; ++mb) *reinterpret_cast<f32x4*>(&s_o[w][r][mb * 16 + c * 4]) = o[d0 / 16 + mb];
         __syncthreads();
-        // One channel a thread while that is one each (half the latency), four beyond.
-        auto combine = [&](auto channels) {
-            constexpr int N = decltype(channels)::value;
-            for (int idx = tid; idx < nh * (kChan / N); idx += kThreads) {
-                const int head = idx / (kChan / N), dl = (idx - head * (kChan / N)) * N;
-                if (d0 + dl >= D) continue;
-                float ms = s_m[0][head];                         // wave 0 has a step, if there is one
+        for (int idx = tid; idx < nh * (kChan / N); idx += kThreads) {
+            const int head = idx / (kChan / N), dl = (idx - head * (kChan / N)) * N;
+            if (d0 + dl >= D) continue;
+            float ms = s_m[0][head];                             // wave 0 has a step, if there is one
 #pragma unroll
-                for (int ww = 1; ww < kDirectWaves; ++ww) ms = fmaxf(ms, s_m[ww][head]);
-                float acc[N] = {}, l = 0.f;
+            for (int ww = 1; ww < kDirectWaves; ++ww) ms = fmaxf(ms, s_m[ww][head]);
+            float acc[N] = {}, l = 0.f;
 #pragma unroll
-                for (int ww = 0; ww < kDirectWaves; ++ww) {
-                    const float fw = power(s_m[ww][head] - ms);  // a wave without steps has m = -inf -> 0
-                    l += fw * s_l[ww][head];
-                    typedef float numbers __attribute__((ext_vector_type(N)));
-                    const numbers x = *reinterpret_cast<const numbers*>(&s_o[ww][head][dl]);
+            for (int ww = 0; ww < kDirectWaves; ++ww) {
+                const float fw = power(s_m[ww][head] - ms);      // a wave without steps has m = -inf -> 0
+                l += fw * s_l[ww][head];
+                typedef float numbers __attribute__((ext_vector_type(N)));
+                const numbers x = *reinterpret_cast<const numbers*>(&s_o[ww][head][dl]);
 #pragma unroll
-                    for (int e = 0; e < N; ++e) acc[e] += fw * x[e];
-                }
-                float trouble = 0.f;
-#pragma unroll
-                for (int e = 0; e < N; ++e) {
-                    acc[e] = ctx > 0 ? acc[e] / l : 0.f;
-                    trouble = general::trouble_of(acc[e], trouble);
-                }
-                if constexpr (N == 4) splitk::store_quad(out + head * D + d0 + dl, acc);
-                else out[head * D + d0 + dl] = (E)acc[0];
-                if (!(trouble == 0.f)) atomicOr(&s_again, 1u << head);
+                for (int e = 0; e < N; ++e) acc[e] += fw * x[e];
             }
-        };
-        if (nh * kChan <= kThreads) combine(std::integral_constant<int, 1>{});
-        else combine(std::integral_constant<int, 4>{});
+            float trouble = 0.f;
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                acc[e] = ctx > 0 ? acc[e] / l : 0.f;
+                trouble = general::trouble_of(acc[e], trouble);
+            }
+            if constexpr (N == 4) splitk::store_quad(out + head * D + d0 + dl, acc);
+            else out[head * D + d0 + dl] = (E)acc[0];
+            if (!(trouble == 0.f)) atomicOr(&s_again, 1u << head);
+        }
     }
     __syncthreads();                                             // (weights in terms turn an infinite sum into NaN)
     const uint32_t all = __builtin_amdgcn_readfirstlane(s_again);
@@ -512,8 +508,10 @@ ag_status launch(const AttnArgs& a, hipStream_t st)
     if (a.max_ctx > 0 && (one_workgroup_a_pair(pairs, pair_bytes, DT == 64 && sizeof(E) == 4, cus) || few_tokens(pairs, a.max_ctx, cus))) {
         const dim3 grid((unsigned)pairs), wg(64 * kDirectWaves);
         prof_before(st);
-        if (a.c.d == DT) hipLaunchKernelGGL((decode_any_direct_kernel<E, DT, true>), grid, wg, 0, st, a, blocks);
-        else hipLaunchKernelGGL((decode_any_direct_kernel<E, DT, false>), grid, wg, 0, st, a, blocks);
+        auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, wg, 0, st, a, blocks); };
+        const bool one = std::min(a.hq / a.c.hkv, kCols) * 64 <= 64 * kDirectWaves;          // channel a thread
+        if (a.c.d == DT) one ? launch(decode_any_direct_kernel<E, DT, true, 1>) : launch(decode_any_direct_kernel<E, DT, true, 4>);
+        else one ? launch(decode_any_direct_kernel<E, DT, false, 1>) : launch(decode_any_direct_kernel<E, DT, false, 4>);
         prof_after(st);
         return hip_check(hipGetLastError(), "decode launch");
     }
