@@ -7,8 +7,9 @@ plain arguments - contiguous GPU tensors of the right dtypes, ints, floats - at 
 fraction of what ctypes costs; what it does not take, and every other entry point,
 goes through ctypes.
 
-There is no fallback: if the library or the module is missing or was not built,
-using it raises.
+There is no fallback for the library: if it is missing or was not built, using it
+raises.  Without the module, or with one built for another torch or Python, every
+call goes through ctypes, and a warning says so once.
 """
 from __future__ import annotations
 
@@ -153,26 +154,46 @@ def lib():
 
 
 _native = None
+_CALLS = ("kv_append", "attn_prefill", "attn_resume", "attn_decode", "attn_decode_static", "decode_step", "attn_merged")
+
+
+class _NoCalls:
+    """In place of a calling module that cannot be used: takes no call, so that ctypes does."""
+
+    def __getattr__(self, name):
+        if name not in _CALLS:
+            raise AttributeError(name)
+        return lambda *args: None
+
+
+def _load_calls():
+    import sys
+    from importlib.machinery import ExtensionFileLoader
+    from importlib.util import module_from_spec, spec_from_file_location
+    l = lib()
+    spec = spec_from_file_location("agcall", CALL_PATH, loader=ExtensionFileLoader("agcall", CALL_PATH))
+    m = module_from_spec(spec)
+    spec.loader.exec_module(m)
+    here = f"torch {torch.__version__} python {sys.version_info[0]}.{sys.version_info[1]}"
+    if getattr(m, "built_for", None) != here:                 # it reads torch's and Python's objects directly
+        raise ImportError(f"{CALL_PATH} is built for {getattr(m, 'built_for', 'an unknown torch')}, this is {here}")
+    m.setup(KVCache, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream,
+            *(C.cast(getattr(l, "ag_" + name), C.c_void_p).value for name in _CALLS))
+    return m
 
 
 def _calls():
     """The module the calls of a serving loop go through, bound to the library."""
     global _native
     if _native is None:
-        from importlib.machinery import ExtensionFileLoader
-        from importlib.util import module_from_spec, spec_from_file_location
-        l = lib()
-        if not os.path.exists(CALL_PATH):
-            raise ImportError(f"{CALL_PATH} is missing: build it with `python -m paper_2603_10342_amd.build` "
-                              "(or __graft_entry__.build())")
-        spec = spec_from_file_location("agcall", CALL_PATH, loader=ExtensionFileLoader("agcall", CALL_PATH))
-        m = module_from_spec(spec)
-        spec.loader.exec_module(m)
-        m.setup(KVCache, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream,
-                *(C.cast(getattr(l, name), C.c_void_p).value
-                  for name in ("ag_kv_append", "ag_attn_prefill", "ag_attn_resume", "ag_attn_decode",
-                               "ag_attn_decode_static", "ag_decode_step", "ag_attn_merged")))
-        _native = m
+        lib()                                                 # (its absence is an error)
+        try:
+            _native = _load_calls()
+        except (ImportError, AttributeError) as e:
+            import warnings
+            warnings.warn(f"calls go through ctypes, at twice the host time: {e} (python -m paper_2603_10342_amd.build builds the module)",
+                          RuntimeWarning, stacklevel=3)
+            _native = _NoCalls()
     return _native
 
 

@@ -63,6 +63,7 @@ def build_call(verbose: bool = False) -> str:
     tmp = CALL + f".tmp{os.getpid()}"
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DAG_BUILT_FOR="torch {torch.__version__} python {sys.version_info[0]}.{sys.version_info[1]}"',
            "-I" + os.path.join(ROOT, "include"), "-isystem", os.path.join(root, "include"),
            "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "py_call.cpp"), "-o", tmp,

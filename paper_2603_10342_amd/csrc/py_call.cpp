@@ -269,5 +269,7 @@ PyMODINIT_FUNC PyInit_agcall()
         {&n_num_kv_heads, "num_kv_heads"}, {&n_head_dim, "head_dim"}, {&n_dtype, "dtype"}};
     for (auto& x : names)
         if (!(*x.at = PyUnicode_InternFromString(x.name))) return nullptr;
-    return PyModule_Create(&module);
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", AG_BUILT_FOR) < 0) { Py_DECREF(m); return nullptr; }       // binding.py looks at it first
+    return m;
 }

@@ -28,6 +28,21 @@ def test_the_module_takes_no_host_tensors_and_ctypes_says_why():
     assert B._calls().kv_append(*args[:-1]) is None                    # too few
 
 
+def test_without_a_module_that_fits_every_call_goes_through_ctypes(tmp_path, monkeypatch):
+    """A missing file, one that is no module, and one built for another torch: a warning, and the calls of before the module."""
+    other = tmp_path / "agcall.so"
+    other.write_bytes(b"not a module")
+    for path, torch_version in [(tmp_path / "nothing.so", torch.__version__), (other, torch.__version__), (B.CALL_PATH, "0.0")]:
+        monkeypatch.setattr(B, "_native", None)
+        monkeypatch.setattr(B, "CALL_PATH", str(path))
+        monkeypatch.setattr(torch, "__version__", torch_version)
+        cache, x, i = small("cpu")
+        with pytest.warns(RuntimeWarning, match="ctypes"), pytest.raises(ValueError, match="contiguous CUDA"):
+            B.ag_kv_append(cache, x(1, 2, 128), x(1, 2, 128), i(0, 1).view(1, 2), i(0), i(1), i(0, 1), 1)
+        assert isinstance(B._native, B._NoCalls)
+        assert all(getattr(B._calls(), name)(1, 2, 3) is None for name in B._CALLS)
+
+
 @pytest.mark.gpu
 def test_plain_calls_equal_the_ctypes_path_and_others_are_refused_as_there():
     torch.manual_seed(5)
