@@ -44,7 +44,7 @@ def test_without_a_module_that_fits_every_call_goes_through_ctypes(tmp_path, mon
 
 
 @pytest.mark.gpu
-def test_plain_calls_equal_the_ctypes_path_and_others_are_refused_as_there():
+def test_plain_calls_equal_the_ctypes_path_and_others_are_refused_as_there(monkeypatch):
     torch.manual_seed(5)
     cache, x, i = small("cuda")
     n = [20, 1]
@@ -53,25 +53,33 @@ def test_plain_calls_equal_the_ctypes_path_and_others_are_refused_as_there():
     k, v, q = r(21, 2, 128), r(21, 2, 128), r(21, 8, 128)
     ws = torch.zeros(1 << 16, dtype=torch.float32, device="cuda")
     outs = []
-    # a torch stream is what the module leaves to ctypes; keywords and positions alike
-    for stream in (None, torch.cuda.current_stream()):
+    # keywords and positions alike
+    side = torch.cuda.Stream()
+    for stream, calls in ((None, B._calls()), (torch.cuda.current_stream(), B._calls()), (side, B._calls()), (side.cuda_stream, B._calls()),
+                          (None, B._NoCalls()), (side, B._NoCalls())):
+        monkeypatch.setattr(B, "_native", calls)
         c2 = B.KVCache(8, 16, 2, 128, B.AG_BF16, "cuda", fill=0.0)
         o = [torch.zeros_like(q) for _ in range(3)] + [torch.zeros_like(q[:2])]
+        st, ds, ws2, ctx2 = torch.zeros_like(o[3]), torch.zeros_like(o[3]), torch.zeros(1 << 20, dtype=torch.float32, device="cuda"), i(21, 2)
+        torch.cuda.synchronize()                                       # all of it is there, whatever stream the calls run on
         B.ag_kv_append(c2, k, v, bt, prefix_lens=prefix, new_lens=new, cu_new=cu, total_new=21, stream=stream)
         B.ag_attn_prefill(c2, q, o[0], bt, new, cu, 21, 20, 8, 0.09, stream=stream)
         B.ag_attn_resume(c2, q, o[1], bt, prefix, new, cu, 21, 20, 20, 8, 0.09, stream)
         B.ag_attn_merged(c2, q, o[2], bt, prefix, new, cu, 21, 20, 20, 8, 0.09, ws, stream)
         B.ag_attn_decode(c2, q[:2], o[3], bt, ctx, 20, 8, 0.09, ws, stream)
-        st, ds = torch.zeros_like(o[3]), torch.zeros_like(o[3])
         B.ag_attn_decode_static(c2, q[:2], ds, bt, ctx, 20, 8, 0.09, stream)
-        B.ag_decode_step(c2, k[:2], v[:2], q[:2], st, bt, i(21, 2), 21, 8, 0.09, torch.zeros(1 << 20, dtype=torch.float32, device="cuda"), stream)
+        B.ag_decode_step(c2, k[:2], v[:2], q[:2], st, bt, ctx2, 21, 8, 0.09, ws2, stream)
         torch.cuda.synchronize()
         outs.append(o + [st, ds, c2.k_pool, c2.v_pool])
-    for a, b in zip(*outs):
-        assert torch.equal(a.view(torch.int16), b.view(torch.int16)) and bool(a.any())
+    for same in zip(*outs):
+        assert all(torch.equal(a.view(torch.int16), same[0].view(torch.int16)) for a in same) and bool(same[0].any())
+    monkeypatch.undo()
     plain = [cache, q[:2], x(2, 8, 128), bt, ctx, 20, 8, 0.09, ws, None]
     call = B._calls().attn_decode
-    assert call(*plain) == B.AG_OK
+    for stream in (None, torch.cuda.current_stream(), side, torch.cuda.ExternalStream(side.cuda_stream), side.cuda_stream):
+        torch.cuda.synchronize()
+        assert call(*plain[:9], stream) == B.AG_OK
+    torch.cuda.synchronize()
     for at, value in [(1, q[:2, ::2]), (1, q[:2].cpu()), (1, None), (1, torch.nn.Parameter(q[:2].float()).as_subclass(type("T", (torch.Tensor,), {}))),
                       (3, bt.long()), (3, bt[0]), (5, 20.0), (5, np.int32(20)), (5, 1 << 40), (7, 1), (8, None), (9, "s")]:
         args = list(plain)
