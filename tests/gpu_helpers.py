@@ -134,10 +134,12 @@ def run_phase(cache, kp, vp, b: I.Batch, kind: str, scale=None):
     return got, ref
 
 
-def gpu_merged(cache, d: DevBatch, scale=None):
+def gpu_merged(cache, d: DevBatch, scale=None, own_kernel=False):
+    """own_kernel: an output that is not 16-byte aligned, which keeps a small queue on the merged kernel (test_dispatch.py)."""
     nbytes = B.ag_attn_merged_workspace_bytes(d.total, d.geom.num_q_heads, d.max_ctx)
     ws = torch.full((max(nbytes, 16) // 4,), float("nan"), dtype=torch.float32, device=DEV)
-    B.ag_attn_merged(cache, d.q, d.out, d.bt, d.prefix, d.new, d.cu, d.total, d.max_new, d.max_ctx,
+    out = torch.full((d.out.numel() + 1,), float("nan"), dtype=d.out.dtype, device=DEV)[1:].view(d.out.shape) if own_kernel else d.out
+    B.ag_attn_merged(cache, d.q, out, d.bt, d.prefix, d.new, d.cu, d.total, d.max_new, d.max_ctx,
                      d.geom.num_q_heads, d.geom.scale if scale is None else scale, ws)
     torch.cuda.synchronize()
-    return to_f64(d.out, d.geom.dtype)
+    return to_f64(out, d.geom.dtype)

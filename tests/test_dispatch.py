@@ -3,6 +3,7 @@ the sources): seen on the CPU, through a HIP runtime that logs launches."""
 import pytest
 
 from launches import launched
+from test_gpu_merged import FEW_ROWS, GROUPS, MIXES, SMALL
 
 
 @pytest.fixture(scope="module")
@@ -61,3 +62,29 @@ F64, F128 = dict(dtype="f32", d=64), dict(dtype="f32")
 def test_decode_one_workgroup_a_pair_or_shares(tmp, alone, batches):
     for b, k in zip(batches, kernels(tmp, *(dict(call="decode", page=32, **b) for b in batches))):
         assert [x.split("<")[0] for x in k] == (["decode_any_direct_kernel"] if alone else ["decode_any_split_kernel", "decode_any_merge_kernel"]), b
+
+
+def queue(sessions, hq=8, hkv=2, **more):
+    prefix, new = sessions
+    return dict(call="merged", hq=hq, hkv=hkv, batch=len(new), total=sum(new), max_new=max(new), max_ctx=max(p + n for p, n in zip(prefix, new)), **more)
+
+
+EXACT, MERGED, PREFILL = f"{SPLIT}<__bf16,128,false,true>", "merged_split_kernel", "prefill_"
+
+
+def test_queues_of_the_gpu_tests_fall_on_the_sides_that_they_name(tmp):
+    both = [MIXES[n] for n in ("empty_and_cold_like", "longest_kept", "only_resumes")] + [FEW_ROWS]
+    want = [(queue(b, hq, hkv, cus=cus), EXACT if cus == 256 else MERGED) for b in both for hq, hkv in (GROUPS if b is FEW_ROWS else [(8, 2)]) for cus in (256, 8)]
+    want += [(queue(MIXES[n], cus=cus), MERGED) for n in ("boundaries", "decodes_and_short_resumes") for cus in (256, 8)]
+    want += [(queue(MIXES["handed_to_the_prefill_kernel"], cus=cus), PREFILL) for cus in (256, 8)]
+    small = [queue(SMALL, hq, hkv) for hq, hkv in GROUPS] + [queue(([200], [12])), queue(([300] * 40, [1] * 40))]
+    want += [(c, EXACT) for c in small] + [(dict(c, out=(1 << 20) + 2), MERGED) for c in small]
+    for (c, name), k in zip(want, kernels(tmp, *(c for c, _ in want))):
+        assert k[0].startswith(name) and len(k) == (2 if name == MERGED else 1), (c, k)
+
+
+@pytest.mark.parametrize("sessions,name", [
+    (([1999] * 64, [1] * 64), MERGED), (([550, 300], [20, 8]), EXACT), (([2400, 900, 900], [100, 1, 1]), EXACT), (([6000, 900, 900], [30, 1, 1]), MERGED),
+    (([2700], [1]), MERGED), (([1100] * 4, [1] * 4), EXACT)])
+def test_queue_in_one_kernel_or_two(tmp, sessions, name):
+    assert kernels(tmp, queue(sessions, 32, 8))[0][0].startswith(name)

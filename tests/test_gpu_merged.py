@@ -55,14 +55,18 @@ def test_merged_batch_matches_oracle(name):
     check_close(got, ref, g.dtype, name)
 
 
-ON_A_PARTITION = [(n, 8, 2) for n in sorted(MIXES)] + [("few_rows", *h) for h in [(4, 4), (32, 8), (16, 2), (16, 1), (6, 2)]]
+FEW_ROWS = [900, 1500, 31, 0, 2100, 300], [9, 33, 1, 65, 1, 3]
+SMALL = [333, 1500, 64, 0], [1, 6, 19, 3]
+GROUPS = [(4, 4), (8, 4), (32, 8), (16, 2), (16, 1), (6, 2), (40, 8)]          # G = 1, 2, 4, 8, 16, 3, 5
+ON_A_PARTITION = [(n, 8, 2) for n in sorted(MIXES)] + [("few_rows", *h) for h in GROUPS]
 
 
 @pytest.mark.parametrize("name,hq,hkv", ON_A_PARTITION)
 def test_both_sides_of_the_line_to_the_split_prefill(name, hq, hkv):
-    """Queues around the rule that hands small ones to the prefill kernel which splits a tile's keys: what is a small queue on the
-    whole device is a large one on 8 CUs, where the merged kernel keeps it.  Both against the oracle."""
-    prefix, new = MIXES.get(name) or ([900, 1500, 31, 0, 2100, 300], [9, 33, 1, 65, 1, 3])
+    """Queues on the whole device and on 8 CUs, against the oracle.  The rule that hands small queues to the prefill kernel which splits
+    a tile's keys takes all of FEW_ROWS and three of the mixes on the whole device and none on 8 CUs; two mixes stay with the merged
+    kernel on both, one goes to the prefill kernels on both (test_dispatch.py)."""
+    prefix, new = MIXES.get(name) or FEW_ROWS
     g = geom(pages=2048, hq=hq, hkv=hkv)
     cache, kp, vp, chunk = filled(g, prefix, new, seed=340 + len(name))
     ref = oracle_attn(kp, vp, chunk)
@@ -81,12 +85,13 @@ def test_both_sides_of_the_line_to_the_split_prefill(name, hq, hkv):
         B.ag_stream_destroy(stream)
 
 
-@pytest.mark.parametrize("hq,hkv", [(4, 4), (8, 4), (32, 8), (16, 2), (16, 1), (6, 2), (40, 8)])
-def test_merged_batch_group_sizes(hq, hkv):
-    """G = 1, 2, 4, 8, 16 fill the 16 columns exactly; 3 and 5 leave one unused."""
+@pytest.mark.parametrize("own_kernel", [False, True])
+@pytest.mark.parametrize("hq,hkv", GROUPS)
+def test_merged_batch_group_sizes(hq, hkv, own_kernel):
+    """G = 1, 2, 4, 8, 16 fill the 16 columns exactly; 3 and 5 leave one unused.  By size the queue goes to the split prefill."""
     g = geom(pages=1024, hq=hq, hkv=hkv)
-    cache, kp, vp, chunk = filled(g, [333, 1500, 64, 0], [1, 6, 19, 3], seed=41 + hq)
-    check_close(gpu_merged(cache, DevBatch(chunk)), oracle_attn(kp, vp, chunk), g.dtype, f"G={hq // hkv}")
+    cache, kp, vp, chunk = filled(g, *SMALL, seed=41 + hq)
+    check_close(gpu_merged(cache, DevBatch(chunk), own_kernel=own_kernel), oracle_attn(kp, vp, chunk), g.dtype, f"G={hq // hkv}")
 
 
 def test_merged_equals_the_resume_and_decode_paths_within_tolerance_and_is_reproducible():
@@ -148,7 +153,8 @@ def test_merged_more_sessions_than_one_pass_of_the_plan():
     check_close(gpu_merged(cache, DevBatch(chunk)), oracle_attn(kp, vp, chunk), g.dtype, "300 sessions")
 
 
-def test_merged_names_the_planted_key_under_the_causal_limit():
+@pytest.mark.parametrize("own_kernel", [False, True])
+def test_merged_names_the_planted_key_under_the_causal_limit(own_kernel):
     """Each row's query points at one key; rows of one item differ in which keys they may see, so a wrong
     per-column limit (the item's instead of the row's) would let a row name a key from its future."""
     g = geom(pages=512, hq=8, hkv=2)
@@ -175,12 +181,55 @@ def test_merged_names_the_planted_key_under_the_causal_limit():
     for b in (fill, chunk):
         gpu_append(cache, DevBatch(b))
         oracle_append(kp, vp, b)
-    got = gpu_merged(cache, DevBatch(chunk))
+    got = gpu_merged(cache, DevBatch(chunk), own_kernel=own_kernel)
     check_close(got, oracle_attn(kp, vp, chunk), g.dtype, "planted")
     want = I.position_bits(tgt_self, 128)
     for i in range(n - 1):                           # the last row's "future" key is itself
         for h in range(8):
             assert np.array_equal(got[i, h] > 0.5, want[i] > 0.5), (i, h)
+
+
+def bf16_terms(x):
+    """A number as three bf16 numbers, 24 bits together."""
+    out = []
+    for _ in range(3):
+        out.append(float(I.bf16_bits_to_f32(I.f32_to_bf16_bits(np.array([x], np.float32)))[0]))
+        x = x - out[-1]
+    return out
+
+
+@pytest.mark.parametrize("own_kernel", [False, True])
+def test_queue_weights_stand_against_the_largest_score(own_kernel):
+    """Two keys of a row weigh 1 and 0.75, which bf16 holds, if weights stand against the row's largest score.  Against a reference that
+    the same wave met eight steps of 32 keys earlier and that lies 0.2 to 7.9 powers of two lower (it may be outgrown by 8 elsewhere)
+    the two would be rounded to 2^-9 of themselves, each its own way.  Values +1 and -1 make the result about 1/7, so that a difference
+    e of the two roundings moves it by 12/49 * e, and e reaches 2^-8: 0.0067 of the result.  Gate: the result's own rounding, 2^-9, and as much again for
+    scores in fp32 (2^-20 of a weight) and the other keys (2^-40): 0.0039."""
+    n = 40
+    g = geom(pages=n * 20, hq=8, hkv=2)
+    l, low = 301, 0.5 * np.log(2.0) * 80
+    k, v, q = np.zeros((n, l, 2, 128), np.float32), np.zeros((n, l, 2, 128), np.float32), np.zeros((n, 8, 128), np.float32)
+    top = 10.0
+    k[..., 0] = -float(low)                                    # 2^-54 of the largest, and less
+    for s, delta in enumerate(np.linspace(0.2, 7.9, n)):
+        for at, score in ((3, top - delta * np.log(2.0)), (260, top), (275, top + np.log(0.75))):
+            k[s, at, :, :3] = bf16_terms(score)
+    v[:, 260], v[:, 275] = 1.0, -1.0
+    q[:, :, :3] = 1.0
+    prefix, new = [l - 1] * n, [1] * n
+    bt = I.deal_block_tables(I.rng_for(61, 0), [l] * n, 16, g.num_pages)
+    fill = make_batch(g, [0] * n, prefix, seed=61, bt=bt, k=k[:, :-1].reshape(-1, 2, 128), v=v[:, :-1].reshape(-1, 2, 128))
+    chunk = make_batch(g, prefix, new, seed=61, bt=bt, stream=2, q=q, k=k[:, -1], v=v[:, -1])
+    cache = make_cache(g)
+    kp, vp = fresh_pools(g)
+    for b in (fill, chunk):
+        gpu_append(cache, DevBatch(b))
+        oracle_append(kp, vp, b)
+    ref = oracle_attn(kp, vp, chunk, scale=1.0)
+    weight = np.exp2(-np.linspace(0.2, 7.9, n))
+    assert np.allclose(ref, (0.25 / (1.75 + weight))[:, None, None], rtol=1e-5)
+    got = gpu_merged(cache, DevBatch(chunk), scale=1.0, own_kernel=own_kernel)
+    assert np.all(np.abs(got - ref) <= 2.0 ** -8 * ref), np.abs(got / ref - 1).max()
 
 
 def test_merged_other_shapes_take_the_general_path():

@@ -84,8 +84,7 @@ def test_plain_calls_equal_the_ctypes_path_and_others_are_refused_as_there(monke
                       (3, bt.long()), (3, bt[0]), (5, 20.0), (5, np.int32(20)), (5, 1 << 40), (7, 1), (8, None), (9, "s")]:
         args = list(plain)
         args[at] = value
-        if at != 3 or value.dim() == 2:
-            assert call(*args) is None, at
+        assert call(*args) is None, at
         if value is None and at == 1:
             with pytest.raises(B.AgError):
                 B.ag_attn_decode(*args)
