@@ -684,19 +684,25 @@ bool merged_mfma_supported(const AttnArgs& a)
 // Whether a queue is small enough for the prefill kernel that splits the keys of 32 (row, head) columns over a workgroup's waves: no
 // plan, no partials in memory and no merge, which are 16 us of a small queue here, but a workgroup walks its keys alone, 8 us +
 // 5.5 us per 1000 tokens.  r: its workgroups per CU.  Up to three, on contexts up to 2200 + 1500 r tokens; 1000 fewer where
-// the queue streams: most sessions are decodes, or every chunk is one group of rows.  Measured over 44 drawn queues (graph replay,
-// append included; this kernel -> that one, us, at r, longest context): 23 -> 10.6 (0.2, 570), 28 -> 14.4 (0.3, 1390), 22 -> 16.6 (0.3, 2130),
-// 24 -> 18.4 (0.2, 1900), 28 -> 20 (0.2, 2500), 32 -> 20.5 (1.8, 1730), 42 -> 29 (1.6, 1870), 68 -> 51 (2.1, 2200), 32 -> 28.7 (0.6, 2900),
-// 26 -> 23 (0.5, 2580).  On the other side 60 -> 63 (1.5, 4900); with the kernel 1 to 10 % faster than it is with exact references, 24 -> 36
-// (0.1, 6000), 35 -> 43 (0.2, 6800), 31 -> 35 (0.55, 5000), 25.8 -> 27.4 (0.3, 3670), streaming 16 -> 18 (0.07, 2700), 94 -> 95 (3.4, 1700).  Many
-// decodes on long contexts are bound by HBM, which equal shares of all the keys keep busy to the end: 79 -> 92 (2.2, 5500, 99 rows
-// of 57 sessions), 64 -> 67 (64 decodes up to 2000).
+// the queue streams: most sessions are decodes, or every chunk is one group of rows.  Measured, graph replay, append included; this kernel ->
+// that one, us, at r, longest context: 23 -> 10.6 (0.2, 570), 28 -> 14.4 (0.3, 1390), 22 -> 16.6 (0.3, 2130), 24 -> 18.4 (0.2, 1900), 28 ->
+// 20 (0.2, 2500), 32 -> 20.5 (1.8, 1730), 42 -> 29 (1.6, 1870), 68 -> 51 (2.1, 2200), 32 -> 28.7 (0.6, 2900), 26 -> 23 (0.5, 2580).  On the
+// other side 25 -> 29 (0.23, 3970), 28 -> 31 (0.55, 4480), 39 -> 53 (0.64, 4570), 60 -> 63 (1.5, 4900), streaming 17 -> 18 (0.02, 2530), 20
+// -> 23 (0.39, 2540), 36 -> 44 (0.88, 3260); up to 700 tokens past the line either is ahead, by 10 %.
+// A CU holds one of that kernel's workgroups, so beyond one a CU the long contexts go in rounds, where equal shares of all the keys keep HBM
+// busy to the end: decodes only up to 1800 tokens then (1500 from 1.5 a CU on), 47.5 -> 56 (1.3, 1820), 79 -> 92 (2.2, 5500, 99
+// rows of 57 sessions), and chunks only up to 2200 unless the KV heads are a multiple of eight.  An XCD takes an eighth of the (head, tile)
+// list, which with fewer heads is a run of sessions, and the XCD with the longest ones ends last: at two heads 54 -> 78 (1.5, 4290), 50 -> 64
+// (1.8, 3750), where 8 heads have 53 -> 34 (1.5, 3740), 66 -> 49 (2.3, 2730), 88 -> 62 (2.2, 4400).
+// Over 2520 drawn queues, on 32 to 256 CUs, the line is 1.28 times faster than this kernel alone (the faster side of each: 1.32); it is over
+// 1.5 % slower at 56, at worst 38 -> 49 us.
 static bool split_preferred(const AttnArgs& a, hipStream_t st)
 {
     const int64_t G = a.hq / a.c.hkv, cus = stream_cus(st);
     if ((uintptr_t)a.out % 16 != 0 || (int64_t)a.total_rows * G > 0x7fffffff) return false;
     const int64_t wgs = a.c.hkv * std::min<int64_t>(a.total_rows * G / 32 + a.batch, (int64_t)a.batch * ((a.max_new * G + 31) / 32));
     const bool decodes = (int64_t)a.total_rows < 2 * (int64_t)a.batch;         // most sessions bring one row
+    if (wgs > cus && a.max_ctx > (decodes ? 1800 : a.c.hkv % 8 ? 2200 : INT32_MAX)) return false;
     if (decodes && 2 * wgs > 3 * cus && a.max_ctx > 1500) return false;
     const int64_t ctx = decodes || a.max_new <= rows_per_group(a.hq, a.c.hkv) ? 1200 : 2200;
     return wgs <= 3 * cus && (a.max_ctx - ctx) * cus <= 1500 * wgs;

@@ -85,6 +85,15 @@ def test_queues_of_the_gpu_tests_fall_on_the_sides_that_they_name(tmp):
 
 @pytest.mark.parametrize("sessions,name", [
     (([1999] * 64, [1] * 64), MERGED), (([550, 300], [20, 8]), EXACT), (([2400, 900, 900], [100, 1, 1]), EXACT), (([6000, 900, 900], [30, 1, 1]), MERGED),
-    (([2700], [1]), MERGED), (([1100] * 4, [1] * 4), EXACT)])
+    (([2700], [1]), MERGED), (([1100] * 4, [1] * 4), EXACT),
+    # more than one workgroup a CU: decodes on contexts past 1800
+    (([1799] * 40, [1] * 40), EXACT), (([1819] * 40, [1] * 40), MERGED)])
 def test_queue_in_one_kernel_or_two(tmp, sessions, name):
     assert kernels(tmp, queue(sessions, 32, 8))[0][0].startswith(name)
+
+
+def test_queue_of_few_heads_and_more_than_one_workgroup_a_cu(tmp):
+    """Chunks on long contexts go by the merged kernel unless the heads spread over the XCDs."""
+    for (hkv, cus, ctx), name in [((8, 256, 3700), EXACT), ((2, 64, 3700), MERGED), ((2, 64, 2100), EXACT), ((2, 256, 2900), EXACT)]:
+        c = queue(([ctx] * 12 + [900] * 6, [36] * 12 + [1] * 6), 4 * hkv, hkv, cus=cus)
+        assert kernels(tmp, c)[0][0].startswith(name), (hkv, cus, ctx)
