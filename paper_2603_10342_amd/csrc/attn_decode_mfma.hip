@@ -315,7 +315,7 @@ __global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_
                     const int head = idx >> 5, d = (idx & (D / 4 - 1)) * 4;
                     const int64_t row = (int64_t)s * hq + (int64_t)g * G + head;
                     float y[4];
-                    merge_coherent<false>(ws_o, ws_ml, row * pmax, min(pieces, pmax), d, D, y);
+                    merge_coherent(ws_o, ws_ml, row * pmax, min(pieces, pmax), d, y);
                     store_quad((__bf16*)a.out + row * D + d, y);
                 }
                 if (tid_e == 0) sa.counters[s * hkv + g] = 0;      // as the next call expects it

@@ -1,6 +1,6 @@
 // Pieces shared by the kernels that deal a batch's contexts in equal shares and merge partials: the decode step and
 // the merged decode + short-resume batch (bf16, head_dim 128, page 16: D and PS below), and the decode step of every other
-// geometry (attn_decode_any.hip), which takes the plan, the merge and the choice rules.  Internal; not part of the ABI.
+// geometry (attn_decode_any.hip), which takes the plan and the merge.  Internal; not part of the ABI.
 #pragma once
 
 #include "ag_internal.h"
@@ -114,17 +114,15 @@ __device__ __forceinline__ void store_quad(E* out, const float (&y)[4])
     }
 }
 
-// Channels d .. d + 3 of a (row, head) with D_ channels, from partials that other workgroups of the SAME launch wrote
-// (store_coherent): read with device-scope loads, which do not hit in this XCD's caches.  Four channels a thread, 16 bytes of
+// Channels d .. d + 3 of a (row, head), from partials that other workgroups of the SAME launch wrote (store_coherent): read with device-scope loads, which do not hit in this XCD's caches.  Four channels a thread, 16 bytes of
 // a partial in two loads: with one channel a thread a group of 16 heads was eight such chains one after another (step of
 // 53 sessions of 750..3260 tokens at 16 / 1 heads 36.4 -> 23.1 us, one session of 8000 at 32 / 8 20.5 -> 15.7, of 1000 8.0 -> 7.4).
-template <bool kNatural>
 __device__ __forceinline__ void merge_coherent(const float* __restrict__ ws_o, const float* __restrict__ ws_ml, int64_t base, int n,
-                                               int d, int D_, float (&y)[4])
+                                               int d, float (&y)[4])
 {
-    merge_channels<4, kNatural, 8>(n, [&](int i, float& m, float& l, float (&o)[4]) {
+    merge_channels<4, false, 8>(n, [&](int i, float& m, float& l, float (&o)[4]) {
         const f32x2 ml = load_coherent(ws_ml + (base + i) * 2);
-        const f32x2 lo = load_coherent(ws_o + (base + i) * D_ + d), hi = load_coherent(ws_o + (base + i) * D_ + d + 2);
+        const f32x2 lo = load_coherent(ws_o + (base + i) * D + d), hi = load_coherent(ws_o + (base + i) * D + d + 2);
         m = ml[0];
         l = ml[1];
         o[0] = lo[0];
@@ -229,8 +227,7 @@ __device__ __forceinline__ bool find_share(const int32_t* __restrict__ ctx_lens,
 // is where that turns for a single session; with more than half of the CUs busy either way, 512 KiB.
 // Measured at 32 / 8 heads, graph replay, shares -> direct.  ag_decode_step, bf16 / 128: one session of 100 tokens 8.5 -> 5.3
 // us, of 512 8.1 -> 7.2, of 1000 8.3 -> 8.8; four of 1000 9.3 -> 12.7; 32 of 100..512 18.2 -> 10.5, 32 of 500..1000 24.4
-// -> 20.0.  Append + ag_attn_decode: fp32 / 128, one of 256 tokens 16.8 -> 13.9, of 512 16.7 -> 18.7, 32 of 512 34.8 ->
-// 31.1; bf16 / 64, one of 1000 10.7 -> 9.4.
+// -> 20.0.  (The other shapes have a line of their own, one_workgroup_a_pair() in attn_decode_any.hip.)
 inline bool direct_preferred(int64_t pairs, int64_t bytes, int cus)
 {
     return pairs <= cus && bytes <= (2 * pairs > cus ? 512 << 10 : 256 << 10);
