@@ -13,8 +13,8 @@
 //     group's keys and values sit in the page as in a 16-token page, only with a larger chunk stride for K.
 //   - Two sub-steps of loads are in flight per wave where a sub-step is 16 KiB or less (head_dim 64 and 128):
 //     with half the bytes per token, one in flight does not cover the latency.
-//   - At 256 channels a sub-step's operands and O^T fill the registers: the fp32 split kernel spills 11, outside its step
-//     loop; the dimensions between 128 and 256, which run as 256 with bounds, spill 44 (bf16: 26), 13 (5) of them read back
+//   - At 256 channels a sub-step's operands and O^T fill the registers: the fp32 split kernel spills 13, outside its step
+//     loop; the dimensions between 128 and 256, which run as 256 with bounds, spill 45 (bf16: 26), 13 (5) of them read back
 //     in every step.
 // Whole decode step, append included (one wave per (row, query head) before -> now): 16 fp32 sessions of 1024..4096
 // tokens at 32 / 8 heads x 128, 2760 -> 75 us (369 MB, 4.9 TB/s; split kernel 66 us); 48 bf16 sessions of 700..5000 at

@@ -19,8 +19,8 @@
 // the layouts of the bf16 kernels, [chunk of 8 channels][key][8] and [chunk of 8 keys][channel][8], two stages.
 // Weights are split in registers.  What bounds it is matrix and vector work one after the other: 96 products of 32 clocks a
 // tile and wave at 128 channels against 128 of 64, and less than that in softmax, splitting and operand reads.
-// Measured, append included, 32 / 8 heads, fp32 products -> terms: four prompts of 300..1500 rows, 128 channels 384 -> 264
-// us (136 TFLOP/s of result); eight of 2048, 2510 -> 1640.  Scores in three accumulators and value products grouped by
+// Measured, append included, 32 / 8 heads, fp32 products -> terms: four prompts of 300..1500 rows, 128 channels 384 -> 266
+// us (135 TFLOP/s of result); eight of 2048, 2510 -> 1630.  Scores in three accumulators and value products grouped by
 // term: 3..5 % slower.  The watch on small numbers is 0.4..1.6 % of it, all in the epilogue.
 //
 // A wave issues in order, and a matrix product behind another holds up the vector work behind it: the weights and the

@@ -13,8 +13,12 @@
 // eight steps at 128 channels, 128 KiB, takes 1.0 us where the same loads alone take 0.9 from L2; scores of the next step
 // beside the weights of this one, a second step's keys in flight, or neighbours starting at other steps of a ring of 4 to 16
 // all measured slower.  Rest of a call on 6000 tokens (35 us): the append, 8 us of start, merge and launch.  Locating a
-// step's pages once for K and V: 36.8 -> 35.1 us there, eight chunks of 50 rows on 2000 tokens 29.0 -> 28.5.  The line to the
-// other kernels is at prefill_split_preferred().
+// step's pages once for K and V: 36.8 -> 35.1 us there, eight chunks of 50 rows on 2000 tokens 29.0 -> 28.5; fp32 at 64 channels 1 to 3
+// % (125.7 -> 123.9).  fp32 at 128 gains 0.6 % on average over 66 drawn batches, but not everywhere: where the waves' one or two steps
+// fall badly it is 4 to 9 % slower (eight chunks of 9 rows on 240..300 tokens, 23.7 -> 26.0 on 270), and 1.5 % with 211 rows on 6000
+// (228.4 -> 232.4; 9 rows 235.1 -> 234.0, 4000 164.8 -> 163.2).  Locating twice there, with an explicit wait for the first values, or with
+// a higher priority for waves of more steps, moves these cases about by as much.  The line to the other kernels is at
+// prefill_split_preferred().
 #include <algorithm>
 #include <atomic>
 
