@@ -4,7 +4,7 @@ whatever is there (a row that falls back on plain arithmetic has other bits)."""
 import pytest
 import torch
 
-from gpu_helpers import DevBatch, make_cache
+from gpu_helpers import DevBatch, gpu_decode, gpu_merged, make_cache
 from helpers import make_batch
 from paper_2603_10342_amd import binding as B
 from paper_2603_10342_amd import inputs as I
@@ -49,3 +49,26 @@ def test_what_no_row_may_see_leaves_every_bit(dtype, d, ps, hq, hkv, per_xcd):
         rows[(chunk.cu[1:] - 1).long()] = False                    # the only rows that see the last key
         for key in (float("nan"), float("inf")):
             assert torch.equal(outputs(g, prefix, new, 0.0, last_key=key)[0][rows], want[rows]), f"a later key of {key}"
+
+
+@pytest.mark.parametrize("per_xcd", [0, 1])
+@pytest.mark.parametrize("dtype,d,ps,hq,hkv", SHAPES)
+def test_decode_and_queue_do_not_see_stale_slots(dtype, d, ps, hq, hkv, per_xcd):
+    """Decodes whose contexts end inside a group, at its end and inside a step; as a decode batch and as a queue beside a chunk."""
+    g = I.Geometry(hq, hkv, d, ps, 6144 // ps + 64, dtype)
+    prefix, new = [0, 15, 16, 37, 150, 700, 4000, 90], [1, 1, 1, 1, 1, 1, 1, 9]
+    want = None
+    with cus(per_xcd):
+        for stale in (0.0, float("nan"), float("inf"), -float("inf")):
+            bt = I.deal_block_tables(I.rng_for(84, 0), [p + n for p, n in zip(prefix, new)], ps, g.num_pages)
+            cache = make_cache(g)
+            cache.k_pool.fill_(stale)
+            cache.v_pool.fill_(stale)
+            fill, chunk = DevBatch(make_batch(g, [0] * 8, prefix, seed=84, bt=bt)), DevBatch(make_batch(g, prefix, new, seed=84, bt=bt, stream=2))
+            for b in (fill, chunk):
+                B.ag_kv_append(cache, b.k_new, b.v_new, b.bt, b.prefix, b.new, b.cu, b.total)
+            got = [gpu_decode(cache, chunk.q[:8].contiguous(), chunk.bt, chunk.ctx, chunk.max_ctx, g), gpu_merged(cache, chunk),
+                   gpu_merged(cache, chunk, own_kernel=True)]
+            want = want or got
+            for a, b in zip(got, want):
+                assert (a == b).all(), f"stale slots of {stale}"
