@@ -19,7 +19,8 @@
 // derives the plan itself from the context lengths (a sum and a scan over the batch: the lengths live on
 // the device, and a planning launch ahead of this one would cost more than it saves).
 //
-//   split kernel, per segment: the 4 waves take contiguous quarters and walk them one step at a time:
+//   split kernel, per segment: the 4 waves take contiguous quarters and walk them one step at a time, the next step's keys
+//   on their way once this one's have been used, and its values likewise:
 //     S^T[token][head] = K[token][:] . Q[head][:]     2 x 4 MFMA 16x16x32 (heads padded to 16)
 //     streaming softmax on S^T (running max m, running sum l; exp2 with log2(e) folded in)
 //     O^T[d][head]    += V^T[d][token] . P^T[token][head]   8 MFMA 16x16x32
@@ -63,25 +64,17 @@ struct StepArgs {
     int32_t* counters;          // [B * Hkv]
 };
 
-constexpr int kQRow = 2 * D + 16;        // bytes of a query row in LDS, padded
-
-// One wave's part of a segment - steps my_u .. my_u + my_n - 1 (at most 32) of pair (s, g), whose context has ctx tokens:
-// the running maximum, the running sum (this lane's share) and O^T of the pair's heads.  Contains one workgroup barrier
-// (Q goes through LDS, written by the first 256 threads).  appends: this wave's last step is the pair's last, and it
-// writes the step's token first.
+// One wave's part of a segment - steps my_u .. my_u + my_n - 1 of pair (s, g), whose context has ctx tokens: the running
+// maximum, the running sum (this lane's share) and O^T of the pair's heads.  appends: this wave's last step is the pair's
+// last, and it writes the step's token first.
 __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& sa, bool appends, int s, int g, int G, int ctx,
-                                             int my_u, int my_n, int tid, unsigned char* s_q, float& m, float& lsum, f32x4 (&o)[8])
+                                             int my_u, int my_n, int lane, float& m, float& lsum, f32x4 (&o)[8])
 {
-    const int hkv = a.c.hkv, hq = a.hq, lane = tid & 63;
+    const int hkv = a.c.hkv, hq = a.hq;
     const __bf16* kpool = (const __bf16*)a.c.k;
     const __bf16* vpool = (const __bf16*)a.c.v;
     const float sl2 = a.scale * kLog2e;
-    // Everything a lane derives from its number is derived again in each segment, behind a barrier the
-    // compiler cannot see through: hoisted out of the segment loop those values would stay in registers across
-    // the step loop, which needs all 128 for the 16 loads of a step to be in flight together.
-    int lane_s = lane;
-    asm volatile("" : "+v"(lane_s));
-    const int r = lane_s & 15, c = lane_s >> 4;
+    const int r = lane & 15, c = lane >> 4;
     // Row r of the first score product is slot (r & 7) of page (r >> 3) of the step; the second product takes
     // slots 8..15.  K page layout [chunk][slot][8]: lanes r = 0..7 of one lane group read 128 contiguous bytes.
     // Lane group c then owns slots (c&1)*4 + {0..3} and 8 + (c&1)*4 + {0..3} of page (c >> 1): exactly the 8
@@ -91,80 +84,104 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& 
     const int v_pg = c >> 1;
     const int v_off = ((c & 1) * D + r) * 8;             // value page [half][channel][8 keys]; + mb * 16 * 8 per block
 
-    // Q of the pair's G heads goes through LDS (rows of 256 B + 16 B of padding, zero beyond G): as the B
-    // operand, column = head r, k = channels kk*32 + c*8 .. +7, read when a step needs it rather than
-    // held in 16 registers across the loads.
-    // Decode step: the segment that ends the pair also appends the step's token (position ctx - 1).  The wave whose
-    // part holds the pair's last step writes it - 16 lanes a 16-byte piece of the key each, every lane two
-    // channels of the value - and waits for these stores before it loads that step (below).
-    // Every load of this prologue (Q, page ids, the new token) is issued before the first of them is used.
-    int tid_q = tid;                                     // the first 256 threads: 16 heads x 16 pieces of 16 bytes
-    asm volatile("" : "+v"(tid_q));
-    const int head_q = tid_q >> 4, ch_q = tid_q & 15;
-    u32x4 qx = {0, 0, 0, 0};
-    if (head_q < G)
-        qx = *reinterpret_cast<const u32x4*>((const __bf16*)a.q + ((int64_t)s * hq + (int64_t)g * G + head_q) * D + ch_q * 8);
-    // physical pages of this wave's steps (lane i: page i of its run, clamped to the session's last page)
-    const int last_lp = ((ctx + PS - 1) >> 4) - 1;
-    int my_pid = 0;
-    if (my_n > 0) my_pid = a.bt[(int64_t)s * a.max_pages + min(2 * my_u + lane_s, last_lp)];
-    u32x4 new_k = {0, 0, 0, 0};
-    __bf16 new_v0 = (__bf16)0.0f, new_v1 = (__bf16)0.0f;
-    if (appends) {
-        const __bf16* ks = sa.k_new + ((int64_t)s * hkv + g) * D;
-        const __bf16* vs = sa.v_new + ((int64_t)s * hkv + g) * D;
-        if (lane_s < 16) new_k = *reinterpret_cast<const u32x4*>(ks + lane_s * 8);
-        new_v0 = vs[lane_s];
-        new_v1 = vs[lane_s + 64];
-    }
-    if (head_q < 16) *reinterpret_cast<u32x4*>(s_q + head_q * kQRow + ch_q * 16) = qx;
-    if (appends) {
-        const int slot = (ctx - 1) & (PS - 1);
-        const int64_t page = __builtin_amdgcn_readlane(my_pid, last_lp - 2 * my_u);   // the run holds the last page
-        __bf16* kdst = (__bf16*)a.c.k + (page * hkv + g) * (int64_t)(D * PS);
-        __bf16* vdst = (__bf16*)a.c.v + (page * hkv + g) * (int64_t)(D * PS);
-        if (lane_s < 16) *reinterpret_cast<u32x4*>(kdst + (lane_s * PS + slot) * 8) = new_k;
-        vdst[v_offset(slot, lane_s, PS, D)] = new_v0;
-        vdst[v_offset(slot, lane_s + 64, PS, D)] = new_v1;
-    }
-
     m = -INFINITY;
     lsum = 0.0f;
 #pragma unroll
     for (int mb = 0; mb < 8; ++mb) o[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    __syncthreads();                                 // Q is in LDS
-    const unsigned char* q_lane = s_q + r * kQRow + c * 16;
+    if (my_n <= 0) return;
 
-#pragma unroll 1
-    for (int st = 0; st < my_n; ++st) {
-        StepRegs x;
-        if (appends && st == my_n - 1) {             // the token this wave appended lies in the page loaded next
-            __builtin_amdgcn_s_waitcnt(0x0070 | (0xF << 8));          // vmcnt(0): its stores have been performed
-            asm volatile("" ::: "memory");
-        }
-        {
-            const int64_t pA = __builtin_amdgcn_readlane(my_pid, 2 * st);
-            const int64_t pB = __builtin_amdgcn_readlane(my_pid, 2 * st + 1);
-            const __bf16* kp = kpool + ((k_pg ? pB : pA) * hkv + g) * (int64_t)(D * PS) + k_off;
-            const __bf16* vp = vpool + ((v_pg ? pB : pA) * hkv + g) * (int64_t)(D * PS) + v_off;
+    // Q of the pair's G heads as the B operand: column = head r (zero beyond G), k = channels kk * 32 + c * 8 .. + 7.  Held in
+    // registers: a wave waits for no other before its epilogue, and for nothing but page ids before its first keys.
+    // Decode step: the segment that ends the pair also appends the step's token (position ctx - 1).  The wave whose
+    // part holds the pair's last step writes it - 16 lanes a 16-byte piece of the key each, every lane two
+    // channels of the value - once its first step's keys are there, and waits for these stores before it loads that step.
+    // Every load of this prologue (page ids, Q, the new token) is issued before the first of them is used.
+    bf16x8 qf[4];
+    {
+        const __bf16* qrow = (const __bf16*)a.q + ((int64_t)s * hq + (int64_t)g * G + min(r, G - 1)) * D + c * 8;
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                x.k1[kk] = ld16_stream(kp + kk * 4 * PS * 8);
-                x.k2[kk] = ld16_stream(kp + kk * 4 * PS * 8 + 64);
-            }
+        for (int kk = 0; kk < 4; ++kk) qf[kk] = ld16(qrow + kk * 32);
+    }
+    const int last_lp = ((ctx + PS - 1) >> 4) - 1;
+    // physical pages of a step, clamped to the session's last page; the address is uniform and the table read-only for the
+    // kernel's lifetime: scalar loads
+    typedef const __attribute__((address_space(4))) int32_t* cptr_t;
+    const cptr_t bt = (cptr_t)(uintptr_t)(a.bt + (int64_t)s * a.max_pages);
+    struct Pages { int a, b; };
+    auto pages_of = [&](int st) { return Pages{bt[min(2 * (my_u + st), last_lp)], bt[min(2 * (my_u + st) + 1, last_lp)]}; };
+    Pages pg = pages_of(0);
+    u32x4 new_k = {0, 0, 0, 0};
+    __bf16 new_v0 = (__bf16)0.0f, new_v1 = (__bf16)0.0f;
+    int64_t last_page = 0;
+    if (appends) {
+        const __bf16* ks = sa.k_new + ((int64_t)s * hkv + g) * D;
+        const __bf16* vs = sa.v_new + ((int64_t)s * hkv + g) * D;
+        last_page = bt[last_lp];
+        if (lane < 16) new_k = *reinterpret_cast<const u32x4*>(ks + lane * 8);
+        new_v0 = vs[lane];
+        new_v1 = vs[lane + 64];
+    }
+
+    StepRegs x;
+    auto load_k = [&](Pages p) {
+        const __bf16* kp = kpool + ((int64_t)(k_pg ? p.b : p.a) * hkv + g) * (int64_t)(D * PS) + k_off;
 #pragma unroll
-            for (int mb = 0; mb < 8; ++mb) x.v[mb] = ld16_stream(vp + mb * 16 * 8);
-            // all 16 loads are in flight before anything waits: left to itself the scheduler starts the
-            // score product on the first keys and issues the value loads a memory latency later
-            __builtin_amdgcn_sched_barrier(0);
+        for (int kk = 0; kk < 4; ++kk) {
+            x.k1[kk] = ld16_stream(kp + kk * 4 * PS * 8);
+            x.k2[kk] = ld16_stream(kp + kk * 4 * PS * 8 + 64);
         }
+    };
+    auto load_v = [&](Pages p) {
+        const __bf16* vp = vpool + ((int64_t)(v_pg ? p.b : p.a) * hkv + g) * (int64_t)(D * PS) + v_off;
+#pragma unroll
+        for (int mb = 0; mb < 8; ++mb) x.v[mb] = ld16_stream(vp + mb * 16 * 8);
+    };
+    auto stores_performed = [&] {                        // the token this wave appended lies in the page loaded next
+        __builtin_amdgcn_s_waitcnt(0x0070 | (0xF << 8));                  // vmcnt(0)
+        asm volatile("" ::: "memory");
+    };
+    auto append = [&] {
+        const int slot = (ctx - 1) & (PS - 1);
+        __bf16* kdst = (__bf16*)a.c.k + (last_page * hkv + g) * (int64_t)(D * PS);
+        __bf16* vdst = (__bf16*)a.c.v + (last_page * hkv + g) * (int64_t)(D * PS);
+        if (lane < 16) *reinterpret_cast<u32x4*>(kdst + (lane * PS + slot) * 8) = new_k;
+        vdst[v_offset(slot, lane, PS, D)] = new_v0;
+        vdst[v_offset(slot, lane + 64, PS, D)] = new_v1;
+    };
+    if (appends && my_n == 1) {
+        append();
+        stores_performed();
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_k(pg);
+    load_v(pg);
+    pg = pages_of(1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+        if (r >= G) qf[kk] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+
+    // One step; unless it is the wave's last, the next step's keys are requested as soon as the score products have taken
+    // this one's, and its values as soon as the second product has: half a step of every wave is always in flight, in the
+    // registers of one.  A read of such pages alone takes 173 us for 1183 MB this way and 182 with 16 loads that are waited
+    // for together (6.8 and 6.5 TB/s).  64 sessions of 1024..8192 tokens, one launch: 201.5 -> 195 us (1181 MB; 512
+    // workgroups instead of 1024 are part of it: page ids are scalar loads a step ahead, so that a share may be of any length).
+    // Only a wave's last step can reach behind the context.
+    auto step = [&](int st, auto last_c) {
+        constexpr bool kLast = decltype(last_c)::value;
         const int tok0 = (my_u + st) * 32;
         f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            const bf16x8 qk = *reinterpret_cast<const bf16x8*>(q_lane + kk * 64);
-            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.k1[kk], qk, s1, 0, 0, 0);
-            s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.k2[kk], qk, s2, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.k1[kk], qf[kk], s1, 0, 0, 0);
+            s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.k2[kk], qf[kk], s2, 0, 0, 0);
+        }
+        if constexpr (!kLast) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (appends && st == 0) append();            // (the first step's keys, requested behind the token, have arrived)
+            if (appends && st + 2 == my_n) stores_performed();
+            load_k(pg);
+            __builtin_amdgcn_sched_barrier(0);
         }
         // s1[i]: token tokb + i, s2[i]: token tokb + 8 + i, of head r
         const int tokb = tok0 + (c >> 1) * PS + (c & 1) * 4;
@@ -172,8 +189,8 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& 
         float xs[8];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            xs[i] = (i < keep) ? s1[i] * sl2 : -INFINITY;
-            xs[4 + i] = (8 + i < keep) ? s2[i] * sl2 : -INFINITY;
+            xs[i] = !kLast || i < keep ? s1[i] * sl2 : -INFINITY;
+            xs[4 + i] = !kLast || 8 + i < keep ? s2[i] * sl2 : -INFINITY;
         }
         float mx = fmaxf(fmaxf(fmaxf(xs[0], xs[1]), fmaxf(xs[2], xs[3])), fmaxf(fmaxf(xs[4], xs[5]), fmaxf(xs[6], xs[7])));
         mx = fmaxf(mx, __shfl_xor(mx, 16));
@@ -190,7 +207,7 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& 
         }
         lsum = lsum * alpha + psum;
         m = m_new;
-        if (tok0 + 32 > ctx) {           // last, partial step: unwritten slots may hold anything, NaN included
+        if (kLast && tok0 + 32 > ctx) {  // last, partial step: unwritten slots may hold anything, NaN included
 #pragma unroll
             for (int mb = 0; mb < 8; ++mb) x.v[mb] = keep_quads(x.v[mb], keep, keep - 8);
         }
@@ -199,7 +216,16 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& 
             o[mb] *= alpha;
             o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.v[mb], pb, o[mb], 0, 0, 0);
         }
-    }
+        if constexpr (!kLast) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_v(pg);
+            pg = pages_of(st + 2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+#pragma unroll 1
+    for (int st = 0; st + 1 < my_n; ++st) step(st, std::false_type{});
+    step(my_n - 1, std::true_type{});
 }
 
 // kStep = false: the split half of ag_attn_decode (partials to the workspace, merged by decode_merge_kernel).
@@ -208,15 +234,16 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& 
 // read that page does it, and waits for its own stores before it loads the page - and the workgroup that is
 // last to finish a pair's segments (an atomic count per pair) merges them, in segment order whoever comes last,
 // so the result does not depend on timing; a pair that lies inside one share is normalised and written directly.
+constexpr int kWorkgroupsPerCu = 2;     // four measured 1.5 % slower: each pays the plan, and each segment a read of page ids
+
 template <bool kStep>
-__global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_t* __restrict__ hdr,
+__global__ __launch_bounds__(256, kWorkgroupsPerCu) void decode_split_kernel(AttnArgs a, int32_t* __restrict__ hdr,
                                                               float* __restrict__ ws_o, float* __restrict__ ws_ml,
                                                               int pmax, StepArgs sa)
 {
     __shared__ float s_o[4][16][D];     // per wave, per (padded) head: unnormalised O
     __shared__ float s_m[4][16];
     __shared__ float s_l[4][16];
-    __shared__ __attribute__((aligned(16))) unsigned char s_q[16 * kQRow];
     __shared__ int s_arrived;           // kStep: how many of the pair's segments had been finished before this one
 
     const int B = a.batch, hkv = a.c.hkv, hq = a.hq;
@@ -243,14 +270,14 @@ __global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_
     for (int f = f0; f < f1 && s < B;) {                 // one segment per pass; every value here is uniform
         const int k = min(n - u, f1 - f);                // steps of this segment, 1 .. q
         if (k <= 0) break;                               // (only if the lengths changed under the kernel: never spin)
-        const int per = (k + 3) >> 2;                    // steps per wave, at most kMaxSteps / 4 = 32
+        const int per = (k + 3) >> 2;                    // steps per wave
         const int my_u = u + w * per;
         const int my_n = max(0, min(per, k - w * per));
 
         const bool appends = kStep && u + k == n && w == (k - 1) / per;        // uniform over the wave
         float m, lsum;
         f32x4 o[8];
-        attend_steps(a, sa, appends, s, g, G, ctx, my_u, my_n, tid, s_q, m, lsum, o);
+        attend_steps(a, sa, appends, s, g, G, ctx, my_u, my_n, lane, m, lsum, o);
         lsum += __shfl_xor(lsum, 16);
         lsum += __shfl_xor(lsum, 32);
 
@@ -340,23 +367,24 @@ __global__ __launch_bounds__(256, 4) void decode_split_kernel(AttnArgs a, int32_
     }
 }
 
-// A batch of few, short contexts: one workgroup of 16 waves per (session, KV head) pair, which shares the pair's steps
+// A batch of few, short contexts: one workgroup of 8 waves per (session, KV head) pair, which shares the pair's steps
 // and writes the result itself - no plan, no partials, no merge (whose dependent round trips are most of a small step:
 // see direct_preferred()).  The waves' results meet in LDS, of which a launch takes what its group size needs.
-constexpr int kDirectWaves = 16;
-constexpr int kDirectMaxSteps = kDirectWaves * 32;                       // page ids of a wave's steps: one per lane
+// (16 waves of 128 registers, all loads of a step waited for together: 32 sessions of 400 tokens, 32 / 8 heads, 11.8 us instead of
+// 10.8; 4 of 300 6.3 instead of 5.75.)
+constexpr int kDirectWaves = 8;
+constexpr int kDirectMaxTokens = 16 << 10;
 inline size_t direct_lds(int G) { return (size_t)kDirectWaves * G * (D + 2) * sizeof(float); }
 
 template <bool kStep>
-__global__ __launch_bounds__(64 * kDirectWaves, 4) void decode_direct_kernel(AttnArgs a, StepArgs sa)
+__global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_direct_kernel(AttnArgs a, StepArgs sa)
 {
     extern __shared__ __attribute__((aligned(16))) float s_dyn[];          // [wave][head][D], then m and l [wave][head]
-    __shared__ __attribute__((aligned(16))) unsigned char s_q[16 * kQRow];
     const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int s = blockIdx.x / hkv, g = blockIdx.x - s * hkv;
-    const int ctx = min(a.ctx_lens[s], kDirectMaxSteps * 32);
+    const int ctx = min(a.ctx_lens[s], kDirectMaxTokens);
     __bf16* out = (__bf16*)a.out + ((int64_t)s * hq + (int64_t)g * G) * D;
     if (ctx <= 0) {                     // uniform over the workgroup
         for (int idx = tid; idx < G * D; idx += 64 * kDirectWaves) out[idx] = (__bf16)0.0f;
@@ -366,7 +394,7 @@ __global__ __launch_bounds__(64 * kDirectWaves, 4) void decode_direct_kernel(Att
     const int my_u = w * per, my_n = max(0, min(per, n - my_u));
     float m, lsum;
     f32x4 o[8];
-    attend_steps(a, sa, kStep && w == (n - 1) / per, s, g, G, ctx, my_u, my_n, tid, s_q, m, lsum, o);
+    attend_steps(a, sa, kStep && w == (n - 1) / per, s, g, G, ctx, my_u, my_n, lane, m, lsum, o);
     lsum += __shfl_xor(lsum, 16);
     lsum += __shfl_xor(lsum, 32);
     const int r = lane & 15, c = lane >> 4;
@@ -461,10 +489,9 @@ int stream_cus(hipStream_t st)
     return n > 0 && n <= all ? n : all;
 }
 
-// Workgroups of a launch: the shares are equal, so what matters is that every CU gets the same number of
-// them, and as few as the longest share (kMaxSteps) allows: each workgroup pays the plan and each segment a
-// dependent page-id read (two per CU measured 1.5 % faster than four on the whole device, and 2-4 % on
-// partitions whose CU count divides the grid; a grid that leaves some CUs one workgroup short loses 4-5 %).
+// Workgroups of a launch of the other shapes (attn_decode_any.hip): the shares are equal, so what matters is that every CU
+// gets the same number of them, and as few as the longest share (kMaxSteps: a lane holds a page id) allows: each workgroup pays
+// the plan and each segment a dependent page-id read (a grid that leaves some CUs one workgroup short loses 4-5 %).
 int share_workgroups(int64_t f_max, hipStream_t st)
 {
     const int64_t unit = 2 * (int64_t)stream_cus(st);
@@ -507,7 +534,6 @@ ag_status decode_static_scratch(void** ptr_out)
 // The same rule for ag_attn_decode and ag_decode_step: their results are bit for bit the same.
 static bool takes_direct(const AttnArgs& a, hipStream_t st)
 {
-    static_assert((512 << 10) / (4 * D) <= kDirectMaxSteps * 32, "a wave's page ids fit its lanes");
     return a.max_ctx > 0 && direct_preferred((int64_t)a.batch * a.c.hkv, (int64_t)a.max_ctx * 4 * D, stream_cus(st));
 }
 
@@ -533,12 +559,10 @@ ag_status launch_decode_mfma(const AttnArgs& a, void* ws, hipStream_t st)
     int32_t* hdr = (int32_t*)ws;
     float* ws_o = (float*)(hdr + header_ints(a.batch));
     float* ws_ml = ws_o + (size_t)a.batch * a.hq * pmax * D;
-    // Upper bound of the step count from the host-known bounds; the grid is sized so that a share is at most
-    // kMaxSteps steps even if every session is max_ctx long.
     const int64_t f_max = (int64_t)a.c.hkv * a.batch * ((a.max_ctx + 31) / 32);
     if (f_max > (1 << 30)) { set_error("decode batch of %lld steps of 32 tokens is beyond one launch", (long long)f_max); return AG_ERR_INVALID_ARG; }
     if (a.max_ctx > 0) {
-        const int grid = share_workgroups(f_max, st);
+        const int grid = kWorkgroupsPerCu * stream_cus(st);
         // the event bracket covers both kernels of the call: the merge kernel writes the output the byte count includes
         prof_before(st);
         hipLaunchKernelGGL(decode_split_kernel<false>, dim3(grid), dim3(256), 0, st, a, hdr, ws_o, ws_ml, pmax, StepArgs{});
@@ -577,7 +601,7 @@ ag_status launch_decode_step(const AttnArgs& a, const void* k_new, const void* v
     const int64_t f_max = (int64_t)a.c.hkv * a.batch * ((a.max_ctx + 31) / 32);
     if (f_max > (1 << 30)) { set_error("decode batch of %lld steps of 32 tokens is beyond one launch", (long long)f_max); return AG_ERR_INVALID_ARG; }
     if (takes_direct(a, st)) return launch_direct<true>(a, StepArgs{(const __bf16*)k_new, (const __bf16*)v_new, counters}, st);
-    const int grid = share_workgroups(std::max<int64_t>(f_max, 1), st);
+    const int grid = kWorkgroupsPerCu * stream_cus(st);
     prof_before(st);
     hipLaunchKernelGGL(decode_split_kernel<true>, dim3(grid), dim3(256), 0, st, a, hdr, ws_o, ws_ml, pmax,
                        StepArgs{(const __bf16*)k_new, (const __bf16*)v_new, counters});
