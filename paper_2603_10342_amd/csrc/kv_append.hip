@@ -26,6 +26,7 @@ constexpr int kTok = 16;   // tokens per workgroup
 // E is the raw storage element (uint16_t for bf16, uint32_t for fp32).
 template <typename E>
 struct alignas(16) Chunk8 { E e[8]; };
+typedef uint32_t Words16 __attribute__((ext_vector_type(4)));
 
 template <typename E>
 __global__ __launch_bounds__(256) void kv_append_kernel(E* __restrict__ k_pool, E* __restrict__ v_pool,
@@ -123,6 +124,25 @@ __global__ __launch_bounds__(256) void kv_append_groups_kernel(E* __restrict__ k
     const int64_t page = bt[(int64_t)s * max_pages + (pos0 >> ps_shift)];
     const int slot0 = pos0 & (ps - 1);                               // in the page
 
+    E* kpage = k_pool + (page * hkv + h) * (int64_t)d * ps;
+    E* vpage = v_pool + (page * hkv + h) * (int64_t)d * ps;
+    if (n_tok == 1) {
+        // A decode's token: straight through registers, marked non-temporal.  What such an append costs is its stores, a few
+        // bytes in each of many lines: left to the write-back at the end of the kernel they take longer (decode step of 64 sessions, 8 heads
+        // x 128 bf16, append included, 118.7 -> 117.1 us).  Longer runs are read again soon and stay in the caches (211 rows on 6007 tokens 36.2 -> 36.6).
+        const int64_t src = ((int64_t)row0 * hkv + h) * d;
+        C8 k;
+        E v = 0;
+        if (tid < chunks) k = *reinterpret_cast<const C8*>(k_new + src + tid * 8);
+        if (tid < d) v = v_new[src + tid];
+        if (tid < chunks) {
+            Words16* dst = reinterpret_cast<Words16*>(kpage + ((int64_t)tid * ps + slot0) * 8);
+#pragma unroll
+            for (int i = 0; i < (int)(sizeof(C8) / 16); ++i) __builtin_nontemporal_store(reinterpret_cast<const Words16*>(&k)[i], dst + i);
+        }
+        if (tid < d) __builtin_nontemporal_store(v, vpage + v_offset(slot0, tid, ps, d));
+        return;
+    }
     for (int idx = tid; idx < n_tok * chunks; idx += 256) {          // rows in, 16 lanes per 8-chunk run
         const int row = idx / chunks, c = idx - row * chunks;
         const int64_t src = ((int64_t)(row0 + row) * hkv + h) * d + c * 8;
@@ -131,8 +151,6 @@ __global__ __launch_bounds__(256) void kv_append_groups_kernel(E* __restrict__ k
     }
     __syncthreads();
 
-    E* kpage = k_pool + (page * hkv + h) * (int64_t)d * ps;
-    E* vpage = v_pool + (page * hkv + h) * (int64_t)d * ps;
     for (int idx = tid; idx < n_tok * chunks; idx += 256) {          // K: neighbouring lanes, neighbouring slots
         const int c = idx / n_tok, i = idx - c * n_tok;
         *reinterpret_cast<C8*>(kpage + ((int64_t)c * ps + slot0 + i) * 8) = lds_k[i * chunks + c];
