@@ -6,8 +6,8 @@
 // one pass over the keys and values, both contractions run on the matrix cores with the heads padded to 16 columns,
 // and a merge kernel combines the segments' partials in order.  Groups of more than 16 heads are cut into blocks
 // of 16, each a pair of its own.  What differs:
-//   - Arithmetic keeps 32 bits where the caches do: fp32 runs on 16x16x4 fp32 products (256 flop per clock and CU:
-//     a step of 16 tokens takes a third of the time its bytes take), with expf on unscaled exponents; bf16 caches
+//   - Arithmetic keeps 32 bits where the caches do: fp32 runs on 16x16x4 fp32 products, with up to four heads on 4x4x1 ones
+//     (attend_few), with expf on unscaled exponents; bf16 caches
 //     multiply the weights as three bf16 terms (bf16_terms.h), so that they stay in 32 bits.
 //   - The 16-token group is the unit of addressing: group i of a context lies in page i / (page_size / 16), and a
 //     group's keys and values sit in the page as in a 16-token page, only with a larger chunk stride for K.
@@ -17,11 +17,13 @@
 //     loop; the dimensions between 128 and 256, which run as 256 with bounds, spill 45 (bf16: 26), 13 (5) of them read back
 //     in every step.
 // Whole decode step, append included (one wave per (row, query head) before -> now): 16 fp32 sessions of 1024..4096
-// tokens at 32 / 8 heads x 128, 2760 -> 75 us (369 MB, 4.9 TB/s; split kernel 66 us); 48 bf16 sessions of 700..5000 at
+// tokens at 32 / 8 heads x 128, 2760 -> 75 us (369 MB; 65.1 since up to four heads have products of their own, 5.7 TB/s); 48 bf16 sessions of 700..5000 at
 // head_dim 64, 32-token pages, 2238 -> 63.5 us (333 MB, 5.2 TB/s; 62.8 with weights in two terms); two fp32 sessions of 300, 4 / 2 heads x 64, 106 -> 12 us.
 // head_dim below its template's DT: loads beyond head_dim repeat its last channels; keys become zeros (as the query
 // does), values land in rows that are not stored.
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "attn_general_row.h"
 #include "attn_split_common.h"
@@ -249,7 +251,217 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, int g, int ctx, 
     lsum += __shfl_xor(lsum, 32);
 }
 
-template <typename E, int DT, bool kExact>
+// ---- fp32, at most four query heads a pair, head_dim DT = 64 or 128 --------------------------------------------
+// The 16 columns of the 16x16x4 products are mostly padding there, and they are what a short step waits for (two sessions of 300
+// tokens at 4 / 2 heads x 64: 2.3 us of a step's 7 for the second and third sub-step of a wave).  The 4x4x1 products have four
+// columns: 16 independent blocks of 4 x 4, at the same rate a product.  A sub-step of a wave is 32 tokens; lane = 32 u + l:
+//   scores  rows = heads, columns = tokens.  B: keys, a lane holds four of eight channels of a token (the 32 bytes that a token has in
+//           a chunk lie in lanes l and l + 32 of one load); A: the queries' two channels, each broadcast to its half of the blocks
+//           from the one that holds it.  The halves' sums are added, so that both hold all 32 tokens.
+//   a 4 x 4 transpose inside each quad of lanes turns "lane = token, register = head" into "lane = head, register = token"
+//   values  rows = heads, columns = channels.  B: values, a lane holds four of the eight tokens of a chunk (slots below 8 in the lower
+//           lanes, the others in the upper: one load is 1 KiB without gaps); A: the weights of the two tokens, each broadcast
+//           to its half.  (Loads of every other 16 bytes, two for the same lines, cost up to 20 % of a batch that HBM bounds.)
+// Neighbouring products write different accumulators, and every sum is shorter than with the other products.
+// Graph replay, append included, 16x16x4 -> 4x4x1, us: 16 sessions of 1024..4096 at 32 / 8 x 128 72.1 -> 65.1 (369 MB), 8 of 100..500 27.1
+// -> 18.0, one of 800 21.3 -> 14.8; at 64 channels one of 300 at 4 / 2 9.2 -> 7.2, 48 of 1000..4000 at 32 / 8 86.5 -> 82.6, of 60..110 10.3 ->
+// 8.9; a session of two at 4 / 2 x 64 with 16 decode steps 171 -> 139.5.  97 batches 1.05 to 1.5 times faster.  Sub-steps of 64 tokens at
+// 64 channels: 0.89 to 1.4.
+constexpr int kFewHeads = 4;
+
+template <int kCtrl>
+__device__ __forceinline__ float dpp(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), kCtrl, 0xF, 0xF, true));
+}
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowRor4 = 0x124, kRowRor8 = 0x128;
+struct Two { float x, y; };
+// {x of the lower half, y of the lower half} and {x of the upper, y of the upper} ...
+__device__ __forceinline__ Two swap_halves(float x, float y)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+    return Two{__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1])};
+}
+// ... the same of even and odd rows of 16 lanes
+__device__ __forceinline__ Two swap_rows(float x, float y)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+    return Two{__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1])};
+}
+// x[i] of lane 4 b + j becomes x[j] of lane 4 b + i
+__device__ __forceinline__ void transpose_quads(f32x4& x, int lane)
+{
+    const bool odd = lane & 1, upper = lane & 2;
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+        const float got = dpp<kQuadXor1>(odd ? x[i] : x[i + 1]);
+        if (odd) x[i] = got; else x[i + 1] = got;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const float got = dpp<kQuadXor2>(upper ? x[i] : x[i + 2]);
+        if (upper) x[i] = got; else x[i + 2] = got;
+    }
+}
+template <class F, int... I>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F f) { (f(std::integral_constant<int, I>{}), ...); }
+
+constexpr int kFewTokens = 32;                                   // of a sub-step
+
+// One wave's part of a pair: sub-steps of tokens token0 + i * kStep, `subs` of them, tokens below `end` only (at most the context's
+// length).  my_pid: lane kGroups * i + k holds the page of group k of sub-step i (of a group behind the last one, anything).
+// m, lsum: of head lane & 3, in every lane; o[h][i]: O of head i at channel 64 h + lane.
+template <int DT, int kStep>
+__device__ __forceinline__ void attend_few(const AttnArgs& a, int s, int g, int nh, int ctx, int end, int token0, int subs, int my_pid,
+                                           float& m, float& lsum, f32x4 (&o)[DT / 64])
+{
+    constexpr int kTok = kFewTokens, kGroups = kTok / 16, kBlocks = DT / 32;         // kBlocks of 32 channels
+    const int hkv = a.c.hkv, ps = a.c.ps, lane = threadIdx.x & 63, l = lane & 31, u = lane >> 5;
+    const int gmask = (1 << (a.c.ps_shift - 4)) - 1, last_grp = (ctx - 1) >> 4;
+    const int64_t block = (int64_t)DT * ps;
+    const float* kpool = (const float*)a.c.k;
+    const float* vpool = (const float*)a.c.v;
+    m = -INFINITY;
+    lsum = 0.f;
+#pragma unroll
+    for (int h = 0; h < DT / 64; ++h) o[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (subs <= 0) return;
+
+    const int head = lane & 3, b = l >> 2, kg = l / (32 / kGroups);
+    float q[DT / 16];                                            // step t of the scores takes channels 8 (t / 4) + 4 u + t % 4: block t % 8 of register t / 8
+    {
+        const float* row = (const float*)a.q + ((int64_t)s * a.hq + (int64_t)g * (a.hq / hkv) + min(head, nh - 1)) * DT;
+#pragma unroll
+        for (int i = 0; i < DT / 16; ++i) q[i] = row[8 * ((8 * i + b) >> 2) + 4 * u + (b & 3)];
+    }
+    u32x4 k[DT / 8], v[DT / 8];                                  // k[chunk]; v[(group * 2 + chunk) * kBlocks + channels]
+    auto load_k = [&](int i) {
+        const int grp0 = (token0 + kStep * i) >> 4, mine = min(kg, last_grp - grp0);         // (a group behind the last one: that again)
+        const int pid = __shfl(my_pid, kGroups * i + mine), gi = (grp0 + mine) & gmask;
+        const float* kp = kpool + ((int64_t)pid * hkv + g) * block + (gi * 16 + (l & 15)) * 8 + 4 * u;
+#pragma unroll
+        for (int c = 0; c < DT / 8; ++c) k[c] = load16(kp + (int64_t)c * ps * 8);
+    };
+    auto load_v = [&](int i) {
+        const int grp0 = (token0 + kStep * i) >> 4;
+#pragma unroll
+        for (int j = 0; j < kGroups; ++j) {
+            const int at = min(j, last_grp - grp0);
+            const int64_t pid = __builtin_amdgcn_readlane(my_pid, kGroups * i + at);
+            const float* vp = vpool + (pid * hkv + g) * block + (int64_t)((grp0 + at) & gmask) * (16 * DT) + l * 8 + 4 * u;
+#pragma unroll
+            for (int chunk = 0; chunk < 2; ++chunk)
+#pragma unroll
+                for (int n = 0; n < kBlocks; ++n) v[(j * 2 + chunk) * kBlocks + n] = load16(vp + chunk * (DT * 8) + n * 256);
+        }
+    };
+    load_k(0);
+    load_v(0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < DT / 16; ++i) q[i] = head < nh ? q[i] : 0.f;
+    f32x4 acc_o[kBlocks];                                        // of this half's tokens: channel 32 n + l
+#pragma unroll
+    for (int n = 0; n < kBlocks; ++n) acc_o[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // The next sub-step's keys are requested once the score products have taken this one's, its values once the second
+    // products have.  (One body with branches: a copy for the last sub-step makes the compiler move the operands about, and spill.)
+#pragma unroll 1
+    for (int i = 0; i < subs; ++i) {
+        const int tok0 = token0 + kStep * i;
+        f32x4 acc[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        unrolled(std::make_integer_sequence<int, DT / 2>{}, [&](auto c) {
+            constexpr int t = c;
+            acc[t & 3] = __builtin_amdgcn_mfma_f32_4x4x1f32(q[t / 8], __builtin_bit_cast(f32x4, k[t / 4])[t & 3], acc[t & 3], 3, t % 8, 0);
+        });
+        if (i + 1 < subs) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_k(i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        f32x4 sc;                                                // register = head, lane = token
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float part = (acc[0][e] + acc[1][e]) + (acc[2][e] + acc[3][e]);
+            const Two t = swap_halves(part, part);
+            sc[e] = t.x + t.y;
+        }
+        transpose_quads(sc, lane);                               // register = token, lane = head
+        const int keep = end - (tok0 + b * 4);
+        float xs[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) xs[e] = e < keep ? sc[e] * a.scale : -INFINITY;
+        float mx = fmaxf(fmaxf(xs[0], xs[1]), fmaxf(xs[2], xs[3]));
+        mx = fmaxf(mx, dpp<kRowRor4>(mx));
+        mx = fmaxf(mx, dpp<kRowRor8>(mx));
+        const Two two = swap_rows(mx, mx);
+        mx = fmaxf(two.x, two.y);
+        const float m_new = fmaxf(m, mx);
+        const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = expf(m - m_ref);
+        float p[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[e] = expf(xs[e] - m_ref);
+        lsum = lsum * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
+        m = m_new;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {                            // where the lower half holds slots 0..7 of a group, the upper holds 8..15
+            const int x = __builtin_bit_cast(int, p[e]);
+            p[e] = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(x, x, kRowRor8, 0xC, 0xF, false));
+        }
+        if (tok0 + kTok > end) {                                 // slots past the last token may hold anything, NaN included
+            const int held = end - tok0 - 8 * u;
+#pragma unroll
+            for (int j = 0; j < 2 * kGroups; ++j)
+#pragma unroll
+                for (int n = 0; n < kBlocks; ++n)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if ((j >> 1) * 16 + (j & 1) * 4 + e >= held) v[j * kBlocks + n][e] = 0u;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float f = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, alpha), e));
+#pragma unroll
+            for (int n = 0; n < kBlocks; ++n) acc_o[n][e] *= f;
+        }
+        unrolled(std::make_integer_sequence<int, 2 * kGroups * 4 * kBlocks>{}, [&](auto c) {
+            constexpr int n = c % kBlocks, e = (c / kBlocks) & 3, j = c / (4 * kBlocks);         // channels, token of the quad, (group, chunk)
+            constexpr int from = (j >> 1) * 4 + (j & 1);
+            acc_o[n] = __builtin_amdgcn_mfma_f32_4x4x1f32(p[e], __builtin_bit_cast(f32x4, v[j * kBlocks + n])[e], acc_o[n], 3, from, 0);
+        });
+        if (i + 1 < subs) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_v(i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < DT / 64; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const Two t = swap_halves(acc_o[2 * h][e], acc_o[2 * h + 1][e]);
+            o[h][e] = t.x + t.y;
+        }
+    lsum += dpp<kRowRor4>(lsum);
+    lsum += dpp<kRowRor8>(lsum);
+    const Two two = swap_rows(lsum, lsum);
+    lsum = two.x + two.y;
+}
+
+// A wave's O of the heads, kChan channels of it, as rows of LDS.
+template <int kChan>
+__device__ __forceinline__ void few_to_lds(float* rows, const f32x4* o, int lane)
+{
+#pragma unroll
+    for (int h = 0; h < kChan / 64; ++h)
+#pragma unroll
+        for (int i = 0; i < kFewHeads; ++i) rows[i * kChan + h * 64 + lane] = o[h][i];
+}
+
+template <typename E, int DT, bool kExact, bool kFew>
 __global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, int32_t* __restrict__ hdr,
                                                                   float* __restrict__ ws_o, float* __restrict__ ws_ml,
                                                                   int pmax, int head_blocks)
@@ -288,21 +500,29 @@ __global__ __launch_bounds__(256, 2) void decode_any_split_kernel(AttnArgs a, in
         const int my_n = max(0, min(per, k - w * per));
 
         float m, lsum;
-        f32x4 o[DT / 16];
+        f32x4 o[kFew ? DT / 64 : DT / 16];
         constexpr int kSub = 32 / SubStep<E, DT>::kTok;          // sub-steps of a step
         int my_pid = 0;
         if (my_n > 0) my_pid = a.bt[(int64_t)s * a.max_pages + (min(2 * my_u + lane, (ctx - 1) >> 4) >> (a.c.ps_shift - 4))];
-        queries_to_lds<E, DT, kExact, 256>(a, s, g, h0, nh, s_q);
-        attend_steps<E, DT, kExact, 1>(a, g, ctx, my_u * kSub, my_n * kSub, my_pid, s_q, m, lsum, o);
+        if constexpr (kFew) {
+            constexpr int kTok = kFewTokens;
+            attend_few<DT, kTok>(a, s, g, nh, ctx, min(ctx, (my_u + my_n) * 32), my_u * 32, (my_n * 32 + kTok - 1) / kTok, my_pid, m, lsum, o);
+        } else {
+            queries_to_lds<E, DT, kExact, 256>(a, s, g, h0, nh, s_q);
+            attend_steps<E, DT, kExact, 1>(a, g, ctx, my_u * kSub, my_n * kSub, my_pid, s_q, m, lsum, o);
+        }
 
-        // o[mb][i] is O^T[channel mb * 16 + c * 4 + i][head r]; the four waves are merged in LDS, kChan channels at a time
+        // o[mb][i] is O^T[channel mb * 16 + c * 4 + i][head r] (kFew: o[h][i] O[head i][channel h * 64 + lane]); the four waves are
+        // merged in LDS, kChan channels at a time
         const int first_wg = (base + pair * n) / sh.q;           // the pair's segments are numbered from this workgroup
         const int piece = wg - first_wg;
-        if (c == 0) { s_m[w][r] = m; s_l[w][r] = lsum; }
+        if (c == 0) { s_m[w][r] = m; s_l[w][r] = lsum; }        // (kFew: lanes 0..3 hold heads 0..3, the others repeat them)
 #pragma unroll
         for (int d0 = 0; d0 < DT; d0 += kChan) {
+            if constexpr (kFew) few_to_lds<kChan>(&s_o[w][0][0], o + d0 / 64, lane);
+            else
 #pragma unroll
-            for (int mb = 0; mb < kChan / 16; ++mb) *reinterpret_cast<f32x4*>(&s_o[w][r][mb * 16 + c * 4]) = o[d0 / 16 + mb];
+                for (int mb = 0; mb < kChan / 16; ++mb) *reinterpret_cast<f32x4*>(&s_o[w][r][mb * 16 + c * 4]) = o[d0 / 16 + mb];
             __syncthreads();
             if (piece < pmax) {
                 for (int idx = tid; idx < nh * (kChan / 4); idx += 256) {        // four channels a thread
@@ -353,7 +573,7 @@ constexpr int kDirectMaxTokens = kDirectWaves * 32 * 32;
 
 // N: channels a thread takes of the waves' results: one while that is one each (half the latency), four beyond.  (Both in one kernel, chosen
 // by the pair's heads, cost short calls 0.15 us: 16 sessions of 200 tokens, 32 / 8 heads x 128, 9.57 -> 9.73.)
-template <typename E, int DT, bool kExact, int N>
+template <typename E, int DT, bool kExact, int N, bool kFew>
 __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel(AttnArgs a, int head_blocks)
 {
     constexpr bool kBf16 = sizeof(E) == 2;
@@ -373,17 +593,21 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
     // The wave's sub-steps are every eighth, so that none has more than one over the others (runs of whole steps gave one wave
     // four sub-steps of 16 tokens where three are the most: two fp32 sessions of 300 tokens, 4 / 2 heads x 64, append included, 11.3 ->
     // 9.5 us; 64 of 60 at 32 / 8 x 128 19.8 -> 17.0; bf16 within 1 %), and which they are does not follow from the length: the page ids are fetched beside it.
-    constexpr int kTok = SubStep<E, DT>::kTok, kGroups = kTok / 16;
+    constexpr int kTok = kFew ? kFewTokens : SubStep<E, DT>::kTok, kGroups = kTok / 16;
     static_assert(kDirectMaxTokens <= kDirectWaves * (64 / kGroups) * kTok, "the page ids of a wave's sub-steps fit its lanes");
     const int my_pid = a.bt[(int64_t)s * a.max_pages +
                             min((kGroups * (w + kDirectWaves * (lane / kGroups)) + lane % kGroups) >> (a.c.ps_shift - 4), a.max_pages - 1)];
-    const int ctx = max(0, min(a.ctx_lens[s], kDirectMaxTokens));
-    queries_to_lds<E, DT, kExact, kThreads>(a, s, g, h0, nh, s_q);
+    const int ctx = __builtin_amdgcn_readfirstlane(max(0, min(a.ctx_lens[s], kDirectMaxTokens)));
     const int n = (ctx + kTok - 1) / kTok, subs = w < n ? (n - w - 1) / kDirectWaves + 1 : 0;
     E* out = (E*)a.out + ((int64_t)s * hq + (int64_t)g * G + h0) * D;
     float m, lsum;
-    f32x4 o[DT / 16];
-    attend_steps<E, DT, kExact, kDirectWaves>(a, g, ctx, w, subs, my_pid, s_q, m, lsum, o);
+    f32x4 o[kFew ? DT / 64 : DT / 16];
+    if constexpr (kFew) {
+        attend_few<DT, kDirectWaves * kTok>(a, s, g, nh, ctx, ctx, w * kTok, subs, my_pid, m, lsum, o);
+    } else {
+        queries_to_lds<E, DT, kExact, kThreads>(a, s, g, h0, nh, s_q);
+        attend_steps<E, DT, kExact, kDirectWaves>(a, g, ctx, w, subs, my_pid, s_q, m, lsum, o);
+    }
 
     const int r = lane & 15, c = lane >> 4;
     auto power = [](float x) { return kBf16 ? __builtin_amdgcn_exp2f(x) : expf(x); };
@@ -392,8 +616,10 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_any_direct_kernel
 #pragma unroll
     for (int d0 = 0; d0 < DT; d0 += kChan) {
         if (d0 > 0) __syncthreads();
+        if constexpr (kFew) few_to_lds<kChan>(&s_o[w][0][0], o + d0 / 64, lane);
+        else
 #pragma unroll
-        for (int mb = 0; mb < kChan / 16; ++mb) *reinterpret_cast<f32x4*>(&s_o[w][r][mb * 16 + c * 4]) = o[d0 / 16 + mb];
+            for (int mb = 0; mb < kChan / 16; ++mb) *reinterpret_cast<f32x4*>(&s_o[w][r][mb * 16 + c * 4]) = o[d0 / 16 + mb];
         __syncthreads();
         for (int idx = tid; idx < nh * (kChan / N); idx += kThreads) {
             const int head = idx / (kChan / N), dl = (idx - head * (kChan / N)) * N;
@@ -505,13 +731,16 @@ ag_status launch(const AttnArgs& a, hipStream_t st)
     static_assert(kDirectMostBytes / (2 * DT * (int)sizeof(E)) <= kDirectMaxTokens, "a wave's page ids fit its lanes");
     const int64_t pairs = (int64_t)a.batch * a.c.hkv * blocks;
     const int cus = stream_cus(st);
+    constexpr bool kFewShape = sizeof(E) == 4 && DT <= 128;
+    const bool few = kFewShape && a.c.d == DT && a.hq / a.c.hkv <= kFewHeads;
     if (a.max_ctx > 0 && (one_workgroup_a_pair(pairs, pair_bytes, DT == 64 && sizeof(E) == 4, cus) || few_tokens(pairs, a.max_ctx, cus))) {
         const dim3 grid((unsigned)pairs), wg(64 * kDirectWaves);
         prof_before(st);
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, wg, 0, st, a, blocks); };
         const bool one = std::min(a.hq / a.c.hkv, kCols) * 64 <= 64 * kDirectWaves;          // channel a thread
-        if (a.c.d == DT) one ? launch(decode_any_direct_kernel<E, DT, true, 1>) : launch(decode_any_direct_kernel<E, DT, true, 4>);
-        else one ? launch(decode_any_direct_kernel<E, DT, false, 1>) : launch(decode_any_direct_kernel<E, DT, false, 4>);
+        if (few) launch(decode_any_direct_kernel<E, DT, true, 1, kFewShape>);
+        else if (a.c.d == DT) one ? launch(decode_any_direct_kernel<E, DT, true, 1, false>) : launch(decode_any_direct_kernel<E, DT, true, 4, false>);
+        else one ? launch(decode_any_direct_kernel<E, DT, false, 1, false>) : launch(decode_any_direct_kernel<E, DT, false, 4, false>);
         prof_after(st);
         return hip_check(hipGetLastError(), "decode launch");
     }
@@ -521,8 +750,9 @@ ag_status launch(const AttnArgs& a, hipStream_t st)
     prof_before(st);
     if (a.max_ctx > 0) {
         const dim3 grid(share_workgroups(steps_bound(a), st)), wg(256);
-        if (a.c.d == DT) hipLaunchKernelGGL((decode_any_split_kernel<E, DT, true>), grid, wg, 0, st, a, hdr, ws_o, ws_ml, pmax, blocks);
-        else hipLaunchKernelGGL((decode_any_split_kernel<E, DT, false>), grid, wg, 0, st, a, hdr, ws_o, ws_ml, pmax, blocks);
+        if (few) hipLaunchKernelGGL((decode_any_split_kernel<E, DT, true, kFewShape>), grid, wg, 0, st, a, hdr, ws_o, ws_ml, pmax, blocks);
+        else if (a.c.d == DT) hipLaunchKernelGGL((decode_any_split_kernel<E, DT, true, false>), grid, wg, 0, st, a, hdr, ws_o, ws_ml, pmax, blocks);
+        else hipLaunchKernelGGL((decode_any_split_kernel<E, DT, false, false>), grid, wg, 0, st, a, hdr, ws_o, ws_ml, pmax, blocks);
         ag_status e = hip_check(hipGetLastError(), "decode split launch");
         if (e) return e;
     }
