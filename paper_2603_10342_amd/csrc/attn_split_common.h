@@ -223,14 +223,17 @@ __device__ __forceinline__ bool find_share(const int32_t* __restrict__ ctx_lens,
 // Whether a decode batch of `pairs` (session, KV head) pairs, each with at most `bytes` of keys and values, takes one
 // workgroup per pair and no merge instead of equal shares.  A step of a small batch is a chain of memory round trips, and
 // the plan, the partials and their merge are most of them; but a CU draws no more than about 57 GB/s, so a pair that one
-// workgroup reads alone must be short, and every pair must have a CU to itself.  256 KiB (512 tokens of bf16 / 128)
-// is where that turns for a single session; with more than half of the CUs busy either way, 512 KiB.
-// Measured at 32 / 8 heads, graph replay, shares -> direct.  ag_decode_step, bf16 / 128: one session of 100 tokens 8.5 -> 5.3
-// us, of 512 8.1 -> 7.2, of 1000 8.3 -> 8.8; four of 1000 9.3 -> 12.7; 32 of 100..512 18.2 -> 10.5, 32 of 500..1000 24.4
-// -> 20.0.  (The other shapes have a line of their own, one_workgroup_a_pair() in attn_decode_any.hip.)
+// workgroup reads alone must be short, and every pair must have a CU to itself.  416 KiB (832 tokens of bf16 / 128) is where
+// that turns for few pairs; with more than half of the CUs busy either way, shares are hardly finer, and 1 MiB.
+// Measured over 150 drawn batches at 256 CUs, ag_decode_step and ag_attn_decode with the append, graph replay, shares / one
+// workgroup: up to 128 pairs, 200 to 300 KiB 1.29 (0.94 to 1.66), to 416 KiB 1.12 (0.79 to 1.47), to 480 KiB 1.05 (0.91 to
+// 1.48), beyond 0.92; more pairs, to 1 MiB 1.18 (1.11 to 1.44), beyond 1.03 (0.83 to 1.12).  Shares come off best where their 256
+// tokens end with the contexts (one session of 1000 tokens, 32 / 8 heads, 7.1 against 8.3 us; of 850 9.1 against 7.0, of 400 9.2
+// against 5.1; 16 of 700 15.6 against 11.0).  (The other shapes have a line of their own, one_workgroup_a_pair() in
+// attn_decode_any.hip.)
 inline bool direct_preferred(int64_t pairs, int64_t bytes, int cus)
 {
-    return pairs <= cus && bytes <= (2 * pairs > cus ? 512 << 10 : 256 << 10);
+    return pairs <= cus && bytes <= (2 * pairs > cus ? 1024 << 10 : 416 << 10);
 }
 
 }  // namespace splitk
