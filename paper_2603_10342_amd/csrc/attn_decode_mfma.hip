@@ -64,6 +64,9 @@ struct StepArgs {
     int32_t* counters;          // [B * Hkv]
 };
 
+// Every store of this wave up to here has been performed at the scope it was made for.
+__device__ __forceinline__ void stores_performed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // One wave's part of a segment - steps my_u .. my_u + my_n - 1 of pair (s, g), whose context has ctx tokens: the running
 // maximum, the running sum (this lane's share) and O^T of the pair's heads.  appends: this wave's last step is the pair's
 // last, and it writes the step's token first.
@@ -136,10 +139,6 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& 
 #pragma unroll
         for (int mb = 0; mb < 8; ++mb) x.v[mb] = ld16_stream(vp + mb * 16 * 8);
     };
-    auto stores_performed = [&] {                        // the token this wave appended lies in the page loaded next
-        __builtin_amdgcn_s_waitcnt(0x0070 | (0xF << 8));                  // vmcnt(0)
-        asm volatile("" ::: "memory");
-    };
     auto append = [&] {
         const int slot = (ctx - 1) & (PS - 1);
         __bf16* kdst = (__bf16*)a.c.k + (last_page * hkv + g) * (int64_t)(D * PS);
@@ -150,7 +149,7 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& 
     };
     if (appends && my_n == 1) {
         append();
-        stores_performed();
+        stores_performed();                              // the token this wave appended lies in the page loaded next
     }
     __builtin_amdgcn_sched_barrier(0);
     load_k(pg);
@@ -330,10 +329,12 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCu) void decode_split_kernel(Att
         }
         if (kStep && !direct) {
             // Count this segment in; whoever completes the pair merges all its segments, in their order.  The
-            // partials were stored at device scope (they go past this XCD's caches), the barrier below waits
-            // until every thread's stores have been performed before the count is raised, and the merging
-            // workgroup reads them at device scope after it has seen the full count: no cache-wide write-back
-            // or invalidate is needed (a device-wide fence costs a multiple of the whole step here).
+            // partials were stored at device scope (they go past this XCD's caches), every wave waits until its
+            // stores have been performed (the barrier by itself orders them only within the workgroup, and does not
+            // wait) before the barrier lets the count be raised, and the merging workgroup reads them at device
+            // scope after it has seen the full count: no cache-wide write-back or invalidate is needed (a
+            // device-wide fence costs a multiple of the whole step here).
+            stores_performed();
             __syncthreads();
             if (tid_e == 0) s_arrived = __hip_atomic_fetch_add(&sa.counters[s * hkv + g], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
