@@ -124,12 +124,49 @@ __global__ __launch_bounds__(256) void kv_append_groups_kernel(E* __restrict__ k
     const int64_t page = bt[(int64_t)s * max_pages + (pos0 >> ps_shift)];
     const int slot0 = pos0 & (ps - 1);                               // in the page
 
-    E* kpage = k_pool + (page * hkv + h) * (int64_t)d * ps;
-    E* vpage = v_pool + (page * hkv + h) * (int64_t)d * ps;
-    if (n_tok == 1) {
-        // A decode's token: straight through registers, marked non-temporal.  What such an append costs is its stores, a few
-        // bytes in each of many lines: left to the write-back at the end of the kernel they take longer (decode step of 64 sessions, 8 heads
-        // x 128 bf16, append included, 118.7 -> 117.1 us).  Longer runs are read again soon and stay in the caches (211 rows on 6007 tokens 36.2 -> 36.6).
+    auto page_of = [&](E* pool) { return pool + (page * hkv + h) * (int64_t)d * ps; };
+    if (n_tok > 1) {
+        for (int idx = tid; idx < n_tok * chunks; idx += 256) {          // rows in, 16 lanes per 8-chunk run
+            const int row = idx / chunks, c = idx - row * chunks;
+            const int64_t src = ((int64_t)(row0 + row) * hkv + h) * d + c * 8;
+            lds_k[idx] = *reinterpret_cast<const C8*>(k_new + src);
+            lds_v[idx] = *reinterpret_cast<const C8*>(v_new + src);
+        }
+        __syncthreads();
+
+        E *kpage = page_of(k_pool), *vpage = page_of(v_pool);
+        for (int idx = tid; idx < n_tok * chunks; idx += 256) {          // K: neighbouring lanes, neighbouring slots
+            const int c = idx / n_tok, i = idx - c * n_tok;
+            *reinterpret_cast<C8*>(kpage + ((int64_t)c * ps + slot0 + i) * 8) = lds_k[i * chunks + c];
+        }
+        const E* lv = reinterpret_cast<const E*>(lds_v);                 // [token][d]
+        if (n_tok == kGroup) {                                           // whole group: V as 8-key chunks
+            for (int idx = tid; idx < 2 * d; idx += 256) {
+                const int half = idx / d, ch = idx - half * d;
+                C8 x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    x.e[e] = lv[(half * 4 + e) * d + ch];
+                    x.e[4 + e] = lv[(8 + half * 4 + e) * d + ch];
+                }
+                *reinterpret_cast<C8*>(vpage + ((int64_t)((slot0 >> 3) + half) * d + ch) * 8) = x;
+            }
+        } else {
+            for (int idx = tid; idx < n_tok * d; idx += 256) {
+                const int ch = idx / n_tok, i = idx - ch * n_tok;
+                vpage[v_offset(slot0 + i, ch, ps, d)] = lv[i * d + ch];
+            }
+        }
+        return;
+    }
+    // A decode's token: straight through registers.  What such an append costs is its stores, a few bytes in each of many lines.
+    // Marked non-temporal they need no write-back at the end of the kernel, but the attention that follows reads these lines from
+    // further away, which a step of few workgroups waits for.  Append and decode, graph replay, through LDS / registers / registers
+    // and marked, bf16 on 8 KV heads: 32 sessions of 100 to 800 tokens, 256 channels 31.6, 31.3, 29.9 us, 128 15.7, 15.4, 14.8; 64 of
+    // 1023 to 4095 118.9, 118.8, 117.3; 8 of 300 to 900 (64 workgroups), 256 channels 21.7, 21.5, 21.2; 2 of 91 to 365 12.7, 12.5,
+    // 12.7, 128 6.8, 6.6, 6.9.  (Longer runs gain nothing from the mark: 211 rows on 6007 tokens 36.2 -> 36.6.)
+    auto one_token = [&](auto put) {
+        E *kpage = page_of(k_pool), *vpage = page_of(v_pool);
         const int64_t src = ((int64_t)row0 * hkv + h) * d;
         C8 k;
         E v = 0;
@@ -138,40 +175,16 @@ __global__ __launch_bounds__(256) void kv_append_groups_kernel(E* __restrict__ k
         if (tid < chunks) {
             Words16* dst = reinterpret_cast<Words16*>(kpage + ((int64_t)tid * ps + slot0) * 8);
 #pragma unroll
-            for (int i = 0; i < (int)(sizeof(C8) / 16); ++i) __builtin_nontemporal_store(reinterpret_cast<const Words16*>(&k)[i], dst + i);
+            for (int i = 0; i < (int)(sizeof(C8) / 16); ++i) put(reinterpret_cast<const Words16*>(&k)[i], dst + i);
         }
-        if (tid < d) __builtin_nontemporal_store(v, vpage + v_offset(slot0, tid, ps, d));
-        return;
-    }
-    for (int idx = tid; idx < n_tok * chunks; idx += 256) {          // rows in, 16 lanes per 8-chunk run
-        const int row = idx / chunks, c = idx - row * chunks;
-        const int64_t src = ((int64_t)(row0 + row) * hkv + h) * d + c * 8;
-        lds_k[idx] = *reinterpret_cast<const C8*>(k_new + src);
-        lds_v[idx] = *reinterpret_cast<const C8*>(v_new + src);
-    }
-    __syncthreads();
-
-    for (int idx = tid; idx < n_tok * chunks; idx += 256) {          // K: neighbouring lanes, neighbouring slots
-        const int c = idx / n_tok, i = idx - c * n_tok;
-        *reinterpret_cast<C8*>(kpage + ((int64_t)c * ps + slot0 + i) * 8) = lds_k[i * chunks + c];
-    }
-    const E* lv = reinterpret_cast<const E*>(lds_v);                 // [token][d]
-    if (n_tok == kGroup) {                                           // whole group: V as 8-key chunks
-        for (int idx = tid; idx < 2 * d; idx += 256) {
-            const int half = idx / d, ch = idx - half * d;
-            C8 x;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                x.e[e] = lv[(half * 4 + e) * d + ch];
-                x.e[4 + e] = lv[(8 + half * 4 + e) * d + ch];
-            }
-            *reinterpret_cast<C8*>(vpage + ((int64_t)((slot0 >> 3) + half) * d + ch) * 8) = x;
-        }
+        if (tid < d) put(v, vpage + v_offset(slot0, tid, ps, d));
+    };
+    if (gridDim.x * gridDim.y < 64) {
+        one_token([](auto x, auto* dst) { *dst = x; });
     } else {
-        for (int idx = tid; idx < n_tok * d; idx += 256) {
-            const int ch = idx / n_tok, i = idx - ch * n_tok;
-            vpage[v_offset(slot0 + i, ch, ps, d)] = lv[i * d + ch];
-        }
+        asm volatile("");                // (keeps the compiler from making one of the two)
+        one_token([](auto x, auto* dst) { __builtin_nontemporal_store(x, dst); });
+        asm volatile("");
     }
 }
 
