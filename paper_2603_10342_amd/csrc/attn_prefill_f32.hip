@@ -57,30 +57,8 @@ constexpr int BN = 32;                  // keys per tile
 constexpr int kRowsAgain = 4;           // rows taken again together (attn_general_row.h)
 constexpr float kSlack = 8.0f;          // how far (in powers of two) a maximum may outgrow the reference before O is rescaled
 
-constexpr float kLargeQuery = 0x1p90f;  // scale * |q| up to which what small keys lose (2^-126, times 128 channels) is nothing
-
-// The smallest size among numbers, zero left out because it is exact: of 2 |bits| - 1, where zero comes out largest.
-struct Least {
-    uint32_t u = ~0u;
-    __device__ __forceinline__ void take(float x) { u = min(u, (__builtin_bit_cast(uint32_t, x) << 1) - 1); }
-    __device__ __forceinline__ bool small(float unit = 1.f) const        // (no number but zeros: NaN)
-    {
-        return __builtin_bit_cast(float, u >> 1) * unit < 0x1p-100f;
-    }
-};
-
 constexpr int plane_bytes(int dt) { return BN * dt * 2; }           // one term of a tile of keys, or of values
 constexpr int lds_bytes(int dt) { return 12 * plane_bytes(dt); }    // two stages of K h, m, l, then two of V h, m, l
-
-constexpr float kWeightUnit = 0x1p48f;  // what a weight of 1 is multiplied as; their sum is in the same unit
-
-__device__ __forceinline__ Terms split8(const f32x4& a, const f32x4& b)
-{
-    Terms t;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) t.set_pair(i, i < 2 ? a[2 * i] : b[2 * i - 4], i < 2 ? a[2 * i + 1] : b[2 * i - 3]);
-    return t;
-}
 
 __device__ __forceinline__ f32x16 product(const u32x4& a, const u32x4& b, const f32x16& c)
 {

@@ -13,12 +13,17 @@
 // eight steps at 128 channels, 128 KiB, takes 1.0 us where the same loads alone take 0.9 from L2; scores of the next step
 // beside the weights of this one, a second step's keys in flight, or neighbours starting at other steps of a ring of 4 to 16
 // all measured slower.  Rest of a call on 6000 tokens (35 us): the append, 8 us of start, merge and launch.  Locating a
-// step's pages once for K and V: 36.8 -> 35.1 us there, eight chunks of 50 rows on 2000 tokens 29.0 -> 28.5; fp32 at 64 channels 1 to 3
-// % (125.7 -> 123.9).  fp32 at 128 gains 0.6 % on average over 66 drawn batches, but not everywhere: where the waves' one or two steps
-// fall badly it is 4 to 9 % slower (eight chunks of 9 rows on 240..300 tokens, 23.7 -> 26.0 on 270), and 1.5 % with 211 rows on 6000
-// (228.4 -> 232.4; 9 rows 235.1 -> 234.0, 4000 164.8 -> 163.2).  Locating twice there, with an explicit wait for the first values, or with
-// a higher priority for waves of more steps, moves these cases about by as much.  The line to the other kernels is at
-// prefill_split_preferred().
+// step's pages once for K and V: 36.8 -> 35.1 us there, eight chunks of 50 rows on 2000 tokens 29.0 -> 28.5.  Waits for K and for V
+// told apart (the compiler cannot, across the branch around the last requests: a copy of the loop body spills at 128 channels, requests
+// without the branch cost a step's traffic): 1.02 to 1.06 at bf16 / 64 on thousands of tokens, 0.97 to 1.0 at bf16 / 128; not taken.
+//
+// fp32 takes every number as three bf16 terms and a product as six of theirs, as attn_prefill_f32.hip does, with its care for small
+// numbers: a step's 128 products of 64 clocks at 128 channels are 96 of 32, beside some 900 vector instructions that split K, V and the
+// weights, one wave's behind the other's on a SIMD.  Queries are split once, into LDS.  At 128 channels V is requested when the scores
+// are there: a step ahead, 46 registers spill (1.26 times the fp32 products over 30 batches, 1.45 so).  us, fp32 products -> terms, graph
+// replay, append included, 32 / 8 heads: 211 rows on 6000 tokens at 128 channels 232 -> 146, 5 rows 221 -> 122, 24 chunks of 20 on 400 75
+// -> 54; at 64 channels 125 -> 83, 118 -> 69 and 46 -> 35.  Error against 64 bits over 39 batches 0.46 to 0.80 of what it was.
+// The line to the other kernels is at prefill_split_preferred().
 #include <algorithm>
 #include <atomic>
 
@@ -41,12 +46,17 @@ constexpr int kColumns = 32;            // (token, head) pairs of a workgroup
 constexpr int kStep = 32;               // keys of a wave's step
 constexpr float kLog2e = 1.4426950408889634f;
 
+__device__ __forceinline__ f32x16 product(const u32x4& a, const u32x4& b, const f32x16& c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
 template <int DT>
 struct Shape {
     static constexpr int waves = DT > 128 ? 4 : 8;          // which share the columns' keys; 512 registers a lane, or 256
     static constexpr int rows_again = DT > 128 ? 1 : 4;     // rows taken again together (attn_general_row.h)
     static constexpr int o_row = DT + 4;                    // floats of a column's partial in LDS, padded
-    static constexpr int lds = waves * kColumns * (o_row + 2) * 4 + 16;
+    static constexpr int lds = waves * kColumns * (o_row + 2) * 4 + 16 + 2 * kColumns * 4;
 };
 
 // kLo: bf16 weights as three terms (bf16_terms.h); false keeps the rounded weights of the bf16 / 128 / 16 kernels.
@@ -61,9 +71,12 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
     constexpr int kK = DT * (int)sizeof(E) / 32;    // 16-byte loads of a lane per step: keys
     constexpr int kMb = DT / 32;
     constexpr bool kTakeAgain = kLo || !kBf16;      // columns that are not finite, in plain arithmetic (attn_general_row.h)
+    // fp32 at 128 channels: V is requested once the scores are there, not a step ahead; with K, O and the scores' two
+    // accumulators it would be more than the registers.
+    constexpr bool kLateV = !kBf16 && DT == 128;
     constexpr int kRuns = kBf16 ? 2 : 4;            // runs of keys a lane's weights fall into: 8 keys (bf16), 4 (fp32)
-    constexpr bool kQInLds = !kBf16;                // fp32 queries are twice the registers and are read a quarter as often
-    constexpr float kSlack = kExact ? 0.f : kBf16 ? 8.0f : 5.5f;   // how far a maximum may outgrow the reference before O is rescaled
+    constexpr bool kQInLds = !kBf16;                // fp32 queries, as three terms, are three times the registers
+    constexpr float kSlack = kExact ? 0.f : 8.0f;   // how far a maximum may outgrow the reference before O is rescaled
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];       // Q in the loop (fp32), then the waves' partials
 
     // ---- which (KV head, session, tile): the XCD a workgroup lands on owns a contiguous range of KV heads ----
@@ -102,16 +115,38 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
     auto fetch_ids = [&](int i) { my_pid = bt[min(2 * (w + kWaves * (i + (lane >> 1))) + (lane & 1), last_grp) >> gshift]; };
     if (my_n > 0) fetch_ids(0);
 
-    // ---- Q^T as B operand: bf16 k-step ks covers channels ks * 16 + hi * 8 .. + 7, fp32 chunk j channels 8 j + hi * 4 .. + 3
-    constexpr int kQRow = DT * 4 + 16;
+    // ---- Q^T as B operand: bf16 k-step ks covers channels ks * 16 + hi * 8 .. + 7, fp32 the four channels 4 hi .. of chunks
+    // 2 ks and 2 ks + 1, as the loads of K bring them: terms in LDS, [term][ks][hi][column][8] ----
+    constexpr int kSteps16 = DT / 16;
+    uint32_t* const s_least = reinterpret_cast<uint32_t*>(lds + Shape<DT>::lds) - 2 * kColumns;       // fp32: smallest size in a column's query ...
+    uint32_t* const s_most = s_least + kColumns;                                                      // ... and largest
     u32x4 qf[kQInLds ? 1 : kK];
     if constexpr (kQInLds) {
-        constexpr int kPieces = DT * 4 / 16;
-        for (int idx = tid; idx < kColumns * kPieces; idx += 64 * kWaves) {
-            const int c = idx / kPieces, p = idx - c * kPieces;
+        if (tid < kColumns) {
+            s_least[tid] = ~0u;
+            s_most[tid] = 0;
+        }
+        __syncthreads();
+        for (int idx = tid; idx < kColumns * kSteps16 * 2; idx += 64 * kWaves) {
+            const int c = idx & (kColumns - 1), h = (idx >> 5) & 1, ks = idx >> 6;
             int t;
             const int64_t r = row_of(min(c, cols - 1), t);
-            *reinterpret_cast<u32x4*>(lds + c * kQRow + p * 16) = *reinterpret_cast<const u32x4*>((const E*)a.q + r * DT + p * 4);
+            const float* qp = (const float*)a.q + r * DT + ks * 16 + h * 4;
+            const f32x4 q0 = *reinterpret_cast<const f32x4*>(qp), q1 = *reinterpret_cast<const f32x4*>(qp + 8);
+            const Terms terms = split8(q0, q1);
+            *reinterpret_cast<u32x4*>(lds + (((0 * kSteps16 + ks) * 2 + h) * kColumns + c) * 16) = terms.h;
+            *reinterpret_cast<u32x4*>(lds + (((1 * kSteps16 + ks) * 2 + h) * kColumns + c) * 16) = terms.m;
+            *reinterpret_cast<u32x4*>(lds + (((2 * kSteps16 + ks) * 2 + h) * kColumns + c) * 16) = terms.l;
+            Least least;
+            float most = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                least.take(q0[e]);
+                least.take(q1[e]);
+                most = fmaxf(most, fmaxf(fabsf(q0[e]), fabsf(q1[e])));
+            }
+            atomicMin(s_least + c, least.u);
+            atomicMax(s_most + c, __builtin_bit_cast(uint32_t, most));
         }
     } else {
         const E* qp = (const E*)a.q + q_row * DT + hi * 8;
@@ -147,68 +182,8 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
                 vx[j * kMb + mb] = *reinterpret_cast<const u32x4*>((j < kRuns / 2 ? vA : vB) + mb * 32 * 8 + (kBf16 ? 0 : (j & 1) * 4));
     };
 
-    const float unit = kBf16 ? a.scale * kLog2e : a.scale;      // bf16 takes its weights as powers of two
-    float m = -INFINITY, lsum = 0.f;
-    f32x16 o[kMb];
-#pragma unroll
-    for (int mb = 0; mb < kMb; ++mb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[mb][i] = 0.f;
-    if (kQInLds) __syncthreads();
-    Groups at = {};                                             // the step requested last
-    if (my_n > 0) {
-        at = locate(0);
-        load_k(at);
-        load_v(at);
-    }
-
-#pragma unroll 1
-    for (int i = 0; i < my_n; ++i) {
-        const int st = w + kWaves * i;
-        f32x16 sc;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sc[e] = 0.f;
-#pragma unroll
-        for (int j = 0; j < kK; ++j) {
-            if constexpr (kBf16) {
-                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kx[j]), __builtin_bit_cast(bf16x8, qf[j]), sc, 0, 0, 0);
-            } else {
-                const f32x4 kf = __builtin_bit_cast(f32x4, kx[j]);
-                const f32x4 q4 = *reinterpret_cast<const f32x4*>(lds + n * kQRow + j * 32 + hi * 16);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], q4[e], sc, 0, 0, 0);
-            }
-        }
-        if (i + 1 < my_n) {
-            at = locate(i + 1);
-            load_k(at);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (st >= first_masked) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int key = st * kStep + (e >> 2) * 8 + hi * 4 + (e & 3);
-                sc[e] = key <= qpos ? sc[e] : -INFINITY;
-            }
-        }
-        float mx = sc[0];
-#pragma unroll
-        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sc[e]);
-        mx *= unit;                                             // scale > 0: max and scaling commute
-        // m is shared by the two lanes of a column: if either lane's own maximum outgrew it, combine them
-        if (__builtin_amdgcn_ballot_w64(mx > m + kSlack) != 0) {
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            const float m_new = fmaxf(m, mx);
-            const float alpha = m_new == -INFINITY ? 1.f : kBf16 ? __builtin_amdgcn_exp2f(m - m_new) : expf(m - m_new);
-            lsum *= alpha;
-#pragma unroll
-            for (int mb = 0; mb < kMb; ++mb)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) o[mb][e] *= alpha;
-            m = m_new;
-        }
-        const float m_ref = m == -INFINITY ? 0.f : m;           // (a column may see none of this wave's keys so far)
-        if (ctx < (st + 1) * kStep) {                           // slots past the last token may hold anything, NaN included
+    auto hide_v = [&](int st) {                                 // slots past the last token may hold anything, NaN included
+        if (ctx < (st + 1) * kStep) {
 #pragma unroll
             for (int j = 0; j < kRuns; ++j) {
                 const int keep = ctx - (st * kStep + j * (kBf16 ? 16 : 8) + hi * 4);
@@ -228,6 +203,83 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
                 }
             }
         }
+    };
+
+    const float unit = a.scale * kLog2e;                        // weights are taken as powers of two
+    float m = -INFINITY, lsum = 0.f;
+    f32x16 o[kMb];
+#pragma unroll
+    for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[mb][i] = 0.f;
+    if (kQInLds) __syncthreads();
+    Groups at = {};                                             // the step requested last
+    if (my_n > 0) {
+        at = locate(0);
+        load_k(at);
+        if (!kLateV) load_v(at);
+    }
+
+#pragma unroll 1
+    for (int i = 0; i < my_n; ++i) {
+        const int st = w + kWaves * i;
+        f32x16 sc, rest;                                        // fp32: the score is sc + rest, the products of leading terms and all smaller ones
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sc[e] = rest[e] = 0.f;
+        if constexpr (kBf16) {
+#pragma unroll
+            for (int j = 0; j < kK; ++j)
+                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kx[j]), __builtin_bit_cast(bf16x8, qf[j]), sc, 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < kSteps16; ++ks) {
+                const unsigned char* at_q = lds + ((ks * 2 + hi) * kColumns + n) * 16;
+                constexpr int kTerm = kSteps16 * 2 * kColumns * 16;
+                const u32x4 qh = *reinterpret_cast<const u32x4*>(at_q), qm = *reinterpret_cast<const u32x4*>(at_q + kTerm), ql = *reinterpret_cast<const u32x4*>(at_q + 2 * kTerm);
+                const Terms k = split8(__builtin_bit_cast(f32x4, kx[2 * ks]), __builtin_bit_cast(f32x4, kx[2 * ks + 1]));
+                rest = product(k.h, ql, rest);
+                sc = product(k.h, qh, sc);
+                rest = product(k.h, qm, rest);
+                rest = product(k.m, qm, rest);
+                rest = product(k.m, qh, rest);
+                rest = product(k.l, qh, rest);
+            }
+        }
+        if (kLateV) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_v(at);
+        }
+        if (i + 1 < my_n) {
+            at = locate(i + 1);
+            load_k(at);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (st >= first_masked) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int key = st * kStep + (e >> 2) * 8 + hi * 4 + (e & 3);
+                sc[e] = key <= qpos ? sc[e] : -INFINITY;
+                if (!kBf16) rest[e] = key <= qpos ? rest[e] : 0.f;      // (a key not to be seen may be anything, NaN included)
+            }
+        }
+        float mx = kBf16 ? sc[0] : sc[0] + rest[0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) mx = fmaxf(mx, kBf16 ? sc[e] : sc[e] + rest[e]);
+        mx *= unit;                                             // scale > 0: max and scaling commute
+        // m is shared by the two lanes of a column: if either lane's own maximum outgrew it, combine them
+        if (__builtin_amdgcn_ballot_w64(mx > m + kSlack) != 0) {
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m, mx);
+            const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m - m_new);
+            lsum *= alpha;
+#pragma unroll
+            for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) o[mb][e] *= alpha;
+            m = m_new;
+        }
+        const float m_ref = m == -INFINITY ? 0.f : m;           // (a column may see none of this wave's keys so far)
+        hide_v(st);
         if constexpr (kBf16) {
             Terms p[2];                                         // (of which only h without kLo)
 #pragma unroll
@@ -254,21 +306,29 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
                 }
         } else {
             float psum = 0.f;
+            Terms p[2];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                sc[e] = expf(fmaf(sc[e], unit, -m_ref));
-                psum += sc[e];
+            for (int e = 0; e < 16; e += 2) {
+                const float p0 = __builtin_amdgcn_exp2f(fmaf(rest[e], unit, fmaf(sc[e], unit, -m_ref))) * kWeightUnit;
+                const float p1 = __builtin_amdgcn_exp2f(fmaf(rest[e + 1], unit, fmaf(sc[e + 1], unit, -m_ref))) * kWeightUnit;
+                psum += p0 + p1;
+                p[e >> 3].set_pair((e & 7) >> 1, p0, p1);
             }
             lsum += psum;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int mb = 0; mb < kMb; ++mb)
-                        o[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(f32x4, vx[j * kMb + mb])[e], sc[j * 4 + e], o[mb], 0, 0, 0);
+                for (int mb = 0; mb < kMb; ++mb) {
+                    const Terms v = split8(__builtin_bit_cast(f32x4, vx[2 * j * kMb + mb]), __builtin_bit_cast(f32x4, vx[(2 * j + 1) * kMb + mb]));
+                    o[mb] = product(v.h, p[j].l, o[mb]);
+                    o[mb] = product(v.h, p[j].m, o[mb]);
+                    o[mb] = product(v.h, p[j].h, o[mb]);
+                    o[mb] = product(v.m, p[j].m, o[mb]);
+                    o[mb] = product(v.m, p[j].h, o[mb]);
+                    o[mb] = product(v.l, p[j].h, o[mb]);
+                }
         }
-        if (i + 1 < my_n) load_v(at);
+        if (!kLateV && i + 1 < my_n) load_v(at);
         __builtin_amdgcn_sched_barrier(0);
     }
 
@@ -285,11 +345,10 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
             const f32x4 x = {o[mb][q4 * 4], o[mb][q4 * 4 + 1], o[mb][q4 * 4 + 2], o[mb][q4 * 4 + 3]};
             *reinterpret_cast<f32x4*>(s_o + (w * kColumns + n) * kORow + mb * 32 + q4 * 8 + hi * 4) = x;
         }
-    uint32_t* const s_again = reinterpret_cast<uint32_t*>(s_l + kWaves * kColumns);       // bit c: column c is not finite
+    uint32_t* const s_again = reinterpret_cast<uint32_t*>(s_l + kWaves * kColumns);       // bit c: column c is not finite (fp32: or too small); [1]: has a zero; [2]: small values
     if (hi == 0) { s_m[w * kColumns + n] = m; s_l[w * kColumns + n] = lsum; }
-    if (kTakeAgain && tid == 0) *s_again = 0;
+    if (kTakeAgain && tid < 3) s_again[tid] = 0;
     __syncthreads();
-    auto power = [](float x) { return kBf16 ? __builtin_amdgcn_exp2f(x) : expf(x); };
     for (int idx = tid; idx < cols * (DT / 8); idx += 64 * kWaves) {
         const int c = idx / (DT / 8), d = (idx - c * (DT / 8)) * 8;
         float ms = s_m[c];                                      // wave 0 has the first keys, which every column sees
@@ -298,7 +357,7 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
         float l = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ww = 0; ww < kWaves; ++ww) {
-            const float f = power(s_m[ww * kColumns + c] - ms);       // a wave that saw no key has m = -inf -> 0
+            const float f = __builtin_amdgcn_exp2f(s_m[ww * kColumns + c] - ms);       // a wave that saw no key has m = -inf -> 0
             l += f * s_l[ww * kColumns + c];
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[e] += f * s_o[(ww * kColumns + c) * kORow + d + e];
@@ -315,12 +374,47 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
             float trouble = general::trouble_of(inv);
 #pragma unroll
             for (int e = 0; e < 8; ++e) trouble = general::trouble_of(acc[e], trouble);
-            if (!(trouble == 0.f)) atomicOr(s_again, 1u << c);
+            bool again = !(trouble == 0.f);
+            if constexpr (!kBf16) {                             // (as in attn_prefill_f32.hip)
+                Least least;
+                bool zero = false;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    least.take(acc[e]);
+                    zero |= acc[e] == 0.f;
+                }
+                again |= least.small(inv);
+                if (d == 0) {
+                    Least least_q;
+                    least_q.u = s_least[c];
+                    again |= least_q.small() || __builtin_bit_cast(float, s_most[c]) * a.scale > kLargeQuery;
+                }
+                if (zero) atomicOr(s_again + 1, 1u << c);
+            }
+            if (again) atomicOr(s_again, 1u << c);
         }
     }
     if constexpr (kTakeAgain) {
         __syncthreads();                                        // what the waves write once more is behind what is there
-        const uint32_t all = __builtin_amdgcn_readfirstlane(*s_again);
+        uint32_t all = __builtin_amdgcn_readfirstlane(*s_again);
+        if constexpr (!kBf16) {
+            const uint32_t zeros = __builtin_amdgcn_readfirstlane(s_again[1]);
+            if (zeros) {                                        // uniform over the workgroup: an output of zero is small unless its channel is all zeros
+                Least least;
+                if (my_n > 0) fetch_ids(0);
+                for (int i = 0; i < my_n; ++i) {
+                    load_v(locate(i));
+                    hide_v(w + kWaves * i);
+#pragma unroll
+                    for (int j = 0; j < kRuns * kMb; ++j)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) least.take(__builtin_bit_cast(f32x4, vx[j])[e]);
+                }
+                if (least.small()) s_again[2] = 1;
+                __syncthreads();
+                if (__builtin_amdgcn_readfirstlane(s_again[2])) all |= zeros;
+            }
+        }
         constexpr uint32_t kMine = kWaves == 8 ? 0x01010101u : 0x11111111u;       // columns w, w + kWaves, ...
         int t;
         if (all) general::attend_rows_again<E, kRowsAgain, DT / 64>(a, all & (kMine << w), row_of(min(n, cols - 1), t), qpos, s, g, s_o + kRowsAgain * DT * w);
@@ -351,36 +445,40 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
 }  // namespace
 
 // Whether the batch's query tiles are too few for the other kernels.  Counted in workgroups of 32 columns per CU of the
-// stream (one is resident at a time): on long contexts up to 2 for the bf16 / 128 / 16 shape, 3 for the others, whose kernels
-// spend twice (bf16, weights in three terms) to three times (fp32, products in six terms) the matrix work.
+// stream (one is resident at a time): on long contexts up to 2 for the bf16 / 128 / 16 shape, 3 for the other bf16 shapes, whose
+// kernels spend twice the matrix work (weights in three terms), more for fp32, where either kernel is bound by its products.
 // Measured at 32 / 8 heads on 256 CUs, append included, the other kernel -> this one: bf16 / 128 / 16, one chunk of
 // 5 rows on 6007 tokens (8 workgroups) 114 -> 37 us, 211 rows (216) 119 -> 43, 400 rows (400) 122 -> 77; four chunks of
 // 150 rows on 3000 (608) 70 -> 70, eight of 100 on 2000 (832) 57 -> 71.  bf16 / 64 / 64: eight of 40 on 2000 (320) 49 ->
-// 32, 32 of 20 on 1000 (768) 32 -> 32, eight of 100 on 2000 (832) 55 -> 58, two prompts of 1000 (2000) 48 -> 54.  fp32 / 128:
-// one chunk of 211 rows on 6000 (216) 589 -> 233, one prompt of 600 (600) 73 -> 57, twelve chunks of 10..100 rows on
-// 1000..3000 (700) 295 -> 249; three of 300 on 5000 (912) 513 -> 762, two prompts of 1000 (2000) 139 -> 215.  bf16 / 256 (graph
+// 32, 32 of 20 on 1000 (768) 32 -> 32, eight of 100 on 2000 (832) 55 -> 58, two prompts of 1000 (2000) 48 -> 54.  bf16 / 256 (graph
 // replay): six of 13 rows on 2200 (112) 120 -> 40, eight of 120 on 2000 (784) 119 -> 100, of 160 on 1500 (1024) 100 -> 107.
 // A workgroup's start and merge cost it about 8 us whatever its keys, so a second one on a CU pays only where there are keys to
 // go through: the line falls to little more than one a CU for the shortest contexts.  Graph replay, this one -> the other: 16 prompts of
-// 50 rows (700 workgroups) bf16 / 64 16.1 -> 10.2 us, fp32 / 64 25.9 -> 14.8, fp32 / 128 36.9 -> 23.0; eight of 100 (660) bf16 / 64
-// 15.7 -> 11.6, bf16 / 128 on pages of 32 19.3 -> 15.2, bf16 / 256 29.9 -> 25.4; eight of 50 (360) bf16 / 128 / 16 12.5 -> 11.4,
-// fp32 / 64 17.6 -> 13.3; four of 200 rows on 300 (630) bf16 / 128 on pages of 32 26.4 -> 23.4; but eight of 60 on 300 (420) bf16 / 64 13.7 ->
+// 50 rows (700 workgroups) bf16 / 64 16.1 -> 10.2 us; eight of 100 (660) bf16 / 64
+// 15.7 -> 11.6, bf16 / 128 on pages of 32 19.3 -> 15.2, bf16 / 256 29.9 -> 25.4; eight of 50 (360) bf16 / 128 / 16 12.5 -> 11.4;
+// four of 200 rows on 300 (630) bf16 / 128 on pages of 32 26.4 -> 23.4; but eight of 60 on 300 (420) bf16 / 64 13.7 ->
 // 15.1, 16 of 30 on 600 (490) 16.7 -> 21.2, five of 60 at 16 / 2 (160) bf16 / 128 / 16 8.2 -> 10.5.
-// Where a row is 512 bytes or more it rises more slowly: 29 of 101 rows on 274 at 8 / 2 heads (755) bf16 / 256 43 -> 39, 21 of 13 on 25
-// (335) 21 -> 17, 19 of 63 on 190 at 16 / 2 (609) fp32 / 128 49 -> 37; but eight of 60 on 300 (512)
-// bf16 / 256 31 -> 37, 16 of 30 on 600 (512) 39 -> 51.  And it does not fall where no chunk has more than 32 columns, so that the
-// other kernel has as many workgroups, three quarters empty: 44 of 3 on 32 (352) fp32 / 128 23 -> 29.  Over 931 drawn batches of these two
-// shapes of 0 to 4 a CU the line costs 1.7 % against the faster side of each.
+// Where a row of bf16 is 512 bytes it rises more slowly: 29 of 101 rows on 274 at 8 / 2 heads (755) bf16 / 256 43 -> 39, 21 of 13 on 25
+// (335) 21 -> 17; but eight of 60 on 300 (512) 31 -> 37, 16 of 30 on 600 (512) 39 -> 51.  And there and at fp32 / 128 it does not fall where no
+// chunk has more than 32 columns, so that the other kernel has as many workgroups, three quarters empty: 44 of 3 on 32 (352) fp32 / 128
+// 23 -> 29.  fp32, over 150 drawn batches, attn_prefill_f32.hip / this one: up to one workgroup a CU 1.0 to 2.8; on a second one
+// contexts decide, below 125 tokens at 64 channels 0.72 to 0.97, 125 to 340 1.0 to 1.3, beyond 1.3 to 1.9, at 128 channels below 64 0.69 to
+// 0.97, to 250 1.0 to 1.4, beyond 1.4 to 1.7; two to three a CU on 350 to 1750 tokens 1.03 to 1.34, on fewer 0.66 to 0.93; three to five at
+// 128 channels on 750 to 1600 1.0 to 1.23, on fewer 0.80 to 1.09; more 0.5 to 0.93.
 bool prefill_split_preferred(const AttnArgs& a, bool rounded, hipStream_t st)
 {
     if ((a.c.d != 64 && a.c.d != 128 && (a.c.d != 256 || a.c.dtype == AG_F32)) || a.c.ps < 16 || (int64_t)a.total_rows * (a.hq / a.c.hkv) > 0x7fffffff ||
         ((uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 != 0) return false;
     const int64_t ctx = a.max_ctx;                  // in thousandths of a workgroup per CU:
-    const bool wide = a.c.d * (a.c.dtype == AG_F32 ? 4 : 2) >= 512;
     const int64_t tiles = tiles_bound(a, kColumns);
-    const bool one_each = wide && tiles == tiles_bound(a, 128);
-    const int64_t line = rounded ? std::max<int64_t>(1125, std::min<int64_t>(875 + 2 * ctx, 2000))
-                                 : std::min<int64_t>(one_each ? 3000 : wide ? 1125 + 4 * ctx : 1250 + 3 * ctx, 3000);
+    auto between = [](int64_t lo, int64_t x, int64_t hi) { return std::max(lo, std::min(x, hi)); };
+    const bool wide = a.c.d * (a.c.dtype == AG_F32 ? 4 : 2) >= 512, one_each = wide && tiles == tiles_bound(a, 128);
+    int64_t line;
+    if (one_each) line = 3000;
+    else if (a.c.dtype == AG_F32 && a.c.d == 64) line = ctx < 125 ? 1000 : between(2000, 2000 + 5 * (ctx - 300), 4000);
+    else if (a.c.dtype == AG_F32) line = ctx < 64 ? 1000 : between(2000, 2000 + 5 * (ctx - 200), 5000);
+    else if (rounded) line = between(1125, 875 + 2 * ctx, 2000);
+    else line = std::min<int64_t>(wide ? 1125 + 4 * ctx : 1250 + 3 * ctx, 3000);
     return 1000 * a.c.hkv * tiles <= line * stream_cus(st);
 }
 

@@ -49,4 +49,28 @@ struct Terms {
     }
 };
 
+// ---- fp32 products as six products of terms (attn_prefill_f32.hip, attn_prefill_split.hip) ----
+constexpr float kLargeQuery = 0x1p90f;  // scale * |q| up to which what small keys lose (2^-126, times 128 channels) is nothing
+
+// The smallest size among numbers, zero left out because it is exact: of 2 |bits| - 1, where zero comes out largest.
+struct Least {
+    uint32_t u = ~0u;
+    __device__ __forceinline__ void take(float x) { u = min(u, (__builtin_bit_cast(uint32_t, x) << 1) - 1); }
+    __device__ __forceinline__ bool small(float unit = 1.f) const        // (no number but zeros: NaN)
+    {
+        return __builtin_bit_cast(float, u >> 1) * unit < 0x1p-100f;
+    }
+};
+
+constexpr float kWeightUnit = 0x1p48f;  // what a weight of 1 is multiplied as; their sum is in the same unit
+
+typedef float Four __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ Terms split8(const Four& a, const Four& b)
+{
+    Terms t;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t.set_pair(i, i < 2 ? a[2 * i] : b[2 * i - 4], i < 2 ? a[2 * i + 1] : b[2 * i - 3]);
+    return t;
+}
+
 }  // namespace ag

@@ -1,0 +1,56 @@
+"""fp32 prefill of few rows, whose products are of three bf16 terms: edges of its steps of 32 keys, of the four waves' shares and
+of its tiles of 32 columns; numbers whose terms leave the products' range, against the fp64 oracle within fp32's own gates."""
+import numpy as np
+import pytest
+
+from gpu_helpers import check_close, make_cache, run_phase
+from helpers import fresh_pools, make_batch
+from paper_2603_10342_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def fill_and_resume(g, prefix, new, seed, sigma_qk=1.0, sigma_v=1.0):
+    prefix, new = np.asarray(prefix, np.int32), np.asarray(new, np.int32)
+    bt = I.deal_block_tables(I.rng_for(seed, 0), prefix + new, g.page_size, g.num_pages)
+    cache = make_cache(g)
+    kp, vp = fresh_pools(g)
+    if prefix.any():
+        run_phase(cache, kp, vp, make_batch(g, np.zeros_like(prefix), prefix, seed=seed, bt=bt, sigma_qk=sigma_qk, sigma_v=sigma_v), "cold")
+    got, ref = run_phase(cache, kp, vp, make_batch(g, prefix, new, seed=seed, bt=bt, stream=2, sigma_qk=sigma_qk, sigma_v=sigma_v), "resume")
+    check_close(got / sigma_v, ref / sigma_v, g.dtype, f"{g}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("ps,hq,hkv", [(16, 6, 2), (64, 4, 4), (32, 40, 2), (128, 3, 1)])
+def test_edges(d, ps, hq, hkv):
+    g = I.Geometry(hq, hkv, d, ps, 8192 // ps, I.F32)
+    fill_and_resume(g, [0, 31, 95, 127, 128, 500, 1, 4200], [1, 1, 33, 8, 9, 16, 40, 5], seed=61)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("sigma_qk,sigma_v", [(1.0, 1e-36), (1.0, 1e-33), (1.0, 1e37), (1e-15, 1.0)])
+def test_ends_of_the_range(d, sigma_qk, sigma_v):
+    g = I.Geometry(8, 2, d, 16, 64, I.F32)
+    fill_and_resume(g, [0, 200], [45, 61], seed=64, sigma_qk=sigma_qk, sigma_v=sigma_v)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("scale_q,scale_k", [(1e-30, 1e30), (1e30, 1e-30), (1e25, 1e-26)])
+def test_large_and_tiny_factors_of_ordinary_scores(d, scale_q, scale_k):
+    g = I.Geometry(8, 2, d, 16, 64, I.F32)
+    b = make_batch(g, [0, 0], [45, 61], seed=65, sigma_qk=1.0, sigma_v=1.0)
+    b.q, b.k_new = (b.q * np.float32(scale_q)).astype(np.float32), (b.k_new * np.float32(scale_k)).astype(np.float32)
+    got, ref = run_phase(make_cache(g), *fresh_pools(g), b, "cold")
+    check_close(got, ref, I.F32, f"D={d} q {scale_q} k {scale_k}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_zero_values_and_zero_keys(d):
+    g = I.Geometry(8, 2, d, 16, 64, I.F32)
+    b = make_batch(g, [0, 0], [45, 61], seed=66, sigma_qk=1.0, sigma_v=1.0)
+    b.v_new[:, :, ::2] = 0
+    b.k_new[:45] = 0
+    got, ref = run_phase(make_cache(g), *fresh_pools(g), b, "cold")
+    assert np.all(got[:, :, ::2] == 0)
+    check_close(got, ref, I.F32, f"D={d}")
