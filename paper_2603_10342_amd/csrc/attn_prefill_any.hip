@@ -56,7 +56,7 @@ __device__ __forceinline__ void with_operands(At at, Use use)
 }
 
 template <typename E, int DT, bool kExact>
-__global__ __launch_bounds__(256, DT > 128 ? 1 : 2) void prefill_any_kernel(AttnArgs a, int tiles_max, int per_xcd, int total_work)
+__global__ __launch_bounds__(256, DT > 128 ? 1 : 2) void prefill_any_kernel(AttnArgs a, Deal deal)
 {
     constexpr bool kBf16 = sizeof(E) == 2;
     constexpr int BN = 128 / (int)sizeof(E);        // keys per tile
@@ -68,15 +68,13 @@ __global__ __launch_bounds__(256, DT > 128 ? 1 : 2) void prefill_any_kernel(Attn
     constexpr float kSlack = kBf16 ? 8.0f : 5.5f;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];       // [2 stages][K tile, V tile]
 
-    // ---- which (KV head, session, tile): the XCD a workgroup lands on owns a contiguous range of KV heads ----
-    const int xcd = blockIdx.x & 7, ord = blockIdx.x >> 3;
-    const unsigned wk = (unsigned)(xcd * per_xcd + ord);
-    if (wk >= (unsigned)total_work) return;
+    // ---- which (KV head, session, tile) ----
     const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv;
     const int D = kExact ? DT : a.c.d, ps = a.c.ps;
-    const int g = (int)(wk / (unsigned)tiles_max);
+    int g, j;
+    if (!place_of(deal, hkv, g, j)) return;
     int s = -1, qt = 0, N = 0, P = 0, row0 = 0;
-    find_tile<kColumns>(a, (int)(wk - (unsigned)g * (unsigned)tiles_max), G, s, qt, N, P, row0);
+    find_tile<kColumns>(a, j, G, s, qt, N, P, row0);
     if (s < 0) return;                              // beyond the batch's tiles
     const int ctx = P + N;
     const int col0 = qt * kColumns, cols = min(N * G - col0, kColumns);       // valid columns of the tile
@@ -331,10 +329,9 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
         ag_status e = allow_dynamic_lds((const void*)prefill_any_kernel<E, DT, kExact>, lds, told);
         if (e) return e;
     }
-    const int64_t tiles_max = tiles_bound(a), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
+    const Deal deal = deal_of(a, tiles_bound(a), stream_cus(st) * (DT > 128 ? 1 : 2) / 8);
     prof_before(st);
-    hipLaunchKernelGGL((prefill_any_kernel<E, DT, kExact>), dim3((unsigned)(per_xcd * 8)), dim3(256), lds, st, a, (int)tiles_max,
-                       (int)per_xcd, (int)total);
+    hipLaunchKernelGGL((prefill_any_kernel<E, DT, kExact>), dim3((unsigned)workgroups_of(deal)), dim3(256), lds, st, a, deal);
     prof_after(st);
     return hip_check(hipGetLastError(), "prefill launch");
 }

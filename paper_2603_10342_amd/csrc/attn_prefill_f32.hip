@@ -67,7 +67,7 @@ __device__ __forceinline__ f32x16 product(const u32x4& a, const u32x4& b, const 
 
 // unit: scale log2(e), as weights are taken as powers of two
 template <int DT>
-__global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnArgs a, float unit, int tiles_max, int per_xcd, int total_work)
+__global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnArgs a, float unit, Deal deal)
 {
     constexpr int kPlane = plane_bytes(DT);
     constexpr int kUnits = BN * DT / 8 / 256;       // runs of eight numbers a thread moves of a K tile, and of a V tile
@@ -75,14 +75,12 @@ __global__ __launch_bounds__(256, DT > 64 ? 1 : 2) void prefill_f32_kernel(AttnA
     constexpr int kAhead = 4;                       // LDS operand reads run this many operands ahead of their use
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
-    // ---- which (KV head, session, tile): the XCD a workgroup lands on owns a contiguous range of KV heads ----
-    const int xcd = blockIdx.x & 7, ord = blockIdx.x >> 3;
-    const unsigned wk = (unsigned)(xcd * per_xcd + ord);
-    if (wk >= (unsigned)total_work) return;
+    // ---- which (KV head, session, tile) ----
     const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv, ps = a.c.ps;
-    const int g = (int)(wk / (unsigned)tiles_max);
+    int g, j;
+    if (!place_of(deal, hkv, g, j)) return;
     int s = -1, qt = 0, N = 0, P = 0, row0 = 0;
-    find_tile<kColumns>(a, (int)(wk - (unsigned)g * (unsigned)tiles_max), G, s, qt, N, P, row0);
+    find_tile<kColumns>(a, j, G, s, qt, N, P, row0);
     if (s < 0) return;                              // beyond the batch's tiles
     const int ctx = P + N;
     const int col0 = qt * kColumns, cols = min(N * G - col0, kColumns);       // valid columns of the tile
@@ -473,9 +471,9 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
         if (e) return e;
     }
     const float unit = (float)(a.scale * 1.4426950408889634);
-    const int64_t tiles_max = tiles_bound(a), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
+    const Deal deal = deal_of(a, tiles_bound(a), stream_cus(st) * (DT > 64 ? 1 : 2) / 8);
     prof_before(st);
-    hipLaunchKernelGGL((prefill_f32_kernel<DT>), dim3((unsigned)(per_xcd * 8)), dim3(256), lds, st, a, unit, (int)tiles_max, (int)per_xcd, (int)total);
+    hipLaunchKernelGGL((prefill_f32_kernel<DT>), dim3((unsigned)workgroups_of(deal)), dim3(256), lds, st, a, unit, deal);
     prof_after(st);
     return hip_check(hipGetLastError(), "prefill launch");
 }

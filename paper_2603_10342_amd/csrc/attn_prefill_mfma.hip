@@ -36,10 +36,9 @@
 // Tiles wholly above a wave's rows are skipped; the tiles on the diagonal are
 // masked before the weights are taken.
 //
-// Workgroups are numbered so that the XCD a workgroup lands on (id % 8) owns a
-// contiguous range of KV heads, and inside it session-major, longest query
-// tile first: the workgroups resident together read one session's K/V for one
-// KV head, which then stays in that XCD's L2.  The grid lists the batch's real
+// KV heads are dealt to the XCDs (tile_list.h), and a head's tiles are listed
+// session-major, longest context first: the workgroups resident together read
+// few sessions' K/V for one KV head, which then stays in that XCD's L2.  The grid lists the batch's real
 // tiles only (each workgroup finds its tile from the chunk lengths): empty
 // workgroups are not free, the dispatcher takes as long over them as over
 // the others.
@@ -72,7 +71,7 @@ constexpr int lds_bytes(int nw, int dt) { return (kKStages + kVStages) * tile_by
 // (attn_tile32.h); the bf16 / 128 / 16 shape runs without.  kPage16: pages of 16 tokens, whose groups need no place
 // inside the page.
 template <int NW, int DT, bool kLo, bool kPage16>
-__global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, int tiles_max, int per_xcd, int total_work)
+__global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, Deal deal)
 {
     constexpr int kCols = 32 * NW;          // columns per workgroup
     constexpr int kTile = tile_bytes(DT);
@@ -80,9 +79,6 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, in
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
     // ---- which (KV head, session, query tile) ----
-    const int xcd = blockIdx.x & 7, ord = blockIdx.x >> 3;
-    const unsigned wk = (unsigned)(xcd * per_xcd + ord);
-    if (wk >= (unsigned)total_work) return;
     const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv;
     // Work order: KV head, then session, then query tile (longest first).
     // The grid holds `tiles_max` tiles per KV head, a host-side bound on sum_s ceil(N_s G / kCols); which (session,
@@ -90,9 +86,10 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, in
     // A grid of batch x ceil(max_new G / kCols) tiles would be mostly empty
     // workgroups when chunk lengths differ much, and launching a workgroup of this size takes the dispatcher of
     // an XCD most of a microsecond, whether it has work or not.
-    const int g = (int)(wk / (unsigned)tiles_max);
+    int g, j;
+    if (!place_of(deal, hkv, g, j)) return;
     int s = -1, qt = 0, N = 0, P = 0, row0 = 0;
-    find_tile<kCols>(a, (int)(wk - (unsigned)g * (unsigned)tiles_max), G, s, qt, N, P, row0);
+    find_tile<kCols>(a, j, G, s, qt, N, P, row0);
     if (s < 0) return;                              // beyond the batch's tiles
     const int ctx = P + N;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
@@ -373,11 +370,11 @@ static ag_status launch_prefill_nw(const AttnArgs& a, hipStream_t st)
         ag_status e = allow_dynamic_lds((const void*)prefill_mfma_kernel<NW, DT, kLo, kPage16>, lds, told);
         if (e) return e;
     }
-    const int64_t tiles_max = tiles_bound(a, 32 * NW), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
-    if (per_xcd * 8 > 0x7fffffff) { set_error("too many query tiles for one launch"); return AG_ERR_INVALID_ARG; }
+    if (a.c.hkv * tiles_bound(a, 32 * NW) + 8 > 0x7fffffff) { set_error("too many query tiles for one launch"); return AG_ERR_INVALID_ARG; }
+    const Deal deal = deal_of(a, tiles_bound(a, 32 * NW), stream_cus(st) * (8 / NW) / 8);
     prof_before(st);
-    hipLaunchKernelGGL((prefill_mfma_kernel<NW, DT, kLo, kPage16>), dim3((unsigned)(per_xcd * 8)), dim3(64 * NW), lds, st, a,
-                       (int)tiles_max, (int)per_xcd, (int)total);
+    hipLaunchKernelGGL((prefill_mfma_kernel<NW, DT, kLo, kPage16>), dim3((unsigned)workgroups_of(deal)), dim3(64 * NW), lds, st, a,
+                       deal);
     prof_after(st);
     return hip_check(hipGetLastError(), "prefill launch");
 }

@@ -64,7 +64,7 @@ struct Shape {
 // those of the decode queue's own kernels do.  Queues, ten batches: error against 64 bits 0.92 to 0.96 of theirs, where a reference
 // that may be outgrown had 0.99 to 1.05; it costs 1 to 10 % of a small queue (rescaling O in most steps).
 template <typename E, int DT, bool kLo, bool kExact = false>
-__global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void prefill_split_kernel(AttnArgs a, int tiles_max, int per_xcd, int total_work)
+__global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void prefill_split_kernel(AttnArgs a, Deal deal)
 {
     constexpr int kWaves = Shape<DT>::waves, kORow = Shape<DT>::o_row, kRowsAgain = Shape<DT>::rows_again;
     constexpr bool kBf16 = sizeof(E) == 2;
@@ -79,14 +79,12 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
     constexpr float kSlack = kExact ? 0.f : 8.0f;   // how far a maximum may outgrow the reference before O is rescaled
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];       // Q in the loop (fp32), then the waves' partials
 
-    // ---- which (KV head, session, tile): the XCD a workgroup lands on owns a contiguous range of KV heads ----
-    const int xcd = blockIdx.x & 7, ord = blockIdx.x >> 3;
-    const unsigned wk = (unsigned)(xcd * per_xcd + ord);
-    if (wk >= (unsigned)total_work) return;
+    // ---- which (KV head, session, tile) ----
     const int hkv = a.c.hkv, hq = a.hq, G = hq / hkv, ps = a.c.ps;
-    const int g = (int)(wk / (unsigned)tiles_max);
+    int g, j;
+    if (!place_of(deal, hkv, g, j)) return;
     int s = -1, qt = 0, N = 0, P = 0, row0 = 0;
-    find_tile<kColumns>(a, (int)(wk - (unsigned)g * (unsigned)tiles_max), G, s, qt, N, P, row0);
+    find_tile<kColumns>(a, j, G, s, qt, N, P, row0);
     if (s < 0) return;                              // beyond the batch's tiles
     const int ctx = P + N;
     const int col0 = qt * kColumns, cols = min(N * G - col0, kColumns);
@@ -434,10 +432,10 @@ ag_status launch_kernel(const AttnArgs& a, hipStream_t st)
     static std::atomic<uint64_t> told{0};
     ag_status e = allow_dynamic_lds((const void*)prefill_split_kernel<E, DT, kLo, kExact>, lds, told);
     if (e) return e;
-    const int64_t tiles_max = tiles_bound(a, kColumns), total = a.c.hkv * tiles_max, per_xcd = (total + 7) / 8;
+    const Deal deal = deal_of(a, tiles_bound(a, kColumns), stream_cus(st) / 8);
     prof_before(st);
-    hipLaunchKernelGGL((prefill_split_kernel<E, DT, kLo, kExact>), dim3((unsigned)(per_xcd * 8)), dim3(64 * Shape<DT>::waves), lds, st, a,
-                       (int)tiles_max, (int)per_xcd, (int)total);
+    hipLaunchKernelGGL((prefill_split_kernel<E, DT, kLo, kExact>), dim3((unsigned)workgroups_of(deal)), dim3(64 * Shape<DT>::waves), lds, st, a,
+                       deal);
     prof_after(st);
     return hip_check(hipGetLastError(), "prefill launch");
 }

@@ -1,10 +1,61 @@
-// The compact tile list of the prefill kernels: which (session, query tile) tile number j of a KV head is.  Internal.
+// The compact tile list of the prefill kernels: which (KV head, tile number) a workgroup takes, and which (session, query tile)
+// tile number j of a KV head is.  Internal.
 #pragma once
+
+#include <algorithm>
 
 #include "ag_internal.h"
 #include "find_session.h"
 
 namespace ag {
+
+// Workgroups land on XCD blockIdx.x % 8.  KV heads are dealt to the XCDs, so that a head's keys and values stay in the L2s of
+// few: 8 / gcd(heads, 8) XCDs share a set of heads and its list of tiles, longest context first (find_tile()).  While an XCD's part
+// of the list fits it at once, each takes one run of it, whose keys are the fewest sessions'.  A longer list is dealt in turn, in
+// runs of up to four tiles of a session (eight runs an XCD at least): in one run each, the XCD with the longest contexts, or with the ends
+// of the prompts, ends long after the others - but for prompts of one length that come out even, where a run is whole prompts and
+// begins with their longest tiles.  Graph replay, append included, one run -> dealt, us: 16 / 1 heads x 128, 26 chunks of 4..732
+// rows on 133..6759 tokens 381 -> 228, three prompts of 99..3867 138 -> 81; 8 / 2 six of 39..3985 160 -> 109; 16 / 2, 31 of about 200 on
+// 1418..5227 262 -> 187, 23 of 7..31 on 1190..1378 28.8 -> 19.5 (single tiles 25.2), fp32 x 64 eleven of 209..472 on 461..2721 331 -> 222;
+// 6 / 2 x 256 13 of 150..850 83 -> 61; but 16 / 2 four prompts of 1151..1419 46.6 -> 50.7.  Where it fits, dealt: 6 / 2, 23 of 26..57 on 892..6241
+// 39.9 -> 55.4, 16 / 1, 15 of 9..54 on 365..817 14.1 -> 16.1, but 16 / 2 pages of 32, 12 of 12..385 on 306..2893 138 -> 111.  Over 130 and over 110
+// drawn batches of heads that eight does not divide 1.073 and 1.069 on average (runs of eight 1.066, of a sixteenth of the list 1.068, single tiles always 1.060).
+struct Deal {
+    int tiles_max;          // tiles of a KV head, a bound
+    int items;              // tiles of a set of heads
+    int share;              // log2 of the XCDs that share a set
+    int run;                // consecutive tiles that go to one XCD
+};
+
+// at_once: workgroups of an XCD that are resident together
+inline Deal deal_of(const AttnArgs& a, int64_t tiles_max, int at_once)
+{
+    int share = 3;
+    while (share > 0 && a.c.hkv % (16 >> share) == 0) --share;
+    const int64_t heads = a.c.hkv >> (3 - share), items = heads * tiles_max, part = (items + (1 << share) - 1) >> share;
+    const int64_t prompts = heads * a.batch, each = (prompts + (1 << share) - 1) >> share;
+    const bool even = a.max_ctx == a.max_new && 5 * (int64_t)a.total_rows >= 4 * (int64_t)a.batch * a.max_new && 7 * prompts >= 6 * (each << share);
+    const int64_t session = (tiles_max + a.batch - 1) / a.batch;
+    const int64_t run = share == 0 || part <= at_once || even ? part : std::max<int64_t>(1, std::min({session, part / 8, (int64_t)4}));
+    return Deal{(int)tiles_max, (int)items, share, (int)run};
+}
+inline int64_t workgroups_of(const Deal& d)
+{
+    const int64_t round = (int64_t)d.run << d.share;
+    return 8 * ((d.items + round - 1) / round) * d.run;
+}
+
+__device__ __forceinline__ bool place_of(const Deal& d, int hkv, int& g, int& j)
+{
+    const unsigned xcd = blockIdx.x & 7, ord = blockIdx.x >> 3, run = (unsigned)d.run;
+    const unsigned before = ord < run ? 0 : ord / run;                          // runs this XCD has taken
+    const unsigned k = ((before << d.share) + (xcd & ((1u << d.share) - 1)) - before) * run + ord;
+    if (k >= (unsigned)d.items) return false;
+    const unsigned head = k / (unsigned)d.tiles_max;
+    g = (int)(xcd >> d.share) * (hkv >> (3 - d.share)) + (int)head;
+    j = (int)(k - head * (unsigned)d.tiles_max);
+    return true;
+}
 
 // Tiles of C columns, G columns a row.  s stays -1 when tile j is nobody's; otherwise s, its tile qt (the session's tiles
 // count down: longest context first), its lengths N and P and its first row row0.
