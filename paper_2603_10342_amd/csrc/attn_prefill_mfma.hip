@@ -57,6 +57,8 @@ namespace {
 
 using namespace tile32;
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 // K stages: 3 (K(t+2) is requested while K(t) is used); V stages: 2 (V(t) requested while V(t-1) is used; a third
 // measured no faster).  At head_dim 128 that is 80 KiB: two 4-wave workgroups or one 8-wave workgroup per CU.
 constexpr int kVStages = 2;
@@ -70,8 +72,9 @@ constexpr int lds_bytes(int nw, int dt) { return (kKStages + kVStages) * tile_by
 // is shared by twice the columns) at the price of coarser query tiles.  kLo: weights as three bf16 terms
 // (attn_tile32.h); the bf16 / 128 / 16 shape runs without.  kPage16: pages of 16 tokens, whose groups need no place
 // inside the page.
-template <int NW, int DT, bool kLo, bool kPage16>
-__global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, Deal deal)
+// kHalves: two sets of NW waves take every other key tile of the same columns, see prefill_halves_kernel.
+template <int NW, int DT, bool kLo, bool kPage16, int kHalves>
+__device__ __forceinline__ void attend_tile(const AttnArgs& a, const Deal& deal)
 {
     constexpr int kCols = 32 * NW;          // columns per workgroup
     constexpr int kTile = tile_bytes(DT);
@@ -92,9 +95,11 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, De
     find_tile<kCols>(a, j, G, s, qt, N, P, row0);
     if (s < 0) return;                              // beyond the batch's tiles
     const int ctx = P + N;
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, w = kHalves == 1 ? tid >> 6 : (tid >> 6) & (NW - 1), lane = tid & 63;
     const int wu = __builtin_amdgcn_readfirstlane(w);           // the same value, known to be uniform: used only
                                                                  // where a scalar is required (page ids, M0)
+    const int half = kHalves == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6) / NW;
+    auto tile = [&](int t) { return kHalves == 1 ? t : kHalves * t + half; };      // the key tile of iteration t
     const int n = lane & 31, hi = lane >> 5;
     const __bf16* kpool = (const __bf16*)a.c.k;
     const __bf16* vpool = (const __bf16*)a.c.v;
@@ -109,8 +114,8 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, De
     const int k_stride = kPage16 ? 256 : a.c.ps * 16;                          // bytes between a K page's chunks
 
     // ---- tile requests: direct global-to-LDS loads, kPer + kPer wave-wide instructions per wave and tile ----
-    unsigned char* const k_lds = lds;                       // K tile t lives at k_lds + (t % 3) * kTile
-    unsigned char* const v_lds = lds + kKStages * kTile;    // V tile t lives at v_lds + (t % 2) * kTile
+    unsigned char* const k_lds = lds + half * ((kKStages + kVStages) * kTile);     // K of iteration t lives at k_lds + (t % 3) * kTile
+    unsigned char* const v_lds = k_lds + kKStages * kTile;                         // V at v_lds + (t % 2) * kTile
     const int kgrp = lane >> 4, kslot = lane & 15;          // K: lane = key of the tile (group, slot)
     const int kmask[4] = {kgrp == 0 ? -1 : 0, kgrp == 1 ? -1 : 0, kgrp == 2 ? -1 : 0, kgrp == 3 ? -1 : 0};
 
@@ -122,6 +127,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, De
     // (16 key tiles) by one direct load each, two windows resident, and every lane reads the id it needs
     // (its own group's of the K tile, the wave's group's of the V tile) with an ordinary LDS read.
     constexpr bool kLdsIds = ids_in_lds(NW);
+    static_assert(!kLdsIds || kHalves == 1, "two sets of waves leave no room for page ids");
     struct Pages { int k; int v; };                            // k: the page of this LANE's group of the K tile; v: of the wave's group of the V tile
     const int v_grp = (wu * 4) / NW;                           // group of a V tile this wave brings in (a group's two 8-key chunks)
     auto id_of = [&](int grp) { return bt[min(grp, last_grp) >> gshift]; };
@@ -188,10 +194,10 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, De
     if constexpr (kLdsIds) {
         if (wu == 0) refill_ids(0);
     }
-    pages_scalar(0, 0, pg);
-    request_k(0, 0, pg.k);
-    pages_scalar(1, 0, pg);                          // (beyond a short context's last group the ids repeat: read, never used)
-    request_k(1, 1, pg.k);
+    pages_scalar(tile(0), 0, pg);
+    request_k(tile(0), 0, pg.k);
+    pages_scalar(tile(1), 0, pg);                    // (beyond a short context's last group the ids repeat: read, never used)
+    request_k(tile(1), 1, pg.k);
 
     const int col0 = qt * kCols;
     const int cols = min(N * G - col0, kCols);                  // valid columns of this workgroup
@@ -227,7 +233,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, De
     const unsigned char* const k_lane = k_lds + n * 16 + hi * 1024;
     const unsigned char* const v_lane = v_lds + n * 16 + hi * (DT * 16);
 
-    pages_scalar(min(2, n_tiles - 1), 0, pg);        // what iteration 0 requests: V(0) and K(2)
+    pages_scalar(min(tile(2), n_tiles - 1), min(tile(0), n_tiles - 1), pg);        // what iteration 0 requests: V(0) and K(2)
     AG_WAIT_VMCNT(0);
     __syncthreads();
     f32x16 sc[2];
@@ -240,7 +246,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, De
     // shape.  Every wave runs all n_tiles + 1 iterations (the barriers are workgroup-wide); the pieces a wave
     // does not need are skipped.
     auto iter = [&](int t, Weights<kLo>& p_prev, Weights<kLo>& p_cur) {
-        const int tv = min(t, n_tiles - 1);          // the V tile that must have landed when this iteration ends
+        const int tv = min(tile(t), n_tiles - 1);    // the V tile that must have landed when this iteration ends
         if constexpr (kLdsIds) {
             // The window holding tile t + 4 comes in one iteration before its first id is read (iteration t + 1
             // reads those of K(t + 4)); issued ahead of this iteration's tile requests, it has landed when wave 0
@@ -249,16 +255,16 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, De
             if (wu == 0 && ((t + 4) & 15) == 0) refill_ids((t + 4) >> 4);
         }
         request_v(tv, t % kVStages, pg.v);
-        request_k(min(t + 2, n_tiles - 1), t + 2, pg.k);
+        request_k(min(tile(t + 2), n_tiles - 1), t + 2, pg.k);
         Pages nxt;                                    // ids for the next iteration's requests
-        pages_of(min(t + 3, n_tiles - 1), min(t + 1, n_tiles - 1), nxt);
-        const bool do_sm = t < wave_tiles, do_pv = t >= 1 && t <= wave_tiles;
+        pages_of(min(tile(t + 3), n_tiles - 1), min(tile(t + 1), n_tiles - 1), nxt);
+        const bool do_sm = tile(t) < wave_tiles, do_pv = t >= 1 && tile(t - 1) < wave_tiles;
         const unsigned char* kb = k_lane + (t % kKStages) * kTile;
         const unsigned char* vb = v_lane + ((t + kVStages - 1) % kVStages) * kTile;   // V(t-1)
         if (do_sm) {
             qk_tile<DT>(kb, qf, sc);
-            if (t >= first_masked) {                 // the tile straddles this wave's diagonal
-                const int kbase = t * BN + hi * 4;
+            if (tile(t) >= first_masked) {           // the tile straddles this wave's diagonal
+                const int kbase = tile(t) * BN + hi * 4;
 #pragma unroll
                 for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -276,14 +282,36 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, De
     };
 
 #pragma unroll 1
-    for (int t = 0; t <= n_tiles; t += 2) {
+    for (int t = 0; t <= (n_tiles + kHalves - 1) / kHalves; t += 2) {
         iter(t, pb, pa);
-        if (t + 1 <= n_tiles) iter(t + 1, pa, pb);
+        if (t + 1 <= (n_tiles + kHalves - 1) / kHalves) iter(t + 1, pa, pb);
     }
 
     // ---- normalise, transpose through LDS, store rows contiguously ----
     AG_WAIT_VMCNT(0);                                // the last (redundant) tile requests still write to LDS
     __syncthreads();
+    if constexpr (kHalves == 2) {                    // the second half's sums, lane by lane
+        f32x4* const part = reinterpret_cast<f32x4*>(lds + w * (DT * 128)) + lane;
+        float* const ml = reinterpret_cast<float*>(lds + NW * (DT * 128)) + w * 128 + lane;
+        if (half == 1) {
+#pragma unroll
+            for (int i = 0; i < DT / 8; ++i)
+                part[i * 64] = f32x4{o[i >> 2][(i & 3) * 4], o[i >> 2][(i & 3) * 4 + 1], o[i >> 2][(i & 3) * 4 + 2], o[i >> 2][(i & 3) * 4 + 3]};
+            ml[0] = m;
+            ml[64] = lsum;
+        }
+        __syncthreads();
+        if (half == 1) return;
+        const float m1 = ml[0], top = fmaxf(m, m1);
+        const float f0 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - top), f1 = m1 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m1 - top);
+        lsum = lsum * f0 + ml[64] * f1;
+#pragma unroll
+        for (int i = 0; i < DT / 8; ++i) {
+            const f32x4 x = part[i * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[i >> 2][(i & 3) * 4 + e] = o[i >> 2][(i & 3) * 4 + e] * f0 + x[e] * f1;
+        }
+    }
     lsum += __shfl_xor(lsum, 32);
     const float inv = 1.0f / lsum;
     constexpr int kChunks = DT / 8;                 // 16-byte pieces of a row
@@ -296,7 +324,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, De
             for (int i = 0; i < 16; ++i) trouble = general::trouble_of(o[mb][i], trouble);
         again = __builtin_amdgcn_ballot_w64(n < cols_w && !(trouble == 0.f));
     }
-    unsigned char* ob = lds + w * (32 * DT * 2);    // this wave's [32 columns][DT ch] bf16, rows XOR-swizzled
+    unsigned char* ob = lds + w * (32 * DT * 2 * kHalves);      // (where this wave read its sums)  this wave's [32 columns][DT ch] bf16, rows XOR-swizzled
 #pragma unroll
     for (int mb = 0; mb < DT / 32; ++mb)
 #pragma unroll
@@ -327,6 +355,15 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, De
         general::attend_rows_again<__bf16, 4, DT / 64>(a, again, (int64_t)base_row + (unsigned)my_row, qpos, s, g, reinterpret_cast<float*>(ob));
     }
 }
+
+template <int NW, int DT, bool kLo, bool kPage16>
+__global__ __launch_bounds__(64 * NW, 2) void prefill_mfma_kernel(AttnArgs a, Deal deal) { attend_tile<NW, DT, kLo, kPage16, 1>(a, deal); }
+
+// Few workgroups on long contexts: a launch is as long as its longest chain of key tiles, one wave a SIMD.  Here two sets of four
+// waves take every other tile of the same 128 columns, with key and value stages of their own, and their sums meet in LDS at the
+// end; a CU holds one such workgroup instead of two.  Which batches: launch_tiles().
+template <int DT, bool kLo, bool kPage16>
+__global__ __launch_bounds__(512, 2) void prefill_halves_kernel(AttnArgs a, Deal deal) { attend_tile<4, DT, kLo, kPage16, 2>(a, deal); }
 
 }  // namespace
 
@@ -379,6 +416,21 @@ static ag_status launch_prefill_nw(const AttnArgs& a, hipStream_t st)
     return hip_check(hipGetLastError(), "prefill launch");
 }
 
+template <int DT, bool kLo, bool kPage16>
+static ag_status launch_prefill_halves(const AttnArgs& a, hipStream_t st)
+{
+    constexpr int lds = 2 * lds_bytes(4, DT);
+    static std::atomic<uint64_t> told{0};
+    ag_status e = allow_dynamic_lds((const void*)prefill_halves_kernel<DT, kLo, kPage16>, lds, told);
+    if (e) return e;
+    if (a.c.hkv * tiles_bound(a, 128) + 8 > 0x7fffffff) { set_error("too many query tiles for one launch"); return AG_ERR_INVALID_ARG; }
+    const Deal deal = deal_of(a, tiles_bound(a, 128), stream_cus(st) / 8);
+    prof_before(st);
+    hipLaunchKernelGGL((prefill_halves_kernel<DT, kLo, kPage16>), dim3((unsigned)workgroups_of(deal)), dim3(512), lds, st, a, deal);
+    prof_after(st);
+    return hip_check(hipGetLastError(), "prefill launch");
+}
+
 // lo: weights in 32 bits (see kLo)
 static ag_status launch_tiles(const AttnArgs& a, bool lo, hipStream_t st)
 {
@@ -405,6 +457,16 @@ static ag_status launch_tiles(const AttnArgs& a, bool lo, hipStream_t st)
     const bool alike = !ragged && (lo ? 3 * rows <= ctx || (10 * large > 7 * cus && 5 * rows <= 4 * ctx) : 5 * rows <= 2 * ctx);
     const bool pays = large <= cus ? a.max_ctx <= 1536 || alike : a.max_ctx > 1536 && 4 * large >= (lo || ragged ? 10 : 7) * cus;
     const bool big = a.max_new >= 512 && 8 * large >= 5 * cus && pays;
+    // Two sets of waves (prefill_halves_kernel) while every CU has one workgroup of 128 columns at most; on short contexts the
+    // larger start and the sums' exchange cost more than half of a chain, and beyond one a CU a second one waits for the first where it
+    // ran beside it.  Graph replay, append included, 128 columns -> this, us (128 columns a CU): ten chunks of 8..372 rows on 345..3355
+    // at 16 / 1 heads (1) 84 -> 58, five of 7..495 on 507..6532 at 16 / 2 (0.65) 127 -> 102, five of 141..690 on 385..6190 at 8 / 2 (0.55) 119
+    // -> 98, four of 131..302 on 476..2926 (0.97) 44 -> 40, one prompt of 1700 (0.96) 35 -> 32, four at 16 / 1 of up to 664 rows on 500, 30.5
+    // -> 28.8, two prompts of 424 on pages of 64 (0.85) 23.9 -> 24.1; but 13 prompts of 57..180 at 16 / 1 (0.8) 14.3 -> 16.1, five of 223..342 at
+    // 16 / 2 (0.73) 16.2 -> 17.5, 31 chunks of 26..110 on 765..948 at 16 / 1 (1.04) 38.8 -> 47.4, five of 46..532 on 1187..3571 (1.2) 87 -> 92 (but 26
+    // of about 300 on 130..3153 at 4 / 4, pages of 32 (1.35) 137 -> 100), nine prompts of 400 (1.7) 24.0 -> 30.5.
+    const bool halves = !big && a.max_ctx >= 512 && a.c.hkv * tiles_bound(a, 128) <= cus;
+    if (halves) return !lo ? launch_prefill_halves<128, false, true>(a, st) : a.c.d == 128 ? launch_prefill_halves<128, true, false>(a, st) : launch_prefill_halves<64, true, false>(a, st);
     if (!lo) return big ? launch_prefill_nw<8, 128, false, true>(a, st) : launch_prefill_nw<4, 128, false, true>(a, st);
     if (a.c.d == 128) return big ? launch_prefill_nw<8, 128, true, false>(a, st) : launch_prefill_nw<4, 128, true, false>(a, st);
     return launch_prefill_nw<4, 64, true, false>(a, st);

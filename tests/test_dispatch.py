@@ -97,3 +97,12 @@ def test_queue_of_few_heads_and_more_than_one_workgroup_a_cu(tmp):
     for (hkv, cus, ctx), name in [((8, 256, 3700), EXACT), ((2, 64, 3700), MERGED), ((2, 64, 2100), EXACT), ((2, 256, 2900), EXACT)]:
         c = queue(([ctx] * 12 + [900] * 6, [36] * 12 + [1] * 6), 4 * hkv, hkv, cus=cus)
         assert kernels(tmp, c)[0][0].startswith(name), (hkv, cus, ctx)
+
+
+@pytest.mark.parametrize("halves,batches", [
+    (True, [dict(batch=1, prefix=2000, new=700), dict(batch=1, prefix=2000, new=900, page=32), dict(batch=1, prefix=4000, new=900, d=64), dict(batch=4, new=600, **H82)]),
+    (False, [dict(batch=2, prefix=2000, new=700), dict(batch=1, new=480), dict(batch=1, prefix=6000, new=300), dict(batch=8, new=4096)]),
+])
+def test_two_sets_of_waves_in_a_prefill_workgroup(tmp, halves, batches):
+    for b, k in zip(batches, kernels(tmp, *(dict(call="resume", **b) for b in batches))):
+        assert len(k) == 1 and k[0].startswith("prefill_halves_kernel") == halves, (b, k)
