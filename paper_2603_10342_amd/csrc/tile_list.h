@@ -48,10 +48,11 @@ inline int64_t workgroups_of(const Deal& d)
 __device__ __forceinline__ bool place_of(const Deal& d, int hkv, int& g, int& j)
 {
     const unsigned xcd = blockIdx.x & 7, ord = blockIdx.x >> 3, run = (unsigned)d.run;
-    const unsigned before = ord < run ? 0 : ord / run;                          // runs this XCD has taken
+    unsigned before = 0, head = 0;              // runs this XCD has taken; divisions only where they are needed
+    if (ord >= run) before = ord / run;
     const unsigned k = ((before << d.share) + (xcd & ((1u << d.share) - 1)) - before) * run + ord;
     if (k >= (unsigned)d.items) return false;
-    const unsigned head = k / (unsigned)d.tiles_max;
+    if (k >= (unsigned)d.tiles_max) head = k / (unsigned)d.tiles_max;
     g = (int)(xcd >> d.share) * (hkv >> (3 - d.share)) + (int)head;
     j = (int)(k - head * (unsigned)d.tiles_max);
     return true;
