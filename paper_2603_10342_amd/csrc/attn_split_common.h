@@ -226,7 +226,7 @@ __device__ __forceinline__ bool find_share(const int32_t* __restrict__ ctx_lens,
 // workgroup reads alone must be short, and every pair must have a CU to itself.  416 KiB (832 tokens of bf16 / 128) is where
 // that turns for few pairs; with more than half of the CUs busy either way, shares are hardly finer, and 1 MiB.
 // Measured over 150 drawn batches at 256 CUs, ag_decode_step and ag_attn_decode with the append, graph replay, shares / one
-// workgroup: up to 128 pairs, 200 to 300 KiB 1.29 (0.94 to 1.66), to 416 KiB 1.12 (0.79 to 1.47), to 480 KiB 1.05 (0.91 to
+// workgroup (shares before a wave waited for its partials, which costs them about 0.3 us): up to 128 pairs, 200 to 300 KiB 1.29 (0.94 to 1.66), to 416 KiB 1.12 (0.79 to 1.47), to 480 KiB 1.05 (0.91 to
 // 1.48), beyond 0.92; more pairs, to 1 MiB 1.18 (1.11 to 1.44), beyond 1.03 (0.83 to 1.12).  Shares come off best where their 256
 // tokens end with the contexts (one session of 1000 tokens, 32 / 8 heads, 7.1 against 8.3 us; of 850 9.1 against 7.0, of 400 9.2
 // against 5.1; 16 of 700 15.6 against 11.0).  (The other shapes have a line of their own, one_workgroup_a_pair() in
