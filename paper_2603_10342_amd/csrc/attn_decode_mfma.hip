@@ -185,9 +185,12 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& 
         // s1[i]: token tokb + i, s2[i]: token tokb + 8 + i, of head r
         const int tokb = tok0 + (c >> 1) * PS + (c & 1) * 4;
         const int keep = ctx - tokb;     // token tokb + j exists iff j < keep
+        // Rounded before the maximum is taken off (the compiler would make one operation of the two, but not in a wave's last
+        // step): equal scores have equal weights wherever they stand, and the maximum's is 1.
         float xs[8];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
+#pragma clang fp contract(off)
             xs[i] = !kLast || i < keep ? s1[i] * sl2 : -INFINITY;
             xs[4 + i] = !kLast || 8 + i < keep ? s2[i] * sl2 : -INFINITY;
         }
