@@ -14,7 +14,7 @@
 // the context) the CUs that drew long parts ran up to 45 % over the mean and the step took 112 us where the
 // bytes need 95.  Instead, the (session, KV head) pairs are laid end to end in units of one wave step
 // (32 tokens, two pages), F steps in all, and workgroup w of W takes steps [w q, (w + 1) q) with
-// q = max(8, ceil(F / W)): every workgroup, hence every CU, moves the same number of bytes.  A workgroup's
+// q = max(8, ceil(F / W)), at most 128: every workgroup, hence every CU, moves the same number of bytes.  A workgroup's
 // share covers one pair or the end of one and the start of the next (a "segment" each); every workgroup
 // derives the plan itself from the context lengths (a sum and a scan over the batch: the lengths live on
 // the device, and a planning launch ahead of this one would cost more than it saves).
@@ -163,8 +163,7 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& 
     // One step; unless it is the wave's last, the next step's keys are requested as soon as the score products have taken
     // this one's, and its values as soon as the second product has: half a step of every wave is always in flight, in the
     // registers of one.  A read of such pages alone takes 173 us for 1183 MB this way and 182 with 16 loads that are waited
-    // for together (6.8 and 6.5 TB/s).  64 sessions of 1024..8192 tokens, one launch: 201.5 -> 195 us (1181 MB; 512
-    // workgroups instead of 1024 are part of it: page ids are scalar loads a step ahead, so that a share may be of any length).
+    // for together (6.8 and 6.5 TB/s).  64 sessions of 1024..8192 tokens, one launch: 201.5 -> 197 us (1181 MB).
     // Only a wave's last step can reach behind the context.
     auto step = [&](int st, auto last_c) {
         constexpr bool kLast = decltype(last_c)::value;
@@ -236,10 +235,8 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& 
 // read that page does it, and waits for its own stores before it loads the page - and the workgroup that is
 // last to finish a pair's segments (an atomic count per pair) merges them, in segment order whoever comes last,
 // so the result does not depend on timing; a pair that lies inside one share is normalised and written directly.
-constexpr int kWorkgroupsPerCu = 2;     // four measured 1.5 % slower: each pays the plan, and each segment a read of page ids
-
 template <bool kStep>
-__global__ __launch_bounds__(256, kWorkgroupsPerCu) void decode_split_kernel(AttnArgs a, int32_t* __restrict__ hdr,
+__global__ __launch_bounds__(256, 2) void decode_split_kernel(AttnArgs a, int32_t* __restrict__ hdr,
                                                               float* __restrict__ ws_o, float* __restrict__ ws_ml,
                                                               int pmax, StepArgs sa)
 {
@@ -493,9 +490,12 @@ int stream_cus(hipStream_t st)
     return n > 0 && n <= all ? n : all;
 }
 
-// Workgroups of a launch of the other shapes (attn_decode_any.hip): the shares are equal, so what matters is that every CU
-// gets the same number of them, and as few as the longest share (kMaxSteps: a lane holds a page id) allows: each workgroup pays
-// the plan and each segment a dependent page-id read (a grid that leaves some CUs one workgroup short loses 4-5 %).
+// Workgroups of a launch: the shares are equal, so what matters is that every CU gets the same number of them, and as few as the
+// longest share (kMaxSteps) allows: each workgroup pays the plan and each segment a read of page ids (two per CU measured 1.5 %
+// faster than four, and a grid that leaves some CUs one workgroup short loses 4-5 %).  At most kMaxSteps: in attn_decode_any.hip a lane
+// holds a page id; here the largest weight of a wave's part is 1 and loses nothing in rounding, and longer parts have fewer of
+// them.  64 sessions of 1024..8192 tokens in two workgroups a CU whatever their shares, in this many: 194 / 197 us (1 to 4 % over 15
+// batches of long contexts), error against 64 bits 2.185e-3 / 2.168e-3.
 int share_workgroups(int64_t f_max, hipStream_t st)
 {
     const int64_t unit = 2 * (int64_t)stream_cus(st);
@@ -563,10 +563,12 @@ ag_status launch_decode_mfma(const AttnArgs& a, void* ws, hipStream_t st)
     int32_t* hdr = (int32_t*)ws;
     float* ws_o = (float*)(hdr + header_ints(a.batch));
     float* ws_ml = ws_o + (size_t)a.batch * a.hq * pmax * D;
+    // Upper bound of the step count from the host-known bounds; the grid is sized so that a share is at most
+    // kMaxSteps steps even if every session is max_ctx long.
     const int64_t f_max = (int64_t)a.c.hkv * a.batch * ((a.max_ctx + 31) / 32);
     if (f_max > (1 << 30)) { set_error("decode batch of %lld steps of 32 tokens is beyond one launch", (long long)f_max); return AG_ERR_INVALID_ARG; }
     if (a.max_ctx > 0) {
-        const int grid = kWorkgroupsPerCu * stream_cus(st);
+        const int grid = share_workgroups(f_max, st);
         // the event bracket covers both kernels of the call: the merge kernel writes the output the byte count includes
         prof_before(st);
         hipLaunchKernelGGL(decode_split_kernel<false>, dim3(grid), dim3(256), 0, st, a, hdr, ws_o, ws_ml, pmax, StepArgs{});
@@ -605,7 +607,7 @@ ag_status launch_decode_step(const AttnArgs& a, const void* k_new, const void* v
     const int64_t f_max = (int64_t)a.c.hkv * a.batch * ((a.max_ctx + 31) / 32);
     if (f_max > (1 << 30)) { set_error("decode batch of %lld steps of 32 tokens is beyond one launch", (long long)f_max); return AG_ERR_INVALID_ARG; }
     if (takes_direct(a, st)) return launch_direct<true>(a, StepArgs{(const __bf16*)k_new, (const __bf16*)v_new, counters}, st);
-    const int grid = kWorkgroupsPerCu * stream_cus(st);
+    const int grid = share_workgroups(std::max<int64_t>(f_max, 1), st);
     prof_before(st);
     hipLaunchKernelGGL(decode_split_kernel<true>, dim3(grid), dim3(256), 0, st, a, hdr, ws_o, ws_ml, pmax,
                        StepArgs{(const __bf16*)k_new, (const __bf16*)v_new, counters});

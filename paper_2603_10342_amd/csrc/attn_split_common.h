@@ -156,7 +156,7 @@ constexpr int kMinSplit = 256;
 // Workgroup w of W takes steps [w q, (w + 1) q) of the batch's (session, KV head) contexts laid end to end, one step =
 // 32 tokens, q = max(kMinSteps, ceil(F / W)).
 constexpr int kMinSteps = kMinSplit / 32;      // a workgroup's share is at least this many steps (256 tokens)
-constexpr int kMaxSteps = 128;                 // attn_decode_any.hip: and at most this many (share_workgroups() sizes the grid for it)
+constexpr int kMaxSteps = 128;                 // and at most this many (share_workgroups() sizes the grid for it)
 
 __device__ __forceinline__ int steps_of(int ctx) { return ctx > 0 ? (ctx + 31) >> 5 : 0; }
 
@@ -188,7 +188,7 @@ __device__ __forceinline__ bool find_share(const int32_t* __restrict__ ctx_lens,
     const int F = heads * __builtin_amdgcn_readfirstlane(total);
     if (F == 0) return false;
     const int q = max(kMinSteps, (F + W - 1) / W);
-    const int f0 = wg * q;              // (F <= 2^30 by the launchers' checks: no overflow)
+    const int f0 = wg * q;              // q <= kMaxSteps by the launcher's choice of W: no overflow
     if (kPublish && wg == 0 && tid == 0) hdr[0] = q;
     if (f0 >= F) return false;          // uniform over the workgroup
     sh.q = q;

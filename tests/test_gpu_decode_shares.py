@@ -1,17 +1,19 @@
-"""bf16 / 128 / page 16 decode in shares: what a step's arithmetic promises, read from the workspace that the split kernel leaves
-behind."""
+"""bf16 / 128 / page 16 decode in shares: what a step's arithmetic and the cuts of the shares promise, read from the workspace that
+the split kernel leaves behind, and both forms of the step against the fp64 oracle in shares of up to 128 steps."""
 import numpy as np
 import pytest
 import torch
 
-from gpu_helpers import DevBatch, gpu_append, i32, make_cache
-from helpers import make_batch
+from gpu_helpers import DevBatch, check_close, gpu_append, i32, make_cache, to_dev, to_f64
+from helpers import fresh_pools, make_batch, oracle_append
+from oracle import oracle as O
 from paper_2603_10342_amd import binding as B
 from paper_2603_10342_amd import inputs as I
+from test_gpu_decode_step import both_ways, same_bits
 
 pytestmark = pytest.mark.gpu
 
-STEP, MIN_STEPS = 32, 8
+STEP, MIN_STEPS, MAX_STEPS = 32, 8, 128
 
 
 def split_workspace(batch, g, max_ctx):
@@ -41,3 +43,36 @@ def test_equal_scores_have_equal_weights():
     used = -(-ctx // (share * STEP))
     assert share == MIN_STEPS and np.abs(m[:, 0]).max() > 16           # half a unit in the last place there is 1e-6, ten times that of a weight
     assert np.array_equal(l[:, :used], np.broadcast_to(np.minimum(share * STEP, ctx - np.arange(used) * share * STEP), (16, used)).astype(np.float32))
+
+
+@pytest.mark.parametrize("lo,hi,bound", [(3000, 6000, 6000), (200, 400, 6000), (40, 4500, 16000)])
+def test_shares_of_at_most_128_steps_on_eight_cus(lo, hi, bound):
+    """Twelve sessions on eight CUs, more shares than two a CU; then contexts far below the bound."""
+    g = I.Geometry(8, 2, 128, 16, 6000, I.BF16)
+    c = I.make_decode(batch=12, lo=lo, hi=hi, num_pages=g.num_pages, geom=g, seed=82, sigma_qk=1.0, sigma_v=1.0)
+    bound = max(bound, int(c.ctx_lens.max()))
+    kp, vp = fresh_pools(g)
+    for b in (c.fill, c.step):
+        oracle_append(kp, vp, b)
+    ref = O.decode(kp, vp, g.dtype, c.step.q, c.block_tables, c.ctx_lens, g.num_q_heads, g.scale)
+    stream = B.ag_stream_create_cumask(B.ag_cumask_build(B.ag_device_info()["num_cus"], 8, 0, 1))
+    try:
+        c1, out1, c2, out2, _, _ = both_ways(g, c.fill, c.step, stream=stream)
+        check_close(to_f64(out1, g.dtype), ref, g.dtype, "step")
+        assert same_bits(out1, out2) and same_bits(c1.k_pool, c2.k_pool) and same_bits(c1.v_pool, c2.v_pool)
+        table = np.zeros((12, max(-(-bound // 16), c.block_tables.shape[1])), np.int32)
+        table[:, :c.block_tables.shape[1]] = c.block_tables
+        ws, _, _ = split_workspace(12, g, bound)
+        q, out = to_dev(c.step.q, g.dtype), torch.empty_like(out1)
+        torch.cuda.synchronize()
+        B.ag_attn_decode(c2, q, out, i32(table), i32(c.ctx_lens), bound, g.num_q_heads, g.scale, ws, stream=stream)
+        torch.cuda.synchronize()
+        check_close(to_f64(out, g.dtype), ref, g.dtype, "decode")
+        share = int(ws[:1].view(torch.int32)[0])
+    finally:
+        torch.cuda.synchronize()
+        B.ag_stream_destroy(stream)
+    steps = 2 * int(sum(-(-int(x) // STEP) for x in c.ctx_lens))
+    most = 2 * 12 * -(-bound // STEP)
+    shares = 16 * -(-most // (16 * MAX_STEPS))                         # two workgroups a CU, as many rounds of them as 128 steps ask for
+    assert share == max(MIN_STEPS, -(-steps // shares)) <= MAX_STEPS
