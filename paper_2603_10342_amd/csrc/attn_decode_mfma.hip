@@ -70,6 +70,9 @@ __device__ __forceinline__ void stores_performed() { asm volatile("s_waitcnt vmc
 // One wave's part of a segment - steps my_u .. my_u + my_n - 1 of pair (s, g), whose context has ctx tokens: the running
 // maximum, the running sum (this lane's share) and O^T of the pair's heads.  appends: this wave's last step is the pair's
 // last, and it writes the step's token first.
+// kOwnMax: a step's weights stand against the step's own maximum, whose weight is then 1 and loses nothing in rounding, instead of
+// against the running one.
+template <bool kOwnMax>
 __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& sa, bool appends, int s, int g, int G, int ctx,
                                              int my_u, int my_n, int lane, float& m, float& lsum, f32x4 (&o)[8])
 {
@@ -198,15 +201,17 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& 
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         const float m_new = fmaxf(m, mx);          // finite: token tok0 exists
         const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+        const float m_ref = kOwnMax ? fmaxf(mx, -3e38f) : m_new;          // (scores of -inf: weights of zero)
+        const float beta = kOwnMax ? __builtin_amdgcn_exp2f(m_ref - m_new) : 1.f;
         float psum = 0.f;
         bf16x8 pb;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float p = __builtin_amdgcn_exp2f(xs[e] - m_new);
+            const float p = __builtin_amdgcn_exp2f(xs[e] - m_ref);
             psum += p;
             pb[e] = (__bf16)p;
         }
-        lsum = lsum * alpha + psum;
+        lsum = lsum * alpha + (kOwnMax ? psum * beta : psum);
         m = m_new;
         if (kLast && tok0 + 32 > ctx) {  // last, partial step: unwritten slots may hold anything, NaN included
 #pragma unroll
@@ -215,7 +220,10 @@ __device__ __forceinline__ void attend_steps(const AttnArgs& a, const StepArgs& 
 #pragma unroll
         for (int mb = 0; mb < 8; ++mb) {
             o[mb] *= alpha;
-            o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.v[mb], pb, o[mb], 0, 0, 0);
+            if constexpr (kOwnMax)
+                o[mb] += beta * __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.v[mb], pb, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            else
+                o[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.v[mb], pb, o[mb], 0, 0, 0);
         }
         if constexpr (!kLast) {
             __builtin_amdgcn_sched_barrier(0);
@@ -276,7 +284,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_kernel(AttnArgs a, int32_
         const bool appends = kStep && u + k == n && w == (k - 1) / per;        // uniform over the wave
         float m, lsum;
         f32x4 o[8];
-        attend_steps(a, sa, appends, s, g, G, ctx, my_u, my_n, lane, m, lsum, o);
+        attend_steps<false>(a, sa, appends, s, g, G, ctx, my_u, my_n, lane, m, lsum, o);
         lsum += __shfl_xor(lsum, 16);
         lsum += __shfl_xor(lsum, 32);
 
@@ -371,8 +379,10 @@ __global__ __launch_bounds__(256, 2) void decode_split_kernel(AttnArgs a, int32_
 // A batch of few, short contexts: one workgroup of 8 waves per (session, KV head) pair, which shares the pair's steps
 // and writes the result itself - no plan, no partials, no merge (whose dependent round trips are most of a small step:
 // see direct_preferred()).  The waves' results meet in LDS, of which a launch takes what its group size needs.
-// (16 waves of 128 registers, all loads of a step waited for together: 32 sessions of 400 tokens, 32 / 8 heads, 11.8 us instead of
-// 10.8; 4 of 300 6.3 instead of 5.75.)
+// (16 waves of 128 registers, all loads of a step waited for together: 32 sessions of 400 tokens, 32 / 8 heads, 11.9 us instead of
+// 11.0; 4 of 300 6.25 instead of 5.54.)  With half the waves a part is twice as long; weights against each step's own maximum keep
+// the error against 64 bits where that had it (2.00e-3 to 2.06e-3 over 14 batches, 0.98 to 1.0 of it; against the running one 1.01 to 1.023), for
+// about 0.1 us (5.43 -> 5.54, 10.98 -> 11.03).
 constexpr int kDirectWaves = 8;
 constexpr int kDirectMaxTokens = 16 << 10;
 inline size_t direct_lds(int G) { return (size_t)kDirectWaves * G * (D + 2) * sizeof(float); }
@@ -395,7 +405,7 @@ __global__ __launch_bounds__(64 * kDirectWaves, 2) void decode_direct_kernel(Att
     const int my_u = w * per, my_n = max(0, min(per, n - my_u));
     float m, lsum;
     f32x4 o[8];
-    attend_steps(a, sa, kStep && w == (n - 1) / per, s, g, G, ctx, my_u, my_n, lane, m, lsum, o);
+    attend_steps<true>(a, sa, kStep && w == (n - 1) / per, s, g, G, ctx, my_u, my_n, lane, m, lsum, o);
     lsum += __shfl_xor(lsum, 16);
     lsum += __shfl_xor(lsum, 32);
     const int r = lane & 15, c = lane >> 4;

@@ -9,7 +9,7 @@ from helpers import fresh_pools, make_batch, oracle_append
 from oracle import oracle as O
 from paper_2603_10342_amd import binding as B
 from paper_2603_10342_amd import inputs as I
-from test_gpu_decode_step import both_ways, same_bits
+from test_gpu_decode_step import both_ways, same_bits, step_workspace
 
 pytestmark = pytest.mark.gpu
 
@@ -76,3 +76,36 @@ def test_shares_of_at_most_128_steps_on_eight_cus(lo, hi, bound):
     most = 2 * 12 * -(-bound // STEP)
     shares = 16 * -(-most // (16 * MAX_STEPS))                         # two workgroups a CU, as many rounds of them as 128 steps ask for
     assert share == max(MIN_STEPS, -(-steps // shares)) <= MAX_STEPS
+
+
+@pytest.mark.parametrize("step", [True, False])
+@pytest.mark.parametrize("ctx", [100, 256, 500, 512])
+def test_one_workgroup_a_pair_rounds_no_step_s_largest_weight(ctx, step):
+    """One key of every 32 counts, the odd steps' at exp(-0.2): a weight against its step's own maximum is 1 and exact.  Values of 1
+    and of about -exp(0.2) leave a result near the rounding of such a weight to bf16, 2^-9, so that one that is rounded shows."""
+    g = I.Geometry(16, 1, 128, 16, 40, I.BF16)
+    low, value = I.stored_to_f64(I.store(np.array([-0.2, -1.22], np.float32), I.BF16), I.BF16)
+    fill = make_batch(g, [0], [ctx], seed=83, sigma_qk=1.0, sigma_v=1.0)
+    k, v, q = np.zeros((ctx, 1, 128), np.float32), np.ones((ctx, 1, 128), np.float32), np.zeros((ctx, 16, 128), np.float32)
+    k[:, 0, 0] = -200
+    k[7::64, 0, 0] = 0
+    k[39::64, 0, 0] = low
+    v[32:] = np.where(np.arange(32, ctx) // 32 % 2 == 1, value, 1)[:, None, None]
+    q[:, :, 0] = 1
+    fill = make_batch(g, [0], [ctx], seed=83, k=k, v=v, q=q)
+    even, odd = len(range(7, ctx, 64)), len(range(39, ctx, 64))
+    want = (even + odd * value * np.exp(low)) / (even + odd * np.exp(low))
+    df = DevBatch(fill)
+    cache = make_cache(g)
+    qn = df.q[-1:].contiguous()
+    out = torch.empty_like(qn)
+    gpu_append(cache, df)
+    if step:
+        ws, _ = step_workspace(1, g, ctx)
+        B.ag_decode_step(cache, df.k_new[-1:].contiguous(), df.v_new[-1:].contiguous(), qn, out, df.bt, i32([ctx]), ctx, 16, 1.0, ws)
+    else:
+        B.ag_attn_decode(cache, qn, out, df.bt, i32([ctx]), ctx, 16, 1.0, split_workspace(1, g, ctx)[0])
+    torch.cuda.synchronize()
+    got = to_f64(out, g.dtype)
+    # the result's own rounding, and sums in fp32 of up to 16 numbers of 1 that cancel to it
+    assert np.all(np.abs(got - want) <= 2.0 ** -9 * abs(want) + 16 * 2.0 ** -24 * 1.22), (got.reshape(-1)[:4], want)
