@@ -222,18 +222,19 @@ __device__ __forceinline__ bool find_share(const int32_t* __restrict__ ctx_lens,
 
 // Whether a decode batch of `pairs` (session, KV head) pairs, each with at most `bytes` of keys and values, takes one
 // workgroup per pair and no merge instead of equal shares.  A step of a small batch is a chain of memory round trips, and
-// the plan, the partials and their merge are most of them; but a CU draws no more than about 57 GB/s, so a pair that one
-// workgroup reads alone must be short, and every pair must have a CU to itself.  416 KiB (832 tokens of bf16 / 128) is where
-// that turns for few pairs; with more than half of the CUs busy either way, shares are hardly finer, and 1 MiB.
-// Measured over 150 drawn batches at 256 CUs, ag_decode_step and ag_attn_decode with the append, graph replay, shares / one
-// workgroup (shares before a wave waited for its partials, which costs them about 0.3 us): up to 128 pairs, 200 to 300 KiB 1.29 (0.94 to 1.66), to 416 KiB 1.12 (0.79 to 1.47), to 480 KiB 1.05 (0.91 to
-// 1.48), beyond 0.92; more pairs, to 1 MiB 1.18 (1.11 to 1.44), beyond 1.03 (0.83 to 1.12).  Shares come off best where their 256
-// tokens end with the contexts (one session of 1000 tokens, 32 / 8 heads, 7.1 against 8.3 us; of 850 9.1 against 7.0, of 400 9.2
-// against 5.1; 16 of 700 15.6 against 11.0).  (The other shapes have a line of their own, one_workgroup_a_pair() in
-// attn_decode_any.hip.)
+// the plan, the partials and their merge are most of them; but beyond 256 KiB a workgroup alone takes 4 to 5 us for every further 256
+// KiB, so the longest pair must be short (the host knows no other length), and every pair must have a CU to itself.  416 KiB (832
+// tokens of bf16 / 128) is where that turns for few pairs; with more than half of the CUs busy either way, shares are hardly
+// finer, and 512 KiB.
+// Shares / one workgroup at 256 CUs, graph replay, ag_decode_step and ag_attn_decode with the append.  320 batches of 16 to 256 pairs
+// and up to the line, alike, unlike or one session long among short ones: 0.97 to 2.05 up to 832 tokens, 0.88 to 1.53 at 1024 with more
+// than 128 pairs (the worst with 200 tokens beside: 17 sessions, 8 KV heads, 11.3 us against 12.9; all of 1024 tokens 19.1 against 15.5).
+// Beyond, sessions that are alike still gain, 1.10 to 1.23 up to 1 MiB, but one of 1280, 1536, 2048 tokens among others of 64 or 200 loses:
+// 0.76 to 1.06, 0.66 to 0.93, 0.54 to 0.74.  Few pairs at 1024 tokens: 0.67 to 1.55.  Shares come off best where their 256 tokens
+// end with the contexts.  (The other shapes have a line of their own, one_workgroup_a_pair() in attn_decode_any.hip.)
 inline bool direct_preferred(int64_t pairs, int64_t bytes, int cus)
 {
-    return pairs <= cus && bytes <= (2 * pairs > cus ? 1024 << 10 : 416 << 10);
+    return pairs <= cus && bytes <= (2 * pairs > cus ? 512 << 10 : 416 << 10);
 }
 
 }  // namespace splitk

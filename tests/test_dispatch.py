@@ -64,6 +64,19 @@ def test_decode_one_workgroup_a_pair_or_shares(tmp, alone, batches):
         assert [x.split("<")[0] for x in k] == (["decode_any_direct_kernel"] if alone else ["decode_any_split_kernel", "decode_any_merge_kernel"]), b
 
 
+@pytest.mark.parametrize("alone,batches", [
+    (True, [dict(batch=1, max_ctx=832), dict(batch=16, max_ctx=832), dict(batch=17, max_ctx=1024), dict(batch=32, max_ctx=1024), dict(batch=6, max_ctx=1024, hq=8, hkv=1, cus=8)]),
+    (False, [dict(batch=1, max_ctx=833), dict(batch=16, max_ctx=833), dict(batch=17, max_ctx=1025), dict(batch=33, max_ctx=100), dict(batch=20, max_ctx=2048),
+             dict(batch=6, max_ctx=1025, hq=8, hkv=1, cus=8), dict(batch=9, max_ctx=100, hq=8, hkv=1, cus=8)]),
+])
+def test_decode_and_step_of_the_main_shape(tmp, alone, batches):
+    """One line for both, with more than half of the CUs busy and with fewer: their results are the same bits."""
+    for b, k in zip(batches, kernels(tmp, *(dict(call="decode", **b) for b in batches))):
+        assert [x.split("<")[0] for x in k] == (["decode_direct_kernel"] if alone else ["decode_split_kernel", "decode_merge_kernel"]), b
+    for b, k in zip(batches, kernels(tmp, *(dict(call="step", **b) for b in batches))):
+        assert [x.split("<")[0] for x in k] == ["decode_direct_kernel" if alone else "decode_split_kernel"], b
+
+
 def queue(sessions, hq=8, hkv=2, **more):
     prefix, new = sessions
     return dict(call="merged", hq=hq, hkv=hkv, batch=len(new), total=sum(new), max_new=max(new), max_ctx=max(p + n for p, n in zip(prefix, new)), **more)
