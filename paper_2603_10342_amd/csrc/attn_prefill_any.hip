@@ -354,7 +354,7 @@ ag_status launch_for_dim(const AttnArgs& a, hipStream_t st)
 bool prefill_any_supported(const AttnArgs& a)
 {
     return a.c.ps >= 16 && (((uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 == 0) &&
-           a.c.hkv * tiles_bound(a) + 8 <= 0x7fffffff && (int64_t)a.total_rows * (a.hq / a.c.hkv) <= 0x7fffffff;
+           a.c.hkv * tiles_bound(a) + kDealtPast <= 0x7fffffff && (int64_t)a.total_rows * (a.hq / a.c.hkv) <= 0x7fffffff;
 }
 
 ag_status launch_prefill_any(const AttnArgs& a, hipStream_t st)

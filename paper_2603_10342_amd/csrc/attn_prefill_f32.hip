@@ -484,7 +484,7 @@ bool prefill_f32_supported(const AttnArgs& a)
 {
     return a.c.dtype == AG_F32 && (a.c.d == 64 || a.c.d == 128) && a.c.ps >= 16 &&
            (((uintptr_t)a.q | (uintptr_t)a.out | (uintptr_t)a.c.k | (uintptr_t)a.c.v) % 16 == 0) &&
-           a.c.hkv * tiles_bound(a) + 8 <= 0x7fffffff && (int64_t)a.total_rows * (a.hq / a.c.hkv) <= 0x7fffffff;
+           a.c.hkv * tiles_bound(a) + kDealtPast <= 0x7fffffff && (int64_t)a.total_rows * (a.hq / a.c.hkv) <= 0x7fffffff;
 }
 
 ag_status launch_prefill_f32(const AttnArgs& a, hipStream_t st)

@@ -395,7 +395,7 @@ static int64_t tiles_bound(const AttnArgs& a, int cols)
 bool prefill_mfma_lo_supported(const AttnArgs& a)
 {
     return a.c.dtype == AG_BF16 && (a.c.d == 128 || (a.c.d == 64 && a.max_ctx > 2 * (int64_t)a.max_new)) && a.c.ps >= 16 && aligned16(a) &&
-           a.c.hkv * tiles_bound(a, 128) + 8 <= 0x7fffffff && (int64_t)a.total_rows * (a.hq / a.c.hkv) <= 0x7fffffff;
+           a.c.hkv * tiles_bound(a, 128) + kDealtPast <= 0x7fffffff && (int64_t)a.total_rows * (a.hq / a.c.hkv) <= 0x7fffffff;
 }
 
 template <int NW, int DT, bool kLo, bool kPage16>
@@ -407,7 +407,7 @@ static ag_status launch_prefill_nw(const AttnArgs& a, hipStream_t st)
         ag_status e = allow_dynamic_lds((const void*)prefill_mfma_kernel<NW, DT, kLo, kPage16>, lds, told);
         if (e) return e;
     }
-    if (a.c.hkv * tiles_bound(a, 32 * NW) + 8 > 0x7fffffff) { set_error("too many query tiles for one launch"); return AG_ERR_INVALID_ARG; }
+    if (a.c.hkv * tiles_bound(a, 32 * NW) + kDealtPast > 0x7fffffff) { set_error("too many query tiles for one launch"); return AG_ERR_INVALID_ARG; }
     const Deal deal = deal_of(a, tiles_bound(a, 32 * NW), stream_cus(st) * (8 / NW) / 8);
     prof_before(st);
     hipLaunchKernelGGL((prefill_mfma_kernel<NW, DT, kLo, kPage16>), dim3((unsigned)workgroups_of(deal)), dim3(64 * NW), lds, st, a,
@@ -423,7 +423,7 @@ static ag_status launch_prefill_halves(const AttnArgs& a, hipStream_t st)
     static std::atomic<uint64_t> told{0};
     ag_status e = allow_dynamic_lds((const void*)prefill_halves_kernel<DT, kLo, kPage16>, lds, told);
     if (e) return e;
-    if (a.c.hkv * tiles_bound(a, 128) + 8 > 0x7fffffff) { set_error("too many query tiles for one launch"); return AG_ERR_INVALID_ARG; }
+    if (a.c.hkv * tiles_bound(a, 128) + kDealtPast > 0x7fffffff) { set_error("too many query tiles for one launch"); return AG_ERR_INVALID_ARG; }
     const Deal deal = deal_of(a, tiles_bound(a, 128), stream_cus(st) / 8);
     prof_before(st);
     hipLaunchKernelGGL((prefill_halves_kernel<DT, kLo, kPage16>), dim3((unsigned)workgroups_of(deal)), dim3(512), lds, st, a, deal);

@@ -39,6 +39,8 @@ inline Deal deal_of(const AttnArgs& a, int64_t tiles_max, int at_once)
     const int64_t run = share == 0 || part <= at_once || even ? part : std::max<int64_t>(1, std::min({session, part / 8, (int64_t)4}));
     return Deal{(int)tiles_max, (int)items, share, (int)run};
 }
+// At most kDealtPast more than there are tiles: a last round of runs of four on eight XCDs, or of one on each.
+constexpr int kDealtPast = 32;
 inline int64_t workgroups_of(const Deal& d)
 {
     const int64_t round = (int64_t)d.run << d.share;

@@ -119,3 +119,14 @@ def test_queue_of_few_heads_and_more_than_one_workgroup_a_cu(tmp):
 def test_two_sets_of_waves_in_a_prefill_workgroup(tmp, halves, batches):
     for b, k in zip(batches, kernels(tmp, *(dict(call="resume", **b) for b in batches))):
         assert len(k) == 1 and k[0].startswith("prefill_halves_kernel") == halves, (b, k)
+
+
+@pytest.mark.parametrize("shape", [dict(d=128, page=32), dict(dtype="f32", d=64), dict(d=64), dict(d=64, page=32)])
+def test_a_grid_at_the_end_of_its_range(tmp, shape):
+    """105 KV heads of 20452225 tiles each, 22 short of 2^31 in all: dealt to the XCDs in runs of four they would be 2^31 workgroups,
+    one past what a launch may have, and the call is refused; with fewer sessions it is launched."""
+    call = dict(call="resume", hq=105, hkv=105, total=0x7fffffff, max_new=640, max_ctx=840, **shape)
+    with pytest.raises(AssertionError, match="too many rows"):
+        launched([dict(call, batch=4090445)], tmp)
+    (k,) = launched([dict(call, batch=4090440)], tmp)
+    assert k[0].startswith("prefill_") and int(k[0].rsplit(" ", 1)[1]) <= 0x7fffffff, k
