@@ -20,7 +20,8 @@
 // fp32 takes every number as three bf16 terms and a product as six of theirs, as attn_prefill_f32.hip does, with its care for small
 // numbers: a step's 128 products of 64 clocks at 128 channels are 96 of 32, beside some 900 vector instructions that split K, V and the
 // weights, one wave's behind the other's on a SIMD.  Queries are split once, into LDS.  At 128 channels V is requested when the scores
-// are there: a step ahead, 46 registers spill (1.26 times the fp32 products over 30 batches, 1.45 so).  us, fp32 products -> terms, graph
+// are there: a step ahead, 46 registers spill (1.26 times the fp32 products over 30 batches, 1.45 so); four spill as it is, one of them read
+// back in every step.  us, fp32 products -> terms, graph
 // replay, append included, 32 / 8 heads: 211 rows on 6000 tokens at 128 channels 232 -> 146, 5 rows 221 -> 122, 24 chunks of 20 on 400 75
 // -> 54; at 64 channels 125 -> 83, 118 -> 69 and 46 -> 35.  Error against 64 bits over 39 batches 0.46 to 0.80 of what it was.
 // The line to the other kernels is at prefill_split_preferred().
@@ -96,7 +97,7 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n = lane & 31, hi = lane >> 5;
+    int n = lane & 31, hi = lane >> 5;
     const int first_token = columns.token(0), last_token = columns.token(cols - 1);
     int token;
     const int64_t q_row = row_of(min(n, cols - 1), token);      // columns beyond the tile repeat the last one
@@ -330,68 +331,145 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
         __builtin_amdgcn_sched_barrier(0);
     }
 
+    // fp32: this wave's keys once more, with fp32 products, where a column's numbers leave the terms' range: a query channel or a result
+    // below 2^-100 (zeros aside), values above about 2^70, or what is not finite, which then goes on row by row.  5 rows on 6000 tokens
+    // at 32 / 8 heads, one channel of values of 1e-33, row by row -> so: 866 -> 194 us at 64 channels (ordinary values 69, fp32 products
+    // alone 118), 1990 -> 367 at 128 (123, 223); an infinite value 980 -> 992 and 2178 -> 2204.  A result of zero only has the values
+    // read again, for small ones: 69 -> 81, 123 -> 148.
+    auto attend_in_fp32 = [&] {
+        asm("" : "+v"(n), "+v"(hi));                         // (nothing is kept in registers for it across the loop above)
+        constexpr int kQRow = DT * 4 + 16, kPieces = DT / 4;    // Q in LDS, rows padded
+        for (int idx = tid; idx < kColumns * kPieces; idx += 64 * kWaves) {
+            const int c = idx / kPieces, p = idx - c * kPieces;
+            int t;
+            const int64_t r = row_of(min(c, cols - 1), t);
+            *reinterpret_cast<u32x4*>(lds + c * kQRow + p * 16) = *reinterpret_cast<const u32x4*>((const float*)a.q + r * DT + p * 4);
+        }
+        __syncthreads();
+        m = -INFINITY;
+        lsum = 0.f;
+#pragma unroll
+        for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[mb][e] = 0.f;
+        if (my_n > 0) fetch_ids(0);
+#pragma unroll 1
+        for (int i = 0; i < my_n; ++i) {
+            const int st = w + kWaves * i;
+            const Groups here = locate(i);
+            load_k(here);
+            load_v(here);
+            f32x16 sc;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) sc[e] = 0.f;
+#pragma unroll
+            for (int j = 0; j < kK; ++j) {
+                const f32x4 kf = __builtin_bit_cast(f32x4, kx[j]), q4 = *reinterpret_cast<const f32x4*>(lds + n * kQRow + j * 32 + hi * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], q4[e], sc, 0, 0, 0);
+            }
+            float mx = -INFINITY;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int key = st * kStep + (e >> 2) * 8 + hi * 4 + (e & 3);
+                sc[e] = key <= qpos ? sc[e] : -INFINITY;
+                mx = fmaxf(mx, sc[e]);
+            }
+            mx *= a.scale;
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m, mx), m_ref = m_new == -INFINITY ? 0.f : m_new, alpha = expf(m - m_ref);
+            hide_v(st);
+            float psum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                sc[e] = expf(fmaf(sc[e], a.scale, -m_ref));
+                psum += sc[e];
+            }
+            lsum = lsum * alpha + psum;
+            m = m_new;
+#pragma unroll
+            for (int mb = 0; mb < kMb; ++mb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) o[mb][e] *= alpha;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int mb = 0; mb < kMb; ++mb)
+                        o[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(f32x4, vx[j * kMb + mb])[e], sc[j * 4 + e], o[mb], 0, 0, 0);
+        }
+    };
+
     // ---- the waves' partials through LDS; o[mb][q4 * 4 + e] is O^T[channel mb * 32 + q4 * 8 + hi * 4 + e][column n] ----
-    lsum += __shfl_xor(lsum, 32);
-    if (kQInLds) __syncthreads();                               // Q has been read
     float* const s_o = reinterpret_cast<float*>(lds);           // [wave][column][o_row]
     float* const s_m = s_o + kWaves * kColumns * kORow;
     float* const s_l = s_m + kWaves * kColumns;
-#pragma unroll
-    for (int mb = 0; mb < kMb; ++mb)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            const f32x4 x = {o[mb][q4 * 4], o[mb][q4 * 4 + 1], o[mb][q4 * 4 + 2], o[mb][q4 * 4 + 3]};
-            *reinterpret_cast<f32x4*>(s_o + (w * kColumns + n) * kORow + mb * 32 + q4 * 8 + hi * 4) = x;
-        }
     uint32_t* const s_again = reinterpret_cast<uint32_t*>(s_l + kWaves * kColumns);       // bit c: column c is not finite (fp32: or too small); [1]: has a zero; [2]: small values
-    if (hi == 0) { s_m[w * kColumns + n] = m; s_l[w * kColumns + n] = lsum; }
-    if (kTakeAgain && tid < 3) s_again[tid] = 0;
-    __syncthreads();
-    for (int idx = tid; idx < cols * (DT / 8); idx += 64 * kWaves) {
-        const int c = idx / (DT / 8), d = (idx - c * (DT / 8)) * 8;
-        float ms = s_m[c];                                      // wave 0 has the first keys, which every column sees
+    auto put_partials = [&] {
+        lsum += __shfl_xor(lsum, 32);
+        if (kQInLds) __syncthreads();                           // Q has been read
 #pragma unroll
-        for (int ww = 1; ww < kWaves; ++ww) ms = fmaxf(ms, s_m[ww * kColumns + c]);
-        float l = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int mb = 0; mb < kMb; ++mb)
 #pragma unroll
-        for (int ww = 0; ww < kWaves; ++ww) {
-            const float f = __builtin_amdgcn_exp2f(s_m[ww * kColumns + c] - ms);       // a wave that saw no key has m = -inf -> 0
-            l += f * s_l[ww * kColumns + c];
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const f32x4 x = {o[mb][q4 * 4], o[mb][q4 * 4 + 1], o[mb][q4 * 4 + 2], o[mb][q4 * 4 + 3]};
+                *reinterpret_cast<f32x4*>(s_o + (w * kColumns + n) * kORow + mb * 32 + q4 * 8 + hi * 4) = x;
+            }
+        if (hi == 0) { s_m[w * kColumns + n] = m; s_l[w * kColumns + n] = lsum; }
+        if (kTakeAgain && tid < 3) s_again[tid] = 0;
+        __syncthreads();
+    };
+    // Channels d .. d + 7 of columns of `which`: merged, stored, and handed to use() before they are normalised.
+    auto merge = [&](uint32_t which, auto power, auto use) {
+        for (int idx = tid; idx < cols * (DT / 8); idx += 64 * kWaves) {
+            const int c = idx / (DT / 8), d = (idx - c * (DT / 8)) * 8;
+            if (!(which >> c & 1)) continue;
+            float ms = s_m[c];                                  // wave 0 has the first keys, which every column sees
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] += f * s_o[(ww * kColumns + c) * kORow + d + e];
-        }
-        const float inv = 1.0f / l;
-        int t;
-        E* out = (E*)a.out + row_of(c, t) * DT + d;
-        E y[8];
+            for (int ww = 1; ww < kWaves; ++ww) ms = fmaxf(ms, s_m[ww * kColumns + c]);
+            float l = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) y[e] = (E)(acc[e] * inv);
+            for (int ww = 0; ww < kWaves; ++ww) {
+                const float f = power(s_m[ww * kColumns + c] - ms);       // a wave that saw no key has m = -inf -> 0
+                l += f * s_l[ww * kColumns + c];
 #pragma unroll
-        for (int e = 0; e < (int)sizeof(E) / 2; ++e) reinterpret_cast<u32x4*>(out)[e] = reinterpret_cast<const u32x4*>(y)[e];
-        if constexpr (kTakeAgain) {
+                for (int e = 0; e < 8; ++e) acc[e] += f * s_o[(ww * kColumns + c) * kORow + d + e];
+            }
+            const float inv = 1.0f / l;
+            int t;
+            E* out = (E*)a.out + row_of(c, t) * DT + d;
+            E y[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) y[e] = (E)(acc[e] * inv);
+#pragma unroll
+            for (int e = 0; e < (int)sizeof(E) / 2; ++e) reinterpret_cast<u32x4*>(out)[e] = reinterpret_cast<const u32x4*>(y)[e];
             float trouble = general::trouble_of(inv);
 #pragma unroll
             for (int e = 0; e < 8; ++e) trouble = general::trouble_of(acc[e], trouble);
-            bool again = !(trouble == 0.f);
-            if constexpr (!kBf16) {                             // (as in attn_prefill_f32.hip)
-                Least least;
-                bool zero = false;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    least.take(acc[e]);
-                    zero |= acc[e] == 0.f;
-                }
-                again |= least.small(inv);
-                if (d == 0) {
-                    Least least_q;
-                    least_q.u = s_least[c];
-                    again |= least_q.small() || __builtin_bit_cast(float, s_most[c]) * a.scale > kLargeQuery;
-                }
-                if (zero) atomicOr(s_again + 1, 1u << c);
-            }
-            if (again) atomicOr(s_again, 1u << c);
+            if (kTakeAgain) use(c, d, acc, inv, !(trouble == 0.f));
         }
-    }
+    };
+    put_partials();
+    merge(~0u, [](float x) { return __builtin_amdgcn_exp2f(x); }, [&](int c, int d, const float (&acc)[8], float inv, bool again) {
+        if constexpr (!kBf16) {                                 // (as in attn_prefill_f32.hip)
+            Least least;
+            bool zero = false;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                least.take(acc[e]);
+                zero |= acc[e] == 0.f;
+            }
+            again |= least.small(inv);
+            if (d == 0) {
+                Least least_q;
+                least_q.u = s_least[c];
+                again |= least_q.small() || __builtin_bit_cast(float, s_most[c]) * a.scale > kLargeQuery;
+            }
+            if (zero) atomicOr(s_again + 1, 1u << c);
+        }
+        if (again) atomicOr(s_again, 1u << c);
+    });
     if constexpr (kTakeAgain) {
         __syncthreads();                                        // what the waves write once more is behind what is there
         uint32_t all = __builtin_amdgcn_readfirstlane(*s_again);
@@ -411,6 +489,14 @@ __global__ __launch_bounds__((64 * Shape<DT>::waves), (DT > 128 ? 1 : 2)) void p
                 if (least.small()) s_again[2] = 1;
                 __syncthreads();
                 if (__builtin_amdgcn_readfirstlane(s_again[2])) all |= zeros;
+            }
+            if (all) {
+                __syncthreads();                                // (the bits and the partials have been read)
+                attend_in_fp32();
+                put_partials();
+                merge(all, [](float x) { return expf(x); }, [&](int c, int, const float (&)[8], float, bool again) { if (again) atomicOr(s_again, 1u << c); });
+                __syncthreads();
+                all = __builtin_amdgcn_readfirstlane(*s_again);
             }
         }
         constexpr uint32_t kMine = kWaves == 8 ? 0x01010101u : 0x11111111u;       // columns w, w + kWaves, ...

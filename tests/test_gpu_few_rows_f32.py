@@ -2,9 +2,11 @@
 of its tiles of 32 columns; numbers whose terms leave the products' range, against the fp64 oracle within fp32's own gates."""
 import numpy as np
 import pytest
+import torch
 
-from gpu_helpers import check_close, make_cache, run_phase
-from helpers import fresh_pools, make_batch
+from gpu_helpers import DevBatch, check_close, gpu_append, gpu_resume, make_cache, run_phase
+from helpers import fresh_pools, make_batch, oracle_append, oracle_attn
+from paper_2603_10342_amd import binding as B
 from paper_2603_10342_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
@@ -54,3 +56,50 @@ def test_zero_values_and_zero_keys(d):
     got, ref = run_phase(make_cache(g), *fresh_pools(g), b, "cold")
     assert np.all(got[:, :, ::2] == 0)
     check_close(got, ref, I.F32, f"D={d}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("what", ["query", "value", "large value"])
+def test_numbers_out_of_the_terms_range_on_a_long_context(d, what):
+    """Five rows on 6000 tokens, a query channel of 1e-35 in one row, a value channel of 1e-33 or values of 2^80: taken with fp32
+    products, at less than five times an ordinary call's time (row by row: eleven to sixteen times)."""
+    g = I.Geometry(32, 8, d, 16, 400, I.F32)
+    bt = I.deal_block_tables(I.rng_for(67, 0), [6005], 16, g.num_pages)
+    first, b = (make_batch(g, [p], [n], seed=67, bt=bt, stream=i, sigma_qk=1.0, sigma_v=1.0) for i, (p, n) in enumerate([(0, 6000), (6000, 5)]))
+
+    def timed(first, b):
+        cache = make_cache(g)
+        gpu_append(cache, DevBatch(first))
+        df = DevBatch(b)
+        gpu_append(cache, df)
+        got, best = gpu_resume(cache, df), np.inf
+        for _ in range(5):
+            at = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            at[0].record()
+            for _ in range(5):
+                B.ag_attn_resume(cache, df.q, df.out, df.bt, df.prefix, df.new, df.cu, df.total, df.max_new, df.max_ctx, g.num_q_heads, g.scale)
+            at[1].record()
+            at[1].synchronize()
+            best = min(best, at[0].elapsed_time(at[1]))
+        return got, best
+
+    _, usual = timed(first, b)
+    size = 1.0
+    if what == "query":
+        b.q[2, 9, 5] = 1e-35
+    elif what == "value":
+        for x in (first, b):
+            x.v_new[:, :, 7] *= np.float32(1e-33)
+    else:
+        size = 2.0 ** 80
+        for x in (first, b):
+            x.v_new *= np.float32(size)
+    got, took = timed(first, b)
+    kp, vp = fresh_pools(g)
+    oracle_append(kp, vp, first)
+    oracle_append(kp, vp, b)
+    ref = oracle_attn(kp, vp, b)
+    check_close(got / size, ref / size, I.F32, f"D={d} {what}")
+    if what == "value":
+        check_close(got[:, :, 7] * 1e33, ref[:, :, 7] * 1e33, I.F32, f"D={d} {what}, its channel")
+    assert took < 5 * usual, (usual, took)
