@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_helpers import DevBatch, check_close, gpu_append, gpu_decode, gpu_merged, gpu_prefill, i32, make_cache, pools_match, run_phase, to_dev
+from gpu_helpers import DevBatch, check_close, gpu_append, gpu_decode, gpu_merged, gpu_prefill, i32, make_cache, pools_match, run_phase, to_dev, to_f64
 from helpers import fresh_pools, make_batch, oracle_append, oracle_attn
 from oracle import oracle as O
 from paper_2603_10342_amd import binding as B
@@ -66,12 +66,19 @@ def test_decode_shares_that_span_many_short_sessions(dtype, d):
 
 
 @pytest.mark.parametrize("dtype,d,ps,hq,hkv", [(I.BF16, 128, 16, 8, 2), (I.BF16, 128, 16, 16, 1), (I.BF16, 64, 32, 8, 2),
-                                               (I.BF16, 256, 16, 6, 2), (I.F32, 64, 16, 40, 2), (I.F32, 128, 16, 8, 2)])
+                                               (I.BF16, 256, 16, 6, 2), (I.F32, 64, 16, 40, 2), (I.F32, 128, 16, 8, 2), (I.F32, 64, 16, 4, 1)])
 @pytest.mark.parametrize("cus_per_xcd", [0, 1])
 def test_decode_at_the_line_between_one_workgroup_per_pair_and_shares(dtype, d, ps, hq, hkv, cus_per_xcd):
-    """max_ctx at and one past 256 KiB of keys and values per pair, on the whole device and on 8 CUs (where six pairs or
-    more are over half of them, and nine or more never get one each); lengths from one token to the bound, some empty."""
-    line = (256 << 10) // (2 * d * (4 if dtype == I.F32 else 2))
+    """max_ctx at and one past the most that one workgroup goes through alone: 416 KiB of keys and values a pair for bf16 / 128 / 16, 432 of
+    fp32 at 64 channels, 448 of the others, on the whole device; 512 KiB and 1 MiB on 8 CUs where the six pairs of one KV head are over
+    half of them (more never get one each).  Lengths from one token to the bound, some empty.  bf16 / 128 / 16: the step in one
+    launch as well, with the same bits on either side."""
+    main = (dtype, d, ps) == (I.BF16, 128, 16)
+    if cus_per_xcd and hkv == 1:
+        kib = 512 if main else 1024
+    else:
+        kib = 416 if main else 432 if (dtype, d) == (I.F32, 64) else 448
+    line = (kib << 10) // (2 * d * (4 if dtype == I.F32 else 2))
     stream = None
     if cus_per_xcd:
         stream = B.ag_stream_create_cumask(B.ag_cumask_build(B.ag_device_info()["num_cus"], 8, 0, cus_per_xcd))
@@ -95,6 +102,16 @@ def test_decode_at_the_line_between_one_workgroup_per_pair_and_shares(dtype, d, 
                 got = gpu_decode(cache, to_dev(qn, dtype), df.bt, i32(ctx), top, g)
             assert np.all(got[ctx == 0] == 0)
             check_close(got[live], ref, dtype, f"decode up to {top} D={d} {hq}/{hkv}")
+            if main:
+                last = [int(fill.cu_new[i + 1]) - 1 for i in range(len(ctx))]          # a session's newest token, taken again
+                k, v = (to_dev(x[last], dtype) for x in (fill.k_new, fill.v_new))
+                q, ws = to_dev(qn, dtype), torch.zeros(B.ag_decode_step_workspace_bytes(len(ctx), hq, d, top) // 4, dtype=torch.float32, device="cuda")
+                out = torch.full_like(q, float("nan"))
+                torch.cuda.synchronize()
+                B.ag_decode_step(cache, k, v, q, out, df.bt, i32(ctx), top, hq, g.scale, ws, stream=stream)
+                torch.cuda.synchronize()
+                assert np.array_equal(to_f64(out, dtype), got)
+                pools_match(cache, kp, vp, dtype)
     finally:
         torch.cuda.synchronize()
         if stream:
