@@ -3,6 +3,7 @@ the sources): seen on the CPU, through a HIP runtime that logs launches."""
 import pytest
 
 from launches import launched
+from test_gpu_halves import ACROSS, SHAPES
 from test_gpu_merged import FEW_ROWS, GROUPS, MIXES, SMALL
 
 
@@ -119,6 +120,27 @@ def test_queue_of_few_heads_and_more_than_one_workgroup_a_cu(tmp):
 def test_two_sets_of_waves_in_a_prefill_workgroup(tmp, halves, batches):
     for b, k in zip(batches, kernels(tmp, *(dict(call="resume", **b) for b in batches))):
         assert len(k) == 1 and k[0].startswith("prefill_halves_kernel") == halves, (b, k)
+
+
+def test_two_sets_of_waves_in_the_gpu_tests(tmp):
+    batches = [dict(call="resume", hq=hq, hkv=1, d=d, page=ps, batch=2, total=sum(new), max_new=max(new), max_ctx=max(p + n for p, n in zip(prefix, new)), cus=8)
+               for hq, prefix, new in ACROSS for d, ps in SHAPES]
+    for b, k in zip(batches, kernels(tmp, *batches)):
+        assert k[0].startswith("prefill_halves_kernel"), (b, k)
+
+
+# fp32: 1000 tiles of 32 columns to 256 CUs a thousandth; at 32 / 8 heads eight rows are a tile, and a batch of equal sessions of 8 k rows has 8 k tiles a session
+@pytest.mark.parametrize("d,prefix,new,most", [
+    # 64 channels: one workgroup a CU below 125 tokens, two up to 300, then five thousandths a token more, four at most
+    (64, 100, 24, 256), (64, 101, 24, 512), (64, 276, 24, 512), (64, 476, 24, 768), (64, 676, 24, 1024), (64, 3000, 24, 1024),
+    # 128: one below 64 tokens, two up to 200, five at most from 800 on
+    (128, 39, 24, 256), (128, 40, 24, 512), (128, 176, 24, 512), (128, 376, 24, 768), (128, 776, 24, 1280), (128, 3000, 24, 1280),
+])
+def test_few_rows_of_fp32(tmp, d, prefix, new, most):
+    """The last batch of 24-row chunks, 24 tiles each, that the kernel of few rows takes."""
+    batches = [dict(call="resume", dtype="f32", d=d, batch=b, prefix=prefix, new=new) for b in (most // 24, most // 24 + 1)]
+    few, tiles = kernels(tmp, *batches)
+    assert few[0].startswith(SPLIT) and tiles[0].startswith("prefill_f32_kernel"), (few, tiles)
 
 
 @pytest.mark.parametrize("shape", [dict(d=128, page=32), dict(dtype="f32", d=64), dict(d=64), dict(d=64, page=32)])

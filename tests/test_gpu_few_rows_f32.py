@@ -1,5 +1,5 @@
-"""fp32 prefill of few rows, whose products are of three bf16 terms: edges of its steps of 32 keys, of the four waves' shares and
-of its tiles of 32 columns; numbers whose terms leave the products' range, against the fp64 oracle within fp32's own gates."""
+"""fp32 prefill of few rows, whose products are of three bf16 terms: edges of its steps of 32 keys, of the eight waves' rounds (256
+keys), of the 32 steps that a wave's page ids last for (8192 keys) and of its tiles of 32 columns; numbers whose terms leave the products' range, against the fp64 oracle within fp32's own gates."""
 import numpy as np
 import pytest
 import torch
@@ -31,6 +31,16 @@ def test_edges(d, ps, hq, hkv):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("ps,hq,hkv", [(16, 6, 2), (128, 3, 1)])
+@pytest.mark.parametrize("prefix,new", [([254, 255, 256, 510, 511, 512], [1, 1, 1, 1, 2, 1]), ([8190, 8400], [3, 5])])
+def test_ends_of_the_waves_rounds(d, ps, hq, hkv, prefix, new):
+    """Contexts of 255, 256, 257, 511, 513 and 513 tokens, where a wave has one own step or two, or its second is the last one and partial;
+    and of more than 8192, where it fetches page ids again."""
+    g = I.Geometry(hq, hkv, d, ps, 20480 // ps, I.F32)
+    fill_and_resume(g, prefix, new, seed=68)
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("sigma_qk,sigma_v", [(1.0, 1e-36), (1.0, 1e-33), (1.0, 1e37), (1e-15, 1.0)])
 def test_ends_of_the_range(d, sigma_qk, sigma_v):
     g = I.Geometry(8, 2, d, 16, 64, I.F32)
@@ -56,6 +66,24 @@ def test_zero_values_and_zero_keys(d):
     got, ref = run_phase(make_cache(g), *fresh_pools(g), b, "cold")
     assert np.all(got[:, :, ::2] == 0)
     check_close(got, ref, I.F32, f"D={d}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_zero_results_beside_values_below_the_terms_range(d):
+    """Channels of zeros only, of values of 1e-38 that cancel to zero, and of values of 1e-33: the values are read again behind a result of
+    zero, and the tile is taken once more where any of them is small."""
+    g = I.Geometry(8, 2, d, 16, 64, I.F32)
+    b = make_batch(g, [0, 0], [45, 300], seed=69, sigma_qk=1.0, sigma_v=1.0)
+    b.v_new[:, :, 0] = 0
+    b.v_new[:, 1, 3] *= np.float32(1e-33)
+    b.v_new[:, 0, 5] = np.where(np.arange(345) % 2, np.float32(1e-38), np.float32(-1e-38))
+    b.k_new[:, 0] = b.k_new[:1, 0]                              # KV head 0: equal weights, so that channel 5 cancels in every other row
+    got, ref = run_phase(make_cache(g), *fresh_pools(g), b, "cold")
+    assert np.all(got[:, :, 0] == 0)
+    check_close(got, ref, I.F32, f"D={d}")
+    check_close(got[:, 4:, 3] * 1e33, ref[:, 4:, 3] * 1e33, I.F32, f"D={d} channel 3")
+    # a result has at most the rounding of its sums, of up to 300 numbers of 1e-38 that weigh 1 / 300 at least, and its own, of 2^-149
+    assert np.abs(got[:, :4, 5] - ref[:, :4, 5]).max() <= 300 * 2.0 ** -24 * 1e-38 + 300 * 2.0 ** -149
 
 
 @pytest.mark.parametrize("d", [64, 128])
